@@ -1144,13 +1144,19 @@ kvq_status_t cache_error(kvq_cache_t* c, int32_t layer, bool l1, const void* k_r
     const Layer& L = c->layers[(size_t)layer];
     if (L.T == 0) return KVQ_E_STATE;
     hipStream_t s = as_stream(hip_stream);
-    double* err = reinterpret_cast<double*>(c->arena + c->flags_off + 16);  // two accumulators behind the flags
-    if (kvq_launch_fill_u32(reinterpret_cast<uint32_t*>(err), 0u, 4, s) != hipSuccess) return KVQ_E_HIP;
+    // The workgroups store their sums straight into the pinned staging ring, where the host adds them up behind the
+    // synchronization this call makes anyway: no accumulators to clear, no copy back.
+    const int wgs = kvq_error_workgroups(L.T, c->units);
+    c->ring_events.stream = s;
+    const int64_t at = c->ring_ctl.reserve(c->ring_events, (uint64_t)wgs * 2 * sizeof(double), 256);
+    if (at < 0) return KVQ_E_HIP;
     if (kvq_launch_error(l1, c->arena, c->table_dev(layer), k_ref_dev, v_ref_dev, gk_dev, gv_dev, L.T, c->tpp, c->units,
-                         err, s) != hipSuccess)
+                         reinterpret_cast<double*>(c->ring_dev + at), s) != hipSuccess)
         return KVQ_E_HIP;
-    if (hipMemcpyAsync(out_host, err, 2 * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess) return KVQ_E_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return KVQ_E_HIP;
+    const double* partial = reinterpret_cast<const double*>(c->ring + at);
+    out_host[0] = out_host[1] = 0.0;
+    for (int i = 0; i < wgs; ++i) { out_host[0] += partial[2 * i]; out_host[1] += partial[2 * i + 1]; }
     return KVQ_OK;
 }
 }  // namespace

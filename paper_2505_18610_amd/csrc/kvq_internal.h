@@ -72,9 +72,13 @@ hipError_t kvq_launch_quant16(int dst_bits, uint8_t* arena, const KvqRequantJob*
 hipError_t kvq_launch_reparam_store(const float* lambda, float* dst, int n, hipStream_t s);
 hipError_t kvq_launch_calibrate(const void* k, int batch, int n_kv_heads, int n_tokens, float alpha, float floor_,
                                 float* lambda, hipStream_t s);
+// partial: 2 doubles (K, V) for each of kvq_error_workgroups() workgroups, at most KVQ_ERR_MAX_WGS (four per compute
+// unit: 16 wavefronts, what hides the latency of the row loads); device-visible memory
+#define KVQ_ERR_MAX_WGS 1024
+int kvq_error_workgroups(int n_tokens, int units);
 hipError_t kvq_launch_error(bool l1, const uint8_t* arena, const KvqPageDesc* table, const void* k_ref,
                             const void* v_ref, const float* gk, const float* gv, int n_tokens, int tiles_per_page,
-                            int units, double* err, hipStream_t s);
+                            int units, double* partial, hipStream_t s);
 hipError_t kvq_launch_stream_read(const void* buf, size_t bytes, int n_workgroups, uint32_t* sink, hipStream_t s);
 hipError_t kvq_launch_fill_u32(uint32_t* dst, uint32_t value, size_t n, hipStream_t s);
 

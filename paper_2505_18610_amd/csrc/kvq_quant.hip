@@ -6,6 +6,8 @@
 // every lane quantizes the 64 slots it will later feed to the matrix cores.
 #include "kvq_quant_dev.h"
 
+#include <algorithm>
+
 namespace {
 
 using namespace kvq_q;
@@ -452,71 +454,189 @@ __global__ __launch_bounds__(64) void kvq_shrink_kernel(uint8_t* __restrict__ ar
 }
 
 // --------------------------------------------------------------------------------- reconstruction error
-// grid.x = 2 * tiles (even: K tile, odd: V tile), grid.y = unit, 64 threads.  Over the tile's stored tokens, with
-// x_hat = code * S + Z (or the raw value of a 16-bit tile) and x the reference fp16 tensor [unit][token][128]:
-//   L1 = false: adds (x_hat - x)^2                       into err[0] (K) or err[1] (V)
-//   L1 = true:  adds |g * (x_hat - x)| (g = 1 if no gradient tensor [unit][token][128] fp32 is given), the terms
-//               of the sensitivity of Sec. 3.2, Eq. 5
-// fp32 inside a tile, fp64 across tiles.
+// 16 bytes from the address of any element (a reference may be a view that starts at an odd one): one 16-byte load.
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+__device__ inline u32x4 load16_any(const void* p) { return *static_cast<const u32x4_any*>(p); }
+// 8 codes of B bits (piece p of a lane's string) -> 8 bytes, the inverse of pack8.
+template <int B>
+__device__ inline void unpack8(const uint32_t* str, int p, uint32_t* w0, uint32_t* w1) {
+    if constexpr (B == 8) {
+        *w0 = str[2 * p]; *w1 = str[2 * p + 1];
+    } else if constexpr (B == 4) {
+        const uint32_t lo = str[p] & 0x0f0f0f0fu, hi = (str[p] >> 4) & 0x0f0f0f0fu;
+        *w0 = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
+        *w1 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
+    } else {
+        const uint32_t h = str[p >> 1] >> (16 * (p & 1));
+        uint32_t a = h & 0xffu, b = (h >> 8) & 0xffu;
+        a = (a | (a << 12)) & 0x000f000fu; b = (b | (b << 12)) & 0x000f000fu;
+        *w0 = (a | (a << 6)) & 0x03030303u;
+        *w1 = (b | (b << 6)) & 0x03030303u;
+    }
+}
+// Byte codes of one tile string -> LDS [32 tokens][128 channels]; the columns of row t are rotated by 32 (t / 8), which
+// puts the four lane quarters of a V string, whose rows are 8 apart, into different banks.
+template <int B>
+__device__ inline void rows_of_string(uint8_t* lds, const uint8_t* code, int which, int lane) {
+    const int j = lane >> 4, n = lane & 15;
+    uint32_t str[2 * B];
+    load_chunks_stream<B>(code, lane, str);
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        uint32_t w[2];
+        unpack8<B>(str, p, &w[0], &w[1]);
+        if (!which) {
+            const int t = 8 * (n >> 2) + 4 * (p >> 2) + (n & 3);
+            uint32_t* dst = reinterpret_cast<uint32_t*>(lds + t * 128 + ((32 * (p & 3) + 32 * (t >> 3) + 8 * j) & 127));
+            dst[0] = w[0]; dst[1] = w[1];
+        } else {
+            const int col = (16 * p + n + 32 * j) & 127;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) lds[(8 * j + i) * 128 + col] = (uint8_t)(w[i >> 2] >> (8 * (i & 3)));
+        }
+    }
+}
+// The same for raw fp16 values: [32 tokens][128 channels] halves, rows rotated by 64 bytes per 8 tokens.
+__device__ inline void rows_of_raw(uint8_t* lds, const uint8_t* code, int which, int lane) {
+    const int j = lane >> 4, n = lane & 15;
+    uint32_t in[32];
+    load_chunks_stream<16>(code, lane, in);
+    if (!which) {
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const int t = 8 * (n >> 2) + 4 * (p >> 2) + (n & 3);
+            *reinterpret_cast<u32x4*>(lds + t * 256 + ((64 * (p & 3) + 64 * (t >> 3) + 16 * j) & 255)) =
+                u32x4{in[4 * p], in[4 * p + 1], in[4 * p + 2], in[4 * p + 3]};
+        }
+    } else {
+#pragma unroll
+        for (int d = 0; d < 32; ++d) {
+            const int i = (2 * d) & 7, col = (2 * (16 * (d >> 2) + n) + 64 * j) & 255;
+            *reinterpret_cast<uint16_t*>(lds + (8 * j + i) * 256 + col) = (uint16_t)(in[d] & 0xffff);
+            *reinterpret_cast<uint16_t*>(lds + (8 * j + i + 1) * 256 + col) = (uint16_t)(in[d] >> 16);
+        }
+    }
+}
+
+// Over a block's stored tokens, with x_hat = code * S + Z (or the raw value of a 16-bit tile) and x the reference fp16
+// tensor [unit][token][128]: partial[2 * workgroup + which] = sum over the workgroup's share of K (which = 0), V (1) of
+//   L1 = false: (x_hat - x)^2
+//   L1 = true:  |g * (x_hat - x)| (g = 1 if no gradient tensor [unit][token][128] fp32 is given), the terms of the
+//               sensitivity of Sec. 3.2, Eq. 5
+// fp32 inside a lane's 32 elements of a row, fp64 beyond; the host adds the workgroups up in order.
+//
+// Bound by the references and gradients (4 + 8 bytes per cached token and channel against at most 2 of codes), which are
+// rows while the codes are tiles: every wavefront turns one tile string to rows in LDS and then reads both with 16-byte
+// loads, a lane taking 32 consecutive channels of a token like the quantizers' owner lanes (16 lanes to a row instead
+// needs more registers and measured 12 % slower; streaming loads twice as slow, a lane's four loads share a line).  A
+// fixed number of workgroups strides over the strings and leaves two numbers each, without atomics.  64 units x 2,048
+// tokens at 4 bits with gradients (219 MB): 41 us, 5.3 TB/s; with 2- and 4-byte loads in the codes' own order and an fp64
+// atomic per tile on two addresses 304 us.
+#define KVQ_ERR_WAVES 4
 template <bool L1>
-__global__ __launch_bounds__(64) void kvq_error_kernel(const uint8_t* __restrict__ arena,
+__global__ __launch_bounds__(64 * KVQ_ERR_WAVES) void kvq_error_kernel(const uint8_t* __restrict__ arena,
                                                        const KvqPageDesc* __restrict__ table,
                                                        const uint16_t* __restrict__ k_ref,
                                                        const uint16_t* __restrict__ v_ref,
                                                        const float* __restrict__ gk, const float* __restrict__ gv,
-                                                       int n_tokens, int tpp, double* __restrict__ err) {
-    const int lane = threadIdx.x, j = lane >> 4, n = lane & 15;
-    const int which = blockIdx.x & 1, tile = blockIdx.x >> 1, unit = blockIdx.y;
-    const int page = tile / tpp, tip = tile - page * tpp;
-    const KvqPageDesc pd = table[page];
-    const int B = (int)pd.bits;
-    const uint64_t tslot = (uint64_t)unit * tpp + tip;
-    const uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * (uint32_t)B);
-    const uint16_t* meta = reinterpret_cast<const uint16_t*>(arena + (uint64_t)pd.meta_off256 * 256u +
-                                                             tslot * KVQ_META_TILE_BYTES);
-    const uint64_t unit_base = (uint64_t)unit * n_tokens * KVQ_D;
-    const uint16_t* ref = (which ? v_ref : k_ref) + unit_base;
-    const float* grad = which ? gv : gk;
-    const int tok0 = tile * KVQ_TILE_TOKENS;
-    float acc = 0.f;
-    for (int slot = 0; slot < 64; ++slot) {
-        int t, d, g;
-        if (!which) {
-            const int p = slot >> 3, i = slot & 7, sub = p >> 2;
-            g = p & 3;
-            t = 8 * (n >> 2) + 4 * sub + (n & 3);
-            d = 32 * g + 8 * j + i;
-        } else {
-            const int nt = slot >> 3, i = slot & 7;
-            t = 8 * j + i;
-            d = 16 * nt + n;
-            g = d >> 5;
+                                                       int n_tokens, int tpp, int n_tiles, int64_t n_strings,
+                                                       double* __restrict__ partial) {
+    __shared__ __attribute__((aligned(16))) uint8_t rows[KVQ_ERR_WAVES][32 * 256];
+    __shared__ double sums[KVQ_ERR_WAVES];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int which = wave & 1, grp = lane & 3;  // a wavefront's strings are all of K or all of V: the stride is even
+    uint8_t* const lds = rows[wave];
+    const uint16_t* const ref = which ? v_ref : k_ref;
+    const float* const grad = which ? gv : gk;
+    double total = 0.0;
+    for (int64_t s = (int64_t)blockIdx.x * KVQ_ERR_WAVES + wave; s < n_strings; s += (int64_t)gridDim.x * KVQ_ERR_WAVES) {
+        const int64_t r = s >> 1;
+        const int unit = (int)(r / n_tiles), tile = (int)(r - (int64_t)unit * n_tiles);
+        const int page = tile / tpp, tip = tile - page * tpp;
+        const KvqPageDesc pd = table[page];
+        const uint64_t tslot = (uint64_t)unit * tpp + tip;
+        const uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * pd.bits);
+        const uint16_t* meta = reinterpret_cast<const uint16_t*>(arena + (uint64_t)pd.meta_off256 * 256u +
+                                                                 tslot * KVQ_META_TILE_BYTES) + (which ? 256 : 0);
+        const bool raw = pd.bits == 16 && !pd.int16;
+        switch (pd.bits) {
+            case 2: rows_of_string<2>(lds, code, which, lane); break;
+            case 4: rows_of_string<4>(lds, code, which, lane); break;
+            case 8: rows_of_string<8>(lds, code, which, lane); break;
+            default:
+                if (raw) {
+                    rows_of_raw(lds, code, which, lane);
+                } else {  // byte planes: high bytes, then low bytes
+                    rows_of_string<8>(lds, code, which, lane);
+                    rows_of_string<8>(lds + 4096, code + 512u * 8, which, lane);
+                }
         }
-        if (tok0 + t >= n_tokens) continue;
-        const uint32_t bit = (uint32_t)slot * (uint32_t)B;
-        const uint8_t* at = code + kvq_tile_byte(lane, bit >> 3);
-        // x_hat - x = code * S + (Z - x): the difference of two fp16 numbers is exact in fp32 and the fused
-        // multiply-add rounds once, so large codes times large scales lose nothing before the subtraction
-        const uint64_t at_ref = (uint64_t)(tok0 + t) * KVQ_D + d;
-        const float x = h2f(ref[at_ref]);
-        const int mi = which ? 256 + kvq_vmeta_index(t, g) : t * 4 + g;
-        float dx;
-        if (B == 16 && pd.int16) {  // byte planes: slot s of the lane's high-byte string, then of its low-byte string
-            const uint32_t c = ((uint32_t)code[kvq_tile_byte(lane, (uint32_t)slot)] << 8) |
-                               (uint32_t)code[512u * 8 + kvq_tile_byte(lane, (uint32_t)slot)];
-            dx = fmaf((float)c, h2f(meta[mi]), h2f(meta[mi + 128]) - x);
-        } else if (B == 16) {
-            dx = h2f(*reinterpret_cast<const uint16_t*>(at)) - x;
-        } else {
-            const uint32_t c = ((uint32_t)*at >> (bit & 7u)) & ((1u << B) - 1u);
-            dx = fmaf((float)c, h2f(meta[mi]), h2f(meta[mi + 128]) - x);
+        wave_sync_lds();
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            const int t = 16 * pass + (lane >> 2), tok = tile * KVQ_TILE_TOKENS + t;
+            const uint64_t row = ((uint64_t)unit * n_tokens + min(tok, n_tokens - 1)) * KVQ_D + 32 * grp;
+            uint32_t x[16];
+            float g[32];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const u32x4 v = load16_any(ref + row + 8 * c);
+                x[4 * c] = v.x; x[4 * c + 1] = v.y; x[4 * c + 2] = v.z; x[4 * c + 3] = v.w;
+            }
+            if (L1 && grad) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const u32x4 v = load16_any(grad + row + 4 * c);
+                    g[4 * c] = __uint_as_float(v.x); g[4 * c + 1] = __uint_as_float(v.y);
+                    g[4 * c + 2] = __uint_as_float(v.z); g[4 * c + 3] = __uint_as_float(v.w);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 32; ++e) g[e] = 1.0f;
+            }
+            float acc[4] = {0.f, 0.f, 0.f, 0.f};
+            // x_hat - x = code * S + (Z - x): the difference of two fp16 numbers is exact in fp32 and the fused
+            // multiply-add rounds once, so large codes times large scales lose nothing before the subtraction
+            if (raw) {
+                const u32x4* hp = reinterpret_cast<const u32x4*>(lds + t * 256 + ((64 * grp + 64 * (t >> 3)) & 255));
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const u32x4 h = hp[c];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int sh = 16 * (e & 1);
+                        const float dx = h2f((uint16_t)(h[e >> 1] >> sh)) - h2f((uint16_t)(x[4 * c + (e >> 1)] >> sh));
+                        acc[e & 3] += L1 ? fabsf(g[8 * c + e] * dx) : dx * dx;
+                    }
+                }
+            } else {
+                const int mi = which ? kvq_vmeta_index(t, grp) : t * 4 + grp;
+                const float S = h2f(meta[mi]), Z = h2f(meta[mi + 128]);
+                const int at = t * 128 + ((32 * grp + 32 * (t >> 3)) & 127);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const u32x4 b = reinterpret_cast<const u32x4*>(lds + at)[c];
+                    u32x4 lo = {0u, 0u, 0u, 0u};
+                    if (pd.int16) lo = reinterpret_cast<const u32x4*>(lds + 4096 + at)[c];
+                    const float hi_weight = pd.int16 ? 256.0f : 1.0f;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const float cd = fmaf((float)((b[e >> 2] >> (8 * (e & 3))) & 0xffu), hi_weight,
+                                              (float)((lo[e >> 2] >> (8 * (e & 3))) & 0xffu));  // exact
+                        const float dx = fmaf(cd, S, Z - h2f((uint16_t)(x[8 * c + (e >> 1)] >> (16 * (e & 1)))));
+                        acc[e & 3] += L1 ? fabsf(g[16 * c + e] * dx) : dx * dx;
+                    }
+                }
+            }
+            if (tok < n_tokens) total += (double)((acc[0] + acc[1]) + (acc[2] + acc[3]));
         }
-        if (L1) acc += fabsf(grad ? grad[unit_base + at_ref] * dx : dx);
-        else acc += dx * dx;
+        wave_sync_lds();
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if (lane == 0) atomicAdd(&err[which], (double)acc);
+    for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
+    if (lane == 0) sums[wave] = total;
+    __syncthreads();
+    if (threadIdx.x < 2) partial[2 * blockIdx.x + threadIdx.x] = sums[threadIdx.x] + sums[threadIdx.x + 2];
 }
 
 // ------------------------------------------------------------------------ channel-wise reparameterization
@@ -635,15 +755,21 @@ hipError_t kvq_launch_shrink(int dst_bits, int strategy, uint8_t* arena, const K
     return hipGetLastError();
 }
 
+int kvq_error_workgroups(int n_tokens, int units) {
+    const int64_t strings = 2ll * ((n_tokens + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS) * units;
+    return (int)std::min<int64_t>((strings + KVQ_ERR_WAVES - 1) / KVQ_ERR_WAVES, KVQ_ERR_MAX_WGS);
+}
+
 hipError_t kvq_launch_error(bool l1, const uint8_t* arena, const KvqPageDesc* table, const void* k_ref,
                             const void* v_ref, const float* gk, const float* gv, int n_tokens, int tiles_per_page,
-                            int units, double* err, hipStream_t s) {
+                            int units, double* partial, hipStream_t s) {
     const int n_tiles = (n_tokens + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
-    const dim3 grid(2 * n_tiles, units), block(64);
+    const int64_t n_strings = 2ll * n_tiles * units;
+    const dim3 grid(kvq_error_workgroups(n_tokens, units)), block(64 * KVQ_ERR_WAVES);
     const uint16_t* k = static_cast<const uint16_t*>(k_ref);
     const uint16_t* v = static_cast<const uint16_t*>(v_ref);
-    if (l1) hipLaunchKernelGGL(kvq_error_kernel<true>, grid, block, 0, s, arena, table, k, v, gk, gv, n_tokens, tiles_per_page, err);
-    else hipLaunchKernelGGL(kvq_error_kernel<false>, grid, block, 0, s, arena, table, k, v, gk, gv, n_tokens, tiles_per_page, err);
+    if (l1) hipLaunchKernelGGL(kvq_error_kernel<true>, grid, block, 0, s, arena, table, k, v, gk, gv, n_tokens, tiles_per_page, n_tiles, n_strings, partial);
+    else hipLaunchKernelGGL(kvq_error_kernel<false>, grid, block, 0, s, arena, table, k, v, gk, gv, n_tokens, tiles_per_page, n_tiles, n_strings, partial);
     return hipGetLastError();
 }
 

@@ -1,0 +1,54 @@
+"""Reconstruction error and sensitivity at the sizes where their kernels change course: one token, tile and
+page remainders, more strings than a launch has wavefronts, every tier, references that are not 16-byte aligned."""
+import numpy as np
+import pytest
+import torch
+
+import kvq_synth
+import paper_2505_18610_amd as kq
+from gpu_util import make_pair, append_both
+
+pytestmark = pytest.mark.gpu
+
+
+def odd_view(x):
+    """The array on the device, starting one element behind a 16-byte boundary."""
+    flat = torch.empty(x.size + 8, dtype=torch.from_numpy(x).dtype, device="cuda")
+    flat.fill_(float("nan"))
+    flat[1:1 + x.size] = torch.from_numpy(x.reshape(-1)).cuda()
+    return flat[1:1 + x.size].view(x.shape)
+
+
+@pytest.mark.parametrize("B,Hkv,P,tiers,tier16", [
+    (1, 1, 32, ((1, 16),), 0),
+    (1, 2, 64, ((64, 2), (64, 4), (64, 8), (33, 16)), 0),
+    (2, 3, 32, ((32, 8), (96, 2), (31, 16)), 1),
+    (1, 1, 96, ((192, 4), (5, 8)), 0),
+    (3, 5, 64, ((4992, 2), (64, 16)), 0),        # 2 x 158 x 15 strings: more than 1,024 workgroups of four
+])
+def test_errors_against_the_oracle(B, Hkv, P, tiers, tier16):
+    T = sum(n for n, _ in tiers)
+    K, V = kvq_synth.make_kv(61, 0, B, Hkv, 0, T)
+    oc, gc = make_pair(1, B, 2 * Hkv, Hkv, T, P, tier16=tier16)
+    t = 0
+    for n, bits in tiers:
+        append_both(oc, gc, 0, K[:, :, t:t + n], V[:, :, t:t + n], bits)
+        t += n
+    rng = np.random.default_rng(5)
+    Kr = (K.astype(np.float32) + rng.standard_normal(K.shape, dtype=np.float32)).astype(np.float16)
+    Vr = (V.astype(np.float32) + rng.standard_normal(V.shape, dtype=np.float32)).astype(np.float16)
+    gk, gv = (rng.standard_normal(K.shape, dtype=np.float32) for _ in range(2))
+    want = oc.reconstruction_sq_error(0, Kr, Vr)
+    Kh, Vh = oc.dequantized(0)
+    dk, dv = np.abs(Kh - Kr.astype(np.float64)), np.abs(Vh - Vr.astype(np.float64))
+    want_one = (dk.sum(), dv.sum())
+    want_g = ((np.abs(gk).astype(np.float64) * dk).sum(), (np.abs(gv).astype(np.float64) * dv).sum())
+    for dev in (lambda x: torch.from_numpy(x).cuda(), odd_view):
+        got = gc.kvq_cache_sq_error(0, dev(Kr), dev(Vr))
+        # a lane adds 8 fp32 terms per accumulator, each rounded twice: 10 x 2^-24, fp64 from there on
+        assert np.allclose(got, want, rtol=1e-6, atol=0), (got, want)
+        one = gc.kvq_cache_sensitivity(0, dev(Kr), dev(Vr))
+        got = gc.kvq_cache_sensitivity(0, dev(Kr), dev(Vr), dev(gk), dev(gv))
+        for a, b in ((one, want_one), (got, want_g)):
+            assert np.allclose(a, b, rtol=1e-6, atol=0), (a, b)
+    gc.close()
