@@ -1,4 +1,4 @@
-"""Reconstruction error and sensitivity at the sizes where their kernels change course: one token, tile and
+"""Reconstruction error, sensitivity and factor calibration at the sizes where their kernels change course: one token, tile and
 page remainders, more strings than a launch has wavefronts, every tier, references that are not 16-byte aligned."""
 import numpy as np
 import pytest
@@ -6,6 +6,7 @@ import torch
 
 import kvq_synth
 import paper_2505_18610_amd as kq
+from oracle import calibrate_lambda
 from gpu_util import make_pair, append_both
 
 pytestmark = pytest.mark.gpu
@@ -52,3 +53,15 @@ def test_errors_against_the_oracle(B, Hkv, P, tiers, tier16):
         for a, b in ((one, want_one), (got, want_g)):
             assert np.allclose(a, b, rtol=1e-6, atol=0), (a, b)
     gc.close()
+
+
+@pytest.mark.parametrize("B,Hkv,T", [(1, 1, 1), (1, 2, 15), (2, 1, 129), (3, 4, 257), (1, 8, 4097), (40, 32, 17)])
+def test_calibration_at_slice_edges(B, Hkv, T):
+    K, _ = kvq_synth.make_kv(62, 0, B, Hkv, 0, T)
+    K[0, Hkv - 1, T - 1, 127] = -3000.0  # the last element read decides its channel
+    want = calibrate_lambda(K, 0.5)
+    for dev in (lambda x: torch.from_numpy(x).cuda(), odd_view):
+        lam = torch.full((Hkv, 128), -1.0, dtype=torch.float32, device="cuda")
+        kq.kvq_calibrate_lambda(dev(K), 0.5, lam)
+        # maxima are exact; pow in fp64 rounded to fp32: one ulp
+        assert np.allclose(lam.cpu().numpy(), want, rtol=1.2e-7, atol=0)
