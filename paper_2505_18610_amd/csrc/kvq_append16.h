@@ -30,11 +30,18 @@ __device__ inline u32x4 scale_keys8(u32x4 v, const float* rinv) {
                  scale_pair(v.w, r1.z, r1.w)};
 }
 
+// Rotary embedding (Sec. 3.3, Eq. 9) of one channel: own * cos - partner * sin in the lower half of the head, own * cos +
+// partner * sin in the upper.  Every product and the sum are separate fp32 operations (the empty asm keeps them from being
+// contracted or fused with the conversion); the result is rounded to fp16.
+__device__ inline uint16_t rope1(uint16_t own, uint16_t partner, float c, float sn, bool upper) {
+    float p1 = h2f(own) * c, p2 = h2f(partner) * sn;
+    asm volatile("" : "+v"(p1), "+v"(p2));
+    float sum = upper ? p1 + p2 : p1 - p2;
+    asm volatile("" : "+v"(sum));
+    return f2h_rn(sum);
+}
 // Rotary embedding (Sec. 3.3, Eq. 9) of 8 consecutive channels ch0 .. ch0+7 of one token: own = these channels,
 // partner = the channels ch0 +- 64 of the same token, cs = the token's table row [cos 64 | sin 64] (fp32).
-//   lower half (ch < 64):  own * cos - partner * sin        upper half:  own * cos + partner * sin
-// Every product and the sum are separate fp32 operations (the empty asm keeps them from being contracted or
-// fused with the conversion); the result is rounded to fp16.
 __device__ inline u32x4 rope8(u32x4 own, u32x4 partner, const float* cs, int ch0) {
     const int i0 = ch0 & 63;
     const bool upper = ch0 >= 64;
@@ -44,17 +51,11 @@ __device__ inline u32x4 rope8(u32x4 own, u32x4 partner, const float* cs, int ch0
     uint32_t* r = reinterpret_cast<uint32_t*>(&out);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        float res[2];
+        r[e] = 0u;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const float c = cs[i0 + 2 * e + h], sn = cs[64 + i0 + 2 * e + h];
-            float p1 = h2f((uint16_t)(o[e] >> (16 * h))) * c, p2 = h2f((uint16_t)(p[e] >> (16 * h))) * sn;
-            asm volatile("" : "+v"(p1), "+v"(p2));
-            float sum = upper ? p1 + p2 : p1 - p2;
-            asm volatile("" : "+v"(sum));
-            res[h] = sum;
-        }
-        r[e] = (uint32_t)f2h_rn(res[0]) | ((uint32_t)f2h_rn(res[1]) << 16);
+        for (int h = 0; h < 2; ++h)
+            r[e] |= (uint32_t)rope1((uint16_t)(o[e] >> (16 * h)), (uint16_t)(p[e] >> (16 * h)), cs[i0 + 2 * e + h],
+                                    cs[64 + i0 + 2 * e + h], upper) << (16 * h);
     }
     return out;
 }

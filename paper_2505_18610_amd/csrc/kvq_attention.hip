@@ -35,8 +35,8 @@ __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_append_kernel(
 // The same for a cache whose 16-bit tier holds integer codes in byte planes (KVQ_TIER16_INT16).
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_i16_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    if (__builtin_amdgcn_readfirstlane(P.flags[0] & 1u)) attention_body<true, true>(P, sh);
-    else attention_body<false, true>(P, sh);
+    if (__builtin_amdgcn_readfirstlane(P.flags[0] & 1u)) attention_body<true, true, false, false>(P, sh);
+    else attention_body<false, true, false, false>(P, sh);
 }
 
 // Same thread count as the attention kernel, so both merge variants add in the same order.

@@ -20,9 +20,7 @@
 
 #include "kvq_internal.h"
 #include "kvq_append16.h"
-#ifdef KVQ_WITH_I16_APPEND
 #include "kvq_quant_dev.h"
-#endif
 
 namespace {
 
@@ -787,6 +785,11 @@ struct AttnShared {
     unsigned claim_ctr;
     u32x4 desc[KVQ_DESC_CACHE];
     __attribute__((aligned(16))) uint8_t meta[KVQ_ATTN_WAVES * KVQ_WAVE_LDS_BYTES];
+    // the token a fused append adds: K, V
+    __attribute__((aligned(16))) uint16_t new_bits[2][KVQ_D];  // as stored: fp16 values, or codes of the integer tier
+    __attribute__((aligned(16))) float new_x[2][KVQ_D];        // what attention sees of it: the value, or code * S + Z
+    uint16_t new_sz[2][KVQ_NGRP][2];                           // (S, Z) of its groups (integer tier)
+    float new_score[16];                                       // its score per head, log2 units
 };
 
 
@@ -908,8 +911,127 @@ __device__ inline void merge_splits(const KvqAttnParams& P, int unit, int tid, f
 
 static_assert(KVQ_ATTN_WAVES * 16 * KVQ_OPAD >= KVQ_MERGE_LDS_FLOATS, "the wavefront slab doubles as scratch of the split merge");
 
+// ---- A one-token append fused into the launch (kvq_append_decode_attention).  The workgroup of a unit's last split does
+// it.  The token is never read back from the cache: its rows wait in LDS from the staging phase on, its score and its V
+// row enter the merge of the wavefront partials as a ninth partial of one token, and its elements are stored behind the
+// join of the wavefronts, when nobody reads the tile any more.  The streaming loop covers the older tokens only and knows
+// nothing of it.  (Written at the start, waited for and read back with its tile, the token cost 3 to 4 us of every step.)
+
+// K (which = 0) or V (1) row of the new token -> LDS, one wavefront, two channels per lane: rotation and
+// reparameterization exactly as the append kernels carry them out (kvq_append16.h), in the integer tier Eq. 1-2 with
+// 2^16 - 1 levels (kvq_quant_dev.h).
+template <bool I16>
+__device__ inline void stage_new_token(const KvqAttnParams& P, AttnShared& sh, int unit, int hk, int which, int lane) {
+    uint32_t w;
+    __builtin_memcpy(&w, static_cast<const uint16_t*>(which ? P.app_v : P.app_k) + (size_t)unit * KVQ_D + 2 * lane, 4);
+    if (!which && P.app_rope) {
+        const float* cs = P.app_rope + ((2 * lane) & 63);  // the token's row: cos 64 | sin 64
+        const uint32_t partner = (uint32_t)__shfl_xor((int)w, 32);  // channels +- 64
+        uint32_t r = 0u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            r |= (uint32_t)kvq_dev::rope1((uint16_t)(w >> (16 * h)), (uint16_t)(partner >> (16 * h)), cs[h], cs[64 + h], lane >= 32) << (16 * h);
+        w = r;
+    }
+    if (!which && P.app_rinv) {
+        const float* r = P.app_rinv + hk * KVQ_D + 2 * lane;
+        w = kvq_dev::scale_pair(w, r[0], r[1]);
+    }
+    float x0 = mixf(w, 0), x1 = mixf(w, 1);
+    if constexpr (I16) {
+        float mn = fminf(x0, x1), mx = fmaxf(x0, x1);
+        for (int o = 1; o < 16 * P.app_gspan; o <<= 1) {  // a group of 32, 64 or 128 channels is 16, 32 or 64 lanes
+            mn = fminf(mn, __shfl_xor(mn, o));
+            mx = fmaxf(mx, __shfl_xor(mx, o));
+        }
+        uint16_t S, Z;
+        float Sf;
+        kvq_q::group_params(mn, mx, 65535, &S, &Z, &Sf);
+        const uint32_t c0 = kvq_q::code_of(x0, mn, Sf, 65535), c1 = kvq_q::code_of(x1, mn, Sf, 65535);
+        w = c0 | (c1 << 16);
+        const float Zf = kvq_dev::h2f(Z);
+        x0 = fmaf((float)c0, Sf, Zf);
+        x1 = fmaf((float)c1, Sf, Zf);
+        if ((lane & 15) == 0) { sh.new_sz[which][lane >> 4][0] = S; sh.new_sz[which][lane >> 4][1] = Z; }
+    }
+    *reinterpret_cast<uint32_t*>(&sh.new_bits[which][2 * lane]) = w;
+    *reinterpret_cast<float2v*>(&sh.new_x[which][2 * lane]) = float2v{x0, x1};
+}
+
+// Scores of the new token for heads 2 * wave and 2 * wave + 1 (32 lanes each, 4 channels per lane).
+__device__ inline void score_new_token(AttnShared& sh, float scale_log2, int wave, int lane) {
+    const int head = 2 * wave + (lane >> 5), d = 4 * (lane & 31);
+    const half4 q = *reinterpret_cast<const half4*>(&sh.q[head * KVQ_D + d]);
+    const float4v k = *reinterpret_cast<const float4v*>(&sh.new_x[0][d]);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = fmaf((float)q[i], k[i], s);
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) s += __shfl_xor(s, o);
+    if ((lane & 31) == 0) sh.new_score[head] = s * scale_log2;
+}
+
+// The new token's K (which = 0) or V (1) elements -> its tile, one wavefront.  A tile that it starts is zeroed first, codes
+// and (integer tier) metadata, so that the slots of tokens to come are well defined, as the append kernels leave them.
+template <bool I16>
+__device__ inline void store_new_token(const KvqAttnParams& P, const AttnShared& sh, int unit, int which, int lane) {
+    const int tile = P.app_t_old / KVQ_TILE_TOKENS, t = P.app_t_old - tile * KVQ_TILE_TOKENS;
+    const int tip = tile - (tile / P.tiles_per_page) * P.tiles_per_page;
+    const uint64_t tslot = (uint64_t)unit * P.tiles_per_page + tip;
+    uint8_t* const code = const_cast<uint8_t*>(P.arena) + (uint64_t)P.app_desc.code_off256 * 256u + (tslot * 2 + which) * (512u * 16);
+    uint8_t* const meta = const_cast<uint8_t*>(P.arena) + (uint64_t)P.app_desc.meta_off256 * 256u + tslot * KVQ_META_TILE_BYTES;
+    if (t == 0) {
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int c = 0; c < 8; ++c) *reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16) = zero;
+        if (I16 && lane < 32) *reinterpret_cast<u32x4*>(meta + 512 * which + lane * 16) = zero;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the elements below go to addresses other lanes have just zeroed
+    }
+    if (!which) {  // lane = 4 grp + j: channels 32 grp + 8 j .. + 7 are consecutive slots of one lane's string
+        int ln, slot;
+        const int ch = 8 * ((lane & 3) + 4 * ((lane >> 2) & 3));
+        kvq_k_slot(t, ch, &ln, &slot);
+        if (lane < 16) {
+            if constexpr (I16) {
+                uint32_t hi[2], lo[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t a = *reinterpret_cast<const uint32_t*>(&sh.new_bits[0][ch + 4 * h]);
+                    const uint32_t b = *reinterpret_cast<const uint32_t*>(&sh.new_bits[0][ch + 4 * h + 2]);
+                    lo[h] = __builtin_amdgcn_perm(b, a, 0x06040200u);
+                    hi[h] = __builtin_amdgcn_perm(b, a, 0x07050301u);
+                }
+                *reinterpret_cast<u32x2*>(code + kvq_tile_byte(ln, (uint32_t)slot)) = u32x2{hi[0], hi[1]};
+                *reinterpret_cast<u32x2*>(code + 512u * 8 + kvq_tile_byte(ln, (uint32_t)slot)) = u32x2{lo[0], lo[1]};
+            } else {
+                *reinterpret_cast<u32x4*>(code + kvq_tile_byte(ln, 2u * slot)) = *reinterpret_cast<const u32x4*>(&sh.new_bits[0][ch]);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ch = lane + 64 * h;
+            int ln, slot;
+            kvq_v_slot(t, ch, &ln, &slot);
+            const uint16_t v = sh.new_bits[1][ch];
+            if constexpr (I16) {
+                code[kvq_tile_byte(ln, (uint32_t)slot)] = (uint8_t)(v >> 8);
+                code[512u * 8 + kvq_tile_byte(ln, (uint32_t)slot)] = (uint8_t)v;
+            } else {
+                *reinterpret_cast<uint16_t*>(code + kvq_tile_byte(ln, 2u * slot)) = v;
+            }
+        }
+    }
+    if (I16 && lane < 8) {  // S of the four groups, then Z
+        const int g = lane & 3, z = lane >> 2;
+        uint16_t* m = reinterpret_cast<uint16_t*>(meta + 512 * which + 256 * z);
+        m[which ? kvq_vmeta_index(t, g) : t * 4 + g] = sh.new_sz[which][g][z];
+    }
+}
+
 // End of a workgroup's range: merge of its eight wavefront partials through LDS, then either the output (one split),
 // the partial for the separate merge kernel, or the fused merge of the unit's split partials.
+template <bool I16, bool APPEND>
 __device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnShared& sh, WaveState& st, int split, int unit) {
     // the thread index is taken afresh, opaque to the compiler: nothing derived from it stays in a register across
     // the streaming loop for the sake of this epilogue
@@ -940,7 +1062,10 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnSha
         for (int nt = 0; nt < 8; ++nt)
             *reinterpret_cast<float4v*>(&red_o[wave][n * KVQ_OPAD + 16 * nt + 4 * j]) = st.o[nt];
     }
+    const bool appends = APPEND && P.app_t_old >= 0 && split == ns - 1;
+    if (appends) score_new_token(sh, P.scale_log2, wave, lane);  // here it hides in the wait for the slowest wavefront
     __syncthreads();  // the eight wavefronts of the workgroup have joined
+    if (appends && wave < 2) store_new_token<I16>(P, sh, unit, wave, lane);
     KVQ_STAMP(6);
 
     const bool direct = (ns == 1);
@@ -959,6 +1084,7 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnSha
             const int head = pr >> 6, d = 2 * (pr & 63);
             float M = -INFINITY;
             for (int w = 0; w < KVQ_ATTN_WAVES; ++w) M = fmaxf(M, sh.red_m[w][head]);
+            if (appends) M = fmaxf(M, sh.new_score[head]);
             float2v a = {0.f, 0.f};
             float L = 0.f;
             for (int w = 0; w < KVQ_ATTN_WAVES; ++w) {
@@ -968,6 +1094,13 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnSha
                 a[0] = fmaf(o2[0], f, a[0]);
                 a[1] = fmaf(o2[1], f, a[1]);
                 L = fmaf(sh.red_l[w][head], f, L);
+            }
+            if (appends) {
+                const float f = __builtin_amdgcn_exp2f(sh.new_score[head] - M);
+                const float2v v2 = *reinterpret_cast<const float2v*>(&sh.new_x[1][d]);
+                a[0] = fmaf(v2[0], f, a[0]);
+                a[1] = fmaf(v2[1], f, a[1]);
+                L += f;
             }
             acc[r] = a;
             ml[r] = float2v{M, L};
@@ -1026,12 +1159,12 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnSha
 }
 
 // The whole kernel for one of the two V paths (SAFE: overflow-proof, see accumulate_tile) and one of the two kinds
-// of 16-bit tier (I16: integer codes in byte planes; else raw fp16, which is also the kind a one-token append can
-// be fused into).  A cache has one kind only, so each kernel carries the code of one.
+// of 16-bit tier (I16: integer codes in byte planes; else raw fp16).  A cache has one kind only, so each kernel carries
+// the code of one.
 // BATCH: the workgroup's (split, unit) come from the caller (ragged batch); else they are the workgroup's grid indices,
 // read where they are needed (handing them in as values costs the single-cache kernels scalar registers they lack).
-// APPEND: the kernel can carry out a one-token append into the raw fp16 tier (P.app_t_old >= 0) before it attends.
-template <bool SAFE, bool I16, bool BATCH = false, bool APPEND = !I16>
+// APPEND: the kernel can carry out a one-token append into the 16-bit tier (P.app_t_old >= 0) and attend to that token too.
+template <bool SAFE, bool I16, bool BATCH, bool APPEND>
 __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShared& sh, const int split_in = 0,
                                                const int unit_in = 0) {
     const int split = BATCH ? split_in : (int)blockIdx.x, unit = BATCH ? unit_in : (int)blockIdx.y;
@@ -1075,41 +1208,11 @@ __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShare
         *reinterpret_cast<u32x4*>(&q_lds[head * KVQ_D + c16 * 8]) = qv;
         desc_lds[tid] = dv;
     }
-    // A one-token append fused into this launch: the workgroup whose range ends with the new token's tile writes
-    // the token.  Its wavefront 0 does that after the staging barrier, waits until the stores have reached L2 and
-    // takes the chunk that holds the tile as its first one (nobody else can claim it); the other seven wavefronts
-    // start on the rest of the range meanwhile.
-    const int tile_new = (APPEND && P.app_t_old >= 0) ? P.app_t_old / KVQ_TILE_TOKENS : -1;
-    const bool appends = APPEND && tile_new >= t_begin && tile_new < t_end;
-    const bool one_window = p_last - p_first <= KVQ_DESC_CACHE;
-    // the first chunk of every wavefront is fixed (see below); the counter starts behind them
-    if (tid == 0) claim_ctr = (appends && one_window) ? KVQ_ATTN_WAVES - 1 : KVQ_ATTN_WAVES;
+    // waves 4 and 5 have nothing else to stage
+    if (APPEND && P.app_t_old >= 0 && split == P.n_splits - 1 && (wave == 4 || wave == 5))
+        stage_new_token<I16>(P, sh, unit, hk, wave & 1, lane);
+    if (tid == 0) claim_ctr = KVQ_ATTN_WAVES;  // the first chunk of every wavefront is fixed, the counter starts behind them
     __syncthreads();
-    if (APPEND && appends && wave == 0) {
-        const int tip = tile_new - (tile_new / tpp) * tpp;
-        const uint64_t tslot = (uint64_t)unit * tpp + tip;
-        uint8_t* code = const_cast<uint8_t*>(P.arena) + (uint64_t)P.app_desc.code_off256 * 256u + tslot * 2 * (512u * 16);
-        const uint16_t* in_k = static_cast<const uint16_t*>(P.app_k) + (size_t)unit * KVQ_D;
-        const uint16_t* in_v = static_cast<const uint16_t*>(P.app_v) + (size_t)unit * KVQ_D;
-#ifdef KVQ_WITH_I16_APPEND
-        if constexpr (I16) {  // integer tier: the token is quantized (Eq. 1-2, 2^16 - 1 levels); the reduction slab is free
-            uint8_t* meta = const_cast<uint8_t*>(P.arena) + (uint64_t)P.app_desc.meta_off256 * 256u + tslot * KVQ_META_TILE_BYTES;
-            auto& lds = *reinterpret_cast<uint8_t (*)[2][KVQ_LDS_CODES]>(&sh.red_o[0][0]);
-            kvq_q::append_i16_string(lds, code, meta, in_k, 0, tile_new * KVQ_TILE_TOKENS, P.app_t_old, P.app_t_old + 1,
-                                     P.app_gspan, P.app_rope, P.app_rinv, hk, lane);
-            kvq_q::wave_sync_lds();
-            kvq_q::append_i16_string(lds, code + 512u * 16, meta, in_v, 1, tile_new * KVQ_TILE_TOKENS, P.app_t_old,
-                                     P.app_t_old + 1, P.app_gspan, nullptr, nullptr, 0, lane);
-        } else
-#endif
-        {
-            kvq_dev::append16_tile(code, in_k, 0, tile_new * KVQ_TILE_TOKENS, P.app_t_old, P.app_t_old + 1, lane, P.app_rope,
-                                   P.app_rinv ? P.app_rinv + hk * KVQ_D : nullptr);
-            kvq_dev::append16_tile(code + 512u * 16, in_v, 1, tile_new * KVQ_TILE_TOKENS, P.app_t_old, P.app_t_old + 1, lane,
-                                   nullptr, nullptr);
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
     KVQ_STAMP(1);
     QOps Q;
     Q.cls = -1;
@@ -1133,11 +1236,10 @@ __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShare
     if (lane < 8) reinterpret_cast<uint32_t*>(my_meta + KVQ_WAVE_LDS_CONST)[lane] = lane < 4 ? 0x3c003c00u : 0u;
     for (int pc = p_first; pc < p_last; pc += KVQ_DESC_CACHE) {
         const int pn = min(KVQ_DESC_CACHE, p_last - pc);
-        const bool reserve = appends && pc + KVQ_DESC_CACHE >= p_last;  // the window that ends with the new tile
         if (pc != p_first) {  // further descriptor windows of a very long range
             __syncthreads();
             if (tid < pn) desc_lds[tid] = reinterpret_cast<const u32x4*>(P.table)[pc + tid];
-            if (tid == 0) claim_ctr = reserve ? KVQ_ATTN_WAVES - 1 : KVQ_ATTN_WAVES;
+            if (tid == 0) claim_ctr = KVQ_ATTN_WAVES;
             __syncthreads();
         }
         ctx.page0 = pc;
@@ -1149,33 +1251,12 @@ __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShare
         if (n_t <= 0) continue;
         const int singles = (tpp & 1) ? n_t : (pc + KVQ_DESC_CACHE >= p_last ? min(KVQ_TAIL_SINGLES, n_t) : 0);
         ctx.n_pairs = (n_t - singles) >> 1;
-        const int n_all = n_t - ctx.n_pairs;
-        // The first chunk of every wavefront is fixed, from then on chunks are claimed one at a time.  Normally it
-        // is the wavefront's own index.  With a fused append the last chunk is kept out of the claimable range:
-        // wavefront 0 starts with it, wavefronts 1..7 with chunks 0..6.
-        int first;
-        if (!reserve) {
-            ctx.n_chunks = n_all;
-            first = wave;
-            ctx.static_stride = KVQ_ATTN_WAVES;
-            ctx.next_static = P.deterministic ? wave + KVQ_ATTN_WAVES : -1;
-            start_desc(ctx, first);
-        } else {
-            ctx.static_stride = KVQ_ATTN_WAVES - 1;
-            if (wave == 0) {
-                first = n_all - 1;
-                ctx.next_static = P.deterministic ? 0x3fffff00 : -1;  // deterministic mode: nothing after it
-                ctx.n_chunks = n_all;
-                start_desc(ctx, first);
-            } else {
-                first = wave - 1;
-                ctx.next_static = P.deterministic ? wave - 1 + (KVQ_ATTN_WAVES - 1) : -1;
-                ctx.n_chunks = n_all - 1;
-                start_desc(ctx, first);
-            }
-        }
+        ctx.n_chunks = n_t - ctx.n_pairs;
+        // The first chunk of every wavefront is the one of its own index, from then on chunks are claimed one at a time.
+        ctx.static_stride = KVQ_ATTN_WAVES;
+        ctx.next_static = P.deterministic ? wave + KVQ_ATTN_WAVES : -1;
+        start_desc(ctx, wave);
         ctx.next = finish_desc(ctx);
-        ctx.n_chunks = reserve ? n_all - 1 : n_all;
         while (ctx.next.bits != 0u) {
             switch (ctx.next.bits) {
                 case 16:
@@ -1196,7 +1277,7 @@ __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShare
     }
 
     KVQ_STAMP(2);
-    finish_workgroup(P, sh, st, split, unit);
+    finish_workgroup<I16, APPEND>(P, sh, st, split, unit);
 }
 
 }  // namespace

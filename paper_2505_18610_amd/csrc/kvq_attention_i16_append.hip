@@ -1,8 +1,6 @@
-// Decode attention over a cache with an integer 16-bit tier, with the one-token append of kvq_append_decode_attention in
-// front: the workgroup that owns the last tile quantizes the new token (Eq. 1-2 with 2^16 - 1 levels) into the tile's
-// byte planes before it attends.  A translation unit of its own, like the ragged-batch kernels: what shares a unit
-// with the main kernels changes their inlining and register allocation.
-#define KVQ_WITH_I16_APPEND
+// Decode attention over a cache with an integer 16-bit tier, with the one-token append of kvq_append_decode_attention: the
+// new token is quantized (Eq. 1-2 with 2^16 - 1 levels) inside the launch.  A translation unit of its own, like the
+// ragged-batch kernels: what shares a unit with the main kernels changes their inlining and register allocation.
 #include "kvq_attention_body.h"
 
 namespace {

@@ -518,7 +518,6 @@ namespace {
 
 // What a deferred single-token append into the 16-bit tier leaves for the attention launch to do.
 struct DeferredAppend {
-    bool int16_too = false;  // in: the attention launch that follows can also append into the integer 16-bit tier
     bool active = false;
     int t_old = 0;
     KvqPageDesc desc{};
@@ -636,7 +635,7 @@ kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, 
         L.poisoned = true;
         return st;
     }
-    if (!c->dry && defer && n_new == 1 && e == 16 && (!c->int16() || defer->int16_too)) {
+    if (!c->dry && defer && n_new == 1 && e == 16) {
         defer->active = true;
         defer->t_old = t_old;
         defer->desc = c->desc(L.pages[(size_t)(t_old / P)]);
@@ -773,7 +772,9 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     if (c->dry) return KVQ_E_STATE;
     Layer& L = c->layers[(size_t)layer];
     if (L.T == 0 || L.poisoned) return KVQ_E_STATE;
-    const int n_tiles = (L.T + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
+    // a token that the launch itself appends is not read from the cache: the tiles of the older ones are split
+    const int n_tokens = app && app->active ? app->t_old : L.T;
+    const int n_tiles = (n_tokens + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
     int n_splits = c->splits_override;
     if (n_splits <= 0) {
         // One workgroup per compute unit when a good part of the tiles is 2 bits wide (those are bound by vector
@@ -801,7 +802,7 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     p.part_ml = reinterpret_cast<float*>(c->arena + c->part_ml_off);
     p.counters = reinterpret_cast<uint32_t*>(c->arena + c->counters_off);
     p.flags = c->flags_dev();
-    p.n_tokens = L.T;
+    p.n_tokens = n_tokens;
     p.tiles_per_page = c->tpp;
     p.tpp_magic = c->tpp > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)c->tpp - 1) / (uint64_t)c->tpp) : 0u;
     p.gqa = c->gqa;
@@ -970,7 +971,6 @@ kvq_status_t kvq_append_decode_attention(kvq_cache_t* c, int32_t layer, const vo
     if (!q_dev || !out_dev) return KVQ_E_INVALID;  // nothing may be appended when the attention cannot follow
     if (c && c->dry) return KVQ_E_STATE;
     DeferredAppend app;
-    app.int16_too = true;
     kvq_status_t st = append_impl(c, layer, k_dev, v_dev, 1, 0, cos_sin_dev, hip_stream, &app);
     if (st != KVQ_OK) return st;
     return attention_impl(c, layer, q_dev, out_dev, out_is_fp32, softmax_scale, hip_stream, &app, k_dev, v_dev, cos_sin_dev);

@@ -32,7 +32,7 @@ struct KvqAttnParams {
     float* part_ml;            // [unit][split][16] pairs (running max in log2 units, sum)
     uint32_t* counters;        // [unit] arrival counters of the fused merge (kept at zero between launches)
     const uint32_t* flags;     // [0] bit 0: some V scale of the cache is >= 256 (set by the quantizing kernels)
-    int32_t n_tokens;
+    int32_t n_tokens;          // tokens read from the cache (without the one this launch appends)
     int32_t tiles_per_page;
     uint32_t tpp_magic;        // ceil(2^32 / tiles_per_page) (unused when tiles_per_page == 1)
     int32_t gqa;               // query heads per KV head
@@ -45,8 +45,8 @@ struct KvqAttnParams {
     int32_t int16_tier;        // 1: 16-bit pages hold integer codes in byte planes (selects the kernel)
     float scale_log2;          // softmax scale * log2(e)
     int32_t split_begin[KVQ_MAX_SPLITS + 1];  // tile index where each split starts
-    // a one-token append into the 16-bit tier done by the workgroup that owns the last tile (app_t_old < 0: none)
-    int32_t app_t_old;         // tokens before the append; n_tokens already counts the new one
+    // a one-token append into the 16-bit tier done by the workgroup of a unit's last split (app_t_old < 0: none)
+    int32_t app_t_old;         // tokens before the append
     KvqPageDesc app_desc;      // page of the new token
     const void* app_k;         // fp16 [batch, n_kv_heads, 1, 128]
     const void* app_v;

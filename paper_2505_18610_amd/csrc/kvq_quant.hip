@@ -151,8 +151,6 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
 
 // Append into the integer 16-bit tier: Eq. 1-2 with 2^16 - 1 levels by the same owner lanes; the high and the low
 // bytes of the codes then travel through LDS and into the tile's two byte planes like two 8-bit tiles.
-// (The same steps as kvq_q::append_i16_string, which the attention kernel uses for its fused one-token append, written
-// out here: as a call of that function this kernel measured 15 % slower on bulk appends, forced inlining or not.)
 __global__ __launch_bounds__(64) void kvq_append_i16_kernel(uint8_t* __restrict__ arena,
                                                             const KvqPageDesc* __restrict__ table,
                                                             const uint16_t* __restrict__ k_in,

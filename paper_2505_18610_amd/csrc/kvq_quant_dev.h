@@ -1,6 +1,5 @@
 // Device code of the quantizers shared by the append, requantization and attention kernels (gfx950): Eq. 1-2 by
-// "owner" lanes, the way codes travel through LDS into the tile layout of kvq_layout.h, and the append of new tokens
-// into a tile of the integer 16-bit tier.
+// "owner" lanes and the way codes travel through LDS into the tile layout of kvq_layout.h.
 #ifndef KVQ_QUANT_DEV_H
 #define KVQ_QUANT_DEV_H
 
@@ -276,86 +275,6 @@ __device__ inline KvqPageDesc append_desc(const KvqPageDesc* table, const KvqApp
         asm volatile("" : "+s"(r.code_off256), "+s"(r.meta_off256));
     }
     return r;
-}
-
-// Appends the tokens [t_old, t_new) that fall into one tile of the integer 16-bit tier to its K (which = 0) or V (1)
-// string: Eq. 1-2 with 2^16 - 1 levels by the owner lanes; the high and the low bytes of the codes then travel through
-// LDS into the tile's two byte planes like two 8-bit tiles.  A tile that already holds tokens gets the bytes of the new
-// tokens only (the append that started the tile has zeroed the slots and the metadata of the tokens to come); a new
-// tile is written whole.  One wavefront.
-//   code: the string (its high-byte plane; the low-byte plane follows), meta: the tile's metadata,
-//   in: fp16 rows [t_new - t_old][128] of this (sequence, KV head), tok0: first token of the tile,
-//   rope: [t_new - t_old][128] cos | sin rows or null, rinv: [n_kv_heads][128] reciprocal reparameterization factors or
-//   null, head: this unit's KV head,
-//   lds: scratch of this wavefront alone.
-__device__ __forceinline__ void append_i16_string(uint8_t (&lds)[2][KVQ_LDS_CODES], uint8_t* __restrict__ code,
-                                         uint8_t* __restrict__ meta, const uint16_t* __restrict__ in, int which, int tok0,
-                                         int t_old, int t_new, int gspan, const float* __restrict__ rope,
-                                         const float* __restrict__ rinv, int head, int lane) {
-    const int j = lane >> 4, n = lane & 15;
-    const int grp = lane & 3;
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int tl = 16 * pass + (lane >> 2);
-        const int tok = tok0 + tl;
-        const bool isnew = tok >= t_old && tok < t_new;
-        uint32_t w[16];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (isnew) {
-                const uint16_t* row = in + (uint64_t)(tok - t_old) * KVQ_D;
-                if (which) v = *reinterpret_cast<const u32x4*>(row + 32 * grp + 8 * c);
-                else v = load_key8(row, 32 * grp + 8 * c, rope ? rope + (uint64_t)(tok - t_old) * KVQ_D : nullptr,
-                                   rinv ? rinv + head * KVQ_D : nullptr);
-            }
-            w[4 * c] = v.x; w[4 * c + 1] = v.y; w[4 * c + 2] = v.z; w[4 * c + 3] = v.w;
-        }
-        float codes[32], lo[32];
-        uint16_t S, Z;
-        quantize_owner<16>(w, codes, &S, &Z, gspan);
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {  // exact: integers below 2^16
-            const float hi = floorf(codes[e] * 0.00390625f);
-            lo[e] = codes[e] - 256.0f * hi;
-            codes[e] = hi;
-        }
-        scatter_codes(lds[0], which, tl, grp, codes);
-        scatter_codes(lds[1], which, tl, grp, lo);
-        if (tok >= t_old) store_meta_owner(meta, which, tl, grp, S, Z);
-    }
-    wave_sync_lds();
-    const bool has_old = tok0 < t_old;  // then only the bytes of the new tokens are stored: nothing is read back
-#pragma unroll
-    for (int plane = 0; plane < 2; ++plane) {
-        uint32_t str[16];
-        gather_string<8>(lds[plane], which, lane, str);
-        uint8_t* dst = code + plane * (512u * 8);
-        if (!has_old) {
-            store_chunks<8>(dst, lane, str);
-        } else if (!which) {  // K: dwords 8 sub .. 8 sub + 7 of a lane are one token
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                const int tok = tok0 + 8 * (n >> 2) + 4 * sub + (n & 3);
-                if (tok >= t_old && tok < t_new) {
-#pragma unroll
-                    for (int c = 2 * sub; c < 2 * sub + 2; ++c)
-                        *reinterpret_cast<u32x4*>(dst + (c * 64 + lane) * 16) =
-                            u32x4{str[4 * c], str[4 * c + 1], str[4 * c + 2], str[4 * c + 3]};
-                }
-            }
-        } else {              // V: slot 4 d + e of a lane is token 8 j + ((4 d + e) & 7)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int tok = tok0 + 8 * j + i;
-                if (tok >= t_old && tok < t_new) {
-#pragma unroll
-                    for (int d = (i >> 2); d < 16; d += 2)
-                        dst[((d >> 2) * 64 + lane) * 16 + (d & 3) * 4 + (i & 3)] = (uint8_t)(str[d] >> (8 * (i & 3)));
-                }
-            }
-        }
-    }
 }
 
 }  // namespace kvq_q
