@@ -753,24 +753,6 @@ __device__ inline void run_chunks(WaveState& st, QOps& Q, const _Float16* q_lds,
     }
 }
 
-// Device-scope (all XCDs) relaxed accesses: they go through to memory instead of living in one XCD's L2, so
-// split partials can be handed to the merging workgroup without whole-cache write-backs or invalidations.
-__device__ inline void store_agent(float* p, float v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline float load_agent(const float* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ inline float2v load_pair(const float* p, bool agent) {  // 8 bytes at p (8-byte aligned)
-    if (agent) {
-        const unsigned long long u = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-        return float2v{__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32))};
-    }
-    return *reinterpret_cast<const float2v*>(p);
-}
-
 #define KVQ_DESC_CACHE 256  // page descriptors staged in LDS per chunk of the split's range
 #define KVQ_OPAD 132  // padded row of the LDS reduction slab (floats)
 
@@ -801,94 +783,102 @@ struct AttnShared {
 #define KVQ_STAMP(k) do { } while (0)
 #define KVQ_STAMP_ID() do { } while (0)
 #endif
-#define KVQ_MERGE_LDS_FLOATS (KVQ_MAX_SPLITS * 16 * 3 + 16 + (KVQ_ATTN_THREADS / 32) * 32 * 4)
+// Maximum / sum over the 32 lanes of a half wavefront, in every lane, in a fixed order: four steps inside a row of 16 lanes
+// as data-parallel moves (a shuffle through LDS costs several times their latency), the step across rows as a swizzle.
+template <bool SUM>
+__device__ inline float reduce32(float x) {
+    const auto step = [](float a, float b) { return SUM ? a + b : fmaxf(a, b); };
+#define KVQ_DPP(ctrl) __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), ctrl, 0xf, 0xf, true))
+    x = step(x, KVQ_DPP(0xB1));   // quad_perm 1 0 3 2
+    x = step(x, KVQ_DPP(0x4E));   // quad_perm 2 3 0 1
+    x = step(x, KVQ_DPP(0x141));  // row_half_mirror
+    x = step(x, KVQ_DPP(0x140));  // row_mirror
+#undef KVQ_DPP
+    return step(x, __uint_as_float((uint32_t)__builtin_amdgcn_ds_swizzle((int)__float_as_uint(x), 0x401F)));  // lane ^ 16
+}
+
+#define KVQ_MERGE_LDS_FLOATS ((KVQ_ATTN_THREADS / 32) * (KVQ_MAX_SPLITS + 32 * 4))
 
 // Merge of the split partials of one unit by a workgroup of KVQ_ATTN_THREADS threads.  Threads work in 16 slots
 // of 32 (one head, 4 channels per thread); with fewer than 16 heads the splits of a head are dealt to several
-// slot groups.  Every global load is issued before the first one is waited for, so the merge costs one memory
-// round trip, three barriers and the store.  Per split the partials hold (max, sum) pairs per head and the
-// un-normalised output rows.  lds: KVQ_MERGE_LDS_FLOATS floats.  Call it with the whole workgroup.
+// slot groups.  Per split the partials hold (max, sum) pairs per head and the un-normalised output rows.
+// What bounds it is latency: one workgroup per unit, a trip to memory and what depends on it.  Every load is issued before
+// the first wait, and every slot works out the weights of its head's splits by itself from the pairs, which arrive
+// first (a lane takes up to four splits; maximum and denominator are half-wavefront reductions), so that no barrier
+// stands between the loads and the sum; one barrier combines the slot groups.  lds: KVQ_MERGE_LDS_FLOATS floats.  Call it with the whole workgroup.
 template <bool AGENT>
 __device__ inline void merge_splits(const KvqAttnParams& P, int unit, int tid, float* lds) {
     const int g = P.gqa, ns = P.n_splits;
     const int b = unit / P.n_kv_heads, hk = unit - b * P.n_kv_heads;
-    const float* po = P.part_o + (size_t)unit * ns * 16 * KVQ_D;
-    const float* pml = P.part_ml + (size_t)unit * ns * 32;
-    float* ml_lds = lds;                               // [split][16] (m, l)
-    float* f_lds = lds + KVQ_MAX_SPLITS * 32;          // [split][16] weight of the split in the merged sum
-    float* invl_lds = f_lds + KVQ_MAX_SPLITS * 16;     // [16]
-    float* rec_lds = invl_lds + 16;                    // [slot][32][4]
+    float* rec_lds = lds + (KVQ_ATTN_THREADS / 32) * KVQ_MAX_SPLITS;  // [slot][32][4]
     const int slots = KVQ_ATTN_THREADS >> 5;           // 16 >= g
     const int G = max(1, min(slots / g, ns));          // slot groups sharing the splits of one head
     const int slot = tid >> 5, d4 = tid & 31;
     const int sgi = slot / g, head = slot - sgi * g;
     const bool active = sgi < G;
-    // ---- every load of the first round: (m, l) pairs, then this thread's share of the partial outputs
-    float2v mlr[4];
+    float* const f_lds = lds + slot * KVQ_MAX_SPLITS;  // weights of this slot's head, per split
+    // The unit's pairs and partial outputs as buffers of ns splits: no branch per lane -- a split index beyond ns is out
+    // of range and reads zeros, and so does an idle thread, whose offset is put out of range.  AGENT: device-scope
+    // loads (sc1).  A load instruction costs its issue slots whether or not it is in range (16 cycles of the compute unit
+    // each), so their number follows the split count in steps.
+    constexpr int AUX = AGENT ? 16 : 0;
+    const __amdgpu_buffer_rsrc_t pairs = __builtin_amdgcn_make_buffer_rsrc(
+        P.part_ml + (size_t)unit * ns * 32, 0, ns * 32 * (int)sizeof(float), 0x00020000);
+    const __amdgpu_buffer_rsrc_t slab = __builtin_amdgcn_make_buffer_rsrc(
+        P.part_o + (size_t)unit * ns * 16 * KVQ_D, 0, ns * 16 * KVQ_D * (int)sizeof(float), 0x00020000);
+    u32x2 ml[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const int e = tid + k * KVQ_ATTN_THREADS;      // pair index: split * g + head
-        mlr[k] = float2v{-INFINITY, 0.f};
-        if (e < ns * g) { const int sp = e / g, h = e - sp * g; mlr[k] = load_pair(pml + sp * 32 + 2 * h, AGENT); }
+        ml[k] = u32x2{0u, 0u};
+        const uint32_t off = active ? (uint32_t)((d4 + 32 * k) * 32 + 2 * head) * 4u : 0x80000000u;
+        if (32 * k < ns) ml[k] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(pairs, (int)off, 0, AUX));
     }
-    // The unit's partial outputs as a buffer of ns splits: 16-byte loads (half the load instructions of 8-byte pairs,
-    // and their issue is what the merge of many splits waits for), no branch -- a split index beyond ns is out of
-    // range and reads zeros, and so does an idle thread, whose offset is put out of range.  AGENT: device-scope
-    // loads (sc1), as the 8-byte atomic loads of the (m, l) pairs are.
-    const __amdgpu_buffer_rsrc_t slab =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(po), 0, ns * 16 * KVQ_D * (int)sizeof(float), 0x00020000);
-    // A load instruction costs its issue slots whether or not it is in range, so with few splits per slot group
-    // only the first four are issued.
-    const bool many = ns > 4 * G;
+    const int per_slot = (ns + G - 1) / G;             // splits per slot group
     float4v v[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         const int sp = sgi + k * G;
         const uint32_t off = active ? (uint32_t)((sp * 16 + head) * KVQ_D + 4 * d4) * 4u : 0x80000000u;
         v[k] = float4v{0.f, 0.f, 0.f, 0.f};
-        if (k < 4 || many)
-            v[k] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(slab, (int)off, 0, AGENT ? 16 : 0));
+        if (k < 2 || (k < 4 && per_slot > 2) || (k < 8 && per_slot > 4) || per_slot > 8)
+            v[k] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(slab, (int)off, 0, AUX));
     }
+    // ---- the head's common maximum, weights and denominator, by the slot's 32 lanes
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (d4 + 32 * k < ns) m = fmaxf(m, __uint_as_float(ml[k].x));
+    m = reduce32<false>(m);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const int e = tid + k * KVQ_ATTN_THREADS;
-        if (e < ns * g) { const int sp = e / g, h = e - sp * g; ml_lds[(sp * 16 + h) * 2] = mlr[k][0]; ml_lds[(sp * 16 + h) * 2 + 1] = mlr[k][1]; }
-    }
-    __syncthreads();
-    // ---- per head (slot = head, 32 lanes over the splits): common maximum, weights, denominator
-    if (slot < g) {
-        float m = -INFINITY;
-        for (int sp = d4; sp < ns; sp += 32) m = fmaxf(m, ml_lds[(sp * 16 + slot) * 2]);
-#pragma unroll
-        for (int o = 1; o < 32; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
-        float l = 0.f;
-        for (int sp = d4; sp < ns; sp += 32) {
-            const float ms = ml_lds[(sp * 16 + slot) * 2];
+        if (d4 + 32 * k < ns) {
+            const float ms = __uint_as_float(ml[k].x);
             const float f = (ms == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms - m);
-            f_lds[sp * 16 + slot] = f;
-            l += ml_lds[(sp * 16 + slot) * 2 + 1] * f;
+            f_lds[d4 + 32 * k] = f;
+            l = fmaf(__uint_as_float(ml[k].y), f, l);
         }
-        // fixed-order tree: the same for both merge variants and from launch to launch
-#pragma unroll
-        for (int o = 1; o < 32; o <<= 1) l += __shfl_xor(l, o);
-        if (d4 == 0) invl_lds[slot] = 1.0f / l;
     }
-    __syncthreads();
-    // ---- weighted sum of this thread's splits (further rounds only beyond 16 * G splits)
+    l = reduce32<true>(l);
+    wave_lds_sync();  // a slot lies in one wavefront
+    // ---- weighted sum of this thread's splits (further rounds, eight loads at a time, only beyond 16 * G splits)
     float4v acc = {0.f, 0.f, 0.f, 0.f};
     if (active) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int sp = sgi + k * G;
-            if (sp < ns) {
-                const float f = f_lds[sp * 16 + head];
-                acc += v[k] * f;
-            }
+            if (sp < ns) acc += v[k] * f_lds[sp];
         }
-        for (int sp = sgi + 16 * G; sp < ns; sp += G) {
-            const float* src = po + ((size_t)sp * 16 + head) * KVQ_D + 4 * d4;
-            const float2v a = load_pair(src, AGENT), c2 = load_pair(src + 2, AGENT);
-            acc += float4v{a[0], a[1], c2[0], c2[1]} * f_lds[sp * 16 + head];
+        for (int k0 = 16; k0 < per_slot; k0 += 8) {
+            float4v w[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                w[k] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(
+                    slab, (((sgi + (k0 + k) * G) * 16 + head) * KVQ_D + 4 * d4) * 4, 0, AUX));
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int sp = sgi + (k0 + k) * G;
+                if (sp < ns) acc += w[k] * f_lds[sp];
+            }
         }
     }
     if (G > 1) {  // combine the slot groups in a fixed order
@@ -898,7 +888,7 @@ __device__ inline void merge_splits(const KvqAttnParams& P, int unit, int tid, f
             for (int k = 1; k < G; ++k) acc += *reinterpret_cast<const float4v*>(rec_lds + (size_t)((k * g + head) * 32 + d4) * 4);
     }
     if (active && sgi == 0) {
-        const float inv = invl_lds[head];
+        const float inv = 1.0f / l;
         const size_t oi = ((size_t)b * P.n_q_heads + hk * g + head) * KVQ_D + 4 * d4;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
