@@ -763,6 +763,18 @@ void tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles, int* n2, int
     }
 }
 
+// Most splits of one (sequence, KV head) that pay.  A range of up to 20 tiles is left to one workgroup, whose eight
+// wavefronts take two or three tiles each: publishing and merging partials costs 2.5 us, more than halving such a range
+// saves (10 tiles: 6.9 us in one split, 8.7 at best in several; 20 tiles of 16 bits 9.1 and 9.0; 32 tiles 10.3 and 9.5).
+// Beyond that a split saves its share of the range's time (0.9 us per 1,000 units of tile cost) and costs about 0.07 us of
+// the merge, which is least at sqrt(cost / 80) splits: 24 tiles of mixed widths 9.3 us with 8 splits (11.0 with two of
+// 12 tiles, the former bound of 16 tiles per split), 79 tiles of 16 bits 10.6 us with 16 (11.9 with 5), 128 tiles of 2 bits
+// 10.8 us with 12 (11.5 with 8), 128K tokens of 2 bits 21.6 us with 64 and 22.9 with 128.
+int useful_splits(uint64_t cost, int n_tiles) {
+    if (n_tiles <= 20) return 1;
+    return std::max(1, std::min(std::min(n_tiles, KVQ_MAX_SPLITS), (int)std::sqrt((double)cost / 80.0)));
+}
+
 // Fills the parameter block of one attention launch over block `layer`.  wgs_share > 0: the number of workgroups this
 // cache may use (its share of a ragged batch); 0: the whole device.
 kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, void* out_dev, int32_t out_is_fp32,
@@ -778,17 +790,19 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     int n_splits = c->splits_override;
     if (n_splits <= 0) {
         // One workgroup per compute unit when a good part of the tiles is 2 bits wide (those are bound by vector
-        // issue and want every unit).  A block of wider tiles is bound by HBM, and there three quarters of the
-        // units stream measurably faster than all of them (4 to 7 % on 4-, 8- and 16-bit blocks).
+        // issue and want every unit) or the ranges are short (what counts is the length of one: 8K tokens of 4 bits x 32
+        // units 15.1 us on all units, 16.5 on three quarters).  A block of long ranges of wider tiles is bound by HBM, and
+        // there three quarters of the units stream measurably faster than all of them (4 to 7 % at 32K tokens x 64 units
+        // of 4, 8 and 16 bits, 37,000 units of cost per workgroup; even between 9,000 and 19,000).
+        int n2 = 0, n_all = 0;
+        uint64_t cost = 0;
+        tile_census(c, L, n_tiles, &n2, &n_all, &cost);
         int wgs = wgs_share;
         if (wgs <= 0) {
-            int n2 = 0, n_all = 0;
-            uint64_t cost = 0;
-            tile_census(c, L, n_tiles, &n2, &n_all, &cost);
             wgs = c->target_workgroups;
-            if (4 * n2 < n_all) wgs = std::max(c->units, wgs * 3 / 4);
+            if (4 * n2 < n_all && cost * (uint64_t)c->units > 12000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);
         }
-        n_splits = std::min(wgs / std::max(1, c->units), (n_tiles + 15) / 16);
+        n_splits = std::min(wgs / std::max(1, c->units), useful_splits(cost, n_tiles));
     }
     n_splits = std::max(1, std::min(n_splits, std::min(KVQ_MAX_SPLITS, n_tiles)));
     plan_splits(c, L, n_tiles, n_splits);
@@ -875,7 +889,7 @@ kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, co
     }
     // The device's workgroups are dealt to the caches so that the most loaded workgroup is as light as possible:
     // every cache starts with one split per (sequence, KV head); the cache whose workgroups carry the most tile
-    // time gets one more split, as long as the workgroups last (and its splits keep 16 tiles or more).
+    // time gets one more split, as long as the workgroups last (and the cache's splits pay).
     std::vector<uint64_t> cost((size_t)n);  // tile time of one (sequence, KV head) of the cache
     std::vector<int> splits((size_t)n, 1), max_splits((size_t)n);
     int used = 0;
@@ -886,7 +900,7 @@ kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, co
         const int n_tiles = (L.T + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
         int a = 0, b = 0;
         tile_census(c, L, n_tiles, &a, &b, &cost[(size_t)i]);
-        max_splits[(size_t)i] = std::max(1, std::min(KVQ_MAX_SPLITS, (n_tiles + 15) / 16));
+        max_splits[(size_t)i] = useful_splits(cost[(size_t)i], n_tiles);
         used += c->units;
     }
     // (every compute unit is used: with ranges of unequal length the heaviest workgroup decides the launch time,

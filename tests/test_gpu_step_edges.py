@@ -1,0 +1,75 @@
+"""Decode attention where its split plan and merge change course, and the fused append at the edges of tiles and pages."""
+import numpy as np
+import pytest
+import torch
+
+import kvq_synth
+import paper_2505_18610_amd as kq
+from gpu_util import MAX_ABS, REL_L2, append_both, assert_same_cache, attention_errors, check_attention, dev, make_pair
+
+pytestmark = pytest.mark.gpu
+
+
+# gqa g leaves 16 // g slot groups: 16 splits per group in the first round of loads, eight more in each further one; a lane
+# takes the (max, sum) pairs of four splits 32 apart
+@pytest.mark.parametrize("g", [1, 3, 7, 16])
+def test_merge_of_any_split_count(g):
+    T, P = 128 * 32 - 5, 64
+    oc, gc = make_pair(1, 1, 2 * g, 2, T, P)
+    K, V = kvq_synth.make_kv(71, 0, 1, 2, 0, T)
+    append_both(oc, gc, 0, K[:, :, :2048], V[:, :, :2048], 4)
+    append_both(oc, gc, 0, K[:, :, 2048:], V[:, :, 2048:], 16)
+    q = kvq_synth.make_q(71, 0, 1, 2 * g, T - 1)
+    G = 16 // g
+    for splits in sorted({1, 2, 3, G, G + 1, 2 * G + 1, 4 * G + 1, 8 * G + 1, 16 * G, 16 * G + 1, 24 * G + 1, 31, 32, 33, 65, 97, 127, 128}):
+        if splits <= 128:
+            for fused in (1, 0):
+                gc.kvq_cache_set_option(kq.KVQ_OPT_SPLITS, splits)
+                gc.kvq_cache_set_option(kq.KVQ_OPT_FUSED_MERGE, fused)
+                check_attention(oc, gc, 0, q)
+    gc.close()
+
+
+@pytest.mark.parametrize("tiles", [1, 8, 19, 20, 21, 22, 33, 100])
+def test_planned_splits(tiles):
+    T = 32 * tiles - 3
+    oc, gc = make_pair(1, 2, 10, 2, T, 32)
+    K, V = kvq_synth.make_kv(72, 0, 2, 2, 0, T)
+    wide = 32 * (tiles // 2)
+    if wide:
+        append_both(oc, gc, 0, K[:, :, :wide], V[:, :, :wide], 2)
+    append_both(oc, gc, 0, K[:, :, wide:], V[:, :, wide:], 16)
+    check_attention(oc, gc, 0, kvq_synth.make_q(72, 0, 2, 10, T - 1))
+    gc.close()
+
+
+@pytest.mark.parametrize("tier16", [0, 1])
+@pytest.mark.parametrize("group", [32, 64, 128])
+@pytest.mark.parametrize("batched", [False, True])
+def test_fused_append_from_the_first_token_on(tier16, group, batched):
+    """The first token of a block, of a tile and of a page, and one in the middle of each; the last token of a page."""
+    B, Hkv, g, P, T = 2, 2, 3, 64, 135
+    oc, gc = make_pair(1, B, g * Hkv, Hkv, T, P, group=group, tier16=tier16)
+    K, V = kvq_synth.make_kv(73, 0, B, Hkv, 0, T)
+    V[:, :, 40] *= 50.0
+    t = 0
+    for stop in (3, 31, 34, 63, 66, 95, 98, 127, 130, T):
+        while t < stop:
+            k, v, q = K[:, :, t:t + 1], V[:, :, t:t + 1], kvq_synth.make_q(73, 0, B, g * Hkv, t)
+            out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+            oc.append(0, k, v, 0)
+            if batched:
+                kq.kvq_append_decode_attention_batch([gc], 0, [dev(k)], [dev(v)], [dev(q)], [out])
+            else:
+                gc.kvq_append_decode_attention(0, dev(k), dev(v), dev(q), out)
+            mx, rl = attention_errors(out.cpu().numpy(), oc.attention(0, q))
+            # the bounds of every attention test, the absolute one scaled by the largest value
+            assert mx <= MAX_ABS * max(1.0, float(np.abs(V[:, :, :t + 1]).max()) / 4) and rl <= REL_L2, (t, mx, rl)
+            t += 1
+            if t < stop:  # a bulk append in between: both ways of writing a tile meet in it
+                n = min(stop - 1 - t, 29)
+                if n > 0:
+                    append_both(oc, gc, 0, K[:, :, t:t + n], V[:, :, t:t + n], 0)
+                    t += n
+        assert_same_cache(oc, gc, 0)
+    gc.close()
