@@ -1,6 +1,6 @@
-// Device code shared by the append kernel and the attention kernel: writing new fp16 tokens into a tile of the
-// 16-bit tier (raw values in the tile layout of kvq_layout.h), with the optional rotary embedding (Sec. 3.3, Eq. 9)
-// and channel-wise reparameterization (Sec. 3.3, Eq. 7) of the keys on the way.
+// Device code shared by the append kernels and the attention kernels: the optional rotary embedding (Sec. 3.3, Eq. 9) and
+// channel-wise reparameterization (Sec. 3.3, Eq. 7) of new keys, and the writing of new fp16 tokens into a tile of the
+// 16-bit tier (raw values in the tile layout of kvq_layout.h).
 #ifndef KVQ_APPEND16_H
 #define KVQ_APPEND16_H
 
@@ -14,18 +14,21 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ inline float h2f(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
 __device__ inline uint16_t f2h_rn(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }  // RNE
 
-// K Lambda^{-1} of Eq. 7 on 8 consecutive channels (4 dwords of fp16 pairs): fp32 product with the channel's
-// reciprocal factor, rounded to nearest-even into fp16.
-// The product is rounded to fp32 first and to fp16 second, as two separate IEEE operations: the empty asm keeps the
-// compiler from fusing them into a mixed-precision instruction that rounds the exact product once (1 fp16 ulp apart
-// in about one element of 10^4).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));  // tables of fp32 need not start at a multiple of 16 bytes
+
+// K Lambda^{-1} of Eq. 7 on one pair of channels: fp32 product with the channel's reciprocal factor, rounded to
+// nearest-even into fp16.  The product is rounded to fp32 first and to fp16 second, as two separate IEEE operations: the
+// empty asm keeps the compiler from fusing them into a mixed-precision instruction that rounds the exact product once
+// (1 fp16 ulp apart in about one element of 10^4).
 __device__ inline uint32_t scale_pair(uint32_t w, float r_lo, float r_hi) {
     float lo = h2f((uint16_t)(w & 0xffff)) * r_lo, hi = h2f((uint16_t)(w >> 16)) * r_hi;
-    asm volatile("" : "+v"(lo), "+v"(hi));
+    asm("" : "+v"(lo), "+v"(hi));
     return (uint32_t)f2h_rn(lo) | ((uint32_t)f2h_rn(hi) << 16);
 }
+// 8 consecutive channels; rinv: their reciprocal factors.
 __device__ inline u32x4 scale_keys8(u32x4 v, const float* rinv) {
-    const float4 r0 = *reinterpret_cast<const float4*>(rinv), r1 = *reinterpret_cast<const float4*>(rinv + 4);
+    const f32x4 r0 = *reinterpret_cast<const f32x4_any*>(rinv), r1 = *reinterpret_cast<const f32x4_any*>(rinv + 4);
     return u32x4{scale_pair(v.x, r0.x, r0.y), scale_pair(v.y, r0.z, r0.w), scale_pair(v.z, r1.x, r1.y),
                  scale_pair(v.w, r1.z, r1.w)};
 }
@@ -35,141 +38,136 @@ __device__ inline u32x4 scale_keys8(u32x4 v, const float* rinv) {
 // contracted or fused with the conversion); the result is rounded to fp16.
 __device__ inline uint16_t rope1(uint16_t own, uint16_t partner, float c, float sn, bool upper) {
     float p1 = h2f(own) * c, p2 = h2f(partner) * sn;
-    asm volatile("" : "+v"(p1), "+v"(p2));
+    asm("" : "+v"(p1), "+v"(p2));
     float sum = upper ? p1 + p2 : p1 - p2;
-    asm volatile("" : "+v"(sum));
+    asm("" : "+v"(sum));
     return f2h_rn(sum);
 }
-// Rotary embedding (Sec. 3.3, Eq. 9) of 8 consecutive channels ch0 .. ch0+7 of one token: own = these channels,
-// partner = the channels ch0 +- 64 of the same token, cs = the token's table row [cos 64 | sin 64] (fp32).
-__device__ inline u32x4 rope8(u32x4 own, u32x4 partner, const float* cs, int ch0) {
-    const int i0 = ch0 & 63;
-    const bool upper = ch0 >= 64;
-    const uint32_t* o = reinterpret_cast<const uint32_t*>(&own);
-    const uint32_t* p = reinterpret_cast<const uint32_t*>(&partner);
-    u32x4 out;
-    uint32_t* r = reinterpret_cast<uint32_t*>(&out);
+// Eight consecutive angles of a token's table row [cos 64 | sin 64].
+struct Angles8 { f32x4 c[2], s[2]; };
+__device__ inline Angles8 load_angles8(const float* row, int i0) {
+    Angles8 a;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        a.c[h] = *reinterpret_cast<const f32x4_any*>(row + i0 + 4 * h);
+        a.s[h] = *reinterpret_cast<const f32x4_any*>(row + 64 + i0 + 4 * h);
+    }
+    return a;
+}
+// 8 consecutive channels of one token; partner: the channels +- 64 of the same token.
+__device__ inline u32x4 rope8(u32x4 own, u32x4 partner, const Angles8& a, bool upper) {
+    u32x4 r;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         r[e] = 0u;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-            r[e] |= (uint32_t)rope1((uint16_t)(o[e] >> (16 * h)), (uint16_t)(p[e] >> (16 * h)), cs[i0 + 2 * e + h],
-                                    cs[64 + i0 + 2 * e + h], upper) << (16 * h);
+        for (int h = 0; h < 2; ++h) {
+            const int i = 2 * e + h;
+            r[e] |= (uint32_t)rope1((uint16_t)(own[e] >> (16 * h)), (uint16_t)(partner[e] >> (16 * h)), a.c[i >> 2][i & 3],
+                                    a.s[i >> 2][i & 3], upper) << (16 * h);
+        }
     }
-    return out;
+    return r;
 }
 
-// The new keys' 8 channels ch0.. of the row at `row` (fp16 [128]), rotated and scaled as configured.
-__device__ inline u32x4 load_key8(const uint16_t* row, int ch0, const float* rope_row, const float* rinv_head) {
-    u32x4 v = *reinterpret_cast<const u32x4*>(row + ch0);
-    if (rope_row) v = rope8(v, *reinterpret_cast<const u32x4*>(row + (ch0 ^ 64)), rope_row, ch0);
-    if (rinv_head) v = scale_keys8(v, rinv_head + ch0);
-    return v;
-}
+// The new rows of one unit as a buffer: a lane whose token is not new (before t_old or at or after t_new) gets an offset
+// beyond it (n_new < 2^23 rows of 256 bytes end below 2^31) and reads zeros -- no branch around the loads.
+struct NewRows {
+    __amdgpu_buffer_rsrc_t rsrc;
+    int t_old, n_new;
+    __device__ NewRows(const uint16_t* in, int t_old_, int n_new_)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(in), 0, n_new_ * (KVQ_D * 2), 0x00020000)),
+          t_old(t_old_), n_new(n_new_) {}
+    __device__ uint32_t offset(int tok) const {
+        const uint32_t rel = (uint32_t)(tok - t_old);
+        return rel < (uint32_t)n_new ? rel * (uint32_t)(KVQ_D * 2) : 0x80000000u;
+    }
+    __device__ bool has(int tok) const { return (uint32_t)(tok - t_old) < (uint32_t)n_new; }
+    __device__ u32x4 load(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0); }
+    __device__ u32x4 load_stream(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 2); }
+    // index of the token's table row; tokens that are not new get a row that exists
+    __device__ uint64_t row(int tok) const { return (uint64_t)max(0, min(tok - t_old, n_new - 1)); }
+};
 
-// One wavefront writes the tokens [t_old, t_new) that fall into one K (which = 0) or V (which = 1) tile of a
-// 16-bit page.  code: the tile; in: the unit's new rows, fp16 [t_new - t_old][128]; tok0: the tile's first token.
-// A tile that holds no older token is written in full (slots of tokens that are not there yet are zero, so
-// partially filled tiles stay well defined); otherwise only the new tokens' elements are stored - whole 16-byte
-// chunks for K, single fp16 values for V.  rope: table of the new tokens, fp32 [t_new - t_old][128], or null;
-// rinv_head: the 128 reciprocal reparameterization factors of this KV head, or null (keys only).
-// STREAM: a tile written in full goes out with streaming stores (bulk appends: the tile is read much later; not for a
-// caller that reads the tile back at once).
-template <bool STREAM = false>
-__device__ inline void append16_tile(uint8_t* code, const uint16_t* in, int which, int tok0, int t_old, int t_new,
-                                     int lane, const float* rope, const float* rinv_head) {
+// One wavefront writes the new tokens that fall into one K tile of a 16-bit page.  code: the tile; tok0: its first token.
+// A tile that holds no older token is written in full with streaming stores (it is read much later; slots of tokens that
+// are not there yet are zero, so partially filled tiles stay well defined); otherwise only the new tokens' 16-byte chunks
+// are stored.  rope: table of the new tokens, fp32 [n_new][128], or null; rinv_head: the 128 reciprocal reparameterization
+// factors of this KV head, or null.
+// A lane holds all four channel groups of its two tokens, so the rotation's partner channels are its own registers and
+// eight angles serve two groups; all loads are issued before the arithmetic.  (With the angles read one by one and the
+// partner read again, 8,192 new tokens x 32 units took 271 us with rotation against 56 without.)
+__device__ inline void append16_k_tile(uint8_t* code, const NewRows& rows, int tok0, int lane, const float* rope,
+                                       const float* rinv_head) {
     const int j = lane >> 4, n = lane & 15;
-    const bool has_old = tok0 < t_old;
-    uint16_t raw[64];
-    if (!which) {
+    u32x4 v[2][4];
+    bool isnew[2];
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+        const int tok = tok0 + 8 * (n >> 2) + 4 * sub + (n & 3);
+        isnew[sub] = rows.has(tok);
+        const uint32_t off = rows.offset(tok) + 16u * j;
+#pragma unroll
+        for (int grp = 0; grp < 4; ++grp) v[sub][grp] = rows.load(off + 64u * grp);
+    }
+    if (rope) {
+        Angles8 a[2][2];
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
-            const int tok = tok0 + 8 * (n >> 2) + 4 * sub + (n & 3);
-            const bool isnew = tok >= t_old && tok < t_new;
+            const float* row = rope + rows.row(tok0 + 8 * (n >> 2) + 4 * sub + (n & 3)) * KVQ_D;
 #pragma unroll
-            for (int grp = 0; grp < 4; ++grp) {
-                u32x4 v = {0u, 0u, 0u, 0u};
-                if (isnew)
-                    v = load_key8(in + (uint64_t)(tok - t_old) * KVQ_D, 32 * grp + 8 * j,
-                                  rope ? rope + (uint64_t)(tok - t_old) * KVQ_D : nullptr, rinv_head);
-                const int s0 = (sub * 4 + grp) * 8;
-                raw[s0 + 0] = v.x & 0xffff; raw[s0 + 1] = v.x >> 16;
-                raw[s0 + 2] = v.y & 0xffff; raw[s0 + 3] = v.y >> 16;
-                raw[s0 + 4] = v.z & 0xffff; raw[s0 + 5] = v.z >> 16;
-                raw[s0 + 6] = v.w & 0xffff; raw[s0 + 7] = v.w >> 16;
+            for (int p = 0; p < 2; ++p) a[sub][p] = load_angles8(row, 32 * p + 8 * j);
+        }
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const u32x4 lo = rope8(v[sub][p], v[sub][p + 2], a[sub][p], false);
+                const u32x4 hi = rope8(v[sub][p + 2], v[sub][p], a[sub][p], true);
+                const u32x4 zero = {0u, 0u, 0u, 0u};  // (a rotated zero may come out negative)
+                v[sub][p] = isnew[sub] ? lo : zero;
+                v[sub][p + 2] = isnew[sub] ? hi : zero;
             }
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int tok = tok0 + 8 * j + i;
-            const bool isnew = tok >= t_old && tok < t_new;
-#pragma unroll
-            for (int nt = 0; nt < 8; ++nt)
-                raw[nt * 8 + i] = isnew ? in[(uint64_t)(tok - t_old) * KVQ_D + 16 * nt + n] : (uint16_t)0;
-        }
     }
-    if (has_old) {
-        if (!which) {
+    if (rinv_head) {
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                const int tok = tok0 + 8 * (n >> 2) + 4 * sub + (n & 3);
-                if (tok >= t_old && tok < t_new) {
+        for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-                    for (int c = 4 * sub; c < 4 * sub + 4; ++c)
-                        *reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16) =
-                            u32x4{(uint32_t)raw[8 * c] | ((uint32_t)raw[8 * c + 1] << 16),
-                                  (uint32_t)raw[8 * c + 2] | ((uint32_t)raw[8 * c + 3] << 16),
-                                  (uint32_t)raw[8 * c + 4] | ((uint32_t)raw[8 * c + 5] << 16),
-                                  (uint32_t)raw[8 * c + 6] | ((uint32_t)raw[8 * c + 7] << 16)};
-                }
+            for (int grp = 0; grp < 4; ++grp) v[sub][grp] = scale_keys8(v[sub][grp], rinv_head + 32 * grp + 8 * j);
+    }
+    if (tok0 < rows.t_old) {
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+            if (isnew[sub]) {
+#pragma unroll
+                for (int grp = 0; grp < 4; ++grp)
+                    *reinterpret_cast<u32x4*>(code + ((sub * 4 + grp) * 64 + lane) * 16) = v[sub][grp];
             }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int tok = tok0 + 8 * j + i;
-                if (tok >= t_old && tok < t_new) {
-#pragma unroll
-                    for (int nt = 0; nt < 8; ++nt) {
-                        const int slot = nt * 8 + i;  // 2 bytes at string offset 2 * slot
-                        *reinterpret_cast<uint16_t*>(code + kvq_tile_byte(lane, 2u * slot)) = raw[slot];
-                    }
-                }
-            }
-        }
         return;
     }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const u32x4 v = {(uint32_t)raw[8 * c] | ((uint32_t)raw[8 * c + 1] << 16),
-                         (uint32_t)raw[8 * c + 2] | ((uint32_t)raw[8 * c + 3] << 16),
-                         (uint32_t)raw[8 * c + 4] | ((uint32_t)raw[8 * c + 5] << 16),
-                         (uint32_t)raw[8 * c + 6] | ((uint32_t)raw[8 * c + 7] << 16)};
-        if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16));
-        else *reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16) = v;
-    }
+    for (int c = 0; c < 8; ++c)
+        __builtin_nontemporal_store(v[c >> 2][c & 3], reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16));
 }
 
-// A V tile of a 16-bit page whose tokens are all new, written by one wavefront through LDS: the rows are read with
-// 16-byte loads (a wavefront instruction covers one contiguous KiB of the input), parked as [token][channel] in LDS
-// and picked up in the tile layout (lane (j, n): tokens 8j .. 8j+7 of channels 16 nt + n), where the plain path reads
-// the same 4,096 values with two-byte loads; streaming stores, as the tile is read much later.  Rows are rotated by 32 bytes per 8 tokens so that the four lane
-// quarters, which read rows 8 apart, use different banks.  lds: 8 KiB of this wavefront alone, 16-byte aligned.
-__device__ inline void append16_v_tile_lds(uint8_t* code, const uint16_t* in, int tok0, int t_old, int t_new, int lane,
-                                           uint8_t* lds) {
+// The same for a V tile, through LDS: the rows are read with 16-byte loads (a wavefront instruction covers one contiguous KiB
+// of the input), parked as [token][channel] and picked up in the tile layout (lane (j, n): tokens 8j .. 8j+7 of channels
+// 16 nt + n).  Rows are rotated by 32 bytes per 8 tokens so that the four lane quarters, which read rows 8 apart, use
+// different banks.  lds: 8 KiB of this wavefront alone, 16-byte aligned.
+__device__ inline void append16_v_tile(uint8_t* code, const NewRows& rows, int tok0, int lane, uint8_t* lds) {
     const int j = lane >> 4, n = lane & 15;
+    u32x4 v[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = rows.load_stream(rows.offset(tok0 + 4 * c + j) + 16u * n);
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        const int chunk = c * 64 + lane, tl = chunk >> 4, ch8 = chunk & 15;
-        const int tok = tok0 + tl;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (tok < t_new) v = *reinterpret_cast<const u32x4*>(in + (uint64_t)(tok - t_old) * KVQ_D + 8 * ch8);
-        *reinterpret_cast<u32x4*>(lds + tl * 256 + ((ch8 * 16 + 32 * (tl >> 3)) & 255)) = v;
+        const int tl = 4 * c + j;
+        *reinterpret_cast<u32x4*>(lds + tl * 256 + ((n * 16 + 32 * (tl >> 3)) & 255)) = v[c];
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const bool has_old = tok0 < rows.t_old;  // then only the new tokens' values are stored
 #pragma unroll
     for (int c = 0; c < 8; ++c) {  // chunk c of the lane's string = channel block nt = c, tokens 8j + 0..7
         uint32_t w[4];
@@ -181,7 +179,15 @@ __device__ inline void append16_v_tile_lds(uint8_t* code, const uint16_t* in, in
             const uint32_t hi = *reinterpret_cast<const uint16_t*>(lds + r1 * 256 + col);
             w[e] = lo | (hi << 16);
         }
-        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16));
+        uint8_t* dst = code + (c * 64 + lane) * 16;
+        if (!has_old) {
+            __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(dst));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (rows.has(tok0 + 8 * j + i))
+                    *reinterpret_cast<uint16_t*>(dst + 2 * i) = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+        }
     }
 }
 

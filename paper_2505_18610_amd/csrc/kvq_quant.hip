@@ -12,39 +12,54 @@ namespace {
 
 using namespace kvq_q;
 
-// grid.x = 2 * (tiles touched) (even: K tile, odd: V tile), grid.y = (sequence, KV head) unit, 64 threads.
+// Work of the append kernels: one wavefront per string, a (tile, K | V) of one (sequence, KV head) unit; the WAVES
+// wavefronts of a workgroup take neighbouring strings of a unit and share nothing.  PLAIN instantiations serve keys that
+// arrive rotated in a block without reparameterization (rope and rinv are null): they carry none of that code, which is
+// the bulk of the general kernels' registers.
+// by_unit: the units of a string follow one another in the grid instead of the strings of a unit.  The table rows of the
+// string's tokens, 512 bytes a token and as much as its keys and values in one unit, are then read by all units at about
+// the same time and come from the caches.  For the 16-bit tiers and at least 98,304 rows of all units together: 8,192
+// rotated tokens x 32 units 59 instead of 74 us (raw fp16), 78 instead of 88 (integer tier), 2,048 x 64 34 instead of 44 and
+// 48 instead of 52; 2,048 x 32 (65,536 rows) 22 instead of 21 and 32 instead of 30.  Into 8, 4 and 2 bits, where the
+// arithmetic weighs more, it loses 3 to 7 % at every size.
+template <bool PLAIN, int WAVES>
+__device__ inline bool append_work(int n_strings, int by_unit, int wave, int* string, int* unit) {
+    int s = blockIdx.x;
+    *unit = blockIdx.y;
+    if (!PLAIN && by_unit) { const int q = s / by_unit; *unit = s - q * by_unit; s = q; }
+    *string = s * WAVES + wave;
+    return *string < n_strings;
+}
+
 // Append into the 16-bit tier: the new rows are copied into the tile layout.
+template <bool PLAIN>
 __global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ arena,
                                                           const KvqPageDesc* __restrict__ table,
                                                           const uint16_t* __restrict__ k_in,
                                                           const uint16_t* __restrict__ v_in, int t_old,
                                                           int n_new, int tpp, int tile0, KvqAppendPages ap,
+                                                          int /* group span: nothing is quantized */,
                                                           const float* __restrict__ rinv, int n_kv_heads,
-                                                          const float* __restrict__ rope) {
+                                                          const float* __restrict__ rope, int n_strings, int by_unit) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[32 * 256];
     const int lane = threadIdx.x;
-    const int which = blockIdx.x & 1;
-    const int tile = tile0 + (blockIdx.x >> 1);
-    const int unit = blockIdx.y;
+    int string, unit;
+    if (!append_work<PLAIN, 1>(n_strings, by_unit, 0, &string, &unit)) return;
+    const int which = string & 1;
+    const int tile = tile0 + (string >> 1);
     const int page = tile / tpp, tip = tile - page * tpp;
     const KvqPageDesc pd = append_desc(table, ap, page);
     const uint64_t tslot = (uint64_t)unit * tpp + tip;
     uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * 16);
-    const uint16_t* in = (which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D;
-    if (which && tile * KVQ_TILE_TOKENS >= t_old) {  // a V tile made of new tokens only: through LDS (wavefront-uniform)
-        __shared__ __attribute__((aligned(16))) uint8_t lds[32 * 256];
-        kvq_dev::append16_v_tile_lds(code, in, tile * KVQ_TILE_TOKENS, t_old, t_old + n_new, lane, lds);
-        return;
-    }
-    kvq_dev::append16_tile<true>(code, in, which, tile * KVQ_TILE_TOKENS, t_old, t_old + n_new, lane, which ? nullptr : rope,
-                                 (rinv && !which) ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
+    const kvq_dev::NewRows rows((which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D, t_old, n_new);
+    if (which) kvq_dev::append16_v_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, lds);  // (wavefront-uniform)
+    else if (PLAIN) kvq_dev::append16_k_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, nullptr, nullptr);
+    else kvq_dev::append16_k_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
 }
 
-// Quantizing append (B = 8, 4, 2), built on the row-owner core: grid.x = ceil(n_strings / KVQ_APPEND_WG_WAVES) workgroups,
-// n_strings = 2 * touched tiles (K and V string of each), grid.y = unit; one wavefront per string.
-// PLAIN: keys arrive rotated and the block has no reparameterization (rope and rinv are null): the instantiation
-// carries none of that code, which is the bulk of the general kernel's registers.
-// Four wavefronts per workgroup, each with a (tile, K | V) string of its own and its own LDS: 1 to 2 % faster on bulk
-// appends than one-wavefront workgroups (a quarter of the workgroups to dispatch); nothing is shared between them.
+// Quantizing append (B = 8, 4, 2), built on the row-owner core.
+// Four wavefronts per workgroup, each with a string and LDS of its own: 1 to 2 % faster on bulk appends than one-wavefront
+// workgroups (a quarter of the workgroups to dispatch).
 #define KVQ_APPEND_WG_WAVES 4
 template <int B, bool PLAIN>
 __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(uint8_t* __restrict__ arena,
@@ -54,57 +69,26 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
                                                           int n_new, int tpp, int tile0, KvqAppendPages ap,
                                                           uint32_t* __restrict__ flags, int gspan,
                                                           const float* __restrict__ rinv, int n_kv_heads,
-                                                          const float* __restrict__ rope, int n_strings) {
+                                                          const float* __restrict__ rope, int n_strings, int by_unit) {
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[KVQ_APPEND_WG_WAVES][KVQ_LDS_CODES];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* const lds = lds_all[wave];
     const int lane = threadIdx.x & 63, j = lane >> 4, n = lane & 15;
-    const int string = blockIdx.x * KVQ_APPEND_WG_WAVES + wave;  // (tile, K | V) of this wavefront
-    if (string >= n_strings) return;
+    int string, unit;
+    if (!append_work<PLAIN, KVQ_APPEND_WG_WAVES>(n_strings, by_unit, wave, &string, &unit)) return;
     const int which = string & 1;
     const int tile = tile0 + (string >> 1);
-    const int unit = blockIdx.y;
     const int page = tile / tpp, tip = tile - page * tpp;
     const KvqPageDesc pd = append_desc(table, ap, page);
     const uint64_t tslot = (uint64_t)unit * tpp + tip;
     uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * B);
     uint8_t* meta = arena + (uint64_t)pd.meta_off256 * 256u + tslot * KVQ_META_TILE_BYTES;
-    const int t_new = t_old + n_new, tok0 = tile * KVQ_TILE_TOKENS;
-    const uint16_t* in = (which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D;
+    const int tok0 = tile * KVQ_TILE_TOKENS;
+    const kvq_dev::NewRows rows((which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D, t_old, n_new);
     const int grp = lane & 3;
-    // every load of the tile first (both passes: 8 x 16 bytes per lane in flight), then the arithmetic
     uint32_t w[2][16];
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int tok = tok0 + 16 * pass + (lane >> 2);
-        u32x4 v[4];
-        if (PLAIN || which) {
-            // Buffer loads with the unit's n_new rows as the buffer: a lane whose token is not new (before t_old or at
-            // or after t_new) gets an offset beyond the buffer (n_new < 2^23 rows of 256 bytes end below 2^31) and
-            // reads zeros, which is what such a token quantizes -- no branch around the loads.
-            const __amdgpu_buffer_rsrc_t rows =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(in), 0, n_new * (KVQ_D * 2), 0x00020000);
-            const uint32_t rel = (uint32_t)(tok - t_old);
-            const uint32_t off = (rel < (uint32_t)n_new ? rel * (uint32_t)(KVQ_D * 2) : 0x80000000u) + 64u * grp;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)(off + 16u * c), 0, 0);
-        } else {
-            const bool isnew = tok >= t_old && tok < t_new;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = u32x4{0u, 0u, 0u, 0u};
-            if (isnew) {
-                const uint16_t* row = in + (uint64_t)(tok - t_old) * KVQ_D;
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    v[c] = load_key8(row, 32 * grp + 8 * c, rope ? rope + (uint64_t)(tok - t_old) * KVQ_D : nullptr,
-                                     rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            w[pass][4 * c] = v[c].x; w[pass][4 * c + 1] = v[c].y; w[pass][4 * c + 2] = v[c].z; w[pass][4 * c + 3] = v[c].w;
-        }
-    }
+    load_owner_rows(w, rows, tok0, lane);
+    if (!PLAIN && !which) prepare_owner_keys(w, rows, tok0, lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         const int tl = 16 * pass + (lane >> 2);
@@ -151,58 +135,32 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
 
 // Append into the integer 16-bit tier: Eq. 1-2 with 2^16 - 1 levels by the same owner lanes; the high and the low
 // bytes of the codes then travel through LDS and into the tile's two byte planes like two 8-bit tiles.
+template <bool PLAIN>
 __global__ __launch_bounds__(64) void kvq_append_i16_kernel(uint8_t* __restrict__ arena,
                                                             const KvqPageDesc* __restrict__ table,
                                                             const uint16_t* __restrict__ k_in,
                                                             const uint16_t* __restrict__ v_in, int t_old,
                                                             int n_new, int tpp, int tile0, KvqAppendPages ap,
                                                             int gspan, const float* __restrict__ rinv,
-                                                            int n_kv_heads, const float* __restrict__ rope) {
+                                                            int n_kv_heads, const float* __restrict__ rope,
+                                                            int n_strings, int by_unit) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][KVQ_LDS_CODES];
     const int lane = threadIdx.x, j = lane >> 4, n = lane & 15;
-    const int which = blockIdx.x & 1;
-    const int tile = tile0 + (blockIdx.x >> 1);
-    const int unit = blockIdx.y;
+    int string, unit;
+    if (!append_work<PLAIN, 1>(n_strings, by_unit, 0, &string, &unit)) return;
+    const int which = string & 1;
+    const int tile = tile0 + (string >> 1);
     const int page = tile / tpp, tip = tile - page * tpp;
     const KvqPageDesc pd = append_desc(table, ap, page);
     const uint64_t tslot = (uint64_t)unit * tpp + tip;
     uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * 16);
     uint8_t* meta = arena + (uint64_t)pd.meta_off256 * 256u + tslot * KVQ_META_TILE_BYTES;
-    const int t_new = t_old + n_new, tok0 = tile * KVQ_TILE_TOKENS;
-    const uint16_t* in = (which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D;
+    const int tok0 = tile * KVQ_TILE_TOKENS;
+    const kvq_dev::NewRows rows((which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D, t_old, n_new);
     const int grp = lane & 3;
-    // every load of the tile first, as in kvq_append_q_kernel: rows that need neither rotation nor reparameterization
-    // come through range-checked buffer loads (a token that is not new reads zeros)
-    const bool plain = which || (!rope && !rinv);  // wavefront-uniform
     uint32_t w[2][16];
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int tok = tok0 + 16 * pass + (lane >> 2);
-        u32x4 v[4];
-        if (plain) {
-            const __amdgpu_buffer_rsrc_t rows =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(in), 0, n_new * (KVQ_D * 2), 0x00020000);
-            const uint32_t rel = (uint32_t)(tok - t_old);
-            const uint32_t off = (rel < (uint32_t)n_new ? rel * (uint32_t)(KVQ_D * 2) : 0x80000000u) + 64u * grp;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)(off + 16u * c), 0, 0);
-        } else {
-            const bool isnew = tok >= t_old && tok < t_new;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = u32x4{0u, 0u, 0u, 0u};
-            if (isnew) {
-                const uint16_t* row = in + (uint64_t)(tok - t_old) * KVQ_D;
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    v[c] = load_key8(row, 32 * grp + 8 * c, rope ? rope + (uint64_t)(tok - t_old) * KVQ_D : nullptr,
-                                     rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            w[pass][4 * c] = v[c].x; w[pass][4 * c + 1] = v[c].y; w[pass][4 * c + 2] = v[c].z; w[pass][4 * c + 3] = v[c].w;
-        }
-    }
+    load_owner_rows(w, rows, tok0, lane);
+    if (!PLAIN && !which) prepare_owner_keys(w, rows, tok0, lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         const int tl = 16 * pass + (lane >> 2);
@@ -723,32 +681,45 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, const KvqPageDesc* table,
     const int gspan = group / KVQ_G;
     int tile0 = t_old / KVQ_TILE_TOKENS;
     int tile1 = (t_old + n_new + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
-    dim3 grid(2 * (tile1 - tile0), units), block(64);
     const int n_strings = 2 * (tile1 - tile0);
-    const dim3 qgrid((n_strings + KVQ_APPEND_WG_WAVES - 1) / KVQ_APPEND_WG_WAVES, units), qblock(64 * KVQ_APPEND_WG_WAVES);
+    const bool plain = !rinv && !rope;
     const uint16_t* k = static_cast<const uint16_t*>(k_in);
     const uint16_t* v = static_cast<const uint16_t*>(v_in);
     KvqAppendPages ap;
     ap.first_page = first_two ? first_page : -1;
     ap.d[0] = first_two ? first_two[0] : KvqPageDesc{0, 0, 0, 0};
     ap.d[1] = first_two ? first_two[1] : KvqPageDesc{0, 0, 0, 0};
+    const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 ? units : 0;
+#define KVQ_APPEND_LAUNCH(kernel_, waves_, extra_)                                                                       \
+    do {                                                                                                                 \
+        const int n_wg = (n_strings + waves_ - 1) / waves_;                                                              \
+        const dim3 grid = by_unit ? dim3((unsigned)n_wg * (unsigned)units) : dim3(n_wg, units);                          \
+        hipLaunchKernelGGL((kernel_), grid, dim3(64 * waves_), 0, s, arena, table, k, v, t_old, n_new, tiles_per_page,   \
+                           tile0, ap, extra_, rinv, n_kv_heads, rope, n_strings, by_unit);                               \
+    } while (0)
+#define KVQ_FLAGS flags, gspan
     switch (bits + (int16 && bits == 16 ? 1 : 0)) {
-        case 17: hipLaunchKernelGGL(kvq_append_i16_kernel, grid, block, 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, tile0, ap, gspan, rinv, n_kv_heads, rope); break;
-        case 16: hipLaunchKernelGGL(kvq_append16_kernel, grid, block, 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, tile0, ap, rinv, n_kv_heads, rope); break;
-        case 8:
-            if (!rinv && !rope) hipLaunchKernelGGL((kvq_append_q_kernel<8, true>), qgrid, qblock, 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, tile0, ap, flags, gspan, rinv, n_kv_heads, rope, n_strings);
-            else hipLaunchKernelGGL((kvq_append_q_kernel<8, false>), qgrid, qblock, 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, tile0, ap, flags, gspan, rinv, n_kv_heads, rope, n_strings);
+        case 17:
+            if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 1, gspan);
+            else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, gspan);
             break;
-        case 4:
-            if (!rinv && !rope) hipLaunchKernelGGL((kvq_append_q_kernel<4, true>), qgrid, qblock, 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, tile0, ap, flags, gspan, rinv, n_kv_heads, rope, n_strings);
-            else hipLaunchKernelGGL((kvq_append_q_kernel<4, false>), qgrid, qblock, 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, tile0, ap, flags, gspan, rinv, n_kv_heads, rope, n_strings);
+        case 16:
+            if (plain) KVQ_APPEND_LAUNCH(kvq_append16_kernel<true>, 1, gspan);
+            else KVQ_APPEND_LAUNCH(kvq_append16_kernel<false>, 1, gspan);
             break;
-        case 2:
-            if (!rinv && !rope) hipLaunchKernelGGL((kvq_append_q_kernel<2, true>), qgrid, qblock, 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, tile0, ap, flags, gspan, rinv, n_kv_heads, rope, n_strings);
-            else hipLaunchKernelGGL((kvq_append_q_kernel<2, false>), qgrid, qblock, 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, tile0, ap, flags, gspan, rinv, n_kv_heads, rope, n_strings);
+#define KVQ_APPEND_CASE(b_)                                                                                              \
+        case b_:                                                                                                         \
+            if (plain) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true>), KVQ_APPEND_WG_WAVES, KVQ_FLAGS);               \
+            else KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false>), KVQ_APPEND_WG_WAVES, KVQ_FLAGS);                    \
             break;
+        KVQ_APPEND_CASE(8)
+        KVQ_APPEND_CASE(4)
+        KVQ_APPEND_CASE(2)
         default: return hipErrorInvalidValue;
     }
+#undef KVQ_APPEND_CASE
+#undef KVQ_FLAGS
+#undef KVQ_APPEND_LAUNCH
     return hipGetLastError();
 }
 

@@ -11,7 +11,6 @@ namespace kvq_q {
 using kvq_dev::u32x4;
 using kvq_dev::h2f;
 using kvq_dev::f2h_rn;
-using kvq_dev::load_key8;
 
 // (S, Z) of one group from its min and max (both exact fp16 values held as float), Eq. 2.
 __device__ inline void group_params(float mn, float mx, int levels, uint16_t* S, uint16_t* Z, float* Sf) {
@@ -98,6 +97,57 @@ __device__ inline float half_minus(uint32_t w, int hi, float mn) {
     if (hi) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(mn));
     else asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(mn));
     return r;
+}
+
+// The owners' rows of a tile, both passes: eight 16-byte loads per lane, all in flight together; tokens that are not new
+// read as zeros, which is what they quantize.
+__device__ inline void load_owner_rows(uint32_t (&w)[2][16], const kvq_dev::NewRows& rows, int tok0, int lane) {
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        const uint32_t off = rows.offset(tok0 + 16 * pass + (lane >> 2)) + 64u * (lane & 3);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const u32x4 v = rows.load(off + 16u * c);
+            w[pass][4 * c] = v.x; w[pass][4 * c + 1] = v.y; w[pass][4 * c + 2] = v.z; w[pass][4 * c + 3] = v.w;
+        }
+    }
+}
+// Rotation and reparameterization of the owners' keys, as configured.  The owner of the channels +- 64 of the same token is
+// the lane two further in the quad, so the partner channels are a data-parallel move away; a lane reads the 32 angles of
+// its channels with 16-byte loads.  (With the partner read again from memory and the angles one by one, 8,192 new tokens
+// x 32 units into 8, 4 or 2 bits took 166 to 172 us with rotation, 45 to 52 without.)
+__device__ inline void prepare_owner_keys(uint32_t (&w)[2][16], const kvq_dev::NewRows& rows, int tok0, int lane,
+                                          const float* rope, const float* rinv_head) {
+    const int grp = lane & 3;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        const int tok = tok0 + 16 * pass + (lane >> 2);
+        const bool isnew = rows.has(tok);
+        if (rope) {
+            const float* row = rope + rows.row(tok) * KVQ_D;
+            kvq_dev::Angles8 a[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[c] = kvq_dev::load_angles8(row, 32 * (grp & 1) + 8 * c);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                u32x4 own = {w[pass][4 * c], w[pass][4 * c + 1], w[pass][4 * c + 2], w[pass][4 * c + 3]}, partner;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)  // quad_perm 2 3 0 1
+                    partner[e] = (uint32_t)__builtin_amdgcn_mov_dpp((int)own[e], 0x4E, 0xf, 0xf, true);
+                own = kvq_dev::rope8(own, partner, a[c], grp >= 2);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[pass][4 * c + e] = isnew ? own[e] : 0u;  // (a rotated zero may be negative)
+            }
+        }
+        if (rinv_head) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const u32x4 v = kvq_dev::scale_keys8(u32x4{w[pass][4 * c], w[pass][4 * c + 1], w[pass][4 * c + 2], w[pass][4 * c + 3]},
+                                                     rinv_head + 32 * grp + 8 * c);
+                w[pass][4 * c] = v.x; w[pass][4 * c + 1] = v.y; w[pass][4 * c + 2] = v.z; w[pass][4 * c + 3] = v.w;
+            }
+        }
+    }
 }
 
 #define KVQ_LDS_CODES_K 4096                       // K: [32 tokens][128 channels] code bytes

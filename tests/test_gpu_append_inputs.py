@@ -1,0 +1,42 @@
+"""Appends of rotated and reparameterized keys at tile and page edges, from inputs that do not start at a multiple of 16 bytes."""
+import numpy as np
+import pytest
+import torch
+
+import kvq_synth
+from gpu_util import assert_same_cache, make_pair
+from oracle import calibrate_lambda, rope_rotate_keys
+
+pytestmark = pytest.mark.gpu
+
+
+def view(x, odd):
+    """The array on the device, `odd` elements behind a multiple of 16 bytes, between NaNs."""
+    flat = torch.full((x.size + 16,), float("nan"), dtype=torch.from_numpy(x).dtype, device="cuda")
+    flat[odd:odd + x.size] = torch.from_numpy(np.ascontiguousarray(x).reshape(-1)).cuda()
+    return flat[odd:odd + x.size].view(x.shape)
+
+
+@pytest.mark.parametrize("odd", [0, 1, 2])
+@pytest.mark.parametrize("reparam", [False, True])
+@pytest.mark.parametrize("bits,tier16,group", [(16, 0, 32), (16, 1, 32), (16, 1, 128), (8, 0, 64), (4, 0, 128), (2, 0, 32)])
+def test_prepared_keys(bits, tier16, group, reparam, odd):
+    """Chunks that start and end inside a tile, at its edge and at a page's; the stored cache equals the oracle's bit for bit."""
+    B, H, P, T = 2, 2, 64, 300
+    K, V = kvq_synth.make_kv(81, 0, B, H, 0, T, rope_base=None)
+    K[:, :, 5] = 0.0                     # rotated zeros
+    cos, sin = kvq_synth.rope_tables(np.arange(T), 1.0e6)
+    table = np.concatenate([cos, sin], 1).astype(np.float32)
+    Krot = rope_rotate_keys(K, cos, sin)
+    oc, gc = make_pair(1, B, H, H, T, P, group=group, tier16=tier16)
+    if reparam:
+        lam = calibrate_lambda(Krot[:, :, :64], 0.5)
+        oc.set_reparam(0, lam)
+        gc.kvq_cache_set_reparam(0, torch.from_numpy(lam).cuda())
+    t = 0
+    for n in (1, 30, 1, 33, 63, 64, 100, 8):
+        oc.append(0, Krot[:, :, t:t + n], V[:, :, t:t + n], bits)
+        gc.kvq_quantize_append_rope(0, view(K[:, :, t:t + n], odd), view(V[:, :, t:t + n], odd), view(table[t:t + n], odd), bits)
+        t += n
+    assert_same_cache(oc, gc, 0)
+    gc.close()
