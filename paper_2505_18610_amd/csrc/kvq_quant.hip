@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
     for (int pass = 0; pass < 2; ++pass) {
         const int tl = 16 * pass + (lane >> 2);
         const int tok = tok0 + tl;
-        float codes[32];
+        uint32_t codes[32];
         uint16_t S, Z;
         quantize_owner<B>(w[pass], codes, &S, &Z, gspan);  // tokens that are not new quantize zeros: codes 0, S = Z = 0
         note_large_v_scale(flags, which, S);
@@ -165,17 +165,11 @@ __global__ __launch_bounds__(64) void kvq_append_i16_kernel(uint8_t* __restrict_
     for (int pass = 0; pass < 2; ++pass) {
         const int tl = 16 * pass + (lane >> 2);
         const int tok = tok0 + tl;
-        float codes[32], lo[32];
+        uint32_t codes[32];
         uint16_t S, Z;
         quantize_owner<16>(w[pass], codes, &S, &Z, gspan);
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {  // exact: integers below 2^16
-            const float hi = floorf(codes[e] * 0.00390625f);
-            lo[e] = codes[e] - 256.0f * hi;
-            codes[e] = hi;
-        }
-        scatter_codes(lds[0], which, tl, grp, codes);
-        scatter_codes(lds[1], which, tl, grp, lo);
+        scatter_codes<1>(lds[0], which, tl, grp, codes);
+        scatter_codes<0>(lds[1], which, tl, grp, codes);
         if (tok >= t_old) store_meta_owner(meta, which, tl, grp, S, Z);
     }
     wave_sync_lds();
@@ -277,7 +271,7 @@ __global__ __launch_bounds__(64) void kvq_quant16_kernel(uint8_t* __restrict__ a
                 w[8 * h + 4 * c] = v.x; w[8 * h + 4 * c + 1] = v.y; w[8 * h + 4 * c + 2] = v.z; w[8 * h + 4 * c + 3] = v.w;
             }
         }
-        float codes[32];
+        uint32_t codes[32];
         uint16_t S, Z;
         quantize_owner<B>(w, codes, &S, &Z, gspan);
         note_large_v_scale(flags, which, S);

@@ -154,13 +154,22 @@ __device__ inline void prepare_owner_keys(uint32_t (&w)[2][16], const kvq_dev::N
 #define KVQ_LDS_VGRP (32 * 32 + 16)                // V: per group [32 channels][32 tokens] code bytes, skewed
 #define KVQ_LDS_CODES (4 * KVQ_LDS_VGRP)           // room for either arrangement
 
-// Eq. 1-2 for the 32 fp16 values in w[16] (two per dword).  codes[e] receives the code of element e as a float.
-// Fast path: a reciprocal multiply, with the IEEE division the definition asks for only where the product lies too
-// close to a half-integer to decide the rounding (see the bound in the body).
+// Eq. 1-2 for the 32 fp16 values in w[16] (two per dword).  The low 8 bits (B = 16: 16 bits) of codes[e] receive the code of
+// element e; the bits above them are not the code's.
 // gspan = G / 32: a quantization group of G = 64 or 128 channels spans 2 or 4 neighbouring owner lanes (the
 // owners of one token's four 32-channel runs are lanes 4k .. 4k+3), which then share min, max and so (S, Z).
+//
+// The definition rounds the correctly rounded fp32 quotient (x - Z) / S to the nearest integer.  The quotient comes from a
+// reciprocal multiply and one correction by the exact remainder: with y = rcp(S) (1 ulp), t = d y and r = d - t S, which a
+// fused multiply-add forms exactly (S has 11 significant bits and t is off by a few ulp, so r has at most 14), q = t + r y
+// differs from d / S by less than 2^-20 ulp before its rounding.  d / S itself is never nearer than 2^-12 ulp to a point
+// where that rounding changes: d - m S, m a midpoint of two fp32 numbers, is a non-zero multiple of half an ulp of m times
+// the last place of S.  So q is the IEEE quotient for every d and S that occur (nothing here is subnormal in fp32), at
+// every width, without a division or a branch.  Six operations per element; the division that used to be carried
+// out near half-integers cost a quarter of the 8-bit passes a slow path of twice the code, and the 16-bit codes all of
+// theirs.
 template <int B>
-__device__ inline void quantize_owner(const uint32_t (&w)[16], float (&codes)[32], uint16_t* S, uint16_t* Z,
+__device__ inline void quantize_owner(const uint32_t (&w)[16], uint32_t (&codes)[32], uint16_t* S, uint16_t* Z,
                                       int gspan) {
     constexpr int levels = (1 << B) - 1;
     uint32_t mn2 = pk_min_u(w[0], w[1]), mx2 = pk_max_u(w[0], w[1]);  // (no plain copy of a loaded register: the copy
@@ -172,66 +181,34 @@ __device__ inline void quantize_owner(const uint32_t (&w)[16], float (&codes)[32
     if (gspan >= 4) { mn = fminf(mn, __shfl_xor(mn, 2)); mx = fmaxf(mx, __shfl_xor(mx, 2)); }
     float Sf;
     group_params(mn, mx, levels, S, Z, &Sf);
-    if constexpr (B == 16) {  // codes up to 65535: the reciprocal shortcut is not accurate enough, divide
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            const float x = h2f((uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffff)));
-            codes[e] = (float)code_of(x, mn, Sf, levels);
-        }
-        return;
-    }
-    // Reciprocal: the hardware's (1 ulp) refined by one Newton step, relative error below 2^-24 (1 + 2^-22).  Then
-    // t = (x - Z) * rcp is within 2^-23 of the true quotient, relatively, and the correctly rounded fp32 quotient the
-    // definition asks for within 2^-24: the two differ by less than 1.8e-7 * (levels + 1), and rint(t) is the
-    // required code unless t lies that close to a half-integer (eps below adds a margin of 1.4).  Only then is the
-    // IEEE division carried out, and only for the elements concerned.
-    float rcp = 0.0f;
-    if (Sf != 0.0f) {
-        const float r0 = __builtin_amdgcn_rcpf(Sf);
-        rcp = fmaf(r0, fmaf(-Sf, r0, 1.0f), r0);
-    }
-    constexpr float near_half = 0.5f - 2.5e-7f * (float)(levels + 1);
-    // No element's quotient exceeds that of the group maximum (x <= mx and every step is monotone), so the clamp to
-    // the top level is decided once per group instead of once per element; a group that needs it (S rounded down
-    // to a subnormal fp16) takes the division path below, which clamps.
-    const bool over = rintf((mx - mn) * rcp) > (float)levels;
-    float worst = 0.0f;
+    const float y = Sf != 0.0f ? __builtin_amdgcn_rcpf(Sf) : 0.0f;  // a zero scale maps the whole group to code 0
 #pragma unroll
     for (int e = 0; e < 32; ++e) {
-        const float t = half_minus(w[e >> 1], e & 1, mn) * rcp;
-        const float r = rintf(t);
-        worst = fmaxf(worst, fabsf(t - r));
-        codes[e] = r;
-    }
-    if (__any(worst > near_half || over)) {
-        asm volatile("" ::: "memory");  // keep this a branch
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            const float x = h2f((uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffff)));
-            const float t = (x - mn) * rcp;
-            if (over || fabsf(t - rintf(t)) > near_half) codes[e] = (float)code_of(x, mn, Sf, levels);
-        }
+        const float d = half_minus(w[e >> 1], e & 1, mn);
+        const float t = d * y;
+        const float q = fmaf(fmaf(-t, Sf, d), y, t);
+        // clamped (a scale rounded down lifts the group maximum above the top level; a NaN comes out as 0), then rounded
+        // to the nearest even integer by adding 1.5 * 2^23, which leaves it in the low bits
+        codes[e] = __float_as_uint(__builtin_amdgcn_fmed3f(q, 0.0f, (float)levels) + 12582912.0f);
     }
 }
 
-// Owner -> LDS.  tl = token in tile, grp = channel group, which = 0 K / 1 V.
-__device__ inline void scatter_codes(uint8_t* lds, int which, int tl, int grp, const float (&codes)[32]) {
+// Owner -> LDS: byte BYTE of every code.  tl = token in tile, grp = channel group, which = 0 K / 1 V.
+template <int BYTE = 0>
+__device__ inline void scatter_codes(uint8_t* lds, int which, int tl, int grp, const uint32_t (&codes)[32]) {
     if (!which) {
         uint32_t d[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            uint32_t v = __builtin_amdgcn_cvt_pk_u8_f32(codes[4 * k], 0u, 0u);
-            v = __builtin_amdgcn_cvt_pk_u8_f32(codes[4 * k + 1], 1u, v);
-            v = __builtin_amdgcn_cvt_pk_u8_f32(codes[4 * k + 2], 2u, v);
-            d[k] = __builtin_amdgcn_cvt_pk_u8_f32(codes[4 * k + 3], 3u, v);
-        }
+        for (int k = 0; k < 8; ++k)
+            d[k] = __builtin_amdgcn_perm(codes[4 * k + 1], codes[4 * k], 0x0c0c0400u + 0x0101u * BYTE) |
+                   __builtin_amdgcn_perm(codes[4 * k + 3], codes[4 * k + 2], 0x04000c0cu + 0x01010000u * BYTE);
         u32x4* dst = reinterpret_cast<u32x4*>(lds + tl * 128 + grp * 32);
         dst[0] = u32x4{d[0], d[1], d[2], d[3]};
         dst[1] = u32x4{d[4], d[5], d[6], d[7]};
     } else {
         uint8_t* dst = lds + grp * KVQ_LDS_VGRP + tl;
 #pragma unroll
-        for (int c = 0; c < 32; ++c) dst[c * 32] = (uint8_t)(uint32_t)codes[c];
+        for (int c = 0; c < 32; ++c) dst[c * 32] = (uint8_t)(codes[c] >> (8 * BYTE));
     }
 }
 
