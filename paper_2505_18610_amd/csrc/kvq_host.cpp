@@ -750,17 +750,24 @@ kvq_status_t kvq_progressive_requant(kvq_cache_t* c, int32_t layer, int32_t segm
 
 namespace {
 
-// Relative time the attention kernel needs for the block's tiles, and how many of them are 2 bits wide.
-void tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles, int* n2, int* n_all, uint64_t* cost) {
-    *n2 = *n_all = 0;
-    *cost = 0;
+// Relative time the attention kernel needs for the block's tiles, how many of them are 2 bits wide, and the bytes of one
+// (sequence, KV head).
+struct TileCensus {
+    int n2 = 0, n_all = 0;
+    uint64_t cost = 0, bytes = 0;
+};
+TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
+    TileCensus t;
     for (size_t i = 0; i < L.pages.size(); ++i) {
         const int nt = std::min(c->tpp, n_tiles - (int)i * c->tpp);
         if (nt <= 0) break;
-        *n_all += nt;
-        if (L.pages[i].bits == 2) *n2 += nt;
-        *cost += (uint64_t)nt * (uint64_t)c->tile_cost[cost_index(L.pages[i].bits)];
+        const int b = L.pages[i].bits;
+        t.n_all += nt;
+        if (b == 2) t.n2 += nt;
+        t.cost += (uint64_t)nt * (uint64_t)c->tile_cost[cost_index(b)];
+        t.bytes += (uint64_t)nt * (2u * kvq_tile_code_bytes(b) + (c->has_meta(b) ? KVQ_META_TILE_BYTES : 0u));
     }
+    return t;
 }
 
 // Most splits of one (sequence, KV head) that pay.  A range of up to 20 tiles is left to one workgroup, whose eight
@@ -790,19 +797,17 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     int n_splits = c->splits_override;
     if (n_splits <= 0) {
         // One workgroup per compute unit when a good part of the tiles is 2 bits wide (those are bound by vector
-        // issue and want every unit) or the ranges are short (what counts is the length of one: 8K tokens of 4 bits x 32
-        // units 15.1 us on all units, 16.5 on three quarters).  A block of long ranges of wider tiles is bound by HBM, and
-        // there three quarters of the units stream measurably faster than all of them (4 to 7 % at 32K tokens x 64 units
-        // of 4, 8 and 16 bits, 37,000 units of cost per workgroup; even between 9,000 and 19,000).
-        int n2 = 0, n_all = 0;
-        uint64_t cost = 0;
-        tile_census(c, L, n_tiles, &n2, &n_all, &cost);
+        // issue and want every unit) or the launch is short (what counts is the length of one range: 8K tokens x 32 units
+        // of 4 bits, 43 MB, 15.1 us on all units and 16.5 on three quarters; of 8 bits, 75 MB, 18.5 and 19.1).  A longer
+        // launch over wider tiles is bound by HBM, and there three quarters of the units stream measurably faster than all of them
+        // (16-bit blocks of 87 to 160 MB 3 to 4 %, 4-, 8- and 16-bit blocks of 350 MB and more 4 to 7 %).
+        const TileCensus t = tile_census(c, L, n_tiles);
         int wgs = wgs_share;
         if (wgs <= 0) {
             wgs = c->target_workgroups;
-            if (4 * n2 < n_all && cost * (uint64_t)c->units > 12000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);
+            if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);
         }
-        n_splits = std::min(wgs / std::max(1, c->units), useful_splits(cost, n_tiles));
+        n_splits = std::min(wgs / std::max(1, c->units), useful_splits(t.cost, n_tiles));
     }
     n_splits = std::max(1, std::min(n_splits, std::min(KVQ_MAX_SPLITS, n_tiles)));
     plan_splits(c, L, n_tiles, n_splits);
@@ -898,8 +903,7 @@ kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, co
         const Layer& L = c->layers[(size_t)layer];
         if (L.T == 0) return KVQ_E_STATE;
         const int n_tiles = (L.T + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
-        int a = 0, b = 0;
-        tile_census(c, L, n_tiles, &a, &b, &cost[(size_t)i]);
+        cost[(size_t)i] = tile_census(c, L, n_tiles).cost;
         max_splits[(size_t)i] = useful_splits(cost[(size_t)i], n_tiles);
         used += c->units;
     }
