@@ -13,14 +13,15 @@
  *     (host tables) and sub-allocates inside the arena; it never allocates or frees device memory.
  *   - Every kernel is enqueued on the given HIP stream (hipStream_t passed as void*, NULL = default stream).
  *     No entry point waits for the stream, except the three that copy results to the host
- *     (kvq_cache_export_segment, kvq_cache_sq_error, kvq_cache_sensitivity).  Small host-to-device uploads (page
- *     tables, job lists, the parameter blocks of a ragged batch) travel through a pinned staging ring of 4 segments of
- *     1 MiB whose reuse is guarded by one HIP event per segment: a call blocks the host only when it has run a whole
- *     ring of uploads ahead of the device, and then only until the oldest segment has been consumed.
+ *     (kvq_cache_export_segment, kvq_cache_sq_error, kvq_cache_sensitivity).  Page table
+ *     entries ride in the arguments of the kernels that make the pages.  What is too long for that (appends over more than
+ *     128 pages, shrinks of more than 192, the parameter blocks of a ragged batch) travels through a pinned staging ring
+ *     of 4 segments of 1 MiB whose reuse is guarded by one HIP event per segment: a call blocks the host only when it has
+ *     run a whole ring ahead of the device, and then only until the oldest segment has been consumed.
  *   - Stream capture: kvq_decode_attention and kvq_decode_attention_static enqueue kernels only and may be captured
  *     into a HIP graph (the cache must not change between capture and replay).  Calls that change a cache or stage
- *     parameter blocks (append, requant, the *_batch calls, set_reparam) use the staging ring and its events and must
- *     not be captured.
+ *     parameter blocks (append, requant, the *_batch calls, set_reparam) move the host tables or use the staging ring and
+ *     its events and must not be captured.
  *   - All calls on one cache must be issued from one thread at a time and on one stream (the host tables
  *     are updated at enqueue time, the device tables in stream order).
  *   - Errors are reported as kvq_status_t; argument, state and budget errors are detected on the host before

@@ -1012,6 +1012,8 @@ __device__ inline void store_new_token(const KvqAttnParams& P, const AttnShared&
             }
         }
     }
+    if (P.app_page >= 0 && unit == 0 && !which && lane == 0)  // nobody reads this entry in this launch
+        const_cast<KvqPageDesc*>(P.table)[P.app_page] = P.app_desc;
     if (I16 && lane < 8) {  // S of the four groups, then Z
         const int g = lane & 3, z = lane >> 2;
         uint16_t* m = reinterpret_cast<uint16_t*>(meta + 512 * which + 256 * z);

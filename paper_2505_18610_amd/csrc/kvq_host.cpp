@@ -317,7 +317,7 @@ kvq_status_t run_lowering_step(kvq_cache* c, int layer, std::vector<Lowering>& l
             jobs[i].src_code_off256 = (uint32_t)(c->unit_off_bytes(p.code_unit) / 256);
             jobs[i].dst_code_off256 = (uint32_t)(c->unit_off_bytes(low[i].new_code) / 256);
             jobs[i].meta_off256 = (uint32_t)(c->unit_off_bytes(fresh_meta ? low[i].new_meta : p.meta_unit) / 256);
-            jobs[i].n_tiles = (uint32_t)((p.n + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS);
+            jobs[i].tiles_page = kvq_job_tiles_page((p.n + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS, low[i].page);
         }
         KvqRequantJob* jd = reinterpret_cast<KvqRequantJob*>(c->arena + c->jobs_off);
         const bool by_arg = jobs.size() <= (size_t)KVQ_JOBS_BY_ARG;  // short lists ride in the kernel arguments
@@ -325,8 +325,8 @@ kvq_status_t run_lowering_step(kvq_cache* c, int layer, std::vector<Lowering>& l
         hipError_t e = hipSuccess;
         if (st == KVQ_OK) {
             const KvqRequantJob* jh = by_arg ? jobs.data() : nullptr;
-            e = fresh_meta ? kvq_launch_quant16(to, c->arena, jd, jh, (int)jobs.size(), c->tpp, c->units, c->flags_dev(), c->cfg.group, s)
-                             : kvq_launch_shrink(to, c->shift_strategy, c->arena, jd, jh, (int)jobs.size(), c->tpp, c->units, c->flags_dev(), s);
+            e = fresh_meta ? kvq_launch_quant16(to, c->arena, c->table_dev(layer), jd, jh, (int)jobs.size(), c->tpp, c->units, c->flags_dev(), c->cfg.group, s)
+                             : kvq_launch_shrink(to, c->shift_strategy, c->arena, c->table_dev(layer), jd, jh, (int)jobs.size(), c->tpp, c->units, c->flags_dev(), s);
         }
         if (st != KVQ_OK || e != hipSuccess) {
             for (auto& w : low) {
@@ -336,20 +336,15 @@ kvq_status_t run_lowering_step(kvq_cache* c, int layer, std::vector<Lowering>& l
             return st != KVQ_OK ? st : KVQ_E_HIP;
         }
     }
-    int lo = (int)L.pages.size(), hi = 0;
     for (auto& w : low) {
         Page& p = L.pages[(size_t)w.page];
         c->buddy.release(p.code_unit, order_of_bits(p.bits));  // reused only by work enqueued later
         p.code_unit = w.new_code;
         if (fresh_meta) p.meta_unit = w.new_meta;
         p.bits = to;
-        lo = std::min(lo, w.page);
-        hi = std::max(hi, w.page + 1);
     }
     L.version++;
-    const kvq_status_t up = upload_table(c, layer, lo, hi, s);
-    if (up != KVQ_OK) L.poisoned = true;  // host tables and device page table disagree
-    return up;
+    return KVQ_OK;
 }
 
 // Lower a set of pages that share (from, to).  Pages of the integer 16-bit tier go down one halving at a time
@@ -520,6 +515,7 @@ namespace {
 struct DeferredAppend {
     bool active = false;
     int t_old = 0;
+    int fresh_page = -1;  // the page the token starts, whose table entry the launch writes; -1: the page exists
     KvqPageDesc desc{};
 };
 
@@ -629,27 +625,34 @@ kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, 
     L.T = T;
     L.version++;
     // From here on the host tables count the new tokens: a failing enqueue leaves the block unusable (poisoned).
-    st = upload_table(c, layer, (int)old_pages, (int)L.pages.size(), s);
-    if (st != KVQ_OK) {
-        release_first_step(c, low);
-        L.poisoned = true;
-        return st;
-    }
     if (!c->dry && defer && n_new == 1 && e == 16) {
         defer->active = true;
         defer->t_old = t_old;
         defer->desc = c->desc(L.pages[(size_t)(t_old / P)]);
+        defer->fresh_page = t_old % P == 0 ? t_old / P : -1;
     } else if (!c->dry) {
-        // short appends (at most two pages touched) carry the page descriptors in the kernel arguments
         const int pg0 = t_old / P, pg1 = (T - 1) / P;
-        KvqPageDesc two[2];
-        const bool by_arg = pg1 - pg0 <= 1;
-        if (by_arg) {
-            two[0] = c->desc(L.pages[(size_t)pg0]);
-            two[1] = c->desc(L.pages[(size_t)pg1]);
+        KvqAppendPages pages;
+        pages.n = pg1 - pg0 + 1 <= KVQ_APPEND_ARG_PAGES ? pg1 - pg0 + 1 : 0;
+        pages.first_page = pg0;
+        pages.fresh = (int)old_pages - pg0;
+        pages.bits = (uint32_t)e;
+        pages.int16 = (e == 16 && c->int16()) ? 1u : 0u;
+        for (int i = 0; i < pages.n; ++i) {
+            const KvqPageDesc d = c->desc(L.pages[(size_t)(pg0 + i)]);
+            pages.code_off256[i] = d.code_off256;
+            pages.meta_off256[i] = d.meta_off256;
+        }
+        if (pages.n == 0) {  // too many for the kernel arguments: the table is uploaded and read
+            st = upload_table(c, layer, (int)old_pages, (int)L.pages.size(), s);
+            if (st != KVQ_OK) {
+                release_first_step(c, low);
+                L.poisoned = true;
+                return st;
+            }
         }
         if (kvq_launch_append(e, c->arena, c->table_dev(layer), k_dev, v_dev, t_old, n_new, c->tpp, c->units,
-                              by_arg ? two : nullptr, pg0, c->flags_dev(), c->cfg.group,
+                              pages, c->flags_dev(), c->cfg.group,
                               L.reparam ? c->lambda_dev(layer) + c->cfg.n_kv_heads * KVQ_D : nullptr, c->cfg.n_kv_heads,
                               cos_sin_dev, c->int16(), s) != hipSuccess) {
             release_first_step(c, low);
@@ -837,12 +840,14 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     std::memcpy(p.split_begin, L.split_begin, sizeof(int32_t) * (size_t)(n_splits + 1));
     for (int i = n_splits + 1; i <= KVQ_MAX_SPLITS; ++i) p.split_begin[i] = n_tiles;
     p.app_t_old = -1;
+    p.app_page = -1;
     p.app_desc = KvqPageDesc{0, 0, 0, 0};
     p.app_k = p.app_v = nullptr;
     p.app_rope = p.app_rinv = nullptr;
     if (app && app->active) {
         p.app_t_old = app->t_old;
         p.app_desc = app->desc;
+        p.app_page = app->fresh_page;
         p.app_k = k_new;
         p.app_v = v_new;
         p.app_rope = cos_sin_dev;
@@ -945,10 +950,13 @@ kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, co
     const KvqAttnParams* params_dev = nullptr;
     kvq_status_t st = stage(lead, params.data(), params.size() * sizeof(KvqAttnParams), s,
                             reinterpret_cast<const void**>(&params_dev));
-    if (st != KVQ_OK) return st;
     std::vector<int> units((size_t)n);
     for (int i = 0; i < n; ++i) units[(size_t)i] = caches[i]->units;
-    return kvq_launch_attention_batch(params_dev, params.data(), units.data(), n, s) == hipSuccess ? KVQ_OK : KVQ_E_HIP;
+    if (st == KVQ_OK && kvq_launch_attention_batch(params_dev, params.data(), units.data(), n, s) != hipSuccess) st = KVQ_E_HIP;
+    if (st != KVQ_OK)  // the host tables count tokens nobody wrote
+        for (int i = 0; i < n; ++i)
+            if (app[(size_t)i].active) caches[i]->layers[(size_t)layer].poisoned = true;
+    return st;
 }
 
 }  // namespace
@@ -991,7 +999,9 @@ kvq_status_t kvq_append_decode_attention(kvq_cache_t* c, int32_t layer, const vo
     DeferredAppend app;
     kvq_status_t st = append_impl(c, layer, k_dev, v_dev, 1, 0, cos_sin_dev, hip_stream, &app);
     if (st != KVQ_OK) return st;
-    return attention_impl(c, layer, q_dev, out_dev, out_is_fp32, softmax_scale, hip_stream, &app, k_dev, v_dev, cos_sin_dev);
+    st = attention_impl(c, layer, q_dev, out_dev, out_is_fp32, softmax_scale, hip_stream, &app, k_dev, v_dev, cos_sin_dev);
+    if (st != KVQ_OK && app.active) c->layers[(size_t)layer].poisoned = true;  // the host tables count a token nobody wrote
+    return st;
 }
 
 kvq_status_t kvq_decode_attention_batch(kvq_cache_t* const* caches, int32_t n_caches, int32_t layer,

@@ -6,12 +6,18 @@
 #include <stdint.h>
 #include "kvq_layout.h"
 
+// The device page tables are written by the kernels that make the pages: an append, a re-quantization or the attention
+// launch that appends a token gets the new entries in its arguments and stores them beside its other output.  (A copy
+// from pinned memory in front of or behind each of them cost 4 us of copy kernel and 2 to 6 us of gaps.)
 struct KvqRequantJob {        // one page to re-quantize
     uint32_t src_code_off256; // source code block
     uint32_t dst_code_off256; // destination code block
     uint32_t meta_off256;     // metadata block (updated in place for 2b -> b, written for fp16 -> b)
-    uint32_t n_tiles;         // tiles of the page that hold tokens; the kernels leave the others alone
+    uint32_t tiles_page;      // low 11 bits: tiles of the page that hold tokens (the kernels leave the others alone); above
+                              // them the page's index in the block's table, whose entry the kernel rewrites
 };
+// a page holds at most 1,024 tiles and a block at most 2^21 pages (2^26 tokens in pages of 32)
+inline uint32_t kvq_job_tiles_page(int n_tiles, int page) { return (uint32_t)n_tiles | ((uint32_t)page << 11); }
 
 // Up to KVQ_JOBS_BY_ARG jobs ride in the kernel arguments (no table upload in front of the launch);
 // longer lists are read from the uploaded table.
@@ -48,6 +54,7 @@ struct KvqAttnParams {
     // a one-token append into the 16-bit tier done by the workgroup of a unit's last split (app_t_old < 0: none)
     int32_t app_t_old;         // tokens before the append
     KvqPageDesc app_desc;      // page of the new token
+    int32_t app_page;          // the table entry the launch has to write (the token starts the page), or -1
     const void* app_k;         // fp16 [batch, n_kv_heads, 1, 128]
     const void* app_v;
     const float* app_rope;     // [1][128] cos | sin of the new position, or null
@@ -59,14 +66,27 @@ struct KvqAttnParams {
 // One append call takes fewer than 2^23 tokens per sequence: the kernels address the rows of a unit's input through a
 // buffer descriptor with 32-bit byte offsets (256 bytes per row; offsets up to a few tiles beyond the last row occur).
 #define KVQ_MAX_APPEND_TOKENS (1 << 23)
-hipError_t kvq_launch_append(int bits, uint8_t* arena, const KvqPageDesc* table, const void* k_in,
+// Pages of one append call.  Up to KVQ_APPEND_ARG_PAGES of them ride in the kernel arguments (n > 0), which also saves
+// the dependent read of the device table; an append that touches more reads the table, which then holds them already.
+#define KVQ_APPEND_ARG_PAGES 128
+struct KvqAppendPages {
+    int32_t n;           // pages the append touches, 0: read the table
+    int32_t first_page;  // index of the first of them
+    int32_t fresh;       // entries fresh .. n - 1 are new: the kernel writes them into the table
+    uint32_t bits;
+    uint32_t int16;
+    uint32_t code_off256[KVQ_APPEND_ARG_PAGES], meta_off256[KVQ_APPEND_ARG_PAGES];
+};
+// table: the block's device page table, read (n == 0) or written (fresh entries)
+hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const void* k_in,
                              const void* v_in, int t_old, int n_new, int tiles_per_page, int units,
-                             const KvqPageDesc* first_two, int first_page, uint32_t* flags, int group,
+                             const KvqAppendPages& pages, uint32_t* flags, int group,
                              const float* rinv, int n_kv_heads, const float* rope, bool int16, hipStream_t s);
-hipError_t kvq_launch_shrink(int dst_bits, int strategy, uint8_t* arena, const KvqRequantJob* jobs_dev,
+// table: the block's device page table; the kernels write the entries of the pages they re-quantize
+hipError_t kvq_launch_shrink(int dst_bits, int strategy, uint8_t* arena, KvqPageDesc* table, const KvqRequantJob* jobs_dev,
                              const KvqRequantJob* jobs_host, int n_jobs, int tiles_per_page, int units,
                              uint32_t* flags, hipStream_t s);
-hipError_t kvq_launch_quant16(int dst_bits, uint8_t* arena, const KvqRequantJob* jobs_dev,
+hipError_t kvq_launch_quant16(int dst_bits, uint8_t* arena, KvqPageDesc* table, const KvqRequantJob* jobs_dev,
                               const KvqRequantJob* jobs_host, int n_jobs, int tiles_per_page, int units,
                               uint32_t* flags, int group, hipStream_t s);
 hipError_t kvq_launch_reparam_store(const float* lambda, float* dst, int n, hipStream_t s);

@@ -34,16 +34,17 @@ __device__ inline bool append_work(int n_strings, int by_unit, int wave, int* st
 // Append into the 16-bit tier: the new rows are copied into the tile layout.
 template <bool PLAIN>
 __global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ arena,
-                                                          const KvqPageDesc* __restrict__ table,
+                                                          KvqPageDesc* __restrict__ table,
                                                           const uint16_t* __restrict__ k_in,
                                                           const uint16_t* __restrict__ v_in, int t_old,
-                                                          int n_new, int tpp, int tile0, KvqAppendPages ap,
+                                                          int n_new, int tpp, int tile0, const KvqAppendPages ap,
                                                           int /* group span: nothing is quantized */,
                                                           const float* __restrict__ rinv, int n_kv_heads,
                                                           const float* __restrict__ rope, int n_strings, int by_unit) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[32 * 256];
     const int lane = threadIdx.x;
     int string, unit;
+    write_fresh_pages(table, ap, lane);
     if (!append_work<PLAIN, 1>(n_strings, by_unit, 0, &string, &unit)) return;
     const int which = string & 1;
     const int tile = tile0 + (string >> 1);
@@ -63,10 +64,10 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ 
 #define KVQ_APPEND_WG_WAVES 4
 template <int B, bool PLAIN>
 __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(uint8_t* __restrict__ arena,
-                                                          const KvqPageDesc* __restrict__ table,
+                                                          KvqPageDesc* __restrict__ table,
                                                           const uint16_t* __restrict__ k_in,
                                                           const uint16_t* __restrict__ v_in, int t_old,
-                                                          int n_new, int tpp, int tile0, KvqAppendPages ap,
+                                                          int n_new, int tpp, int tile0, const KvqAppendPages ap,
                                                           uint32_t* __restrict__ flags, int gspan,
                                                           const float* __restrict__ rinv, int n_kv_heads,
                                                           const float* __restrict__ rope, int n_strings, int by_unit) {
@@ -75,6 +76,7 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
     uint8_t* const lds = lds_all[wave];
     const int lane = threadIdx.x & 63, j = lane >> 4, n = lane & 15;
     int string, unit;
+    if (wave == 0) write_fresh_pages(table, ap, lane);
     if (!append_work<PLAIN, KVQ_APPEND_WG_WAVES>(n_strings, by_unit, wave, &string, &unit)) return;
     const int which = string & 1;
     const int tile = tile0 + (string >> 1);
@@ -137,16 +139,17 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
 // bytes of the codes then travel through LDS and into the tile's two byte planes like two 8-bit tiles.
 template <bool PLAIN>
 __global__ __launch_bounds__(64) void kvq_append_i16_kernel(uint8_t* __restrict__ arena,
-                                                            const KvqPageDesc* __restrict__ table,
+                                                            KvqPageDesc* __restrict__ table,
                                                             const uint16_t* __restrict__ k_in,
                                                             const uint16_t* __restrict__ v_in, int t_old,
-                                                            int n_new, int tpp, int tile0, KvqAppendPages ap,
+                                                            int n_new, int tpp, int tile0, const KvqAppendPages ap,
                                                             int gspan, const float* __restrict__ rinv,
                                                             int n_kv_heads, const float* __restrict__ rope,
                                                             int n_strings, int by_unit) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][KVQ_LDS_CODES];
     const int lane = threadIdx.x, j = lane >> 4, n = lane & 15;
     int string, unit;
+    write_fresh_pages(table, ap, lane);
     if (!append_work<PLAIN, 1>(n_strings, by_unit, 0, &string, &unit)) return;
     const int which = string & 1;
     const int tile = tile0 + (string >> 1);
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(64) void kvq_append_i16_kernel(uint8_t* __restrict_
 // that still holds raw fp16 values: the tile is first laid out [token][channel] in LDS, then quantized by
 // owner lanes exactly like an append.
 template <int B>
-__global__ __launch_bounds__(64) void kvq_quant16_kernel(uint8_t* __restrict__ arena,
+__global__ __launch_bounds__(64) void kvq_quant16_kernel(uint8_t* __restrict__ arena, KvqPageDesc* __restrict__ table,
                                                          const KvqRequantJob* __restrict__ jobs, int tpp,
                                                          uint32_t* __restrict__ flags, int gspan,
                                                          const KvqJobArgs ja) {
@@ -228,7 +231,8 @@ __global__ __launch_bounds__(64) void kvq_quant16_kernel(uint8_t* __restrict__ a
     const int job = idx / tpp, tip = idx - job * tpp;
     const int unit = blockIdx.y;
     const KvqRequantJob jb = ja.n ? ja.jobs[job] : jobs[job];
-    if (tip >= (int)jb.n_tiles) return;  // tiles of a partly filled page that hold no token yet (wavefront-uniform)
+    if (tip >= (int)(jb.tiles_page & 2047u)) return;  // tiles of a partly filled page that hold no token yet (wavefront-uniform)
+    if (blockIdx.y == 0 && tip == 0 && lane == 0) table[jb.tiles_page >> 11] = KvqPageDesc{jb.dst_code_off256, jb.meta_off256, B, 0u};
     const uint64_t tslot = (uint64_t)unit * tpp + tip;
     const uint8_t* src = arena + (uint64_t)jb.src_code_off256 * 256u + (tslot * 2 + which) * (512u * 16);
     uint8_t* dst = arena + (uint64_t)jb.dst_code_off256 * 256u + (tslot * 2 + which) * (512u * B);
@@ -338,14 +342,15 @@ __device__ inline uint32_t trunc_8_to_4(uint32_t w) {  // 4 bytes -> their upper
 //   STRAT 2, Modified Right Shift:            codes >> B,     S <- 2^B S,       Z <- Z + (2^B S - S) / 2
 // Products and the sum are formed in fp32 (the products are exact) and rounded to nearest-even into fp16.
 template <int B, int STRAT>
-__global__ __launch_bounds__(64) void kvq_shrink_kernel(uint8_t* __restrict__ arena,
+__global__ __launch_bounds__(64) void kvq_shrink_kernel(uint8_t* __restrict__ arena, KvqPageDesc* __restrict__ table,
                                                         const KvqRequantJob* __restrict__ jobs, int tpp,
                                                         uint32_t* __restrict__ flags, const KvqJobArgs ja) {
     const int lane = threadIdx.x;
     const int job = blockIdx.x / tpp, tip = blockIdx.x - job * tpp;
     const int unit = blockIdx.y;
     const KvqRequantJob jb = ja.n ? ja.jobs[job] : jobs[job];
-    if (tip >= (int)jb.n_tiles) return;  // tiles of a partly filled page that hold no token yet (wavefront-uniform)
+    if (tip >= (int)(jb.tiles_page & 2047u)) return;  // tiles of a partly filled page that hold no token yet (wavefront-uniform)
+    if (blockIdx.y == 0 && tip == 0 && lane == 0) table[jb.tiles_page >> 11] = KvqPageDesc{jb.dst_code_off256, jb.meta_off256, B, 0u};
     const uint64_t tslot = (uint64_t)unit * tpp + tip;
     const uint8_t* src = arena + (uint64_t)jb.src_code_off256 * 256u + tslot * 2 * (512u * 2 * B);
     uint8_t* dst = arena + (uint64_t)jb.dst_code_off256 * 256u + tslot * 2 * (512u * B);
@@ -668,9 +673,9 @@ __global__ void kvq_fill_u32_kernel(uint32_t* dst, uint32_t value, size_t n) {
 
 }  // namespace
 
-hipError_t kvq_launch_append(int bits, uint8_t* arena, const KvqPageDesc* table, const void* k_in,
+hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const void* k_in,
                              const void* v_in, int t_old, int n_new, int tiles_per_page, int units,
-                             const KvqPageDesc* first_two, int first_page, uint32_t* flags, int group,
+                             const KvqAppendPages& ap, uint32_t* flags, int group,
                              const float* rinv, int n_kv_heads, const float* rope, bool int16, hipStream_t s) {
     const int gspan = group / KVQ_G;
     int tile0 = t_old / KVQ_TILE_TOKENS;
@@ -679,10 +684,6 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, const KvqPageDesc* table,
     const bool plain = !rinv && !rope;
     const uint16_t* k = static_cast<const uint16_t*>(k_in);
     const uint16_t* v = static_cast<const uint16_t*>(v_in);
-    KvqAppendPages ap;
-    ap.first_page = first_two ? first_page : -1;
-    ap.d[0] = first_two ? first_two[0] : KvqPageDesc{0, 0, 0, 0};
-    ap.d[1] = first_two ? first_two[1] : KvqPageDesc{0, 0, 0, 0};
     const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 ? units : 0;
 #define KVQ_APPEND_LAUNCH(kernel_, waves_, extra_)                                                                       \
     do {                                                                                                                 \
@@ -725,14 +726,14 @@ static void fill_job_args(KvqJobArgs& ja, const KvqRequantJob* jobs_host, int n_
 
 // jobs_host != nullptr and n_jobs <= KVQ_JOBS_BY_ARG: the list travels in the kernel arguments and jobs_dev is
 // not read; otherwise jobs_dev must already hold the list (in stream order).
-hipError_t kvq_launch_shrink(int dst_bits, int strategy, uint8_t* arena, const KvqRequantJob* jobs_dev,
+hipError_t kvq_launch_shrink(int dst_bits, int strategy, uint8_t* arena, KvqPageDesc* table, const KvqRequantJob* jobs_dev,
                              const KvqRequantJob* jobs_host, int n_jobs, int tiles_per_page, int units,
                              uint32_t* flags, hipStream_t s) {
     dim3 grid(n_jobs * tiles_per_page, units), block(64);
     KvqJobArgs ja;
     fill_job_args(ja, jobs_host, n_jobs);
 #define KVQ_SHRINK_CASE(B_, S_) \
-    hipLaunchKernelGGL((kvq_shrink_kernel<B_, S_>), grid, block, 0, s, arena, jobs_dev, tiles_per_page, flags, ja)
+    hipLaunchKernelGGL((kvq_shrink_kernel<B_, S_>), grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, flags, ja)
     switch (dst_bits * 4 + strategy) {
         case 8 * 4 + 0: KVQ_SHRINK_CASE(8, 0); break;
         case 8 * 4 + 1: KVQ_SHRINK_CASE(8, 1); break;
@@ -767,16 +768,16 @@ hipError_t kvq_launch_error(bool l1, const uint8_t* arena, const KvqPageDesc* ta
     return hipGetLastError();
 }
 
-hipError_t kvq_launch_quant16(int dst_bits, uint8_t* arena, const KvqRequantJob* jobs_dev,
+hipError_t kvq_launch_quant16(int dst_bits, uint8_t* arena, KvqPageDesc* table, const KvqRequantJob* jobs_dev,
                               const KvqRequantJob* jobs_host, int n_jobs, int tiles_per_page, int units,
                               uint32_t* flags, int group, hipStream_t s) {
     dim3 grid(2 * n_jobs * tiles_per_page, units), block(64);
     KvqJobArgs ja;
     fill_job_args(ja, jobs_host, n_jobs);
     switch (dst_bits) {
-        case 8: hipLaunchKernelGGL(kvq_quant16_kernel<8>, grid, block, 0, s, arena, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
-        case 4: hipLaunchKernelGGL(kvq_quant16_kernel<4>, grid, block, 0, s, arena, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
-        case 2: hipLaunchKernelGGL(kvq_quant16_kernel<2>, grid, block, 0, s, arena, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
+        case 8: hipLaunchKernelGGL(kvq_quant16_kernel<8>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
+        case 4: hipLaunchKernelGGL(kvq_quant16_kernel<4>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
+        case 2: hipLaunchKernelGGL(kvq_quant16_kernel<2>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

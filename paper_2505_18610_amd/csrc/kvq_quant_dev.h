@@ -278,30 +278,29 @@ __device__ inline void store_meta_owner(uint8_t* meta, int which, int tl, int gr
 }
 
 // ------------------------------------------------------------------------------------------------ append
-// Descriptors of the (at most two) pages a short append touches ride in the kernel arguments, which saves the
-// dependent read of the device page table; longer appends look the table up.
-struct KvqAppendPages {
-    KvqPageDesc d[2];
-    int first_page;  // -1: use the table
-};
-// (The offsets are pinned to scalar registers inside each branch: left alone, the two branches are merged into one
-//  load through a selected pointer, which can only be a flat load, and while a flat load is pending every wait for a
-//  global load becomes a wait for all of them.)
+// Descriptor of the page a string lies in, and the table entries of the call's new pages, which the first workgroup writes.
+// (The offsets become scalar inside each branch: left alone, the two branches are merged into one load through a selected
+//  pointer, which can only be a flat load, and while a flat load is pending every wait for a global load becomes a wait
+//  for all of them.)
 __device__ inline KvqPageDesc append_desc(const KvqPageDesc* table, const KvqAppendPages& ap, int page) {
     KvqPageDesc r;
     r.bits = 0u;
     r.int16 = 0u;
-    if (ap.first_page < 0) {
-        r.code_off256 = table[page].code_off256;
-        r.meta_off256 = table[page].meta_off256;
-        asm volatile("" : "+s"(r.code_off256), "+s"(r.meta_off256));
+    page = __builtin_amdgcn_readfirstlane(page);
+    if (ap.n == 0) {
+        r.code_off256 = __builtin_amdgcn_readfirstlane(table[page].code_off256);
+        r.meta_off256 = __builtin_amdgcn_readfirstlane(table[page].meta_off256);
     } else {
-        const bool first = page == ap.first_page;
-        r.code_off256 = first ? ap.d[0].code_off256 : ap.d[1].code_off256;
-        r.meta_off256 = first ? ap.d[0].meta_off256 : ap.d[1].meta_off256;
+        r.code_off256 = ap.code_off256[page - ap.first_page];
+        r.meta_off256 = ap.meta_off256[page - ap.first_page];
         asm volatile("" : "+s"(r.code_off256), "+s"(r.meta_off256));
     }
     return r;
+}
+__device__ inline void write_fresh_pages(KvqPageDesc* table, const KvqAppendPages& ap, int lane) {
+    if (blockIdx.x != 0 || blockIdx.y != 0) return;
+    for (int i = ap.fresh + lane; i < ap.n; i += 64)
+        table[ap.first_page + i] = KvqPageDesc{ap.code_off256[i], ap.meta_off256[i], ap.bits, ap.int16};
 }
 
 }  // namespace kvq_q

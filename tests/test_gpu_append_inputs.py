@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import kvq_synth
-from gpu_util import assert_same_cache, make_pair
+from gpu_util import append_both, assert_same_cache, check_attention, make_pair
 from oracle import calibrate_lambda, rope_rotate_keys
 
 pytestmark = pytest.mark.gpu
@@ -39,4 +39,27 @@ def test_prepared_keys(bits, tier16, group, reparam, odd):
         gc.kvq_quantize_append_rope(0, view(K[:, :, t:t + n], odd), view(V[:, :, t:t + n], odd), view(table[t:t + n], odd), bits)
         t += n
     assert_same_cache(oc, gc, 0)
+    gc.close()
+
+
+@pytest.mark.parametrize("first", [0, 7])
+@pytest.mark.parametrize("pages", [1, 2, 127, 128, 129, 200])
+def test_page_entries_of_long_appends(pages, first):
+    """Up to 128 pages of an append ride in the kernel arguments and are entered into the table by the kernel; more are
+    uploaded.  Later calls (an append to the last page, attention, a shrink of everything) find every page."""
+    B, H, P = 1, 1, 32
+    n = 32 * pages - (first if pages > 1 else first + 3)
+    K, V = kvq_synth.make_kv(82, 0, B, H, 0, first + n + 5)
+    oc, gc = make_pair(1, B, 2 * H, H, first + n + 5, P)
+    t = 0
+    for m in [first, n, 5]:
+        if m:
+            append_both(oc, gc, 0, K[:, :, t:t + m], V[:, :, t:t + m], 16)
+            t += m
+    q = kvq_synth.make_q(82, 0, B, 2 * H, t)
+    check_attention(oc, gc, 0, q)
+    for _ in range(2):
+        assert gc.kvq_progressive_requant(0, segment=0) == oc.requant(0, segment=0)
+        assert_same_cache(oc, gc, 0)
+        check_attention(oc, gc, 0, q)
     gc.close()
