@@ -13,8 +13,7 @@ __device__ __forceinline__ void batch_body(const KvqAttnParams* __restrict__ par
     const KvqAttnParams& P = params[ci];
     const int local = wg - map.wg_begin[ci];
     const int unit = local / P.n_splits, split = local - unit * P.n_splits;  // splits of a unit are neighbours
-    if (__builtin_amdgcn_readfirstlane(P.flags[0] & 1u)) attention_body<true, I16, true, true>(P, sh, split, unit);
-    else attention_body<false, I16, true, true>(P, sh, split, unit);
+    attention_body<I16, true, true>(P, sh, split, unit);
 }
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_batch_kernel(const KvqAttnParams* __restrict__ params,
                                                                                const KvqBatchMap map) {

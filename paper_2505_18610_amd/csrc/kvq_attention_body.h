@@ -529,6 +529,10 @@ __device__ inline void compute_stage(WaveState& st, const QOps& Q, const Stage<B
     if constexpr (B < 16) wave_lds_sync();
 }
 
+// Quotients by launch constants: n / d = mulhi(n, magic), magic = ceil(2^32 / d), exact for n < 2^22, d <= 2^10 and for
+// n, d < 2^16.  (A division of scalars is some thirty dependent instructions, several of which stood in front of the first load.)
+__device__ inline int div_magic(int n, int d, uint32_t magic) { return d == 1 ? n : (int)__umulhi((uint32_t)n, magic); }
+
 // A claimed chunk, resolved to addresses; every member is wavefront-uniform (scalar registers).
 struct Claim {
     int tile;             // first tile
@@ -579,7 +583,7 @@ __device__ inline void start_claim(RunCtx& c) {
 __device__ inline int finish_claim(const RunCtx& c) { return __builtin_amdgcn_readfirstlane(c.claim_v); }
 
 __device__ inline int page_of_tile(const RunCtx& c, int tile) {
-    return c.tpp == 1 ? tile : (int)__umulhi((uint32_t)tile, c.tpp_magic);
+    return div_magic(tile, c.tpp, c.tpp_magic);
 }
 __device__ inline void start_desc(RunCtx& c, int chunk) {
     chunk = __builtin_amdgcn_readfirstlane(chunk);
@@ -809,7 +813,7 @@ __device__ inline float reduce32(float x) {
 template <bool AGENT>
 __device__ inline void merge_splits(const KvqAttnParams& P, int unit, int tid, float* lds) {
     const int g = P.gqa, ns = P.n_splits;
-    const int b = unit / P.n_kv_heads, hk = unit - b * P.n_kv_heads;
+    const int b = div_magic(unit, P.n_kv_heads, P.kv_magic), hk = unit - b * P.n_kv_heads;
     float* rec_lds = lds + (KVQ_ATTN_THREADS / 32) * KVQ_MAX_SPLITS;  // [slot][32][4]
     const int slots = KVQ_ATTN_THREADS >> 5;           // 16 >= g
     const int G = max(1, min(slots / g, ns));          // slot groups sharing the splits of one head
@@ -1032,7 +1036,7 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnSha
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane >> 4, n = lane & 15;
     const int g = P.gqa, ns = P.n_splits;
-    const int b = unit / P.n_kv_heads, hk = unit - b * P.n_kv_heads;
+    const int b = div_magic(unit, P.n_kv_heads, P.kv_magic), hk = unit - b * P.n_kv_heads;
     float (*const red_o)[16 * KVQ_OPAD] = sh.red_o;
 
     set_accumulator_exponent(st, 0);
@@ -1150,68 +1154,22 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnSha
     KVQ_STAMP(5);
 }
 
-// The whole kernel for one of the two V paths (SAFE: overflow-proof, see accumulate_tile) and one of the two kinds
-// of 16-bit tier (I16: integer codes in byte planes; else raw fp16).  A cache has one kind only, so each kernel carries
-// the code of one.
-// BATCH: the workgroup's (split, unit) come from the caller (ragged batch); else they are the workgroup's grid indices,
-// read where they are needed (handing them in as values costs the single-cache kernels scalar registers they lack).
-// APPEND: the kernel can carry out a one-token append into the 16-bit tier (P.app_t_old >= 0) and attend to that token too.
-template <bool SAFE, bool I16, bool BATCH, bool APPEND>
-__device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShared& sh, const int split_in = 0,
-                                               const int unit_in = 0) {
-    const int split = BATCH ? split_in : (int)blockIdx.x, unit = BATCH ? unit_in : (int)blockIdx.y;
+// The streaming phase of a workgroup for one of the two V paths (SAFE: overflow-proof, see accumulate_tile): every
+// wavefront leaves its partial in st.
+template <bool SAFE, bool I16>
+__device__ __forceinline__ void stream_range(const KvqAttnParams& P, AttnShared& sh, WaveState& st, int unit, int t_begin,
+                                             int t_end, int p_first, int p_last) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tpp = P.tiles_per_page;
     _Float16* const q_lds = sh.q;
     unsigned& claim_ctr = sh.claim_ctr;
     u32x4* const desc_lds = sh.desc;
     uint8_t* const meta_lds = sh.meta;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = P.gqa;
-    const int b = unit / P.n_kv_heads, hk = unit - b * P.n_kv_heads;
-
-    KVQ_STAMP(0);
-    KVQ_STAMP_ID();
-    const int tpp = P.tiles_per_page;
-    const int t_begin = P.split_begin[split], t_end = P.split_begin[split + 1];
-    const int p_first = t_begin / tpp, p_last = (t_end + tpp - 1) / tpp;  // pages touched: [p_first, p_last)
-    // stage q (heads beyond g are zero) and the first window of page descriptors with one round trip
-    if (tid < 256) {
-        const int head = tid >> 4, c16 = tid & 15;
-        u32x4 qv = {0u, 0u, 0u, 0u};
-        if (head < g) {
-            qv = *reinterpret_cast<const u32x4*>(static_cast<const _Float16*>(P.q) +
-                                                 ((size_t)b * P.n_q_heads + hk * g + head) * KVQ_D + c16 * 8);
-            if (P.lambda) {  // Q Lambda of the channel-wise reparameterization (Sec. 3.3, Eq. 7): fp32 product, RNE to fp16
-                const float* lam = P.lambda + hk * KVQ_D + c16 * 8;
-                uint32_t* qw = reinterpret_cast<uint32_t*>(&qv);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const _Float16 lo = __builtin_bit_cast(_Float16, (uint16_t)(qw[e] & 0xffff));
-                    const _Float16 hi = __builtin_bit_cast(_Float16, (uint16_t)(qw[e] >> 16));
-                    float plo = (float)lo * lam[2 * e], phi = (float)hi * lam[2 * e + 1];
-                    asm volatile("" : "+v"(plo), "+v"(phi));  // two roundings (fp32, then fp16), never a fused one
-                    const _Float16 nlo = (_Float16)plo, nhi = (_Float16)phi;
-                    qw[e] = (uint32_t)__builtin_bit_cast(uint16_t, nlo) | ((uint32_t)__builtin_bit_cast(uint16_t, nhi) << 16);
-                }
-            }
-        }
-        u32x4 dv = {0u, 0u, 0u, 0u};
-        if (tid < min(KVQ_DESC_CACHE, p_last - p_first)) dv = reinterpret_cast<const u32x4*>(P.table)[p_first + tid];
-        *reinterpret_cast<u32x4*>(&q_lds[head * KVQ_D + c16 * 8]) = qv;
-        desc_lds[tid] = dv;
-    }
-    // waves 4 and 5 have nothing else to stage
-    if (APPEND && P.app_t_old >= 0 && split == P.n_splits - 1 && (wave == 4 || wave == 5))
-        stage_new_token<I16>(P, sh, unit, hk, wave & 1, lane);
-    if (tid == 0) claim_ctr = KVQ_ATTN_WAVES;  // the first chunk of every wavefront is fixed, the counter starts behind them
-    __syncthreads();
-    KVQ_STAMP(1);
     QOps Q;
     Q.cls = -1;
     Q.have_qsum = 0;
     Q.qsum[0] = Q.qsum[1] = 0u;
 
-    WaveState st;
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) st.o[nt] = float4v{0.f, 0.f, 0.f, 0.f};
     st.zl = float4v{0.f, 0.f, 0.f, 0.f};
@@ -1267,6 +1225,63 @@ __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShare
             }
         }
     }
+}
+
+// The whole kernel for one of the two kinds of 16-bit tier (I16: integer codes in byte planes; else raw fp16).  A cache has
+// one kind only, so each kernel carries the code of one.
+// BATCH: the workgroup's (split, unit) come from the caller (ragged batch); else they are the workgroup's grid indices,
+// read where they are needed (handing them in as values costs the single-cache kernels scalar registers they lack).
+// APPEND: the kernel can carry out a one-token append into the 16-bit tier (P.app_t_old >= 0) and attend to that token too.
+template <bool I16, bool BATCH, bool APPEND>
+__device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShared& sh, const int split_in = 0,
+                                               const int unit_in = 0) {
+    const int split = BATCH ? split_in : (int)blockIdx.x, unit = BATCH ? unit_in : (int)blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = P.gqa;
+    const int b = div_magic(unit, P.n_kv_heads, P.kv_magic), hk = unit - b * P.n_kv_heads;
+
+    KVQ_STAMP(0);
+    KVQ_STAMP_ID();
+    // Which V path: needed only behind the staging, whose round trip to memory covers this one.
+    const uint32_t flags = P.flags[0];
+    const int tpp = P.tiles_per_page;
+    const int t_begin = P.split_begin[split], t_end = P.split_begin[split + 1];
+    const int p_first = div_magic(t_begin, tpp, P.tpp_magic), p_last = div_magic(t_end + tpp - 1, tpp, P.tpp_magic);  // pages touched: [p_first, p_last)
+    // stage q (heads beyond g are zero) and the first window of page descriptors with one round trip
+    if (tid < 256) {
+        const int head = tid >> 4, c16 = tid & 15;
+        u32x4 qv = {0u, 0u, 0u, 0u};
+        if (head < g) {
+            qv = *reinterpret_cast<const u32x4*>(static_cast<const _Float16*>(P.q) +
+                                                 ((size_t)b * P.n_q_heads + hk * g + head) * KVQ_D + c16 * 8);
+            if (P.lambda) {  // Q Lambda of the channel-wise reparameterization (Sec. 3.3, Eq. 7): fp32 product, RNE to fp16
+                const float* lam = P.lambda + hk * KVQ_D + c16 * 8;
+                uint32_t* qw = reinterpret_cast<uint32_t*>(&qv);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const _Float16 lo = __builtin_bit_cast(_Float16, (uint16_t)(qw[e] & 0xffff));
+                    const _Float16 hi = __builtin_bit_cast(_Float16, (uint16_t)(qw[e] >> 16));
+                    float plo = (float)lo * lam[2 * e], phi = (float)hi * lam[2 * e + 1];
+                    asm volatile("" : "+v"(plo), "+v"(phi));  // two roundings (fp32, then fp16), never a fused one
+                    const _Float16 nlo = (_Float16)plo, nhi = (_Float16)phi;
+                    qw[e] = (uint32_t)__builtin_bit_cast(uint16_t, nlo) | ((uint32_t)__builtin_bit_cast(uint16_t, nhi) << 16);
+                }
+            }
+        }
+        u32x4 dv = {0u, 0u, 0u, 0u};
+        if (tid < min(KVQ_DESC_CACHE, p_last - p_first)) dv = reinterpret_cast<const u32x4*>(P.table)[p_first + tid];
+        *reinterpret_cast<u32x4*>(&sh.q[head * KVQ_D + c16 * 8]) = qv;
+        sh.desc[tid] = dv;
+    }
+    // waves 4 and 5 have nothing else to stage
+    if (APPEND && P.app_t_old >= 0 && split == P.n_splits - 1 && (wave == 4 || wave == 5))
+        stage_new_token<I16>(P, sh, unit, hk, wave & 1, lane);
+    if (tid == 0) sh.claim_ctr = KVQ_ATTN_WAVES;  // the first chunk of every wavefront is fixed, the counter starts behind them
+    __syncthreads();
+    KVQ_STAMP(1);
+    WaveState st;
+    if (__builtin_amdgcn_readfirstlane(flags & 1u)) stream_range<true, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
+    else stream_range<false, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
 
     KVQ_STAMP(2);
     finish_workgroup<I16, APPEND>(P, sh, st, split, unit);

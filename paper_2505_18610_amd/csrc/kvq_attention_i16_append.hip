@@ -7,8 +7,7 @@ namespace {
 
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_i16_append_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    if (__builtin_amdgcn_readfirstlane(P.flags[0] & 1u)) attention_body<true, true, false, true>(P, sh);
-    else attention_body<false, true, false, true>(P, sh);
+    attention_body<true, false, true>(P, sh);
 }
 
 }  // namespace

@@ -830,6 +830,7 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     p.gqa = c->gqa;
     p.n_q_heads = c->cfg.n_q_heads;
     p.n_kv_heads = c->cfg.n_kv_heads;
+    p.kv_magic = p.n_kv_heads > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)p.n_kv_heads - 1) / (uint64_t)p.n_kv_heads) : 0u;
     p.n_splits = n_splits;
     p.out_fp32 = out_is_fp32 ? 1 : 0;
     p.fused_merge = c->fused_merge;

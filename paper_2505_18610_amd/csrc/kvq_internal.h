@@ -44,6 +44,7 @@ struct KvqAttnParams {
     int32_t gqa;               // query heads per KV head
     int32_t n_q_heads;
     int32_t n_kv_heads;
+    uint32_t kv_magic;         // ceil(2^32 / n_kv_heads) (unused when n_kv_heads == 1)
     int32_t n_splits;
     int32_t out_fp32;
     int32_t fused_merge;
