@@ -17,14 +17,24 @@ __device__ inline uint16_t f2h_rn(float f) { return __builtin_bit_cast(uint16_t,
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_any __attribute__((aligned(4)));  // tables of fp32 need not start at a multiple of 16 bytes
 
+// The fp16 value in the low (hi = 0) or high (hi = 1) half of w times x, rounded once to fp32: a fused multiply-add of
+// mixed precision with -0 as the addend, which leaves every product as it is, instead of a conversion and a product.
+__device__ inline float half_times(uint32_t w, int hi, float x) {
+    float r;
+    if (hi) asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(x), "s"(-0.0f));
+    else asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(x), "s"(-0.0f));
+    return r;
+}
+__device__ inline uint32_t pack_rn2(float lo, float hi) {  // two floats -> fp16, nearest even
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, h2{(_Float16)lo, (_Float16)hi});
+}
+
 // K Lambda^{-1} of Eq. 7 on one pair of channels: fp32 product with the channel's reciprocal factor, rounded to
-// nearest-even into fp16.  The product is rounded to fp32 first and to fp16 second, as two separate IEEE operations: the
-// empty asm keeps the compiler from fusing them into a mixed-precision instruction that rounds the exact product once
-// (1 fp16 ulp apart in about one element of 10^4).
+// nearest-even into fp16: two separate IEEE roundings (the products come out of asm, so the compiler cannot fuse them with the
+// conversion into an instruction that rounds once, 1 fp16 ulp apart in about one element of 10^4).
 __device__ inline uint32_t scale_pair(uint32_t w, float r_lo, float r_hi) {
-    float lo = h2f((uint16_t)(w & 0xffff)) * r_lo, hi = h2f((uint16_t)(w >> 16)) * r_hi;
-    asm("" : "+v"(lo), "+v"(hi));
-    return (uint32_t)f2h_rn(lo) | ((uint32_t)f2h_rn(hi) << 16);
+    return pack_rn2(half_times(w, 0, r_lo), half_times(w, 1, r_hi));
 }
 // 8 consecutive channels; rinv: their reciprocal factors.
 __device__ inline u32x4 scale_keys8(u32x4 v, const float* rinv) {
@@ -33,15 +43,16 @@ __device__ inline u32x4 scale_keys8(u32x4 v, const float* rinv) {
                  scale_pair(v.w, r1.z, r1.w)};
 }
 
-// Rotary embedding (Sec. 3.3, Eq. 9) of one channel: own * cos - partner * sin in the lower half of the head, own * cos +
-// partner * sin in the upper.  Every product and the sum are separate fp32 operations (the empty asm keeps them from being
-// contracted or fused with the conversion); the result is rounded to fp16.
-__device__ inline uint16_t rope1(uint16_t own, uint16_t partner, float c, float sn, bool upper) {
-    float p1 = h2f(own) * c, p2 = h2f(partner) * sn;
-    asm("" : "+v"(p1), "+v"(p2));
-    float sum = upper ? p1 + p2 : p1 - p2;
-    asm("" : "+v"(sum));
-    return f2h_rn(sum);
+// Rotary embedding (Sec. 3.3, Eq. 9) of one pair of channels: own * cos - partner * sin in the lower half of the head, own *
+// cos + partner * sin in the upper.  Every product and the sum are separate fp32 operations, the result is rounded to fp16
+// (the empty asm keeps the sum from being fused with the conversion).  sign: 0x80008000 in the lower half, where it turns
+// the partner's signs over, 0 in the upper; the difference is the sum with the negated product.
+__device__ inline uint32_t rope2(uint32_t own, uint32_t partner, uint32_t sign, float c0, float c1, float s0, float s1) {
+    partner ^= sign;
+    float lo = half_times(own, 0, c0) + half_times(partner, 0, s0);
+    float hi = half_times(own, 1, c1) + half_times(partner, 1, s1);
+    asm("" : "+v"(lo), "+v"(hi));
+    return pack_rn2(lo, hi);
 }
 // Eight consecutive angles of a token's table row [cos 64 | sin 64].
 struct Angles8 { f32x4 c[2], s[2]; };
@@ -55,18 +66,12 @@ __device__ inline Angles8 load_angles8(const float* row, int i0) {
     return a;
 }
 // 8 consecutive channels of one token; partner: the channels +- 64 of the same token.
-__device__ inline u32x4 rope8(u32x4 own, u32x4 partner, const Angles8& a, bool upper) {
+__device__ inline u32x4 rope8(u32x4 own, u32x4 partner, const Angles8& a, uint32_t sign) {
     u32x4 r;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        r[e] = 0u;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int i = 2 * e + h;
-            r[e] |= (uint32_t)rope1((uint16_t)(own[e] >> (16 * h)), (uint16_t)(partner[e] >> (16 * h)), a.c[i >> 2][i & 3],
-                                    a.s[i >> 2][i & 3], upper) << (16 * h);
-        }
-    }
+    for (int e = 0; e < 4; ++e)
+        r[e] = rope2(own[e], partner[e], sign, a.c[e >> 1][(2 * e) & 3], a.c[e >> 1][(2 * e + 1) & 3], a.s[e >> 1][(2 * e) & 3],
+                     a.s[e >> 1][(2 * e + 1) & 3]);
     return r;
 }
 
@@ -83,6 +88,7 @@ struct NewRows {
         return rel < (uint32_t)n_new ? rel * (uint32_t)(KVQ_D * 2) : 0x80000000u;
     }
     __device__ bool has(int tok) const { return (uint32_t)(tok - t_old) < (uint32_t)n_new; }
+    __device__ bool all(int tok0) const { return tok0 >= t_old && tok0 + KVQ_TILE_TOKENS <= t_old + n_new; }  // of a tile
     __device__ u32x4 load(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0); }
     __device__ u32x4 load_stream(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 2); }
     // index of the token's table row; tokens that are not new get a row that exists
@@ -122,12 +128,17 @@ __device__ inline void append16_k_tile(uint8_t* code, const NewRows& rows, int t
         for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                const u32x4 lo = rope8(v[sub][p], v[sub][p + 2], a[sub][p], false);
-                const u32x4 hi = rope8(v[sub][p + 2], v[sub][p], a[sub][p], true);
-                const u32x4 zero = {0u, 0u, 0u, 0u};  // (a rotated zero may come out negative)
-                v[sub][p] = isnew[sub] ? lo : zero;
-                v[sub][p + 2] = isnew[sub] ? hi : zero;
+                const u32x4 lo = rope8(v[sub][p], v[sub][p + 2], a[sub][p], 0x80008000u);
+                v[sub][p + 2] = rope8(v[sub][p + 2], v[sub][p], a[sub][p], 0u);
+                v[sub][p] = lo;
             }
+        if (!rows.all(tok0)) {  // (uniform) the zeros of tokens that are not new: a rotated one may be negative
+            asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+                for (int grp = 0; grp < 4; ++grp) v[sub][grp] = isnew[sub] ? v[sub][grp] : u32x4{0u, 0u, 0u, 0u};
+        }
     }
     if (rinv_head) {
 #pragma unroll

@@ -921,11 +921,7 @@ __device__ inline void stage_new_token(const KvqAttnParams& P, AttnShared& sh, i
     if (!which && P.app_rope) {
         const float* cs = P.app_rope + ((2 * lane) & 63);  // the token's row: cos 64 | sin 64
         const uint32_t partner = (uint32_t)__shfl_xor((int)w, 32);  // channels +- 64
-        uint32_t r = 0u;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            r |= (uint32_t)kvq_dev::rope1((uint16_t)(w >> (16 * h)), (uint16_t)(partner >> (16 * h)), cs[h], cs[64 + h], lane >= 32) << (16 * h);
-        w = r;
+        w = kvq_dev::rope2(w, partner, lane >= 32 ? 0u : 0x80008000u, cs[0], cs[1], cs[64], cs[65]);
     }
     if (!which && P.app_rinv) {
         const float* r = P.app_rinv + hk * KVQ_D + 2 * lane;

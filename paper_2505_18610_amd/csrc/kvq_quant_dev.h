@@ -134,9 +134,14 @@ __device__ inline void prepare_owner_keys(uint32_t (&w)[2][16], const kvq_dev::N
 #pragma unroll
                 for (int e = 0; e < 4; ++e)  // quad_perm 2 3 0 1
                     partner[e] = (uint32_t)__builtin_amdgcn_mov_dpp((int)own[e], 0x4E, 0xf, 0xf, true);
-                own = kvq_dev::rope8(own, partner, a[c], grp >= 2);
+                own = kvq_dev::rope8(own, partner, a[c], grp >= 2 ? 0u : 0x80008000u);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[pass][4 * c + e] = isnew ? own[e] : 0u;  // (a rotated zero may be negative)
+                for (int e = 0; e < 4; ++e) w[pass][4 * c + e] = own[e];
+            }
+            if (!rows.all(tok0)) {  // (uniform) the zeros of tokens that are not new: a rotated one may be negative
+                asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+                for (int e = 0; e < 16; ++e) w[pass][e] = isnew ? w[pass][e] : 0u;
             }
         }
         if (rinv_head) {
@@ -165,7 +170,7 @@ __device__ inline void prepare_owner_keys(uint32_t (&w)[2][16], const kvq_dev::N
 // differs from d / S by less than 2^-20 ulp before its rounding.  d / S itself is never nearer than 2^-12 ulp to a point
 // where that rounding changes: d - m S, m a midpoint of two fp32 numbers, is a non-zero multiple of half an ulp of m times
 // the last place of S.  So q is the IEEE quotient for every d and S that occur (nothing here is subnormal in fp32), at
-// every width, without a division or a branch.  Six operations per element; the division that used to be carried
+// every width, without a division.  Five operations per element (six at 16 bits); the division that used to be carried
 // out near half-integers cost a quarter of the 8-bit passes a slow path of twice the code, and the 16-bit codes all of
 // theirs.
 template <int B>
@@ -187,9 +192,21 @@ __device__ inline void quantize_owner(const uint32_t (&w)[16], uint32_t (&codes)
         const float d = half_minus(w[e >> 1], e & 1, mn);
         const float t = d * y;
         const float q = fmaf(fmaf(-t, Sf, d), y, t);
-        // clamped (a scale rounded down lifts the group maximum above the top level; a NaN comes out as 0), then rounded
-        // to the nearest even integer by adding 1.5 * 2^23, which leaves it in the low bits
-        codes[e] = __float_as_uint(__builtin_amdgcn_fmed3f(q, 0.0f, (float)levels) + 12582912.0f);
+        // rounded to the nearest even integer by adding 1.5 * 2^23, which leaves it in the low bits (those of a NaN are 0);
+        // 16-bit codes are clamped one by one: a scale rounded down lifts every other group's maximum above the top level
+        codes[e] = __float_as_uint((B == 16 ? __builtin_amdgcn_fmed3f(q, 0.0f, (float)levels) : q) + 12582912.0f);
+    }
+    if constexpr (B < 16) {
+        // In the narrow widths only a scale rounded down to a subnormal lifts a code above the top level, and no element's
+        // quotient exceeds that of the group maximum (x <= mx, every step is monotone): decided once per group.
+        const float dm = mx - mn, tm = dm * y;
+        const bool over = fmaf(fmaf(-tm, Sf, dm), y, tm) > (float)levels + 0.25f;
+        if (__any(over)) {
+            asm volatile("" ::: "memory");  // keeps this a branch
+            const uint32_t top = over ? __float_as_uint((float)levels + 12582912.0f) : 0xffffffffu;
+#pragma unroll
+            for (int e = 0; e < 32; ++e) codes[e] = min(codes[e], top);
+        }
     }
 }
 
