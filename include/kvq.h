@@ -316,9 +316,8 @@ kvq_status_t kvq_stream_read_probe(kvq_cache_t* cache, const void* buf_dev, uint
 /* Empties block `layer` (-1: every block) so that the cache can take a new sequence: its pages go back to the arena
  * (reused only by work enqueued later, so on the cache's stream nothing in flight is disturbed), its token count to
  * zero; budget, Fbit, options and the block's reparameterization factors stay (kvq_cache_set_reparam may be called
- * again, the block being empty).  Host bookkeeping only; nothing is enqueued.  Once every block is empty, the
- * device-side flags of the cache (the mark that a V scale >= 256 was seen, which selects the slower overflow-proof
- * attention path) are cleared by the next call that enqueues work, in stream order. */
+ * again, the block being empty).  Host bookkeeping only; nothing is enqueued.  Once every block is empty, the mark
+ * that a V scale >= 256 was seen, which selects the slower overflow-proof attention path, is void. */
 kvq_status_t kvq_cache_reset(kvq_cache_t* cache, int32_t layer);
 
 /* Free bytes left in the arena's page area (host bookkeeping). */

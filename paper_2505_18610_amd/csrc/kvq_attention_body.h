@@ -1239,7 +1239,7 @@ __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShare
     KVQ_STAMP(0);
     KVQ_STAMP_ID();
     // Which V path: needed only behind the staging, whose round trip to memory covers this one.
-    const uint32_t flags = P.flags[0];
+    const uint32_t mark = P.v_mark[0];
     const int tpp = P.tiles_per_page;
     const int t_begin = P.split_begin[split], t_end = P.split_begin[split + 1];
     const int p_first = div_magic(t_begin, tpp, P.tpp_magic), p_last = div_magic(t_end + tpp - 1, tpp, P.tpp_magic);  // pages touched: [p_first, p_last)
@@ -1276,7 +1276,7 @@ __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShare
     __syncthreads();
     KVQ_STAMP(1);
     WaveState st;
-    if (__builtin_amdgcn_readfirstlane(flags & 1u)) stream_range<true, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
+    if (__builtin_amdgcn_readfirstlane(mark) == P.v_epoch) stream_range<true, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
     else stream_range<false, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
 
     KVQ_STAMP(2);

@@ -105,7 +105,8 @@ struct kvq_cache {
     uint64_t unit_bytes = 0;
     uint64_t table_off = 0, jobs_off = 0, part_o_off = 0, part_ml_off = 0, counters_off = 0, flags_off = 0, pages_off = 0;
     uint64_t reparam_off = 0;  // per block: lambda [n_kv_heads][128] fp32, then 1 / lambda
-    uint32_t* flags_dev() const { return reinterpret_cast<uint32_t*>(arena + flags_off); }
+    uint32_t v_epoch = 1;      // see KvqVMark; 0 is what a cleared word holds
+    KvqVMark v_mark() const { return KvqVMark{reinterpret_cast<uint32_t*>(arena + flags_off), v_epoch}; }
     Buddy buddy;
     std::vector<Layer> layers;
     uint8_t* ring = nullptr;
@@ -113,6 +114,7 @@ struct kvq_cache {
     KvqStagingRing<RingEvents, kRingSegments> ring_ctl;
     RingEvents ring_events;
     bool device_ready = false;
+    bool enqueue_failed = false;  // a block was left unusable since the device's counters were last cleared
     int splits_override = 0;
     int fused_merge = 1;
     int deterministic = 0;
@@ -325,8 +327,8 @@ kvq_status_t run_lowering_step(kvq_cache* c, int layer, std::vector<Lowering>& l
         hipError_t e = hipSuccess;
         if (st == KVQ_OK) {
             const KvqRequantJob* jh = by_arg ? jobs.data() : nullptr;
-            e = fresh_meta ? kvq_launch_quant16(to, c->arena, c->table_dev(layer), jd, jh, (int)jobs.size(), c->tpp, c->units, c->flags_dev(), c->cfg.group, s)
-                             : kvq_launch_shrink(to, c->shift_strategy, c->arena, c->table_dev(layer), jd, jh, (int)jobs.size(), c->tpp, c->units, c->flags_dev(), s);
+            e = fresh_meta ? kvq_launch_quant16(to, c->arena, c->table_dev(layer), jd, jh, (int)jobs.size(), c->tpp, c->units, c->v_mark(), c->cfg.group, s)
+                             : kvq_launch_shrink(to, c->shift_strategy, c->arena, c->table_dev(layer), jd, jh, (int)jobs.size(), c->tpp, c->units, c->v_mark(), s);
         }
         if (st != KVQ_OK || e != hipSuccess) {
             for (auto& w : low) {
@@ -652,7 +654,7 @@ kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, 
             }
         }
         if (kvq_launch_append(e, c->arena, c->table_dev(layer), k_dev, v_dev, t_old, n_new, c->tpp, c->units,
-                              pages, c->flags_dev(), c->cfg.group,
+                              pages, c->v_mark(), c->cfg.group,
                               L.reparam ? c->lambda_dev(layer) + c->cfg.n_kv_heads * KVQ_D : nullptr, c->cfg.n_kv_heads,
                               cos_sin_dev, c->int16(), s) != hipSuccess) {
             release_first_step(c, low);
@@ -823,7 +825,8 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     p.part_o = reinterpret_cast<float*>(c->arena + c->part_o_off);
     p.part_ml = reinterpret_cast<float*>(c->arena + c->part_ml_off);
     p.counters = reinterpret_cast<uint32_t*>(c->arena + c->counters_off);
-    p.flags = c->flags_dev();
+    p.v_mark = c->v_mark().word;
+    p.v_epoch = c->v_epoch;
     p.n_tokens = n_tokens;
     p.tiles_per_page = c->tpp;
     p.tpp_magic = c->tpp > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)c->tpp - 1) / (uint64_t)c->tpp) : 0u;
@@ -1261,6 +1264,7 @@ kvq_status_t kvq_cache_reset(kvq_cache_t* c, int32_t layer) {
     const int first = layer < 0 ? 0 : layer, last = layer < 0 ? c->cfg.n_layers : layer + 1;
     for (int l = first; l < last; ++l) {
         Layer& L = c->layers[(size_t)l];
+        c->enqueue_failed = c->enqueue_failed || L.poisoned;
         for (const Page& p : L.pages) {
             c->buddy.release(p.code_unit, order_of_bits(p.bits));
             if (c->has_meta(p.bits)) c->buddy.release(p.meta_unit, 0);
@@ -1271,11 +1275,14 @@ kvq_status_t kvq_cache_reset(kvq_cache_t* c, int32_t layer) {
         L.plan_tiles = -1;
         L.poisoned = false;
     }
-    // An empty cache starts over: the next enqueueing call clears the device flags again (in stream order), among them
-    // the mark that some V scale was large, which would otherwise outlive the data that set it.
+    // An empty cache starts over: the mark that some V scale was large must not outlive the data that set it, and if an
+    // enqueue had failed the next call that enqueues work clears the device's counters and mark again, in stream order.
     bool all_empty = true;
     for (const Layer& L : c->layers) all_empty = all_empty && L.T == 0;
-    if (all_empty) c->device_ready = false;
+    if (all_empty) {
+        if (++c->v_epoch == 0) c->v_epoch = 1;
+        if (c->enqueue_failed) c->device_ready = c->enqueue_failed = false;
+    }
     return KVQ_OK;
 }
 

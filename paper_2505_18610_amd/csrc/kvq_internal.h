@@ -6,6 +6,14 @@
 #include <stdint.h>
 #include "kvq_layout.h"
 
+// Mark of a cache that holds a V scale >= 256 (it selects the attention kernels' overflow-proof V path): the quantizing kernels
+// store the cache's current epoch into the word, the mark is set while the word equals it, and emptying the cache moves the
+// epoch on, so that nothing has to be cleared on the device.
+struct KvqVMark {
+    uint32_t* word;
+    uint32_t epoch;
+};
+
 // The device page tables are written by the kernels that make the pages: an append, a re-quantization or the attention
 // launch that appends a token gets the new entries in its arguments and stores them beside its other output.  (A copy
 // from pinned memory in front of or behind each of them cost 4 us of copy kernel and 2 to 6 us of gaps.)
@@ -37,7 +45,8 @@ struct KvqAttnParams {
     float* part_o;             // [unit][split][16][128] un-normalised partial outputs
     float* part_ml;            // [unit][split][16] pairs (running max in log2 units, sum)
     uint32_t* counters;        // [unit] arrival counters of the fused merge (kept at zero between launches)
-    const uint32_t* flags;     // [0] bit 0: some V scale of the cache is >= 256 (set by the quantizing kernels)
+    const uint32_t* v_mark;    // equal to v_epoch: some V scale of the cache is >= 256 (set by the quantizing kernels)
+    uint32_t v_epoch;
     int32_t n_tokens;          // tokens read from the cache (without the one this launch appends)
     int32_t tiles_per_page;
     uint32_t tpp_magic;        // ceil(2^32 / tiles_per_page) (unused when tiles_per_page == 1)
@@ -81,15 +90,15 @@ struct KvqAppendPages {
 // table: the block's device page table, read (n == 0) or written (fresh entries)
 hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const void* k_in,
                              const void* v_in, int t_old, int n_new, int tiles_per_page, int units,
-                             const KvqAppendPages& pages, uint32_t* flags, int group,
+                             const KvqAppendPages& pages, KvqVMark mark, int group,
                              const float* rinv, int n_kv_heads, const float* rope, bool int16, hipStream_t s);
 // table: the block's device page table; the kernels write the entries of the pages they re-quantize
 hipError_t kvq_launch_shrink(int dst_bits, int strategy, uint8_t* arena, KvqPageDesc* table, const KvqRequantJob* jobs_dev,
                              const KvqRequantJob* jobs_host, int n_jobs, int tiles_per_page, int units,
-                             uint32_t* flags, hipStream_t s);
+                             KvqVMark mark, hipStream_t s);
 hipError_t kvq_launch_quant16(int dst_bits, uint8_t* arena, KvqPageDesc* table, const KvqRequantJob* jobs_dev,
                               const KvqRequantJob* jobs_host, int n_jobs, int tiles_per_page, int units,
-                              uint32_t* flags, int group, hipStream_t s);
+                              KvqVMark mark, int group, hipStream_t s);
 hipError_t kvq_launch_reparam_store(const float* lambda, float* dst, int n, hipStream_t s);
 hipError_t kvq_launch_calibrate(const void* k, int batch, int n_kv_heads, int n_tokens, float alpha, float floor_,
                                 float* lambda, hipStream_t s);

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
                                                           const uint16_t* __restrict__ k_in,
                                                           const uint16_t* __restrict__ v_in, int t_old,
                                                           int n_new, int tpp, int tile0, const KvqAppendPages ap,
-                                                          uint32_t* __restrict__ flags, int gspan,
+                                                          const KvqVMark mark, int gspan,
                                                           const float* __restrict__ rinv, int n_kv_heads,
                                                           const float* __restrict__ rope, int n_strings, int by_unit) {
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[KVQ_APPEND_WG_WAVES][KVQ_LDS_CODES];
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
         uint32_t codes[32];
         uint16_t S, Z;
         quantize_owner<B>(w[pass], codes, &S, &Z, gspan);  // tokens that are not new quantize zeros: codes 0, S = Z = 0
-        note_large_v_scale(flags, which, S);
+        note_large_v_scale(mark, which, S);
         scatter_codes(lds, which, tl, grp, codes);
         if (tok >= t_old) store_meta_owner(meta, which, tl, grp, S, Z);
     }
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64) void kvq_append_i16_kernel(uint8_t* __restrict_
 template <int B>
 __global__ __launch_bounds__(64) void kvq_quant16_kernel(uint8_t* __restrict__ arena, KvqPageDesc* __restrict__ table,
                                                          const KvqRequantJob* __restrict__ jobs, int tpp,
-                                                         uint32_t* __restrict__ flags, int gspan,
+                                                         const KvqVMark mark, int gspan,
                                                          const KvqJobArgs ja) {
     // One LDS block: [pad | raw rows 0..15 | raw rows 16..31].  The codes of both passes go to the first KVQ_LDS_CODES bytes,
     // i.e. the pad and the rows of the first pass, which every lane has read by the time the first codes are written (the
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64) void kvq_quant16_kernel(uint8_t* __restrict__ a
         uint32_t codes[32];
         uint16_t S, Z;
         quantize_owner<B>(w, codes, &S, &Z, gspan);
-        note_large_v_scale(flags, which, S);
+        note_large_v_scale(mark, which, S);
         scatter_codes(lds, which, tl, grp, codes);
         store_meta_owner(meta, which, tl, grp, S, Z);
     }
@@ -344,7 +344,7 @@ __device__ inline uint32_t trunc_8_to_4(uint32_t w) {  // 4 bytes -> their upper
 template <int B, int STRAT>
 __global__ __launch_bounds__(64) void kvq_shrink_kernel(uint8_t* __restrict__ arena, KvqPageDesc* __restrict__ table,
                                                         const KvqRequantJob* __restrict__ jobs, int tpp,
-                                                        uint32_t* __restrict__ flags, const KvqJobArgs ja) {
+                                                        const KvqVMark mark, const KvqJobArgs ja) {
     const int lane = threadIdx.x;
     const int job = blockIdx.x / tpp, tip = blockIdx.x - job * tpp;
     const int unit = blockIdx.y;
@@ -404,8 +404,8 @@ __global__ __launch_bounds__(64) void kvq_shrink_kernel(uint8_t* __restrict__ ar
         reinterpret_cast<uint32_t*>(meta + 256)[lane] = nzk;
         reinterpret_cast<uint32_t*>(meta + 768)[lane] = nzv;
     }
-    note_large_v_scale(flags, 1, (uint16_t)(nv & 0xffff));
-    note_large_v_scale(flags, 1, (uint16_t)(nv >> 16));
+    note_large_v_scale(mark, 1, (uint16_t)(nv & 0xffff));
+    note_large_v_scale(mark, 1, (uint16_t)(nv >> 16));
 }
 
 // --------------------------------------------------------------------------------- reconstruction error
@@ -675,7 +675,7 @@ __global__ void kvq_fill_u32_kernel(uint32_t* dst, uint32_t value, size_t n) {
 
 hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const void* k_in,
                              const void* v_in, int t_old, int n_new, int tiles_per_page, int units,
-                             const KvqAppendPages& ap, uint32_t* flags, int group,
+                             const KvqAppendPages& ap, KvqVMark mark, int group,
                              const float* rinv, int n_kv_heads, const float* rope, bool int16, hipStream_t s) {
     const int gspan = group / KVQ_G;
     int tile0 = t_old / KVQ_TILE_TOKENS;
@@ -692,7 +692,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
         hipLaunchKernelGGL((kernel_), grid, dim3(64 * waves_), 0, s, arena, table, k, v, t_old, n_new, tiles_per_page,   \
                            tile0, ap, extra_, rinv, n_kv_heads, rope, n_strings, by_unit);                               \
     } while (0)
-#define KVQ_FLAGS flags, gspan
+#define KVQ_MARK mark, gspan
     switch (bits + (int16 && bits == 16 ? 1 : 0)) {
         case 17:
             if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 1, gspan);
@@ -704,8 +704,8 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
             break;
 #define KVQ_APPEND_CASE(b_)                                                                                              \
         case b_:                                                                                                         \
-            if (plain) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true>), KVQ_APPEND_WG_WAVES, KVQ_FLAGS);               \
-            else KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false>), KVQ_APPEND_WG_WAVES, KVQ_FLAGS);                    \
+            if (plain) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true>), KVQ_APPEND_WG_WAVES, KVQ_MARK);               \
+            else KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false>), KVQ_APPEND_WG_WAVES, KVQ_MARK);                    \
             break;
         KVQ_APPEND_CASE(8)
         KVQ_APPEND_CASE(4)
@@ -713,7 +713,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
         default: return hipErrorInvalidValue;
     }
 #undef KVQ_APPEND_CASE
-#undef KVQ_FLAGS
+#undef KVQ_MARK
 #undef KVQ_APPEND_LAUNCH
     return hipGetLastError();
 }
@@ -728,12 +728,12 @@ static void fill_job_args(KvqJobArgs& ja, const KvqRequantJob* jobs_host, int n_
 // not read; otherwise jobs_dev must already hold the list (in stream order).
 hipError_t kvq_launch_shrink(int dst_bits, int strategy, uint8_t* arena, KvqPageDesc* table, const KvqRequantJob* jobs_dev,
                              const KvqRequantJob* jobs_host, int n_jobs, int tiles_per_page, int units,
-                             uint32_t* flags, hipStream_t s) {
+                             KvqVMark mark, hipStream_t s) {
     dim3 grid(n_jobs * tiles_per_page, units), block(64);
     KvqJobArgs ja;
     fill_job_args(ja, jobs_host, n_jobs);
 #define KVQ_SHRINK_CASE(B_, S_) \
-    hipLaunchKernelGGL((kvq_shrink_kernel<B_, S_>), grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, flags, ja)
+    hipLaunchKernelGGL((kvq_shrink_kernel<B_, S_>), grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, mark, ja)
     switch (dst_bits * 4 + strategy) {
         case 8 * 4 + 0: KVQ_SHRINK_CASE(8, 0); break;
         case 8 * 4 + 1: KVQ_SHRINK_CASE(8, 1); break;
@@ -770,14 +770,14 @@ hipError_t kvq_launch_error(bool l1, const uint8_t* arena, const KvqPageDesc* ta
 
 hipError_t kvq_launch_quant16(int dst_bits, uint8_t* arena, KvqPageDesc* table, const KvqRequantJob* jobs_dev,
                               const KvqRequantJob* jobs_host, int n_jobs, int tiles_per_page, int units,
-                              uint32_t* flags, int group, hipStream_t s) {
+                              KvqVMark mark, int group, hipStream_t s) {
     dim3 grid(2 * n_jobs * tiles_per_page, units), block(64);
     KvqJobArgs ja;
     fill_job_args(ja, jobs_host, n_jobs);
     switch (dst_bits) {
-        case 8: hipLaunchKernelGGL(kvq_quant16_kernel<8>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
-        case 4: hipLaunchKernelGGL(kvq_quant16_kernel<4>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
-        case 2: hipLaunchKernelGGL(kvq_quant16_kernel<2>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, flags, group / KVQ_G, ja); break;
+        case 8: hipLaunchKernelGGL(kvq_quant16_kernel<8>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, mark, group / KVQ_G, ja); break;
+        case 4: hipLaunchKernelGGL(kvq_quant16_kernel<4>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, mark, group / KVQ_G, ja); break;
+        case 2: hipLaunchKernelGGL(kvq_quant16_kernel<2>, grid, block, 0, s, arena, table, jobs_dev, tiles_per_page, mark, group / KVQ_G, ja); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -281,8 +281,8 @@ __device__ inline void wave_sync_lds() {
 // The attention kernel multiplies probabilities (<= 1) by up to 64 and by the V scale in fp16; a cache that ever
 // holds a V scale of 256 or more (a value range no attention layer produces) is marked and takes the kernel's
 // overflow-proof path instead.
-__device__ inline void note_large_v_scale(uint32_t* flags, int which, uint16_t S) {
-    if (which && h2f(S) >= 256.0f) atomicOr(flags, 1u);
+__device__ inline void note_large_v_scale(const KvqVMark& mark, int which, uint16_t S) {
+    if (which && h2f(S) >= 256.0f) __hip_atomic_store(mark.word, mark.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Owner lanes write the (S, Z) of their group straight to the tile's metadata.
