@@ -21,19 +21,19 @@ unsigned char* g_scratch_ptr[kMaxDevices];  // device address of `scratch` per d
 // grid = (splits, units); 512 threads = 8 wavefronts, one workgroup per compute unit.
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    attention_body<false, false, false>(P, sh);
+    attention_body<false, false, false>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
 }
 
 // The same with a one-token append into the raw fp16 tier in front (kvq_append_decode_attention).
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_append_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    attention_body<false, false, true>(P, sh);
+    attention_body<false, false, true>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
 }
 
 // The same for a cache whose 16-bit tier holds integer codes in byte planes (KVQ_TIER16_INT16).
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_i16_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    attention_body<true, false, false>(P, sh);
+    attention_body<true, false, false>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
 }
 
 // Same thread count as the attention kernel, so both merge variants add in the same order.

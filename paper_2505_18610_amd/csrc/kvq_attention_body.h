@@ -811,7 +811,7 @@ __device__ inline float reduce32(float x) {
 // first (a lane takes up to four splits; maximum and denominator are half-wavefront reductions), so that no barrier
 // stands between the loads and the sum; one barrier combines the slot groups.  lds: KVQ_MERGE_LDS_FLOATS floats.  Call it with the whole workgroup.
 template <bool AGENT>
-__device__ inline void merge_splits(const KvqAttnParams& P, int unit, int tid, float* lds) {
+__device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, float* lds) {
     const int g = P.gqa, ns = P.n_splits;
     const int b = div_magic(unit, P.n_kv_heads, P.kv_magic), hk = unit - b * P.n_kv_heads;
     float* rec_lds = lds + (KVQ_ATTN_THREADS / 32) * KVQ_MAX_SPLITS;  // [slot][32][4]
@@ -915,7 +915,7 @@ static_assert(KVQ_ATTN_WAVES * 16 * KVQ_OPAD >= KVQ_MERGE_LDS_FLOATS, "the wavef
 // reparameterization exactly as the append kernels carry them out (kvq_append16.h), in the integer tier Eq. 1-2 with
 // 2^16 - 1 levels (kvq_quant_dev.h).
 template <bool I16>
-__device__ inline void stage_new_token(const KvqAttnParams& P, AttnShared& sh, int unit, int hk, int which, int lane) {
+__device__ inline void stage_new_token(const KvqAttnHead& P, AttnShared& sh, int unit, int hk, int which, int lane) {
     uint32_t w;
     __builtin_memcpy(&w, static_cast<const uint16_t*>(which ? P.app_v : P.app_k) + (size_t)unit * KVQ_D + 2 * lane, 4);
     if (!which && P.app_rope) {
@@ -964,7 +964,7 @@ __device__ inline void score_new_token(AttnShared& sh, float scale_log2, int wav
 // The new token's K (which = 0) or V (1) elements -> its tile, one wavefront.  A tile that it starts is zeroed first, codes
 // and (integer tier) metadata, so that the slots of tokens to come are well defined, as the append kernels leave them.
 template <bool I16>
-__device__ inline void store_new_token(const KvqAttnParams& P, const AttnShared& sh, int unit, int which, int lane) {
+__device__ inline void store_new_token(const KvqAttnHead& P, const AttnShared& sh, int unit, int which, int lane) {
     const int tile = P.app_t_old / KVQ_TILE_TOKENS, t = P.app_t_old - tile * KVQ_TILE_TOKENS;
     const int tip = tile - (tile / P.tiles_per_page) * P.tiles_per_page;
     const uint64_t tslot = (uint64_t)unit * P.tiles_per_page + tip;
@@ -1024,7 +1024,7 @@ __device__ inline void store_new_token(const KvqAttnParams& P, const AttnShared&
 // End of a workgroup's range: merge of its eight wavefront partials through LDS, then either the output (one split),
 // the partial for the separate merge kernel, or the fused merge of the unit's split partials.
 template <bool I16, bool APPEND>
-__device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnShared& sh, WaveState& st, int split, int unit) {
+__device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShared& sh, WaveState& st, int split, int unit) {
     // the thread index is taken afresh, opaque to the compiler: nothing derived from it stays in a register across
     // the streaming loop for the sake of this epilogue
     int tid = threadIdx.x;
@@ -1153,7 +1153,7 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnParams& P, AttnSha
 // The streaming phase of a workgroup for one of the two V paths (SAFE: overflow-proof, see accumulate_tile): every
 // wavefront leaves its partial in st.
 template <bool SAFE, bool I16>
-__device__ __forceinline__ void stream_range(const KvqAttnParams& P, AttnShared& sh, WaveState& st, int unit, int t_begin,
+__device__ __forceinline__ void stream_range(const KvqAttnHead& P, AttnShared& sh, WaveState& st, int unit, int t_begin,
                                              int t_end, int p_first, int p_last) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tpp = P.tiles_per_page;
@@ -1229,8 +1229,8 @@ __device__ __forceinline__ void stream_range(const KvqAttnParams& P, AttnShared&
 // read where they are needed (handing them in as values costs the single-cache kernels scalar registers they lack).
 // APPEND: the kernel can carry out a one-token append into the 16-bit tier (P.app_t_old >= 0) and attend to that token too.
 template <bool I16, bool BATCH, bool APPEND>
-__device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShared& sh, const int split_in = 0,
-                                               const int unit_in = 0) {
+__device__ __forceinline__ void attention_body(const KvqAttnHead& P, const int t_begin, const int t_end, AttnShared& sh,
+                                               const int split_in = 0, const int unit_in = 0) {
     const int split = BATCH ? split_in : (int)blockIdx.x, unit = BATCH ? unit_in : (int)blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = P.gqa;
@@ -1241,7 +1241,6 @@ __device__ __forceinline__ void attention_body(const KvqAttnParams& P, AttnShare
     // Which V path: needed only behind the staging, whose round trip to memory covers this one.
     const uint32_t mark = P.v_mark[0];
     const int tpp = P.tiles_per_page;
-    const int t_begin = P.split_begin[split], t_end = P.split_begin[split + 1];
     const int p_first = div_magic(t_begin, tpp, P.tpp_magic), p_last = div_magic(t_end + tpp - 1, tpp, P.tpp_magic);  // pages touched: [p_first, p_last)
     // stage q (heads beyond g are zero) and the first window of page descriptors with one round trip
     if (tid < 256) {

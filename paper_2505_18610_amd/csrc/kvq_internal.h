@@ -36,7 +36,7 @@ struct KvqJobArgs {
     KvqRequantJob jobs[KVQ_JOBS_BY_ARG];
 };
 
-struct KvqAttnParams {
+struct KvqAttnHead {
     const uint8_t* arena;
     const KvqPageDesc* table;  // this block's page table
     const void* q;             // fp16 [batch, n_q_heads, 128]
@@ -60,7 +60,6 @@ struct KvqAttnParams {
     int32_t deterministic;     // 1: static chunk-to-wavefront assignment (bit-reproducible summation order)
     int32_t int16_tier;        // 1: 16-bit pages hold integer codes in byte planes (selects the kernel)
     float scale_log2;          // softmax scale * log2(e)
-    int32_t split_begin[KVQ_MAX_SPLITS + 1];  // tile index where each split starts
     // a one-token append into the 16-bit tier done by the workgroup of a unit's last split (app_t_old < 0: none)
     int32_t app_t_old;         // tokens before the append
     KvqPageDesc app_desc;      // page of the new token
@@ -70,6 +69,9 @@ struct KvqAttnParams {
     const float* app_rope;     // [1][128] cos | sin of the new position, or null
     const float* app_rinv;     // [n_kv_heads][128] reciprocal reparameterization factors, or null
     int32_t app_gspan;         // quantization group / 32 (integer 16-bit tier: the new token is quantized, Eq. 1-2)
+};
+struct KvqAttnParams : KvqAttnHead {
+    int32_t split_begin[KVQ_MAX_SPLITS + 1];  // tile index where each split starts
 };
 
 // kvq_quant.hip
