@@ -62,7 +62,12 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ 
 // Four wavefronts per workgroup, each with a string and LDS of its own: 1 to 2 % faster on bulk appends than one-wavefront
 // workgroups (a quarter of the workgroups to dispatch).
 #define KVQ_APPEND_WG_WAVES 4
-template <int B, bool PLAIN>
+#define KVQ_PAIR_MAX_STRINGS 2560
+// PAIR: two wavefronts per string, one for each 16 tokens, two strings per workgroup.  A launch of one or two strings per
+// SIMD (1,024 of them) leaves each alone with some 1,000 to 1,700 vector instructions; shared by two it ends earlier.  Rotated
+// keys, one wavefront against two: 256 strings 6.3 and 5.1 us, 1,024 7.4 and 7.2, 1,536 9.0 and 8.4, 2,560 12.8 and 11.5;
+// from 3,072 on (13.0 and 13.0; 4,096: 15.8 and 17.2) the SIMDs have enough to interleave, so the line is at 2,560.
+template <int B, bool PLAIN, bool PAIR>
 __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(uint8_t* __restrict__ arena,
                                                           KvqPageDesc* __restrict__ table,
                                                           const uint16_t* __restrict__ k_in,
@@ -73,11 +78,12 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
                                                           const float* __restrict__ rope, int n_strings, int by_unit) {
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[KVQ_APPEND_WG_WAVES][KVQ_LDS_CODES];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint8_t* const lds = lds_all[wave];
+    uint8_t* const lds = lds_all[PAIR ? wave >> 1 : wave];
     const int lane = threadIdx.x & 63, j = lane >> 4, n = lane & 15;
     int string, unit;
     if (wave == 0) write_fresh_pages(table, ap, lane);
-    if (!append_work<PLAIN, KVQ_APPEND_WG_WAVES>(n_strings, by_unit, wave, &string, &unit)) return;
+    // (the number of strings is even: with pairs every workgroup has two, K and V of one tile)
+    if (!append_work<PLAIN, PAIR ? 2 : KVQ_APPEND_WG_WAVES>(n_strings, by_unit, PAIR ? wave >> 1 : wave, &string, &unit)) return;
     const int which = string & 1;
     const int tile = tile0 + (string >> 1);
     const int page = tile / tpp, tip = tile - page * tpp;
@@ -88,12 +94,14 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
     const int tok0 = tile * KVQ_TILE_TOKENS;
     const kvq_dev::NewRows rows((which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D, t_old, n_new);
     const int grp = lane & 3;
-    uint32_t w[2][16];
-    load_owner_rows(w, rows, tok0, lane);
-    if (!PLAIN && !which) prepare_owner_keys(w, rows, tok0, lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
+    constexpr int PASSES = PAIR ? 1 : 2;
+    const int pass0 = PAIR ? wave & 1 : 0;
+    uint32_t w[PASSES][16];
+    load_owner_rows(w, rows, tok0 + 16 * pass0, lane);
+    if (!PLAIN && !which) prepare_owner_keys(w, rows, tok0 + 16 * pass0, rows.all(tok0), lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int tl = 16 * pass + (lane >> 2);
+    for (int pass = 0; pass < PASSES; ++pass) {
+        const int tl = 16 * (pass0 + pass) + (lane >> 2);
         const int tok = tok0 + tl;
         uint32_t codes[32];
         uint16_t S, Z;
@@ -102,7 +110,9 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
         scatter_codes(lds, which, tl, grp, codes);
         if (tok >= t_old) store_meta_owner(meta, which, tl, grp, S, Z);
     }
-    wave_sync_lds();
+    if (PAIR) __syncthreads();
+    else wave_sync_lds();
+    if (PAIR && (B == 2 || tok0 < t_old) && pass0 != 0) return;  // one chunk, or one merged with stored tokens: no halves
     uint32_t str[2 * B];
     gather_string<B>(lds, which, lane, str);
     // stored tokens keep their bits
@@ -132,7 +142,19 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
     }
     // a tile made of new tokens only is written once and read much later: streaming stores (with plain stores the
     // bulk appends run a quarter slower)
-    store_chunks_stream<B>(code, lane, str);
+    if constexpr (PAIR && B > 2) {  // each wavefront of the pair stores half of the string's chunks
+        constexpr int HALF = B / 4;
+        const uint32_t second = pass0 ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int c = 0; c < HALF; ++c) {
+            u32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (str[4 * c + e] & ~second) | (str[4 * (c + HALF) + e] & second);
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(code + ((c + HALF * pass0) * 64 + lane) * 16));
+        }
+    } else {
+        store_chunks_stream<B>(code, lane, str);
+    }
 }
 
 // Append into the integer 16-bit tier: Eq. 1-2 with 2^16 - 1 levels by the same owner lanes; the high and the low
@@ -163,7 +185,7 @@ __global__ __launch_bounds__(64) void kvq_append_i16_kernel(uint8_t* __restrict_
     const int grp = lane & 3;
     uint32_t w[2][16];
     load_owner_rows(w, rows, tok0, lane);
-    if (!PLAIN && !which) prepare_owner_keys(w, rows, tok0, lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
+    if (!PLAIN && !which) prepare_owner_keys(w, rows, tok0, rows.all(tok0), lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         const int tl = 16 * pass + (lane >> 2);
@@ -684,28 +706,31 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     const bool plain = !rinv && !rope;
     const uint16_t* k = static_cast<const uint16_t*>(k_in);
     const uint16_t* v = static_cast<const uint16_t*>(v_in);
+    const bool pair = (int64_t)n_strings * units <= KVQ_PAIR_MAX_STRINGS;
     const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 ? units : 0;
-#define KVQ_APPEND_LAUNCH(kernel_, waves_, extra_)                                                                       \
+#define KVQ_APPEND_LAUNCH(kernel_, waves_, per_, extra_)                                                                     \
     do {                                                                                                                 \
         const int n_wg = (n_strings + waves_ - 1) / waves_;                                                              \
         const dim3 grid = by_unit ? dim3((unsigned)n_wg * (unsigned)units) : dim3(n_wg, units);                          \
-        hipLaunchKernelGGL((kernel_), grid, dim3(64 * waves_), 0, s, arena, table, k, v, t_old, n_new, tiles_per_page,   \
+        hipLaunchKernelGGL((kernel_), grid, dim3(64 * waves_ * per_), 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, \
                            tile0, ap, extra_, rinv, n_kv_heads, rope, n_strings, by_unit);                               \
     } while (0)
 #define KVQ_MARK mark, gspan
     switch (bits + (int16 && bits == 16 ? 1 : 0)) {
         case 17:
-            if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 1, gspan);
-            else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, gspan);
+            if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 1, 1, gspan);
+            else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, 1, gspan);
             break;
         case 16:
-            if (plain) KVQ_APPEND_LAUNCH(kvq_append16_kernel<true>, 1, gspan);
-            else KVQ_APPEND_LAUNCH(kvq_append16_kernel<false>, 1, gspan);
+            if (plain) KVQ_APPEND_LAUNCH(kvq_append16_kernel<true>, 1, 1, gspan);
+            else KVQ_APPEND_LAUNCH(kvq_append16_kernel<false>, 1, 1, gspan);
             break;
 #define KVQ_APPEND_CASE(b_)                                                                                              \
         case b_:                                                                                                         \
-            if (plain) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true>), KVQ_APPEND_WG_WAVES, KVQ_MARK);               \
-            else KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false>), KVQ_APPEND_WG_WAVES, KVQ_MARK);                    \
+            if (plain && pair) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true, true>), 2, 2, KVQ_MARK);                \
+            else if (plain) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true, false>), KVQ_APPEND_WG_WAVES, 1, KVQ_MARK); \
+            else if (pair) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false, true>), 2, 2, KVQ_MARK);                   \
+            else KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false, false>), KVQ_APPEND_WG_WAVES, 1, KVQ_MARK);          \
             break;
         KVQ_APPEND_CASE(8)
         KVQ_APPEND_CASE(4)

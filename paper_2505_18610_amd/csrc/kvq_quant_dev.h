@@ -99,11 +99,12 @@ __device__ inline float half_minus(uint32_t w, int hi, float mn) {
     return r;
 }
 
-// The owners' rows of a tile, both passes: eight 16-byte loads per lane, all in flight together; tokens that are not new
+// The owners' rows of 16 tokens per pass from tok0 on: all 16-byte loads in flight together; tokens that are not new
 // read as zeros, which is what they quantize.
-__device__ inline void load_owner_rows(uint32_t (&w)[2][16], const kvq_dev::NewRows& rows, int tok0, int lane) {
+template <int PASSES>
+__device__ inline void load_owner_rows(uint32_t (&w)[PASSES][16], const kvq_dev::NewRows& rows, int tok0, int lane) {
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < PASSES; ++pass) {
         const uint32_t off = rows.offset(tok0 + 16 * pass + (lane >> 2)) + 64u * (lane & 3);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -116,11 +117,12 @@ __device__ inline void load_owner_rows(uint32_t (&w)[2][16], const kvq_dev::NewR
 // the lane two further in the quad, so the partner channels are a data-parallel move away; a lane reads the 32 angles of
 // its channels with 16-byte loads.  (With the partner read again from memory and the angles one by one, 8,192 new tokens
 // x 32 units into 8, 4 or 2 bits took 166 to 172 us with rotation, 45 to 52 without.)
-__device__ inline void prepare_owner_keys(uint32_t (&w)[2][16], const kvq_dev::NewRows& rows, int tok0, int lane,
+template <int PASSES>
+__device__ inline void prepare_owner_keys(uint32_t (&w)[PASSES][16], const kvq_dev::NewRows& rows, int tok0, bool all_new, int lane,
                                           const float* rope, const float* rinv_head) {
     const int grp = lane & 3;
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < PASSES; ++pass) {
         const int tok = tok0 + 16 * pass + (lane >> 2);
         const bool isnew = rows.has(tok);
         if (rope) {
@@ -138,7 +140,7 @@ __device__ inline void prepare_owner_keys(uint32_t (&w)[2][16], const kvq_dev::N
 #pragma unroll
                 for (int e = 0; e < 4; ++e) w[pass][4 * c + e] = own[e];
             }
-            if (!rows.all(tok0)) {  // (uniform) the zeros of tokens that are not new: a rotated one may be negative
+            if (!all_new) {  // (uniform) the zeros of tokens that are not new: a rotated one may be negative
                 asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
                 for (int e = 0; e < 16; ++e) w[pass][e] = isnew ? w[pass][e] : 0u;

@@ -63,3 +63,16 @@ def test_page_entries_of_long_appends(pages, first):
         assert_same_cache(oc, gc, 0)
         check_attention(oc, gc, 0, q)
     gc.close()
+
+
+@pytest.mark.parametrize("bits", [8, 4, 2])
+@pytest.mark.parametrize("B,H,T", [(1, 1, 1), (5, 8, 1024), (5, 8, 1025), (4, 16, 1280)])
+def test_strings_shared_by_two_wavefronts(bits, B, H, T):
+    """Up to 2,560 strings (two per tile and unit) are quantized by two wavefronts each: the last such launch, one tile more, and a
+    launch beyond; a second append continues the partly filled tile."""
+    K, V = kvq_synth.make_kv(83, 0, B, H, 0, T + 6)
+    oc, gc = make_pair(1, B, H, H, T + 6, 64)
+    append_both(oc, gc, 0, K[:, :, :T], V[:, :, :T], bits)
+    append_both(oc, gc, 0, K[:, :, T:], V[:, :, T:], bits)
+    assert_same_cache(oc, gc, 0)
+    gc.close()
