@@ -174,9 +174,8 @@ kvq_status_t kvq_decode_attention_static(kvq_cache_t* cache, int32_t layer, cons
 /* One decode step of a block in one launch: kvq_quantize_append_rope of one token (n_new = 1, entry_bits = 0; k_dev,
  * v_dev: fp16 [batch, n_kv_heads, 1, 128]; cos_sin_dev: fp32 [1][128] or NULL for keys that already carry RoPE)
  * followed by kvq_decode_attention over the block including that token.  When the token enters the 16-bit tier
- * (a window is configured, the policy is OLDEST_FIRST, or the block is still at 16 bits) it is written by the attention
- * kernel itself - by the workgroup that owns the last tile, which reads it back only after its stores have
- * completed; with KVQ_TIER16_INT16 that workgroup quantizes it (Eq. 1-2, 2^16 - 1 levels) - so the small append launch
+ * (a window is configured, the policy is OLDEST_FIRST, or the block is still at 16 bits) the attention kernel itself rotates,
+ * with KVQ_TIER16_INT16 quantizes (Eq. 1-2, 2^16 - 1 levels), attends to and stores it, so that the small append launch
  * and its gap disappear; otherwise the two kernels are launched one after the other.  Bookkeeping, budget check, page allocation and window evictions are those of kvq_quantize_append; the
  * cache contents afterwards are bit-identical to the two separate calls, the outputs equal up to summation order.
  * Errors of the append part leave the cache unchanged and nothing is computed. */
@@ -194,7 +193,7 @@ kvq_status_t kvq_append_decode_attention(kvq_cache_t* cache, int32_t layer, cons
  * kvq_decode_attention_batch: kvq_decode_attention of every cache in one launch.
  * kvq_append_decode_attention_batch: kvq_append_decode_attention of every cache -- one new token each, then attention
  *   -- in one attention launch (plus the small append and eviction launches of those caches whose token does not enter
- *   the raw fp16 tier).  The bookkeeping of all appends is checked before the first one is carried out: on
+ *   the 16-bit tier).  The bookkeeping of all appends is checked before the first one is carried out: on
  *   KVQ_E_BUDGET / KVQ_E_STATE no cache has changed.  (An arena that runs out of pages, KVQ_E_OOM, is only found while
  *   carrying them out; caches before the failing one then hold their new token.)
  * The device's workgroups are shared among the caches in proportion to the time their tiles take.  Results per cache
@@ -279,7 +278,7 @@ kvq_status_t kvq_calibrate_lambda(const void* k_calib_dev, int32_t batch, int32_
  * to compare the bit-width shrinking strategies of Sec. 4.3.1): sq_err_host[0] = sum over all cached K elements of
  * (K_hat - K)^2 with K_hat = code * S + Z (raw value in the 16-bit tier), sq_err_host[1] the same for V.
  * k_ref_dev, v_ref_dev: device, fp16 [batch, n_kv_heads, n_tokens, 128] with n_tokens the block's current length.
- * sq_err_host: host, 2 doubles.  Squares are added in fp32 inside a 32-token tile and in fp64 across tiles.
+ * sq_err_host: host, 2 doubles.  Squares are added in fp32 over 32 channels of a token and in fp64 beyond.
  * Enqueues on the stream, then waits for it (like kvq_cache_export_segment).  KVQ_E_STATE on an empty block or an
  * accounting-only cache. */
 kvq_status_t kvq_cache_sq_error(kvq_cache_t* cache, int32_t layer, const void* k_ref_dev, const void* v_ref_dev,
@@ -290,8 +289,8 @@ kvq_status_t kvq_cache_sq_error(kvq_cache_t* cache, int32_t layer, const void* k
  * value in the 16-bit tier); s_{i,b} of Eq. 5 is their sum for block i held at width b.  k_ref_dev, v_ref_dev as in
  * kvq_cache_sq_error; gk_dev, gv_dev: device, fp32 [batch, n_kv_heads, n_tokens, 128], the gradients of the loss with
  * respect to K and V, or NULL for all-ones (no model at hand: plain L1 reconstruction error).  For a block with
- * reparameterization the stored keys are K Lambda^-1: pass references in that space.  fp32 inside a tile, fp64 across
- * tiles.  Enqueues on the stream, then waits for it. */
+ * reparameterization the stored keys are K Lambda^-1: pass references in that space.  fp32 over 32 channels of a token,
+ * fp64 beyond.  Enqueues on the stream, then waits for it. */
 kvq_status_t kvq_cache_sensitivity(kvq_cache_t* cache, int32_t layer, const void* k_ref_dev, const void* v_ref_dev,
                                    const float* gk_dev, const float* gv_dev, double* s_host, void* hip_stream);
 
