@@ -193,9 +193,10 @@ kvq_status_t kvq_append_decode_attention(kvq_cache_t* cache, int32_t layer, cons
  * kvq_decode_attention_batch: kvq_decode_attention of every cache in one launch.
  * kvq_append_decode_attention_batch: kvq_append_decode_attention of every cache -- one new token each, then attention
  *   -- in one attention launch (plus the small append and eviction launches of those caches whose token does not enter
- *   the 16-bit tier).  The bookkeeping of all appends is checked before the first one is carried out: on
- *   KVQ_E_BUDGET / KVQ_E_STATE no cache has changed.  (An arena that runs out of pages, KVQ_E_OOM, is only found while
- *   carrying them out; caches before the failing one then hold their new token.)
+ *   the 16-bit tier).  The bookkeeping of all appends is checked, and the blocks of all their pages are taken, before the
+ *   first one is carried out: on KVQ_E_BUDGET, KVQ_E_STATE and KVQ_E_OOM no cache has changed.  After KVQ_E_HIP the block
+ *   is unusable (KVQ_E_STATE until kvq_cache_reset) in the cache whose launch failed and in those whose token the attention
+ *   launch was to write; the others hold their new token or, if their append had not begun, are unchanged.
  * The device's workgroups are shared among the caches in proportion to the time their tiles take.  Results per cache
  * are those of the single-cache calls up to floating-point summation order.  The parameter blocks of the launch are
  * read from the pinned staging memory of caches[0]: calls that involve that cache must be issued on one stream. */

@@ -576,53 +576,61 @@ bool append_args_ok(const kvq_cache_t* c, int32_t layer, const void* k_dev, cons
     return true;
 }
 
-// Carries a planned append out.  defer != nullptr: a one-token append into the 16-bit tier is not launched but
-// described in *defer (page allocation, table upload and window evictions happen as usual).
-kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, const void* k_dev, const void* v_dev,
-                           int32_t n_new, const float* cos_sin_dev, hipStream_t s, DeferredAppend* defer) {
-    Layer& L = c->layers[(size_t)layer];
-    const int P = c->cfg.page_tokens, e = pl.e;
-    // allocate the new pages
-    const size_t old_pages = L.pages.size();
+// What a planned append takes from the arena: its new pages, and the pages that leave the window in this call with the
+// blocks they are lowered into behind the append.  All of it is taken before anything changes, so that a full arena can
+// still be reported with nothing changed.
+struct AppendBlocks {
     std::vector<Page> fresh;
-    for (size_t i = old_pages; i < pl.bits.size(); ++i) {
+    std::vector<Lowering> low;
+};
+
+void release_fresh(kvq_cache_t* c, AppendBlocks& bl) {
+    for (Page& p : bl.fresh) {
+        c->buddy.release(p.code_unit, order_of_bits(p.bits));
+        if (c->has_meta(p.bits)) c->buddy.release(p.meta_unit, 0);
+    }
+    bl.fresh.clear();
+}
+void release_append(kvq_cache_t* c, AppendBlocks& bl) {
+    release_first_step(c, bl.low);
+    release_fresh(c, bl);
+}
+
+// Takes the blocks of a planned append; on an error none is held.
+kvq_status_t reserve_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, AppendBlocks& bl, hipStream_t s) {
+    for (size_t i = c->layers[(size_t)layer].pages.size(); i < pl.bits.size(); ++i) {
         Page p;
-        p.bits = e;
-        bool ok = c->buddy.alloc(order_of_bits(e), &p.code_unit);
-        bool ok2 = true;
-        if (ok && c->has_meta(e)) ok2 = c->buddy.alloc(0, &p.meta_unit);
-        if (!ok || !ok2) {
-            if (ok) c->buddy.release(p.code_unit, order_of_bits(e));
-            for (Page& q : fresh) {
-                c->buddy.release(q.code_unit, order_of_bits(e));
-                if (c->has_meta(e)) c->buddy.release(q.meta_unit, 0);
-            }
+        p.bits = pl.e;
+        const bool ok = c->buddy.alloc(order_of_bits(p.bits), &p.code_unit);
+        if (!ok || (c->has_meta(p.bits) && !c->buddy.alloc(0, &p.meta_unit))) {
+            if (ok) c->buddy.release(p.code_unit, order_of_bits(p.bits));
+            release_fresh(c, bl);
             return KVQ_E_OOM;
         }
-        fresh.push_back(p);
+        bl.fresh.push_back(p);
     }
-    auto release_fresh = [&]() {
-        for (Page& q : fresh) {
-            c->buddy.release(q.code_unit, order_of_bits(e));
-            if (c->has_meta(e)) c->buddy.release(q.meta_unit, 0);
-        }
-    };
-    // pages that leave the window in this call are lowered behind the append: their destination blocks are taken now,
-    // while a full arena can still be reported with nothing changed
-    std::vector<Lowering> low;
-    for (int i : pl.evicted) low.push_back(Lowering{i, 16, pl.bcur});
-    if (!alloc_first_step(c, low)) {
-        release_fresh();
+    for (int i : pl.evicted) bl.low.push_back(Lowering{i, 16, pl.bcur});
+    if (!alloc_first_step(c, bl.low)) {
+        release_fresh(c, bl);
         return KVQ_E_OOM;
     }
-    kvq_status_t st = ensure_device(c, s);
-    if (st != KVQ_OK) {
-        release_first_step(c, low);
-        release_fresh();
-        return st;
-    }
+    const kvq_status_t st = ensure_device(c, s);
+    if (st != KVQ_OK) release_append(c, bl);
+    return st;
+}
+
+// Carries a planned append out whose blocks have been taken.  defer != nullptr: a one-token append into the 16-bit tier is
+// not launched but described in *defer.  The caller must then launch the attention with it, or mark the block unusable: the
+// token, and the table entry of a page that it starts, are written by that launch and by nothing else.
+kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, AppendBlocks& bl, const void* k_dev,
+                           const void* v_dev, int32_t n_new, const float* cos_sin_dev, hipStream_t s, DeferredAppend* defer) {
+    Layer& L = c->layers[(size_t)layer];
+    const int P = c->cfg.page_tokens, e = pl.e;
+    const size_t old_pages = L.pages.size();
+    std::vector<Lowering>& low = bl.low;
+    kvq_status_t st = KVQ_OK;
     const int t_old = L.T, T = pl.T;
-    for (Page& p : fresh) L.pages.push_back(p);
+    for (const Page& p : bl.fresh) L.pages.push_back(p);
     for (size_t i = 0; i < L.pages.size(); ++i) L.pages[i].n = pl.cnt[i];
     L.T = T;
     L.version++;
@@ -674,9 +682,11 @@ kvq_status_t append_impl(kvq_cache_t* c, int32_t layer, const void* k_dev, const
     if (!append_args_ok(c, layer, k_dev, v_dev, n_new, entry_bits)) return KVQ_E_INVALID;
     if (n_new == 0) return KVQ_OK;
     AppendPlan pl;
+    AppendBlocks bl;
     kvq_status_t st = plan_append(c, layer, n_new, entry_bits, pl);
+    if (st == KVQ_OK) st = reserve_append(c, layer, pl, bl, as_stream(hip_stream));
     if (st != KVQ_OK) return st;
-    return commit_append(c, layer, pl, k_dev, v_dev, n_new, cos_sin_dev, as_stream(hip_stream), defer);
+    return commit_append(c, layer, pl, bl, k_dev, v_dev, n_new, cos_sin_dev, as_stream(hip_stream), defer);
 }
 
 }  // namespace
@@ -871,36 +881,12 @@ kvq_status_t attention_impl(kvq_cache_t* c, int32_t layer, const void* q_dev, vo
     return kvq_launch_attention(p, c->units, as_stream(hip_stream)) == hipSuccess ? KVQ_OK : KVQ_E_HIP;
 }
 
-// One attention launch over block `layer` of n caches, optionally with each cache's one-token append in front.
-kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, const void* const* k_dev,
-                        const void* const* v_dev, const float* const* cos_sin_dev, const void* const* q_dev,
-                        void* const* out_dev, int32_t out_is_fp32, float softmax_scale, void* hip_stream, bool append) {
-    if (!caches || n < 1 || n > KVQ_MAX_BATCH_CACHES || !q_dev || !out_dev) return KVQ_E_INVALID;
-    if (append && (!k_dev || !v_dev)) return KVQ_E_INVALID;
-    for (int i = 0; i < n; ++i) {
-        kvq_cache_t* c = caches[i];
-        if (!c || layer < 0 || layer >= c->cfg.n_layers || !q_dev[i] || !out_dev[i]) return KVQ_E_INVALID;
-        if (append && (!k_dev[i] || !v_dev[i])) return KVQ_E_INVALID;
-        if (c->dry) return KVQ_E_STATE;
-        if (c->int16() != caches[0]->int16()) return KVQ_E_INVALID;  // one kernel serves one kind of 16-bit tier
-        for (int k = 0; k < i; ++k)
-            if (caches[k] == c) return KVQ_E_INVALID;
-    }
-    hipStream_t s = as_stream(hip_stream);
-    std::vector<DeferredAppend> app((size_t)n);
-    if (append) {
-        // all or nothing as far as the bookkeeping can tell: plan every append before the first one is carried out
-        std::vector<AppendPlan> plans((size_t)n);
-        for (int i = 0; i < n; ++i) {
-            kvq_status_t st = plan_append(caches[i], layer, 1, 0, plans[(size_t)i]);
-            if (st != KVQ_OK) return st;
-        }
-        for (int i = 0; i < n; ++i) {
-            kvq_status_t st = commit_append(caches[i], layer, plans[(size_t)i], k_dev[i], v_dev[i], 1,
-                                            cos_sin_dev ? cos_sin_dev[i] : nullptr, s, &app[(size_t)i]);
-            if (st != KVQ_OK) return st;
-        }
-    }
+// The attention launch of a ragged batch over block `layer` of n caches, with the appends deferred to it (k_dev, v_dev and
+// cos_sin_dev are looked at for those only).
+kvq_status_t batch_attention(kvq_cache_t* const* caches, int32_t n, int32_t layer, const std::vector<DeferredAppend>& app,
+                             const void* const* k_dev, const void* const* v_dev, const float* const* cos_sin_dev,
+                             const void* const* q_dev, void* const* out_dev, int32_t out_is_fp32, float softmax_scale,
+                             hipStream_t s) {
     // The device's workgroups are dealt to the caches so that the most loaded workgroup is as light as possible:
     // every cache starts with one split per (sequence, KV head); the cache whose workgroups carry the most tile
     // time gets one more split, as long as the workgroups last (and the cache's splits pay).
@@ -942,7 +928,7 @@ kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, co
     std::vector<KvqAttnParams> params((size_t)n);
     for (int i = 0; i < n; ++i) {
         kvq_status_t st = fill_attn_params(caches[i], layer, q_dev[i], out_dev[i], out_is_fp32, softmax_scale,
-                                           &app[(size_t)i], append ? k_dev[i] : nullptr, append ? v_dev[i] : nullptr,
+                                           &app[(size_t)i], k_dev ? k_dev[i] : nullptr, v_dev ? v_dev[i] : nullptr,
                                            cos_sin_dev ? cos_sin_dev[i] : nullptr, splits[(size_t)i] * caches[i]->units,
                                            params[(size_t)i]);
         if (st != KVQ_OK) return st;
@@ -957,6 +943,47 @@ kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, co
     std::vector<int> units((size_t)n);
     for (int i = 0; i < n; ++i) units[(size_t)i] = caches[i]->units;
     if (st == KVQ_OK && kvq_launch_attention_batch(params_dev, params.data(), units.data(), n, s) != hipSuccess) st = KVQ_E_HIP;
+    return st;
+}
+
+// One attention launch over block `layer` of n caches, optionally with each cache's one-token append in front.
+kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, const void* const* k_dev,
+                        const void* const* v_dev, const float* const* cos_sin_dev, const void* const* q_dev,
+                        void* const* out_dev, int32_t out_is_fp32, float softmax_scale, void* hip_stream, bool append) {
+    if (!caches || n < 1 || n > KVQ_MAX_BATCH_CACHES || !q_dev || !out_dev) return KVQ_E_INVALID;
+    if (append && (!k_dev || !v_dev)) return KVQ_E_INVALID;
+    for (int i = 0; i < n; ++i) {
+        kvq_cache_t* c = caches[i];
+        if (!c || layer < 0 || layer >= c->cfg.n_layers || !q_dev[i] || !out_dev[i]) return KVQ_E_INVALID;
+        if (append && (!k_dev[i] || !v_dev[i])) return KVQ_E_INVALID;
+        if (c->dry) return KVQ_E_STATE;
+        if (c->int16() != caches[0]->int16()) return KVQ_E_INVALID;  // one kernel serves one kind of 16-bit tier
+        for (int k = 0; k < i; ++k)
+            if (caches[k] == c) return KVQ_E_INVALID;
+    }
+    hipStream_t s = as_stream(hip_stream);
+    std::vector<DeferredAppend> app((size_t)n);
+    kvq_status_t st = KVQ_OK;
+    if (append) {
+        // all or nothing: every append is planned and its blocks are taken before the first one is carried out, so that
+        // what the host can find out, a full arena too, leaves every cache as it was
+        std::vector<AppendPlan> plans((size_t)n);
+        std::vector<AppendBlocks> blocks((size_t)n);
+        for (int i = 0; i < n; ++i) {
+            st = plan_append(caches[i], layer, 1, 0, plans[(size_t)i]);
+            if (st != KVQ_OK) return st;
+        }
+        int held = 0, done = 0;  // caches whose blocks are taken, whose append has been begun
+        while (held < n && (st = reserve_append(caches[held], layer, plans[(size_t)held], blocks[(size_t)held], s)) == KVQ_OK) ++held;
+        while (st == KVQ_OK && done < n) {
+            const int i = done++;
+            st = commit_append(caches[i], layer, plans[(size_t)i], blocks[(size_t)i], k_dev[i], v_dev[i], 1,
+                               cos_sin_dev ? cos_sin_dev[i] : nullptr, s, &app[(size_t)i]);
+        }
+        if (st != KVQ_OK)
+            for (int i = done; i < held; ++i) release_append(caches[i], blocks[(size_t)i]);
+    }
+    if (st == KVQ_OK) st = batch_attention(caches, n, layer, app, k_dev, v_dev, cos_sin_dev, q_dev, out_dev, out_is_fp32, softmax_scale, s);
     if (st != KVQ_OK)  // the host tables count tokens nobody wrote
         for (int i = 0; i < n; ++i)
             if (app[(size_t)i].active) caches[i]->layers[(size_t)layer].poisoned = true;

@@ -1,0 +1,227 @@
+// The library's host code over a fake device: arena and pinned memory are plain host memory, the launchers of
+// paper_2505_18610_amd/csrc/kvq_internal.h are replaced by stubs that do to the page tables what the kernels do and check
+// what the kernels would read.  tests/test_host_stub.py builds it with kvq_host.cpp and a HIP runtime that is stubbed below;
+// argument: the scenario.  Exit code 0 = pass.  No GPU and no HIP library is involved.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "kvq.h"
+#include "../paper_2505_18610_amd/csrc/kvq_internal.h"
+
+// ---- the HIP runtime, as far as the host code uses it
+extern "C" {
+hipError_t hipHostMalloc(void** p, size_t n, unsigned int) { *p = aligned_alloc(256, n); return hipSuccess; }
+hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned int) { *d = h; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) { memset(p, 0, sizeof *p); p->multiProcessorCount = 256; return hipSuccess; }
+}
+
+namespace {
+
+int failures = 0;
+#define CHECK(cond, ...)                                                          \
+    do {                                                                          \
+        if (!(cond)) { ++failures; printf("line %d: %s: ", __LINE__, #cond); printf(__VA_ARGS__); printf("\n"); } \
+    } while (0)
+
+int launches = 0, fail_launch = -1;  // the launch with this number fails
+hipError_t launched() { return launches++ == fail_launch ? hipErrorLaunchFailure : hipSuccess; }
+
+std::map<const uint8_t*, uint64_t> arena_size;  // every arena by its address
+KvqAttnParams last;                             // parameters of the last attention launch
+
+void check_table(const uint8_t* arena, const KvqPageDesc* table, int n_tokens, int tpp) {
+    const int pages = (n_tokens + 32 * tpp - 1) / (32 * tpp);
+    for (int i = 0; i < pages; ++i) {
+        const KvqPageDesc& d = table[i];
+        CHECK(d.bits == 16 || d.bits == 8 || d.bits == 4 || d.bits == 2, "page %d of %d has %u bits", i, pages, d.bits);
+        CHECK((uint64_t)d.code_off256 * 256 < arena_size[arena], "page %d of %d lies at %u", i, pages, d.code_off256);
+    }
+}
+void attention(const KvqAttnParams& p) {
+    last = p;
+    check_table(p.arena, p.table, p.n_tokens, p.tiles_per_page);
+    if (p.app_page >= 0) const_cast<KvqPageDesc*>(p.table)[p.app_page] = p.app_desc;
+    // the plan: the ranges follow one another, and in pages of an even number of tiles they start at even ones unless
+    // they hold a single tile (chunks of two tiles must not straddle pages)
+    const int n_tiles = (p.n_tokens + 31) / 32;
+    CHECK(p.split_begin[0] == 0 && p.split_begin[p.n_splits] == n_tiles, "plan of %d tiles ends at %d", n_tiles, p.split_begin[p.n_splits]);
+    for (int i = 0; i < p.n_splits; ++i) {
+        const int a = p.split_begin[i], b = p.split_begin[i + 1];
+        CHECK(a <= b, "range %d of %d: %d .. %d", i, p.n_splits, a, b);
+        CHECK(b - a <= 1 || p.tiles_per_page % 2 == 1 || a % 2 == 0, "range %d of %d: %d .. %d", i, p.n_splits, a, b);
+    }
+}
+
+}  // namespace
+
+hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const void*, const void*, int t_old, int n_new, int tpp,
+                             int, const KvqAppendPages& ap, KvqVMark, int, const float*, int, const float*, bool int16, hipStream_t) {
+    const hipError_t e = launched();
+    if (e != hipSuccess) return e;
+    for (int i = ap.fresh; i < ap.n; ++i) table[ap.first_page + i] = KvqPageDesc{ap.code_off256[i], ap.meta_off256[i], ap.bits, ap.int16};
+    check_table(arena, table, t_old + n_new, tpp);
+    (void)bits; (void)int16;
+    return hipSuccess;
+}
+static hipError_t requant(int to, KvqPageDesc* table, const KvqRequantJob* dev, const KvqRequantJob* host, int n) {
+    const hipError_t e = launched();
+    if (e != hipSuccess) return e;
+    for (int i = 0; i < n; ++i) {
+        const KvqRequantJob& j = host ? host[i] : dev[i];
+        table[j.tiles_page >> 11] = KvqPageDesc{j.dst_code_off256, j.meta_off256, (uint32_t)to, 0u};
+    }
+    return hipSuccess;
+}
+hipError_t kvq_launch_shrink(int to, int, uint8_t*, KvqPageDesc* table, const KvqRequantJob* dev, const KvqRequantJob* host, int n, int, int,
+                             KvqVMark, hipStream_t) { return requant(to, table, dev, host, n); }
+hipError_t kvq_launch_quant16(int to, uint8_t*, KvqPageDesc* table, const KvqRequantJob* dev, const KvqRequantJob* host, int n, int, int,
+                              KvqVMark, int, hipStream_t) { return requant(to, table, dev, host, n); }
+hipError_t kvq_launch_reparam_store(const float*, float*, int, hipStream_t) { return launched(); }
+hipError_t kvq_launch_calibrate(const void*, int, int, int, float, float, float*, hipStream_t) { return launched(); }
+int kvq_error_workgroups(int, int) { return 1; }
+hipError_t kvq_launch_error(bool, const uint8_t* arena, const KvqPageDesc* table, const void*, const void*, const float*, const float*,
+                            int n_tokens, int tpp, int, double* partial, hipStream_t) {
+    const hipError_t e = launched();
+    if (e != hipSuccess) return e;
+    check_table(arena, table, n_tokens, tpp);
+    partial[0] = partial[1] = 0.0;
+    return hipSuccess;
+}
+hipError_t kvq_launch_stream_read(const void*, size_t, int, uint32_t*, hipStream_t) { return launched(); }
+hipError_t kvq_launch_fill_u32(uint32_t* dst, uint32_t value, size_t n, hipStream_t) {
+    const hipError_t e = launched();
+    if (e == hipSuccess) for (size_t i = 0; i < n; ++i) dst[i] = value;
+    return e;
+}
+hipError_t kvq_static_scratch(unsigned char** ptr) { static unsigned char scratch[KVQ_STATIC_SCRATCH_BYTES]; *ptr = scratch; return hipSuccess; }
+hipError_t kvq_launch_attention(const KvqAttnParams& p, int, hipStream_t) {
+    const hipError_t e = launched();
+    if (e == hipSuccess) attention(p);
+    return e;
+}
+hipError_t kvq_launch_merge(const KvqAttnParams&, int, hipStream_t) { return launched(); }
+hipError_t kvq_launch_attention_batch(const KvqAttnParams*, const KvqAttnParams* p, const int*, int n, hipStream_t) {
+    const hipError_t e = launched();
+    for (int i = 0; i < n && e == hipSuccess; ++i) attention(p[i]);
+    return e;
+}
+
+namespace {
+
+uint16_t input[1 << 10];  // never read by a stub
+float factors[128];
+double sums[2];
+
+struct Cache {
+    kvq_cache_t* c = nullptr;
+    kvq_config_t cfg{};
+    uint8_t* arena = nullptr;
+    // supers: allocation blocks of 16 units (a page of raw 16-bit tokens takes 16 units, metadata one)
+    Cache(int page_tokens, int supers, int tier16, int policy = KVQ_POLICY_PAPER, int window = 0, int batch = 1, int kv = 1) {
+        cfg.n_layers = 1; cfg.batch = batch; cfg.n_kv_heads = kv; cfg.n_q_heads = kv; cfg.head_dim = 128; cfg.group = 32;
+        cfg.max_tokens = 1 << 18; cfg.page_tokens = page_tokens; cfg.policy = policy; cfg.window = window;
+        const uint64_t budget = 1ull << 50;
+        const uint8_t fbit = 2;
+        const uint64_t bytes = kvq_arena_bytes(&cfg, (uint64_t)supers * 16 * 32 * page_tokens * batch * kv);
+        arena = static_cast<uint8_t*>(aligned_alloc(256, (bytes + 255) / 256 * 256));
+        memset(arena, 0xEE, bytes);
+        arena_size[arena] = bytes;
+        CHECK(kvq_cache_create(&cfg, &budget, &fbit, arena, bytes, &c) == KVQ_OK, "create");
+        CHECK(kvq_cache_set_option(c, KVQ_OPT_TIER16, tier16) == KVQ_OK, "tier");
+    }
+    ~Cache() { kvq_cache_destroy(c); free(arena); }
+    Cache(const Cache&) = delete;
+    kvq_status_t append(int n, int bits = 0) { return kvq_quantize_append(c, 0, input, input, n, bits, nullptr); }
+    kvq_status_t attend() { return kvq_decode_attention(c, 0, input, input, 0, 0.f, nullptr); }
+    kvq_status_t step() { return kvq_append_decode_attention(c, 0, input, input, nullptr, input, input, 0, 0.f, nullptr); }
+    int tokens() const { int T = -1; kvq_cache_describe(c, 0, nullptr, 0, nullptr, nullptr, &T, nullptr); return T; }
+    uint64_t free_bytes() const { return kvq_cache_arena_free_bytes(c); }
+};
+
+kvq_status_t batch_step(const std::vector<Cache*>& caches) {
+    std::vector<kvq_cache_t*> cs;
+    for (Cache* c : caches) cs.push_back(c->c);
+    std::vector<const void*> in(cs.size(), input);
+    std::vector<void*> out(cs.size(), input);
+    return kvq_append_decode_attention_batch(cs.data(), (int)cs.size(), 0, in.data(), in.data(), nullptr, in.data(), out.data(), 0, 0.f, nullptr);
+}
+
+// A ragged step in which one cache's arena is full: no cache may change, whatever their order and where in its page the
+// others' token falls, and every cache goes on working.
+void batch_full_arena() {
+    for (int tier16 : {0, 1})
+        for (int full_at : {0, 1, 2})
+            for (int have : {64, 65, 95}) {
+                Cache a(32, 8, tier16), b(32, 8, tier16), full(32, tier16 ? 2 : 1, tier16);
+                std::vector<Cache*> all{&a, &b};
+                all.insert(all.begin() + full_at, &full);
+                CHECK(a.append(have) == KVQ_OK && b.append(33) == KVQ_OK && full.append(32) == KVQ_OK, "prompts");
+                const uint64_t fa = a.free_bytes(), fb = b.free_bytes(), ff = full.free_bytes();
+                const kvq_status_t st = batch_step(all);
+                CHECK(st == KVQ_E_OOM, "%s", kvq_status_string(st));
+                CHECK(a.tokens() == have && b.tokens() == 33 && full.tokens() == 32, "%d %d %d tokens, tier %d, full cache %d", a.tokens(), b.tokens(), full.tokens(), tier16, full_at);
+                CHECK(a.free_bytes() == fa && b.free_bytes() == fb && full.free_bytes() == ff, "blocks not given back");
+                CHECK(a.attend() == KVQ_OK && b.attend() == KVQ_OK && full.attend() == KVQ_OK, "attention");
+                CHECK(batch_step({&a, &b}) == KVQ_OK && a.tokens() == have + 1 && b.tokens() == 34, "the step without the full cache");
+                CHECK(a.step() == KVQ_OK && a.attend() == KVQ_OK && b.attend() == KVQ_OK, "steps");
+            }
+}
+
+// A ragged step in which a launch fails: a cache whose token was not written may not be read any more, one whose append had
+// not begun is unchanged.
+void batch_failing_launch() {
+    for (int which = 0; which < 3; ++which) {
+        Cache a(32, 8, 0), q(32, 8, 0), z(32, 8, 0);
+        // `a` and `z` append inside the attention launch, `q` (8 bits, no window) by a launch of its own in front of it
+        CHECK(a.append(64) == KVQ_OK && q.append(64, 8) == KVQ_OK && z.append(64) == KVQ_OK, "prompts");
+        const uint64_t fz = z.free_bytes();
+        fail_launch = which < 2 ? launches + which : -1;  // 0: q's append; 1: the attention launch
+        const kvq_status_t st = batch_step({&a, &q, &z});
+        fail_launch = -1;
+        if (which == 2) {
+            CHECK(st == KVQ_OK && a.attend() == KVQ_OK && q.attend() == KVQ_OK && z.attend() == KVQ_OK, "%s", kvq_status_string(st));
+            continue;
+        }
+        CHECK(st == KVQ_E_HIP, "%s", kvq_status_string(st));
+        CHECK(a.attend() == KVQ_E_STATE && a.step() == KVQ_E_STATE, "a cache whose token nobody wrote is read, case %d", which);
+        if (which == 0) {
+            CHECK(q.attend() == KVQ_E_STATE, "q");
+            CHECK(z.tokens() == 64 && z.free_bytes() == fz && z.attend() == KVQ_OK && z.step() == KVQ_OK, "z: %d tokens", z.tokens());
+        } else {
+            CHECK(q.attend() == KVQ_OK && q.tokens() == 65, "q holds its token");
+            CHECK(z.attend() == KVQ_E_STATE, "z");
+        }
+        CHECK(kvq_cache_reset(a.c, -1) == KVQ_OK && a.append(64) == KVQ_OK && a.attend() == KVQ_OK, "reset");
+    }
+}
+
+const std::map<std::string, std::function<void()>> scenarios = {
+    {"batch_full_arena", batch_full_arena},
+    {"batch_failing_launch", batch_failing_launch},
+};
+
+}  // namespace
+
+int main(int argc, char** argv) {
+    const auto it = scenarios.find(argc > 1 ? argv[1] : "");
+    if (it == scenarios.end()) { printf("no such scenario\n"); return 2; }
+    it->second();
+    (void)factors; (void)sums; (void)last;
+    printf("%s: %d failures\n", argv[1], failures);
+    return failures ? 1 : 0;
+}
