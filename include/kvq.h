@@ -29,7 +29,8 @@
  *     KVQ_E_OOM of an append is found before anything changes as well (the blocks of the new pages and those that
  *     pages leaving the window are quantized into are taken first).  A HIP failure (KVQ_E_HIP) while a call is
  *     being enqueued can strike after the host tables have been updated; the block is then marked unusable: every
- *     later call on it returns KVQ_E_STATE until kvq_cache_reset empties it (other blocks are unaffected).
+ *     later call that reads or changes its tokens returns KVQ_E_STATE until kvq_cache_reset empties it (other blocks
+ *     are unaffected; kvq_cache_describe still reports the block).
  *   - All sequences of one cache have the same length and share one page table per block; sequences of different
  *     lengths live in caches of their own and are served together by the *_batch entry points.
  *   - head_dim is 128, group is 32, 64 or 128 channels (128 is the paper's setting, Sec. 4.1.2),

@@ -1201,7 +1201,7 @@ kvq_status_t cache_error(kvq_cache_t* c, int32_t layer, bool l1, const void* k_r
     if (!c || layer < 0 || layer >= c->cfg.n_layers || !k_ref_dev || !v_ref_dev || !out_host) return KVQ_E_INVALID;
     if (c->dry) return KVQ_E_STATE;
     const Layer& L = c->layers[(size_t)layer];
-    if (L.T == 0) return KVQ_E_STATE;
+    if (L.T == 0 || L.poisoned) return KVQ_E_STATE;
     hipStream_t s = as_stream(hip_stream);
     // The workgroups store their sums straight into the pinned staging ring, where the host adds them up behind the
     // synchronization this call makes anyway: no accumulators to clear, no copy back.

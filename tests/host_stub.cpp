@@ -210,9 +210,32 @@ void batch_failing_launch() {
     }
 }
 
+// A block whose launch failed after the bookkeeping is refused by every call that reads it, until it is emptied.
+void failed_block_is_refused() {
+    for (int tier16 : {0, 1})
+        for (int fused : {0, 1}) {
+            Cache a(32, 8, tier16);
+            CHECK(a.append(64) == KVQ_OK, "prompt");
+            fail_launch = launches;
+            const kvq_status_t st = fused ? a.step() : a.append(1);
+            fail_launch = -1;
+            CHECK(st == KVQ_E_HIP, "%s", kvq_status_string(st));
+            CHECK(kvq_cache_sq_error(a.c, 0, input, input, sums, nullptr) == KVQ_E_STATE, "squared error");
+            CHECK(kvq_cache_sensitivity(a.c, 0, input, input, factors, factors, sums, nullptr) == KVQ_E_STATE, "sensitivity");
+            CHECK(a.attend() == KVQ_E_STATE && a.step() == KVQ_E_STATE && a.append(1) == KVQ_E_STATE, "attention, appends");
+            CHECK(kvq_decode_attention_static(a.c, 0, input, input, 0, 0.f, nullptr) == KVQ_E_STATE, "static attention");
+            CHECK(batch_step({&a}) == KVQ_E_STATE, "batch");
+            CHECK(kvq_progressive_requant(a.c, 0, 0, 0, nullptr, nullptr) == KVQ_E_STATE, "shrink");
+            CHECK(kvq_cache_export_segment(a.c, 0, 0, KVQ_WHICH_K, input, input, input, nullptr) == KVQ_E_STATE, "export");
+            CHECK(kvq_cache_reset(a.c, 0) == KVQ_OK && a.append(65) == KVQ_OK && a.attend() == KVQ_OK, "reset");
+            CHECK(kvq_cache_sq_error(a.c, 0, input, input, sums, nullptr) == KVQ_OK, "squared error behind the reset");
+        }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
     {"batch_full_arena", batch_full_arena},
     {"batch_failing_launch", batch_failing_launch},
+    {"failed_block_is_refused", failed_block_is_refused},
 };
 
 }  // namespace
@@ -221,7 +244,7 @@ int main(int argc, char** argv) {
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) { printf("no such scenario\n"); return 2; }
     it->second();
-    (void)factors; (void)sums; (void)last;
+    (void)last;
     printf("%s: %d failures\n", argv[1], failures);
     return failures ? 1 : 0;
 }
