@@ -911,7 +911,8 @@ static_assert(KVQ_ATTN_WAVES * 16 * KVQ_OPAD >= KVQ_MERGE_LDS_FLOATS, "the wavef
 // ---- A one-token append fused into the launch (kvq_append_decode_attention).  The workgroup of a unit's last split does
 // it.  The token is never read back from the cache: its rows wait in LDS from the staging phase on, its score and its V
 // row enter the merge of the wavefront partials as a ninth partial of one token, and its elements are stored behind the
-// join of the wavefronts, when nobody reads the tile any more.  The streaming loop covers the older tokens only and knows
+// join of the wavefronts, when nobody reads the tile any more: the last split's range is never empty, so a tile that holds
+// older tokens is read by this workgroup alone.  The streaming loop covers the older tokens only and knows
 // nothing of it.  (Written at the start, waited for and read back with its tile, the token cost 3 to 4 us of every step.)
 
 // K (which = 0) or V (1) row of the new token -> LDS, one wavefront, two channels per lane: rotation and

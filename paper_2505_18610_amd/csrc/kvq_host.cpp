@@ -383,7 +383,8 @@ void build_segments(const kvq_cache* c, const Layer& L, std::vector<kvq_segment_
 // bound by de-quantization work, the wide ones by their bytes).
 int cost_index(int bits) { return bits == 16 ? 3 : bits == 8 ? 2 : bits == 4 ? 1 : 0; }
 
-// Cost-balanced split of the tile range.
+// Cost-balanced split of the tile range (n_splits <= n_tiles, or one split of nothing).  The last range is never empty: the
+// workgroup that holds the last tile is the one that stores the token a launch appends, behind its own reads of that tile.
 void plan_splits(kvq_cache* c, Layer& L, int n_tiles, int n_splits) {
     if (L.plan_tiles == n_tiles && L.plan_splits == n_splits && L.plan_version == L.version) return;
     const int tpp = c->tpp;
@@ -407,7 +408,9 @@ void plan_splits(kvq_cache* c, Layer& L, int n_tiles, int n_splits) {
             if (target > page_end) break;
             uint64_t k = target <= cum ? 0 : (target - cum + cost - 1) / cost;
             if ((tpp & 1) == 0) k = std::min<uint64_t>((k + 1) & ~1ull, (uint64_t)nt);  // chunks are tile pairs
-            L.split_begin[sp++] = (int)i * tpp + (int)k;
+            // at least one tile is left for every later range: what this cuts off an even boundary is a range of one tile
+            L.split_begin[sp] = std::min((int)i * tpp + (int)k, n_tiles - (n_splits - sp));
+            ++sp;
         }
         cum = page_end;
     }

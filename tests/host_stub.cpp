@@ -63,6 +63,8 @@ void attention(const KvqAttnParams& p) {
     for (int i = 0; i < p.n_splits; ++i) {
         const int a = p.split_begin[i], b = p.split_begin[i + 1];
         CHECK(a <= b, "range %d of %d: %d .. %d", i, p.n_splits, a, b);
+        // the workgroup of the last range stores the token the launch appends: nobody else may be reading that tile
+        CHECK(i + 1 < p.n_splits || n_tiles == 0 || b > a, "the last of %d ranges of %d tiles is empty", p.n_splits, n_tiles);
         CHECK(b - a <= 1 || p.tiles_per_page % 2 == 1 || a % 2 == 0, "range %d of %d: %d .. %d", i, p.n_splits, a, b);
     }
 }
@@ -232,10 +234,32 @@ void failed_block_is_refused() {
         }
 }
 
+// The split plan over lengths, widths, page sizes and split counts: what check and attention() above ask of every launch.
+void split_plans() {
+    for (int page : {32, 64, 96, 256})
+        for (int narrow : {0, 1, 5, 10, 40})
+            for (int bits : {8, 2})
+                for (int rest = 1; rest <= 3 * page; rest += page / 4 + 1) {
+                    Cache a(page, 64, 0);
+                    CHECK((narrow == 0 || a.append(narrow * page, bits) == KVQ_OK) && a.append(rest, 16) == KVQ_OK, "prompt");
+                    const int n_tiles = (a.tokens() + 31) / 32;
+                    for (int splits : {0, 2, 3, 5, n_tiles / 2, n_tiles - 1, n_tiles, 128}) {
+                        if (splits < 0 || splits > 128) continue;
+                        CHECK(kvq_cache_set_option(a.c, KVQ_OPT_SPLITS, splits) == KVQ_OK, "option");
+                        CHECK(a.attend() == KVQ_OK, "attention");
+                        CHECK(last.n_splits <= n_tiles && (splits == 0 || last.n_splits == (splits < n_tiles ? splits : n_tiles)), "%d splits", last.n_splits);
+                    }
+                }
+    // a step on top of 640 tokens of 2 bits and 33 of 16 bits, as the library splits it by itself
+    Cache a(64, 64, 0, KVQ_POLICY_PAPER, 64);
+    CHECK(a.append(640, 2) == KVQ_OK && a.append(33, 16) == KVQ_OK && a.step() == KVQ_OK && last.app_t_old == 673, "step");
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
     {"batch_full_arena", batch_full_arena},
     {"batch_failing_launch", batch_failing_launch},
     {"failed_block_is_refused", failed_block_is_refused},
+    {"split_plans", split_plans},
 };
 
 }  // namespace

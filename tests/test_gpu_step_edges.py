@@ -73,3 +73,37 @@ def test_fused_append_from_the_first_token_on(tier16, group, batched):
                     t += n
         assert_same_cache(oc, gc, 0)
     gc.close()
+
+
+@pytest.mark.parametrize("tier16", [0, 1])
+@pytest.mark.parametrize("deterministic", [0, 1])
+@pytest.mark.parametrize("splits", [0, 2, 5, 21, 22])
+def test_fused_append_behind_split_ranges(splits, deterministic, tier16):
+    """Several ranges, up to one per tile: whoever holds the last tile stores the new token.  An infinite value of the new
+    token reaches its own channel and no other one."""
+    B, Hkv, g, P, n2, n16 = 1, 2, 4, 64, 640, 33
+    K, V = kvq_synth.make_kv(74, 0, B, Hkv, 0, n2 + n16 + 3)
+    for special in (False, True) if not tier16 else (False,):
+        oc, gc = make_pair(1, B, g * Hkv, Hkv, n2 + 4 * P, P, window=P, tier16=tier16)
+        gc.kvq_cache_set_option(kq.KVQ_OPT_SPLITS, splits)
+        gc.kvq_cache_set_option(kq.KVQ_OPT_DETERMINISTIC, deterministic)
+        append_both(oc, gc, 0, K[:, :, :n2], V[:, :, :n2], 2)
+        append_both(oc, gc, 0, K[:, :, n2:n2 + n16], V[:, :, n2:n2 + n16], 16)
+        for t in range(n2 + n16, n2 + n16 + (1 if special else 3)):
+            k, v, q = K[:, :, t:t + 1], V[:, :, t:t + 1].copy(), kvq_synth.make_q(74, 0, B, g * Hkv, t)
+            if special:
+                k = np.zeros_like(k)  # a score of 0
+                v[..., 5] = np.inf
+            else:
+                oc.append(0, k, v, 0)
+            out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+            gc.kvq_append_decode_attention(0, dev(k), dev(v), dev(q), out)
+            got = out.cpu().numpy()
+            if special:
+                assert np.isposinf(got[..., 5]).all() and np.isfinite(np.delete(got, 5, axis=-1)).all()
+            else:
+                mx, rl = attention_errors(got, oc.attention(0, q))
+                assert mx <= MAX_ABS and rl <= REL_L2, (t, mx, rl)
+        if not special:
+            assert_same_cache(oc, gc, 0)
+        gc.close()
