@@ -205,9 +205,10 @@ __device__ inline void quantize_owner(const uint32_t (&w)[16], uint32_t (&codes)
         const bool over = fmaf(fmaf(-tm, Sf, dm), y, tm) > (float)levels + 0.25f;
         if (__any(over)) {
             asm volatile("" ::: "memory");  // keeps this a branch
-            const uint32_t top = over ? __float_as_uint((float)levels + 12582912.0f) : 0xffffffffu;
+            const float top = over ? (float)levels + 12582912.0f : INFINITY;
 #pragma unroll
-            for (int e = 0; e < 32; ++e) codes[e] = min(codes[e], top);
+            for (int e = 0; e < 32; ++e)  // (a NaN, whose code is 0, is not above the top)
+                codes[e] = __uint_as_float(codes[e]) > top ? __float_as_uint(top) : codes[e];
         }
     }
 }

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import kvq_synth
+import paper_2505_18610_amd as kq
 from gpu_util import append_both, assert_same_cache, check_attention, make_pair
 from oracle import calibrate_lambda, rope_rotate_keys
 
@@ -75,4 +76,63 @@ def test_strings_shared_by_two_wavefronts(bits, B, H, T):
     append_both(oc, gc, 0, K[:, :, :T], V[:, :, :T], bits)
     append_both(oc, gc, 0, K[:, :, T:], V[:, :, T:], bits)
     assert_same_cache(oc, gc, 0)
+    gc.close()
+
+
+def quantize_any(x, b, group):
+    """Eq. 1-2 for any fp16 input: minimum and maximum over the elements that are numbers, a NaN quotient rounds to code 0."""
+    g = x.astype(np.float32).reshape(x.shape[:-1] + (-1, group))
+    with np.errstate(all="ignore"):
+        Z, mx = np.fmin.reduce(g, -1), np.fmax.reduce(g, -1)
+        S = ((mx - Z) / np.float32((1 << b) - 1)).astype(np.float16)
+        r = np.rint((g - Z[..., None]) / S.astype(np.float32)[..., None])
+        r = np.where(np.isnan(r) | (S == 0)[..., None], 0, np.clip(r, 0, (1 << b) - 1))
+    return r.reshape(x.shape).astype(np.uint16), S, Z
+
+
+def unpack(codes, b):
+    raw = np.ascontiguousarray(codes).view(np.uint8)
+    if b == 16:
+        return raw.reshape(raw.shape[:-1] + (-1, 2)).astype(np.uint16) @ np.array([1, 256], np.uint16)
+    c = (raw[..., None] >> np.arange(0, 8, b, dtype=np.uint8)) & ((1 << b) - 1)
+    return c.reshape(raw.shape[:-1] + (-1,)).astype(np.uint16)
+
+
+@pytest.mark.parametrize("group", [32, 128])
+@pytest.mark.parametrize("bits,way", [(16, "append"), (8, "append"), (4, "append"), (2, "append"), (8, "requant")])
+def test_elements_that_are_no_numbers(bits, way, group):
+    """NaN (code 0) and infinities in groups of ordinary scales, of scales rounded down to a subnormal, whose top codes are
+    clamped, and of scale 0."""
+    B, H, P, T = 1, 2, 64, 200
+    rng = np.random.default_rng(84)
+    X = [rng.standard_normal((B, H, T, 128), dtype=np.float32) for _ in range(2)]
+    for x in X:
+        # tokens 40 ..: steps of 2^-24 up to 1.4 levels' worth: the scale is 2^-24 and the group's maximum above the top level
+        top = 1.4 * ((1 << bits) - 1) * 2.0 ** -24
+        x[:, :, 40:80] = rng.random((B, H, 40, 128)) * top
+        x[:, :, 40:80, ::32] = 0.0
+        x[:, :, 40:80, 1::32] = top
+        x[:, :, 80:90] = 0.25
+        x[:, :, 0:200:3, 5::32] = np.nan
+        x[:, :, 1:200:9, 7::16] = np.nan
+        x[:, :, 2:200:21, 9] = np.inf
+        x[:, :, 5:200:21, 40] = -np.inf
+        x[:, :, 8:200:42] = np.nan
+    K, V = (x.astype(np.float16) for x in X)
+    sign = rng.random(K.shape) < 0.5
+    K[np.isnan(K) & sign] = np.array(0xfe55, np.uint16).view(np.float16)  # the other sign, a payload
+    _, gc = make_pair(1, B, H, H, T, P, group=group, tier16=1 if bits == 16 else 0)
+    dev = lambda x: torch.from_numpy(x).cuda()
+    if way == "append":
+        for a, b in ((0, 47), (47, 139), (139, 200)):
+            gc.kvq_quantize_append(0, dev(K[:, :, a:b].copy()), dev(V[:, :, a:b].copy()), bits)
+    else:
+        gc.kvq_quantize_append(0, dev(K), dev(V), 16)
+        gc.kvq_progressive_requant(0, segment=0)
+    for which, x in ((kq.KVQ_WHICH_K, K), (kq.KVQ_WHICH_V, V)):
+        codes, S, Z = gc.kvq_cache_export_segment(0, 0, which)
+        want, wS, wZ = quantize_any(x, bits, group)
+        got = unpack(codes, bits)
+        assert np.array_equal(got, want), np.argwhere(got != want)[:5]
+        assert np.array_equal(S, wS, equal_nan=True) and np.array_equal(Z.astype(np.float32), wZ, equal_nan=True)
     gc.close()
