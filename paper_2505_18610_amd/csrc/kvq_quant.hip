@@ -627,31 +627,60 @@ __global__ void kvq_reparam_store_kernel(const float* __restrict__ lambda, float
     if (i < n) { const float l = lambda[i]; dst[i] = l; dst[n + i] = 1.0f / l; }
 }
 // Eq. 8, first half: acc[h][i] = max over sequences and tokens of |K|.  acc holds float bit patterns of non-negative
-// values, whose unsigned order is their order.  grid.x = (sequence, KV head) units, grid.y = slices of a unit's tokens, 256
-// threads: 16 lanes x 16 bytes read one row of 128 channels, a workgroup 16 rows at a time, eight loads in flight per
-// lane; the 16 row groups meet in LDS and 128 atomics go out whose result nobody waits for (looking first whether a channel
-// exceeds what is there costs 20 us: the look is a trip to memory at the end of every workgroup, the atomics are not).
-// Bound by the one read of the keys: 32 sequences x 8 heads x 2,048 tokens (134 MB) take 22 us, 6.1 TB/s; with 2-byte
-// loads, a 64-bit division per row and 1,024 slices per head they took 82 us.
+// values, whose unsigned order is their order.  256 threads: 16 lanes x 16 bytes read one row of 128 channels, a workgroup 16
+// rows at a time, eight loads in flight per lane; the 16 row groups meet in LDS and 128 atomics go out whose result nobody
+// waits for (looking first whether a channel exceeds what is there costs 20 us: the look is a trip to memory at the end of
+// every workgroup, the atomics are not).
+//   FLAT = false: grid.x = (sequence, KV head) units, grid.y = slices of a unit's tokens
+//   FLAT = true:  grid.x = KV heads, grid.y = slices of a head's rows, the tokens of all its sequences in turn; a row's place
+//                 is stepped along, 16 rows being step_seqs sequences and step_tokens tokens
+// Bound by the one read of the keys.  32 sequences x 8 heads x 2,048 tokens (134 MB): 24 us over keys read for the first
+// time, 5.6 TB/s, and 21 over the same ones again, which the last-level cache partly holds (82 with 2-byte loads, a 64-bit
+// division per row and 1,024 slices per head).  The stepping costs the long sequences 2 to 3 %; on short ones a workgroup per unit
+// pays its atomics for few rows.  Whole calls over 134 MB of 8 heads, FLAT = false and true: 2,048 tokens a sequence 26.3
+// and 26.8 us, 512 26.9 and 27.4, 256 28.0 and 28.4, 128 32.5 and 29.6, 64 49 and 28, 16 159 and 29, 1 token 2,453 and 28 (64
+// heads, 268 MB: 512 46.7 and 46.4, 256 47.4 and 46.0, 128 49.7 and 46.8): the line is at 256 tokens.
+template <bool FLAT>
 __global__ __launch_bounds__(256) void kvq_absmax_kernel(const uint16_t* __restrict__ k, int n_kv_heads, int n_tokens,
-                                                         int slice_tokens, uint32_t* __restrict__ acc) {
+                                                         int n_rows, int slice_rows, int step_seqs, int step_tokens,
+                                                         uint32_t* __restrict__ acc) {
     __shared__ __attribute__((aligned(16))) uint32_t part[16][KVQ_D / 2];
-    const int unit = blockIdx.x, c8 = threadIdx.x & 15, rg = threadIdx.x >> 4;
-    const int t0 = blockIdx.y * slice_tokens, t1 = min(n_tokens, t0 + slice_tokens);
-    const uint16_t* p = k + (uint64_t)unit * n_tokens * KVQ_D + 8 * c8;
+    const int c8 = threadIdx.x & 15, rg = threadIdx.x >> 4, head = FLAT ? blockIdx.x : blockIdx.x % n_kv_heads;
+    const int r0 = blockIdx.y * slice_rows, r1 = r0 + min(slice_rows, n_rows - r0);
+    int r = r0 + rg;
+    const uint16_t* p;
+    int t = r;
+    int64_t step = 16 * KVQ_D, wrap = 0;
+    if (FLAT) {
+        t = r % n_tokens;
+        const int64_t seq_rows = (int64_t)n_kv_heads * n_tokens;
+        p = k + ((r / n_tokens) * seq_rows + (int64_t)head * n_tokens + t) * KVQ_D + 8 * c8;
+        step = (step_seqs * seq_rows + step_tokens) * KVQ_D;
+        wrap = (seq_rows - n_tokens) * KVQ_D;  // on to the next sequence
+    } else {
+        p = k + ((int64_t)blockIdx.x * n_tokens + t) * KVQ_D + 8 * c8;
+    }
+    const auto next = [&]() {
+        const uint16_t* const at = p;
+        p += step;
+        if (FLAT) {
+            t += step_tokens;
+            if (t >= n_tokens) { t -= n_tokens; p += wrap; }
+        }
+        return at;
+    };
     uint32_t m[4] = {0u, 0u, 0u, 0u};
-    int t = t0 + rg;
-    for (; t + 7 * 16 < t1; t += 8 * 16) {
+    for (; r + 7 * 16 < r1; r += 8 * 16) {
         u32x4 v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = load16_any_stream(p + (uint64_t)(t + 16 * u) * KVQ_D);
+        for (int u = 0; u < 8; ++u) v[u] = load16_any_stream(next());
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
             for (int e = 0; e < 4; ++e) m[e] = pk_max_u(m[e], v[u][e] & 0x7fff7fffu);
     }
-    for (; t < t1; t += 16) {
-        const u32x4 v = load16_any_stream(p + (uint64_t)t * KVQ_D);
+    for (; r < r1; r += 16) {
+        const u32x4 v = load16_any_stream(next());
 #pragma unroll
         for (int e = 0; e < 4; ++e) m[e] = pk_max_u(m[e], v[e] & 0x7fff7fffu);
     }
@@ -661,7 +690,7 @@ __global__ __launch_bounds__(256) void kvq_absmax_kernel(const uint16_t* __restr
         uint32_t w = part[0][threadIdx.x];
 #pragma unroll
         for (int r = 1; r < 16; ++r) w = pk_max_u(w, part[r][threadIdx.x]);
-        uint32_t* dst = acc + (unit % n_kv_heads) * KVQ_D + 2 * threadIdx.x;
+        uint32_t* dst = acc + head * KVQ_D + 2 * threadIdx.x;
 #pragma unroll
         for (int h = 0; h < 2; ++h) atomicMax(dst + h, __float_as_uint(h2f((uint16_t)(w >> (16 * h)))));
     }
@@ -816,13 +845,25 @@ hipError_t kvq_launch_reparam_store(const float* lambda, float* dst, int n, hipS
 hipError_t kvq_launch_calibrate(const void* k, int batch, int n_kv_heads, int n_tokens, float alpha, float floor_,
                                 float* lambda, hipStream_t s) {
     const int n = n_kv_heads * KVQ_D;
+    const int64_t rows = (int64_t)batch * n_tokens;  // of one head; 256 bytes each
+    if (rows >= (1ll << 31) - 256) return hipErrorInvalidValue;  // more than the device holds
     hipLaunchKernelGGL(kvq_fill_u32_kernel, dim3((n + 255) / 256), dim3(256), 0, s, reinterpret_cast<uint32_t*>(lambda), 0u, (size_t)n);
-    // About 1,024 workgroups (four per compute unit), each of at least 128 tokens of one unit: the eight loads of a lane.
-    const int units = batch * n_kv_heads;
-    const int want = std::max(1, (1024 + units - 1) / units);
-    const int slice = std::max(128, ((n_tokens + want - 1) / want + 15) / 16 * 16);
-    hipLaunchKernelGGL(kvq_absmax_kernel, dim3(units, (n_tokens + slice - 1) / slice), dim3(256), 0, s,
-                       static_cast<const uint16_t*>(k), n_kv_heads, n_tokens, slice, reinterpret_cast<uint32_t*>(lambda));
+    // About 1,024 workgroups (four per compute unit), each of at least 128 rows: the eight loads of a lane.
+    const uint16_t* keys = static_cast<const uint16_t*>(k);
+    uint32_t* acc = reinterpret_cast<uint32_t*>(lambda);
+    if (n_tokens >= 256) {
+        const int units = batch * n_kv_heads;
+        const int want = std::max(1, (1024 + units - 1) / units);
+        const int slice = std::max(128, ((n_tokens + want - 1) / want + 15) / 16 * 16);
+        hipLaunchKernelGGL(kvq_absmax_kernel<false>, dim3(units, (n_tokens + slice - 1) / slice), dim3(256), 0, s, keys, n_kv_heads,
+                           n_tokens, n_tokens, slice, 0, 16, acc);
+    } else {
+        // (with more heads than workgroups are wanted, slices of about 2,048 rows, so that the last ones idle little)
+        const int64_t want = std::max<int64_t>((1024 + n_kv_heads - 1) / n_kv_heads, std::min<int64_t>(1024, (rows + 2047) / 2048));
+        const int slice = (int)std::max<int64_t>(128, ((rows + want - 1) / want + 15) / 16 * 16);
+        hipLaunchKernelGGL(kvq_absmax_kernel<true>, dim3(n_kv_heads, (unsigned)((rows + slice - 1) / slice)), dim3(256), 0, s, keys,
+                           n_kv_heads, n_tokens, (int)rows, slice, 16 / n_tokens, 16 % n_tokens, acc);
+    }
     hipLaunchKernelGGL(kvq_lambda_pow_kernel, dim3((n + 255) / 256), dim3(256), 0, s, lambda, n, alpha, floor_);
     return hipGetLastError();
 }

@@ -55,7 +55,8 @@ def test_errors_against_the_oracle(B, Hkv, P, tiers, tier16):
     gc.close()
 
 
-@pytest.mark.parametrize("B,Hkv,T", [(1, 1, 1), (1, 2, 15), (2, 1, 129), (3, 4, 257), (1, 8, 4097), (40, 32, 17)])
+@pytest.mark.parametrize("B,Hkv,T", [(1, 1, 1), (1, 2, 15), (2, 1, 129), (3, 4, 257), (1, 8, 4097), (40, 32, 17),
+                                     (300, 3, 1), (1000, 2, 3), (77, 1, 16), (33, 2, 31), (2, 1100, 3)])
 def test_calibration_at_slice_edges(B, Hkv, T):
     K, _ = kvq_synth.make_kv(62, 0, B, Hkv, 0, T)
     K[0, Hkv - 1, T - 1, 127] = -3000.0  # the last element read decides its channel
@@ -65,3 +66,34 @@ def test_calibration_at_slice_edges(B, Hkv, T):
         kq.kvq_calibrate_lambda(dev(K), 0.5, lam)
         # maxima are exact; pow in fp64 rounded to fp32: one ulp
         assert np.allclose(lam.cpu().numpy(), want, rtol=1.2e-7, atol=0)
+
+
+@pytest.mark.parametrize("B,H,T", [(1 << 21, 8, 1), (3, 1030, 1400)])
+def test_calibration_over_many_sequences_or_heads(B, H, T):
+    """2^24 (sequence, head) pairs of one token: 2^32 threads if each had a workgroup of its own.  More heads than a launch wants
+    workgroups: several slices of a head all the same."""
+    K = torch.empty((B, H, T, 128), dtype=torch.float16, device="cuda").normal_()
+    K[B - 1, H - 1, T - 1, 127] = -3000.0
+    lam = torch.full((H, 128), -1.0, dtype=torch.float32, device="cuda")
+    kq.kvq_calibrate_lambda(K, 1.0, lam)
+    assert torch.equal(lam, K.abs_().amax(dim=(0, 2)).float())
+
+
+def test_calibration_time_does_not_depend_on_how_the_tokens_are_cut_into_sequences():
+    """131,072 tokens of 8 heads as 64 sequences and as 131,072."""
+    K = torch.randn((131072, 8, 1, 128), dtype=torch.float16, device="cuda")
+    lam = torch.empty((8, 128), dtype=torch.float32, device="cuda")
+
+    def best(x):
+        times = []
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            kq.kvq_calibrate_lambda(x, 0.5, lam)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+
+    # a workgroup and its atomics per sequence: 90 times as long
+    assert best(K) < 4 * best(K.view(64, 8, 2048, 128))
