@@ -237,6 +237,7 @@ kvq_status_t kvq_cache_export_segment(kvq_cache_t* cache, int32_t layer, int32_t
  *                   is faster and changes only the floating-point summation order from call to call.
  *   KVQ_OPT_TILE_COST_{2,4,8,16}BIT: relative time one 32-token tile of that width costs the attention kernel
  *                   (1..1000000); the token range of a (sequence, KV head) is cut into splits of equal cost.
+ *                   Only their ratios matter; how many splits there are does not depend on them.
  *   KVQ_OPT_SHIFT_STRATEGY: how later 2b -> b steps of kvq_progressive_requant treat codes, S and Z, for the
  *                   comparison of Sec. 4.3.1 (the step from raw fp16 values is Eq. 1-2 under every strategy):
  *                   KVQ_SHIFT_EQUIVALENT (default, Eq. 3): X_b = ((2^2b - 2^b + 1)(X_2b + 2^(b-1))) >> 3b,

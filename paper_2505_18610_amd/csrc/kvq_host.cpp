@@ -29,6 +29,8 @@ struct RingEvents {
 };
 
 int order_of_bits(int bits) { return bits == 16 ? 4 : bits == 8 ? 3 : bits == 4 ? 2 : 1; }
+// Kernel time of one 2/4/8/16-bit tile, measured, in units of which a workgroup does 1,000 in 0.9 us.
+constexpr int kTileTime[4] = {100, 145, 250, 300};
 bool valid_bits(int b) { return b == 16 || b == 8 || b == 4 || b == 2; }
 
 // Buddy allocator in units.  Code blocks need 2^order units (2-bit: 2, 4-bit: 4, 8-bit: 8, 16-bit: 16),
@@ -122,7 +124,7 @@ struct kvq_cache {
     int tier16 = KVQ_TIER16_FP16;               // what a 16-bit token is: raw fp16, or 16-bit codes with (S, Z)
     bool int16() const { return tier16 == KVQ_TIER16_INT16; }
     bool has_meta(int bits) const { return bits < 16 || int16(); }
-    int tile_cost[4] = {100, 145, 250, 300};  // relative kernel time of one 2/4/8/16-bit tile (measured)
+    int tile_cost[4] = {kTileTime[0], kTileTime[1], kTileTime[2], kTileTime[3]};  // KVQ_OPT_TILE_COST_*
     int target_workgroups = 256;
 
     uint64_t bpth(int bits) const {
@@ -379,8 +381,8 @@ void build_segments(const kvq_cache* c, const Layer& L, std::vector<kvq_segment_
     }
 }
 
-// Relative time one tile of each width costs the attention kernel (measured on MI355X: the narrow widths are
-// bound by de-quantization work, the wide ones by their bytes).
+// Index of a width in kTileTime and tile_cost (the narrow widths are bound by de-quantization work, the wide ones by their
+// bytes).
 int cost_index(int bits) { return bits == 16 ? 3 : bits == 8 ? 2 : bits == 4 ? 1 : 0; }
 
 // Cost-balanced split of the tile range (n_splits <= n_tiles, or one split of nothing).  The last range is never empty: the
@@ -768,11 +770,11 @@ kvq_status_t kvq_progressive_requant(kvq_cache_t* c, int32_t layer, int32_t segm
 
 namespace {
 
-// Relative time the attention kernel needs for the block's tiles, how many of them are 2 bits wide, and the bytes of one
-// (sequence, KV head).
+// What the block's tiles cost by the weights of KVQ_OPT_TILE_COST_* (relative, in a scale the caller chooses) and what they take
+// the attention kernel (in units of kTileTime), how many of them are 2 bits wide, and the bytes of one (sequence, KV head).
 struct TileCensus {
     int n2 = 0, n_all = 0;
-    uint64_t cost = 0, bytes = 0;
+    uint64_t cost = 0, time = 0, bytes = 0;
 };
 TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
     TileCensus t;
@@ -783,6 +785,7 @@ TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
         t.n_all += nt;
         if (b == 2) t.n2 += nt;
         t.cost += (uint64_t)nt * (uint64_t)c->tile_cost[cost_index(b)];
+        t.time += (uint64_t)nt * (uint64_t)kTileTime[cost_index(b)];
         t.bytes += (uint64_t)nt * (2u * kvq_tile_code_bytes(b) + (c->has_meta(b) ? KVQ_META_TILE_BYTES : 0u));
     }
     return t;
@@ -791,13 +794,13 @@ TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
 // Most splits of one (sequence, KV head) that pay.  A range of up to 20 tiles is left to one workgroup, whose eight
 // wavefronts take two or three tiles each: publishing and merging partials costs 2.5 us, more than halving such a range
 // saves (10 tiles: 6.9 us in one split, 8.7 at best in several; 20 tiles of 16 bits 9.1 and 9.0; 32 tiles 10.3 and 9.5).
-// Beyond that a split saves its share of the range's time (0.9 us per 1,000 units of tile cost) and costs about 0.07 us of
-// the merge, which is least at sqrt(cost / 80) splits: 24 tiles of mixed widths 9.3 us with 8 splits (11.0 with two of
+// Beyond that a split saves its share of the range's time (0.9 us per 1,000 units of kTileTime) and costs about 0.07 us of
+// the merge, which is least at sqrt(time / 80) splits: 24 tiles of mixed widths 9.3 us with 8 splits (11.0 with two of
 // 12 tiles, the former bound of 16 tiles per split), 79 tiles of 16 bits 10.6 us with 16 (11.9 with 5), 128 tiles of 2 bits
 // 10.8 us with 12 (11.5 with 8), 128K tokens of 2 bits 21.6 us with 64 and 22.9 with 128.
-int useful_splits(uint64_t cost, int n_tiles) {
+int useful_splits(uint64_t time, int n_tiles) {
     if (n_tiles <= 20) return 1;
-    return std::max(1, std::min(std::min(n_tiles, KVQ_MAX_SPLITS), (int)std::sqrt((double)cost / 80.0)));
+    return std::max(1, std::min(std::min(n_tiles, KVQ_MAX_SPLITS), (int)std::sqrt((double)time / 80.0)));
 }
 
 // Fills the parameter block of one attention launch over block `layer`.  wgs_share > 0: the number of workgroups this
@@ -825,7 +828,7 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
             wgs = c->target_workgroups;
             if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);
         }
-        n_splits = std::min(wgs / std::max(1, c->units), useful_splits(t.cost, n_tiles));
+        n_splits = std::min(wgs / std::max(1, c->units), useful_splits(t.time, n_tiles));
     }
     n_splits = std::max(1, std::min(n_splits, std::min(KVQ_MAX_SPLITS, n_tiles)));
     plan_splits(c, L, n_tiles, n_splits);
@@ -901,8 +904,9 @@ kvq_status_t batch_attention(kvq_cache_t* const* caches, int32_t n, int32_t laye
         const Layer& L = c->layers[(size_t)layer];
         if (L.T == 0) return KVQ_E_STATE;
         const int n_tiles = (L.T + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
-        cost[(size_t)i] = tile_census(c, L, n_tiles).cost;
-        max_splits[(size_t)i] = useful_splits(cost[(size_t)i], n_tiles);
+        const TileCensus t = tile_census(c, L, n_tiles);
+        cost[(size_t)i] = t.cost;
+        max_splits[(size_t)i] = useful_splits(t.time, n_tiles);
         used += c->units;
     }
     // (every compute unit is used: with ranges of unequal length the heaviest workgroup decides the launch time,

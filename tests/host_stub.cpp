@@ -255,11 +255,38 @@ void split_plans() {
     CHECK(a.append(640, 2) == KVQ_OK && a.append(33, 16) == KVQ_OK && a.step() == KVQ_OK && last.app_t_old == 673, "step");
 }
 
+// The tile costs are relative: their scale changes neither how many splits a launch takes nor where they lie.
+void tile_costs_are_relative() {
+    for (int narrow : {8, 30, 200}) {
+        std::vector<int32_t> plan, batch_plan;
+        for (int scale : {0, 1, 5, 25, 3000}) {  // 0: the costs the library comes with, 20 : 29 : 50 : 60
+            Cache a(64, 200, 0), b(64, 200, 0);
+            for (Cache* c : {&a, &b}) {
+                const int costs[4] = {20, 29, 50, 60};
+                for (int i = 0; i < 4 && scale; ++i)
+                    CHECK(kvq_cache_set_option(c->c, KVQ_OPT_TILE_COST_2BIT + i, costs[i] * scale) == KVQ_OK, "option");
+                CHECK(c->append(narrow * 64, 2) == KVQ_OK && c->append(64 * narrow, 4) == KVQ_OK && c->append(100, 16) == KVQ_OK, "prompt");
+            }
+            for (bool batched : {false, true}) {
+                kvq_cache_t* cs[2] = {a.c, b.c};
+                const void* q[2] = {input, input};
+                void* out[2] = {input, input};
+                CHECK((batched ? kvq_decode_attention_batch(cs, 2, 0, q, out, 0, 0.f, nullptr) : a.attend()) == KVQ_OK, "attention");
+                const std::vector<int32_t> now(last.split_begin, last.split_begin + last.n_splits + 1);
+                std::vector<int32_t>& first = batched ? batch_plan : plan;
+                if (scale == 0) first = now;
+                CHECK(now == first, "%zu instead of %zu splits with costs x %d, %d pages, batched %d", now.size() - 1, first.size() - 1, scale, narrow, batched);
+            }
+        }
+    }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
     {"batch_full_arena", batch_full_arena},
     {"batch_failing_launch", batch_failing_launch},
     {"failed_block_is_refused", failed_block_is_refused},
     {"split_plans", split_plans},
+    {"tile_costs_are_relative", tile_costs_are_relative},
 };
 
 }  // namespace
