@@ -164,12 +164,18 @@ __device__ inline void append16_k_tile(uint8_t* code, const NewRows& rows, int t
 // The same for a V tile, through LDS: the rows are read with 16-byte loads (a wavefront instruction covers one contiguous KiB
 // of the input), parked as [token][channel] and picked up in the tile layout (lane (j, n): tokens 8j .. 8j+7 of channels
 // 16 nt + n).  Rows are rotated by 32 bytes per 8 tokens so that the four lane quarters, which read rows 8 apart, use
-// different banks.  lds: 8 KiB of this wavefront alone, 16-byte aligned.
-__device__ inline void append16_v_tile(uint8_t* code, const NewRows& rows, int tok0, int lane, uint8_t* lds) {
+// different banks.  lds: 8 KiB of this wavefront alone, 16-byte aligned.  stream (wavefront-uniform): read the rows with
+// streaming loads, which pass the caches by.
+__device__ inline void append16_v_tile(uint8_t* code, const NewRows& rows, int tok0, int lane, uint8_t* lds, bool stream) {
     const int j = lane >> 4, n = lane & 15;
     u32x4 v[8];
+    if (stream) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) v[c] = rows.load_stream(rows.offset(tok0 + 4 * c + j) + 16u * n);
+        for (int c = 0; c < 8; ++c) v[c] = rows.load_stream(rows.offset(tok0 + 4 * c + j) + 16u * n);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = rows.load(rows.offset(tok0 + 4 * c + j) + 16u * n);
+    }
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         const int tl = 4 * c + j;

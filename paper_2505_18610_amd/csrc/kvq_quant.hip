@@ -31,14 +31,14 @@ __device__ inline bool append_work(int n_strings, int by_unit, int wave, int* st
     return *string < n_strings;
 }
 
-// Append into the 16-bit tier: the new rows are copied into the tile layout.
+// Append into the 16-bit tier: the new rows are copied into the tile layout.  stream_v: see append16_v_tile.
 template <bool PLAIN>
 __global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ arena,
                                                           KvqPageDesc* __restrict__ table,
                                                           const uint16_t* __restrict__ k_in,
                                                           const uint16_t* __restrict__ v_in, int t_old,
                                                           int n_new, int tpp, int tile0, const KvqAppendPages ap,
-                                                          int /* group span: nothing is quantized */,
+                                                          int stream_v,
                                                           const float* __restrict__ rinv, int n_kv_heads,
                                                           const float* __restrict__ rope, int n_strings, int by_unit) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[32 * 256];
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ 
     const uint64_t tslot = (uint64_t)unit * tpp + tip;
     uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * 16);
     const kvq_dev::NewRows rows((which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D, t_old, n_new);
-    if (which) kvq_dev::append16_v_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, lds);  // (wavefront-uniform)
+    if (which) kvq_dev::append16_v_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, lds, stream_v);  // (wavefront-uniform)
     else if (PLAIN) kvq_dev::append16_k_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, nullptr, nullptr);
     else kvq_dev::append16_k_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
 }
@@ -736,6 +736,13 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     const uint16_t* k = static_cast<const uint16_t*>(k_in);
     const uint16_t* v = static_cast<const uint16_t*>(v_in);
     const bool pair = (int64_t)n_strings * units <= KVQ_PAIR_MAX_STRINGS;
+    // How the 16-bit tier's V rows are read: new values have usually just been written and lie in the caches, which streaming
+    // loads make less of.  128 units x 2,000 tokens (131 MB of keys and values) 43 us with plain loads of V and 51 with streaming
+    // ones, 64 x 2,000 21 and 25, 32 x 2,000 10.9 and 12.6 (from 230 MB of buffers in turn 13.4 and 13.0), 600 x 50 12.1 and 13.0,
+    // up to 16 x 1,024 alike.  An input that the 256 MB last-level cache does not hold gains by streaming past it: 64 x 8,192 (268
+    // MB) 86 and 85, from buffers in turn 102 and 94.  Beside keys that are prepared, streaming is the better or the same: 32 x
+    // 2,000 16.0 and 16.0, from buffers in turn 18.9 and 15.8.
+    const int stream_v = !plain || (int64_t)units * n_new * (2 * 256) > (192 << 20);
     const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 ? units : 0;
 #define KVQ_APPEND_LAUNCH(kernel_, waves_, per_, extra_)                                                                     \
     do {                                                                                                                 \
@@ -751,8 +758,8 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
             else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, 1, gspan);
             break;
         case 16:
-            if (plain) KVQ_APPEND_LAUNCH(kvq_append16_kernel<true>, 1, 1, gspan);
-            else KVQ_APPEND_LAUNCH(kvq_append16_kernel<false>, 1, 1, gspan);
+            if (plain) KVQ_APPEND_LAUNCH(kvq_append16_kernel<true>, 1, 1, stream_v);
+            else KVQ_APPEND_LAUNCH(kvq_append16_kernel<false>, 1, 1, stream_v);
             break;
 #define KVQ_APPEND_CASE(b_)                                                                                              \
         case b_:                                                                                                         \

@@ -136,3 +136,30 @@ def test_elements_that_are_no_numbers(bits, way, group):
         assert np.array_equal(got, want), np.argwhere(got != want)[:5]
         assert np.array_equal(S, wS, equal_nan=True) and np.array_equal(Z.astype(np.float32), wZ, equal_nan=True)
     gc.close()
+
+
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("bits,tier16", [(16, 0), (16, 1), (8, 0)])
+def test_one_long_append_writes_what_its_pieces_write(bits, tier16, rope):
+    """64 units x 6,250 tokens at once (205 MB of keys and values: the routes of inputs beyond the caches, of 98,304 rows and more)
+    and in pieces of 1,000: the same arena, byte for byte."""
+    B, H, P, T = 8, 8, 128, 6250
+    g = torch.Generator(device="cuda").manual_seed(85)
+    k, v = (torch.randn((B, H, T, 128), device="cuda", generator=g).half() for _ in range(2))
+    table = torch.randn((T, 128), device="cuda", generator=g)
+    cfg = kq.KvqConfig(1, B, H, H, T, page_tokens=P)
+    arenas = []
+    for step in (T, 1000):
+        arena = torch.zeros(kq.kvq_arena_bytes(cfg, T * B * H * 640 + (64 << 20)), dtype=torch.uint8, device="cuda")
+        gc = kq.KvqCache(cfg, [1 << 50], [2], arena=arena)
+        gc.kvq_cache_set_option(kq.KVQ_OPT_TIER16, tier16)
+        for t in range(0, T, step):
+            piece = [x[:, :, t:t + step].contiguous() for x in (k, v)]
+            if rope:
+                gc.kvq_quantize_append_rope(0, *piece, table[t:t + step].contiguous(), bits)
+            else:
+                gc.kvq_quantize_append(0, *piece, bits)
+        torch.cuda.synchronize()
+        gc.close()
+        arenas.append(arena)
+    assert torch.equal(*arenas)
