@@ -803,19 +803,22 @@ int useful_splits(uint64_t time, int n_tiles) {
     return std::max(1, std::min(std::min(n_tiles, KVQ_MAX_SPLITS), (int)std::sqrt((double)time / 80.0)));
 }
 
-// Fills the parameter block of one attention launch over block `layer`.  wgs_share > 0: the number of workgroups this
-// cache may use (its share of a ragged batch); 0: the whole device.
+int tiles_of(int n_tokens) { return (n_tokens + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS; }
+// A token that the launch itself appends is not read from the cache: the tiles of the older ones are split.
+int tiles_read(const Layer& L, const DeferredAppend& app) { return tiles_of(app.active ? app.t_old : L.T); }
+
+// Fills the parameter block of one attention launch over block `layer`.  batch_splits > 0: the splits per (sequence, KV
+// head) this cache gets in a ragged batch; 0: the whole device serves it.
 kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, void* out_dev, int32_t out_is_fp32,
                               float softmax_scale, const DeferredAppend* app, const void* k_new, const void* v_new,
-                              const float* cos_sin_dev, int wgs_share, KvqAttnParams& p) {
+                              const float* cos_sin_dev, int batch_splits, KvqAttnParams& p) {
     if (!c || layer < 0 || layer >= c->cfg.n_layers || !q_dev || !out_dev) return KVQ_E_INVALID;
     if (c->dry) return KVQ_E_STATE;
     Layer& L = c->layers[(size_t)layer];
     if (L.T == 0 || L.poisoned) return KVQ_E_STATE;
-    // a token that the launch itself appends is not read from the cache: the tiles of the older ones are split
     const int n_tokens = app && app->active ? app->t_old : L.T;
-    const int n_tiles = (n_tokens + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
-    int n_splits = c->splits_override;
+    const int n_tiles = app ? tiles_read(L, *app) : tiles_of(L.T);
+    int n_splits = c->splits_override > 0 ? c->splits_override : batch_splits;
     if (n_splits <= 0) {
         // One workgroup per compute unit when a good part of the tiles is 2 bits wide (those are bound by vector
         // issue and want every unit) or the launch is short (what counts is the length of one range: 8K tokens x 32 units
@@ -823,11 +826,8 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
         // launch over wider tiles is bound by HBM, and there three quarters of the units stream measurably faster than all of them
         // (16-bit blocks of 87 to 160 MB 3 to 4 %, 4-, 8- and 16-bit blocks of 350 MB and more 4 to 7 %).
         const TileCensus t = tile_census(c, L, n_tiles);
-        int wgs = wgs_share;
-        if (wgs <= 0) {
-            wgs = c->target_workgroups;
-            if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);
-        }
+        int wgs = c->target_workgroups;
+        if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);
         n_splits = std::min(wgs / std::max(1, c->units), useful_splits(t.time, n_tiles));
     }
     n_splits = std::max(1, std::min(n_splits, std::min(KVQ_MAX_SPLITS, n_tiles)));
@@ -887,57 +887,89 @@ kvq_status_t attention_impl(kvq_cache_t* c, int32_t layer, const void* q_dev, vo
     return kvq_launch_attention(p, c->units, as_stream(hip_stream)) == hipSuccess ? KVQ_OK : KVQ_E_HIP;
 }
 
+// One cache's part in dealing a batch's workgroups: the tile time of one of its (sequence, KV head) units, how many units it
+// has, the most splits per unit that pay, the splits per unit it gets.
+struct BatchShare {
+    uint64_t cost;
+    int units, max_splits, splits;
+};
+
+// The device's workgroups are dealt to the caches so that the most loaded workgroup is as light as possible: every cache
+// starts with one split per unit; the cache whose workgroups carry the most tile time gets one more split, as long as the
+// workgroups last (and the cache's splits pay).  Every compute unit is used: with ranges of unequal length the heaviest
+// workgroup decides the launch time, which outweighs the few percent a block of equal ranges gains from leaving a quarter of
+// the units idle.
+// The steps of this that make a workgroup lighter which carries more than some load are made in one go for a load at which
+// they fit: they all come before the others, and none of them is refused.  (One by one, each step a look at all caches, they
+// took longer than the launch: 64 caches of 1,000 tokens 18 of the call's 84 us on the host, 16 of 5,000 tokens 4 of 26.)
+void deal_workgroups(std::vector<BatchShare>& share, int wgs) {
+    uint64_t load = 0;
+    for (BatchShare& c : share) { c.splits = 1; load = std::max(load, c.cost); }
+    const auto splits_at = [](const BatchShare& c, uint64_t l) {  // the fewest splits that leave a workgroup no more than l
+        return (int)std::min<uint64_t>((uint64_t)c.max_splits, c.cost / (l + 1) + 1);
+    };
+    const auto used_at = [&](uint64_t l) {
+        int64_t used = 0;
+        for (const BatchShare& c : share) used += (int64_t)splits_at(c, l) * c.units;
+        return used;
+    };
+    int64_t used = used_at(load);
+    if (used > wgs) return;
+    if (const int64_t u = used_at(0); u <= wgs) {  // enough for all that pays
+        load = 0;
+        used = u;
+    }
+    while (load > 0) {
+        const uint64_t less = load - load / 4 - 1;
+        const int64_t u = used_at(less);
+        if (u > wgs) break;
+        load = less;
+        used = u;
+    }
+    std::vector<uint64_t> per_wg(share.size());
+    for (size_t i = 0; i < share.size(); ++i) {
+        share[i].splits = splits_at(share[i], load);
+        per_wg[i] = share[i].cost / (uint64_t)share[i].splits;
+    }
+    for (;;) {
+        size_t pick = share.size();
+        uint64_t worst = 0, refused = 0;
+        for (size_t i = 0; i < share.size(); ++i) {
+            const BatchShare& c = share[i];
+            if (c.splits >= c.max_splits) continue;
+            if (used + c.units > wgs) refused = std::max(refused, per_wg[i]);
+            else if (per_wg[i] > worst) { worst = per_wg[i]; pick = i; }
+        }
+        // stop once a heavier cache could still be split but no longer fits into the workgroups that are left:
+        // more splits elsewhere would not lighten the heaviest workgroup, only add merge work
+        if (pick == share.size() || refused > worst) return;
+        share[pick].splits++;
+        per_wg[pick] = share[pick].cost / (uint64_t)share[pick].splits;
+        used += share[pick].units;
+    }
+}
+
 // The attention launch of a ragged batch over block `layer` of n caches, with the appends deferred to it (k_dev, v_dev and
 // cos_sin_dev are looked at for those only).
 kvq_status_t batch_attention(kvq_cache_t* const* caches, int32_t n, int32_t layer, const std::vector<DeferredAppend>& app,
                              const void* const* k_dev, const void* const* v_dev, const float* const* cos_sin_dev,
                              const void* const* q_dev, void* const* out_dev, int32_t out_is_fp32, float softmax_scale,
                              hipStream_t s) {
-    // The device's workgroups are dealt to the caches so that the most loaded workgroup is as light as possible:
-    // every cache starts with one split per (sequence, KV head); the cache whose workgroups carry the most tile
-    // time gets one more split, as long as the workgroups last (and the cache's splits pay).
-    std::vector<uint64_t> cost((size_t)n);  // tile time of one (sequence, KV head) of the cache
-    std::vector<int> splits((size_t)n, 1), max_splits((size_t)n);
-    int used = 0;
+    std::vector<BatchShare> share((size_t)n);
     for (int i = 0; i < n; ++i) {
         kvq_cache_t* c = caches[i];
         const Layer& L = c->layers[(size_t)layer];
         if (L.T == 0) return KVQ_E_STATE;
-        const int n_tiles = (L.T + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
+        const int n_tiles = tiles_read(L, app[(size_t)i]);
         const TileCensus t = tile_census(c, L, n_tiles);
-        cost[(size_t)i] = t.cost;
-        max_splits[(size_t)i] = useful_splits(t.time, n_tiles);
-        used += c->units;
+        share[(size_t)i] = BatchShare{t.cost, c->units, useful_splits(t.time, n_tiles), 1};
     }
-    // (every compute unit is used: with ranges of unequal length the heaviest workgroup decides the launch time,
-    //  which outweighs the few percent a block of equal ranges gains from leaving a quarter of the units idle)
-    const int wgs = caches[0]->target_workgroups;
-    for (;;) {
-        int pick = -1;
-        uint64_t worst = 0;
-        for (int i = 0; i < n; ++i) {
-            if (splits[(size_t)i] >= max_splits[(size_t)i] || used + caches[i]->units > wgs) continue;
-            const uint64_t per_wg = cost[(size_t)i] / (uint64_t)splits[(size_t)i];
-            if (per_wg > worst) { worst = per_wg; pick = i; }
-        }
-        if (pick < 0) break;
-        // stop once a heavier cache could still be split but no longer fits into the workgroups that are left:
-        // more splits elsewhere would not lighten the heaviest workgroup, only add merge work
-        bool blocked = false;
-        for (int i = 0; i < n; ++i)
-            if (i != pick && cost[(size_t)i] / (uint64_t)splits[(size_t)i] > worst &&
-                splits[(size_t)i] < max_splits[(size_t)i])
-                blocked = true;
-        if (blocked) break;
-        splits[(size_t)pick]++;
-        used += caches[pick]->units;
-    }
+    deal_workgroups(share, caches[0]->target_workgroups);
     std::vector<KvqAttnParams> params((size_t)n);
     for (int i = 0; i < n; ++i) {
         kvq_status_t st = fill_attn_params(caches[i], layer, q_dev[i], out_dev[i], out_is_fp32, softmax_scale,
                                            &app[(size_t)i], k_dev ? k_dev[i] : nullptr, v_dev ? v_dev[i] : nullptr,
-                                           cos_sin_dev ? cos_sin_dev[i] : nullptr, splits[(size_t)i] * caches[i]->units,
-                                           params[(size_t)i]);
+                                           cos_sin_dev ? cos_sin_dev[i] : nullptr, share[(size_t)i].splits, params[(size_t)i]);
         if (st != KVQ_OK) return st;
     }
     // The kernel reads the parameter blocks straight from the pinned staging ring of the first cache (host memory the

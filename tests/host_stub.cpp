@@ -4,11 +4,16 @@
 // argument: the scenario.  Exit code 0 = pass.  No GPU and no HIP library is involved.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <functional>
 #include <map>
+#include <memory>
+#include <random>
 #include <string>
 #include <vector>
 
@@ -43,6 +48,7 @@ hipError_t launched() { return launches++ == fail_launch ? hipErrorLaunchFailure
 
 std::map<const uint8_t*, uint64_t> arena_size;  // every arena by its address
 KvqAttnParams last;                             // parameters of the last attention launch
+std::vector<KvqAttnParams> last_batch;          // of the last batched one
 
 void check_table(const uint8_t* arena, const KvqPageDesc* table, int n_tokens, int tpp) {
     const int pages = (n_tokens + 32 * tpp - 1) / (32 * tpp);
@@ -120,6 +126,7 @@ hipError_t kvq_launch_merge(const KvqAttnParams&, int, hipStream_t) { return lau
 hipError_t kvq_launch_attention_batch(const KvqAttnParams*, const KvqAttnParams* p, const int*, int n, hipStream_t) {
     const hipError_t e = launched();
     for (int i = 0; i < n && e == hipSuccess; ++i) attention(p[i]);
+    last_batch.assign(p, p + n);
     return e;
 }
 
@@ -281,12 +288,95 @@ void tile_costs_are_relative() {
     }
 }
 
+// How a ragged batch shares the workgroups: the same as by giving one split at a time to the cache with the heaviest
+// workgroups.  And dealing them does not dominate the call (step by step: 7 times as long).
+void batch_shares() {
+    std::mt19937 rng(5);
+    const auto R = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+    for (int round = 0; round < 60; ++round) {
+        const int n = round < 3 ? 64 : R(1, 20);
+        std::vector<std::unique_ptr<Cache>> caches;
+        std::vector<kvq_cache_t*> cs;
+        for (int i = 0; i < n; ++i) {
+            caches.emplace_back(new Cache(64, 60, 0, KVQ_POLICY_PAPER, 0, 1, round < 3 ? 1 : 1 << R(0, R(0, 4))));
+            Cache& c = *caches.back();
+            const int bits[3] = {2, 4, 8};
+            const int pages = R(0, R(0, 1) ? 40 : 4);
+            if (round % 4 == 1) for (int k = 0; k < 4; ++k) kvq_cache_set_option(c.c, KVQ_OPT_TILE_COST_2BIT + k, R(1, R(1, 9)));
+            CHECK((pages == 0 || c.append(pages * 64, bits[R(0, 2)]) == KVQ_OK) && c.append(R(1, 300), 16) == KVQ_OK, "prompt");
+            cs.push_back(c.c);
+        }
+        std::vector<const void*> q((size_t)n, input);
+        std::vector<void*> out((size_t)n, input);
+        CHECK(kvq_decode_attention_batch(cs.data(), n, 0, q.data(), out.data(), 0, 0.f, nullptr) == KVQ_OK, "batch");
+        const std::vector<KvqAttnParams> got = last_batch;
+        // the most splits that pay and the tile time of a unit, as the library works them out
+        std::vector<uint64_t> cost;
+        std::vector<int> most, splits((size_t)n, 1);
+        int used = 0;
+        for (int i = 0; i < n; ++i) {
+            kvq_segment_info_t segs[8];
+            int m = 0, weight[4] = {100, 145, 250, 300};
+            if (round % 4 == 1) { cost.clear(); break; }  // (random costs: only the plan checks of attention())
+            kvq_cache_describe(cs[(size_t)i], 0, segs, 8, &m, nullptr, nullptr, nullptr);
+            uint64_t time = 0;
+            int tiles = 0;
+            for (int k = 0; k < m; ++k) {
+                const int nt = (segs[k].token_end + 31) / 32 - segs[k].token_begin / 32;
+                tiles += nt;
+                time += (uint64_t)nt * (uint64_t)weight[segs[k].bits == 16 ? 3 : segs[k].bits == 8 ? 2 : segs[k].bits == 4 ? 1 : 0];
+            }
+            cost.push_back(time);
+            most.push_back(tiles <= 20 ? 1 : std::min(std::min(tiles, 128), (int)std::sqrt((double)time / 80.0)));
+            used += caches[(size_t)i]->cfg.n_kv_heads;
+        }
+        if (cost.empty()) continue;
+        for (;;) {
+            int pick = -1;
+            uint64_t worst = 0;
+            for (int i = 0; i < n; ++i) {
+                if (splits[(size_t)i] >= most[(size_t)i] || used + caches[(size_t)i]->cfg.n_kv_heads > 256) continue;
+                if (cost[(size_t)i] / (uint64_t)splits[(size_t)i] > worst) { worst = cost[(size_t)i] / (uint64_t)splits[(size_t)i]; pick = i; }
+            }
+            bool blocked = pick < 0;
+            for (int i = 0; i < n; ++i)
+                blocked |= splits[(size_t)i] < most[(size_t)i] && cost[(size_t)i] / (uint64_t)splits[(size_t)i] > worst;
+            if (blocked) break;
+            splits[(size_t)pick]++;
+            used += caches[(size_t)pick]->cfg.n_kv_heads;
+        }
+        for (int i = 0; i < n; ++i)
+            CHECK(got[(size_t)i].n_splits == splits[(size_t)i], "round %d, cache %d of %d: %d splits, %d expected", round, i, n, got[(size_t)i].n_splits, splits[(size_t)i]);
+    }
+    double us[2];
+    for (int longer : {0, 1}) {
+        std::vector<std::unique_ptr<Cache>> caches;
+        std::vector<kvq_cache_t*> cs;
+        for (int i = 0; i < 64; ++i) {
+            caches.emplace_back(new Cache(256, 20, 0));
+            CHECK(caches.back()->append(longer ? 500 + 16 * i : 8 * i + 8, 16) == KVQ_OK, "prompt");  // up to 6 pages
+            cs.push_back(caches.back()->c);
+        }
+        std::vector<const void*> q(64, input);
+        std::vector<void*> out(64, input);
+        us[longer] = 1e9;
+        for (int rep = 0; rep < 20; ++rep) {
+            const auto t0 = std::chrono::steady_clock::now();
+            for (int k = 0; k < 20; ++k) kvq_decode_attention_batch(cs.data(), 64, 0, q.data(), out.data(), 0, 0.f, nullptr);
+            us[longer] = std::min(us[longer], std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / 20);
+        }
+    }
+    printf("host time of a batch of 64: one split each %.1f us, several %.1f us\n", us[0], us[1]);
+    CHECK(us[1] < 3 * us[0], "%.1f and %.1f us", us[0], us[1]);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
     {"batch_full_arena", batch_full_arena},
     {"batch_failing_launch", batch_failing_launch},
     {"failed_block_is_refused", failed_block_is_refused},
     {"split_plans", split_plans},
     {"tile_costs_are_relative", tile_costs_are_relative},
+    {"batch_shares", batch_shares},
 };
 
 }  // namespace

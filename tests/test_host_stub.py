@@ -24,7 +24,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["batch_full_arena", "batch_failing_launch", "failed_block_is_refused", "split_plans",
-                                      "tile_costs_are_relative"])
+                                      "tile_costs_are_relative", "batch_shares"])
 def test_host_code_over_a_fake_device(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
