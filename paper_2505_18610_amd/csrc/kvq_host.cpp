@@ -798,9 +798,14 @@ TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
 // the merge, which is least at sqrt(time / 80) splits: 24 tiles of mixed widths 9.3 us with 8 splits (11.0 with two of
 // 12 tiles, the former bound of 16 tiles per split), 79 tiles of 16 bits 10.6 us with 16 (11.9 with 5), 128 tiles of 2 bits
 // 10.8 us with 12 (11.5 with 8), 128K tokens of 2 bits 21.6 us with 64 and 22.9 with 128.
-int useful_splits(uint64_t time, int n_tiles) {
+// A unit or two by themselves take one split per 16 tiles if that is more, as long as half of the compute units stay idle
+// (max_wgs / 2) and the merge issues all its loads in one round: 1,000 tiles of 2 bits and 4 query heads per KV head 13.2 us
+// with 63 splits and 14.8 with 35 in one unit, 13.5 and 14.6 in two, 15.2 and 14.9 in four.
+int useful_splits(const kvq_cache_t* c, uint64_t time, int n_tiles, int max_wgs) {
     if (n_tiles <= 20) return 1;
-    return std::max(1, std::min(std::min(n_tiles, KVQ_MAX_SPLITS), (int)std::sqrt((double)time / 80.0)));
+    const int one_round = 16 * std::max(1, 16 / c->gqa);
+    const int alone = std::min(std::min((n_tiles + 15) / 16, one_round), max_wgs / 2 / c->units);
+    return std::max(1, std::min(std::min(n_tiles, KVQ_MAX_SPLITS), std::max(alone, (int)std::sqrt((double)time / 80.0))));
 }
 
 int tiles_of(int n_tokens) { return (n_tokens + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS; }
@@ -828,7 +833,11 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
         const TileCensus t = tile_census(c, L, n_tiles);
         int wgs = c->target_workgroups;
         if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);
-        n_splits = std::min(wgs / std::max(1, c->units), useful_splits(t.time, n_tiles));
+        n_splits = std::min(wgs / c->units, useful_splits(c, t.time, n_tiles, wgs));
+        // two halves of a range that one workgroup takes in a few rounds do not pay for the merge, unless they are long reads:
+        // 128 units x 21 tiles of 8 bits 9.3 us in one and 10.6 in two, x 28 10.6 and 11.5, x 22 of 16 bits (360 KB) 11.7 and
+        // 12.2; 86 units x 24 of 16 bits (393 KB) 11.3 and 11.0, x 32 13.9 and 12.2
+        if (n_splits == 2 && n_tiles <= 32 && t.bytes <= 375000) n_splits = 1;
     }
     n_splits = std::max(1, std::min(n_splits, std::min(KVQ_MAX_SPLITS, n_tiles)));
     plan_splits(c, L, n_tiles, n_splits);
@@ -962,7 +971,7 @@ kvq_status_t batch_attention(kvq_cache_t* const* caches, int32_t n, int32_t laye
         if (L.T == 0) return KVQ_E_STATE;
         const int n_tiles = tiles_read(L, app[(size_t)i]);
         const TileCensus t = tile_census(c, L, n_tiles);
-        share[(size_t)i] = BatchShare{t.cost, c->units, useful_splits(t.time, n_tiles), 1};
+        share[(size_t)i] = BatchShare{t.cost, c->units, useful_splits(c, t.time, n_tiles, c->target_workgroups), 1};
     }
     deal_workgroups(share, caches[0]->target_workgroups);
     std::vector<KvqAttnParams> params((size_t)n);

@@ -257,6 +257,15 @@ void split_plans() {
                         CHECK(last.n_splits <= n_tiles && (splits == 0 || last.n_splits == (splits < n_tiles ? splits : n_tiles)), "%d splits", last.n_splits);
                     }
                 }
+    // 128 units leave two workgroups to a range, which it takes beyond 32 tiles; one unit by itself takes a split per 16 tiles
+    for (int tiles : {20, 21, 32, 33}) {
+        Cache a(64, 40, 0, KVQ_POLICY_PAPER, 0, 16, 8);
+        CHECK(a.append(32 * tiles - 1, 8) == KVQ_OK && a.attend() == KVQ_OK && last.n_splits == (tiles > 32 ? 2 : 1), "%d tiles, %d splits", tiles, last.n_splits);
+    }
+    Cache wide(64, 100, 0, KVQ_POLICY_PAPER, 0, 16, 8);
+    CHECK(wide.append(24 * 32, 16) == KVQ_OK && wide.attend() == KVQ_OK && wide.attend() == KVQ_OK && last.n_splits == 2, "%d splits", last.n_splits);
+    Cache one(256, 40, 0);
+    CHECK(one.append(32000, 2) == KVQ_OK && one.attend() == KVQ_OK && last.n_splits == 63, "%d splits", last.n_splits);
     // a step on top of 640 tokens of 2 bits and 33 of 16 bits, as the library splits it by itself
     Cache a(64, 64, 0, KVQ_POLICY_PAPER, 64);
     CHECK(a.append(640, 2) == KVQ_OK && a.append(33, 16) == KVQ_OK && a.step() == KVQ_OK && last.app_t_old == 673, "step");
@@ -327,7 +336,8 @@ void batch_shares() {
                 time += (uint64_t)nt * (uint64_t)weight[segs[k].bits == 16 ? 3 : segs[k].bits == 8 ? 2 : segs[k].bits == 4 ? 1 : 0];
             }
             cost.push_back(time);
-            most.push_back(tiles <= 20 ? 1 : std::min(std::min(tiles, 128), (int)std::sqrt((double)time / 80.0)));
+            const int alone = std::min((tiles + 15) / 16, 128 / caches[(size_t)i]->cfg.n_kv_heads);  // (one query head per KV head)
+            most.push_back(tiles <= 20 ? 1 : std::min(std::min(tiles, 128), std::max(alone, (int)std::sqrt((double)time / 80.0))));
             used += caches[(size_t)i]->cfg.n_kv_heads;
         }
         if (cost.empty()) continue;
