@@ -90,6 +90,7 @@ struct NewRows {
     __device__ bool has(int tok) const { return (uint32_t)(tok - t_old) < (uint32_t)n_new; }
     __device__ bool all(int tok0) const { return tok0 >= t_old && tok0 + KVQ_TILE_TOKENS <= t_old + n_new; }  // of a tile
     __device__ u32x4 load(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0); }
+    __device__ uint16_t load_half(uint32_t off) const { return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0); }
     __device__ u32x4 load_stream(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 2); }
     // index of the token's table row; tokens that are not new get a row that exists
     __device__ uint64_t row(int tok) const { return (uint64_t)max(0, min(tok - t_old, n_new - 1)); }
@@ -161,13 +162,29 @@ __device__ inline void append16_k_tile(uint8_t* code, const NewRows& rows, int t
         __builtin_nontemporal_store(v[c >> 2][c & 3], reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16));
 }
 
-// The same for a V tile, through LDS: the rows are read with 16-byte loads (a wavefront instruction covers one contiguous KiB
-// of the input), parked as [token][channel] and picked up in the tile layout (lane (j, n): tokens 8j .. 8j+7 of channels
-// 16 nt + n).  Rows are rotated by 32 bytes per 8 tokens so that the four lane quarters, which read rows 8 apart, use
-// different banks.  lds: 8 KiB of this wavefront alone, 16-byte aligned.  stream (wavefront-uniform): read the rows with
-// streaming loads, which pass the caches by.
+// The same for a V tile.  A tile of new tokens only goes through LDS: the rows are read with 16-byte loads (a wavefront
+// instruction covers one contiguous KiB of the input), parked as [token][channel] and picked up in the tile layout (lane (j,
+// n): tokens 8j .. 8j+7 of channels 16 nt + n).  Rows are rotated by 32 bytes per 8 tokens so that the four lane quarters,
+// which read rows 8 apart, use different banks.  lds: 8 KiB of this wavefront alone, 16-byte aligned.  stream
+// (wavefront-uniform): read the rows with streaming loads, which pass the caches by.
+// A tile that holds older tokens gets the new ones' values one by one, straight from the input: there are few as a rule, one
+// in a decode step, and the trip through LDS only makes the chain longer (kernel of 1 / 8 / 24 tokens x 8 units 2.6 / 3.3 / 3.6
+// us, through LDS 4.7 / 4.8 / 4.6; 1 / 8 / 24 x 600 units 3.0 / 4.6 / 7.2 and 5.1 / 5.2 / 8.0).
 __device__ inline void append16_v_tile(uint8_t* code, const NewRows& rows, int tok0, int lane, uint8_t* lds, bool stream) {
     const int j = lane >> 4, n = lane & 15;
+    if (tok0 < rows.t_old) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (rows.has(tok0 + 8 * j + i)) {
+                const uint32_t off = rows.offset(tok0 + 8 * j + i) + 2u * n;
+                uint16_t x[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) x[c] = rows.load_half(off + 32u * c);
+#pragma unroll
+                for (int c = 0; c < 8; ++c) *reinterpret_cast<uint16_t*>(code + (c * 64 + lane) * 16 + 2 * i) = x[c];
+            }
+        return;
+    }
     u32x4 v[8];
     if (stream) {
 #pragma unroll
@@ -184,7 +201,6 @@ __device__ inline void append16_v_tile(uint8_t* code, const NewRows& rows, int t
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const bool has_old = tok0 < rows.t_old;  // then only the new tokens' values are stored
 #pragma unroll
     for (int c = 0; c < 8; ++c) {  // chunk c of the lane's string = channel block nt = c, tokens 8j + 0..7
         uint32_t w[4];
@@ -196,15 +212,7 @@ __device__ inline void append16_v_tile(uint8_t* code, const NewRows& rows, int t
             const uint32_t hi = *reinterpret_cast<const uint16_t*>(lds + r1 * 256 + col);
             w[e] = lo | (hi << 16);
         }
-        uint8_t* dst = code + (c * 64 + lane) * 16;
-        if (!has_old) {
-            __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(dst));
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (rows.has(tok0 + 8 * j + i))
-                    *reinterpret_cast<uint16_t*>(dst + 2 * i) = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
-        }
+        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16));
     }
 }
 
