@@ -787,18 +787,26 @@ struct AttnShared {
 #define KVQ_STAMP(k) do { } while (0)
 #define KVQ_STAMP_ID() do { } while (0)
 #endif
-// Maximum / sum over the 32 lanes of a half wavefront, in every lane, in a fixed order: four steps inside a row of 16 lanes
-// as data-parallel moves (a shuffle through LDS costs several times their latency), the step across rows as a swizzle.
-template <bool SUM>
-__device__ inline float reduce32(float x) {
-    const auto step = [](float a, float b) { return SUM ? a + b : fmaxf(a, b); };
+// Reductions over 16 or 32 neighbouring lanes, in every lane, in a fixed order: four steps inside a row of 16 lanes as
+// data-parallel moves (a shuffle through LDS costs several times their latency), the step across rows as a swizzle.
+struct Sum { __device__ float operator()(float a, float b) const { return a + b; } };
+struct Max { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+struct Min { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
+template <class Step>
+__device__ inline float reduce16(float x) {
+    const Step step;
 #define KVQ_DPP(ctrl) __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), ctrl, 0xf, 0xf, true))
     x = step(x, KVQ_DPP(0xB1));   // quad_perm 1 0 3 2
     x = step(x, KVQ_DPP(0x4E));   // quad_perm 2 3 0 1
     x = step(x, KVQ_DPP(0x141));  // row_half_mirror
     x = step(x, KVQ_DPP(0x140));  // row_mirror
 #undef KVQ_DPP
-    return step(x, __uint_as_float((uint32_t)__builtin_amdgcn_ds_swizzle((int)__float_as_uint(x), 0x401F)));  // lane ^ 16
+    return x;
+}
+template <class Step>
+__device__ inline float reduce32(float x) {
+    x = reduce16<Step>(x);
+    return Step()(x, __uint_as_float((uint32_t)__builtin_amdgcn_ds_swizzle((int)__float_as_uint(x), 0x401F)));  // lane ^ 16
 }
 
 #define KVQ_MERGE_LDS_FLOATS ((KVQ_ATTN_THREADS / 32) * (KVQ_MAX_SPLITS + 32 * 4))
@@ -855,7 +863,7 @@ __device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, flo
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         if (d4 + 32 * k < ns) m = fmaxf(m, __uint_as_float(ml[k].x));
-    m = reduce32<false>(m);
+    m = reduce32<Max>(m);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         if (d4 + 32 * k < ns) {
@@ -865,7 +873,7 @@ __device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, flo
             l = fmaf(__uint_as_float(ml[k].y), f, l);
         }
     }
-    l = reduce32<true>(l);
+    l = reduce32<Sum>(l);
     wave_lds_sync();  // a slot lies in one wavefront
     // ---- weighted sum of this thread's splits (further rounds, eight loads at a time, only beyond 16 * G splits)
     float4v acc = {0.f, 0.f, 0.f, 0.f};
@@ -933,8 +941,8 @@ __device__ inline void stage_new_token(const KvqAttnHead& P, AttnShared& sh, int
     }
     float x0 = mixf(w, 0), x1 = mixf(w, 1);
     if constexpr (I16) {
-        float mn = fminf(x0, x1), mx = fmaxf(x0, x1);
-        for (int o = 1; o < 16 * P.app_gspan; o <<= 1) {  // a group of 32, 64 or 128 channels is 16, 32 or 64 lanes
+        float mn = reduce16<Min>(fminf(x0, x1)), mx = reduce16<Max>(fmaxf(x0, x1));
+        for (int o = 16; o < 16 * P.app_gspan; o <<= 1) {  // a group of 32, 64 or 128 channels is 16, 32 or 64 lanes
             mn = fminf(mn, __shfl_xor(mn, o));
             mx = fmaxf(mx, __shfl_xor(mx, o));
         }
@@ -960,8 +968,7 @@ __device__ inline void score_new_token(AttnShared& sh, float scale_log2, int wav
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) s = fmaf((float)q[i], k[i], s);
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) s += __shfl_xor(s, o);
+    s = reduce32<Sum>(s);
     if ((lane & 31) == 0) sh.new_score[head] = s * scale_log2;
 }
 
