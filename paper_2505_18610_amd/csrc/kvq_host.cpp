@@ -801,11 +801,19 @@ TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
 // A unit or two by themselves take one split per 16 tiles if that is more, as long as half of the compute units stay idle
 // (max_wgs / 2) and the merge issues all its loads in one round: 1,000 tiles of 2 bits and 4 query heads per KV head 13.2 us
 // with 63 splits and 14.8 with 35 in one unit, 13.5 and 14.6 in two, 15.2 and 14.9 in four.
+// More than eight query heads per KV head leave the merge one slot group, which loads 16 splits a round: beyond 16 splits a
+// range of such a unit keeps 16 tiles (16 heads: 256 tiles of 16 bits x 8 units 14.3 us with 16 splits and 15.7 with 31, 500 tiles x
+// one unit 13.9 with 32 and 14.8 with 43).  A count a little above the 16 of every slot group, which cost one round of the
+// merge's loads, is brought down to it (4 heads, 1,500 tiles of 8 bits x 3 units 15.7 us with 64 splits and 16.3 with 68; 8 heads,
+// 1,000 tiles of 2 bits 14.9 with 32 and 15.8 with 35).
 int useful_splits(const kvq_cache_t* c, uint64_t time, int n_tiles, int max_wgs) {
     if (n_tiles <= 20) return 1;
-    const int one_round = 16 * std::max(1, 16 / c->gqa);
-    const int alone = std::min(std::min((n_tiles + 15) / 16, one_round), max_wgs / 2 / c->units);
-    return std::max(1, std::min(std::min(n_tiles, KVQ_MAX_SPLITS), std::max(alone, (int)std::sqrt((double)time / 80.0))));
+    const int groups = std::max(1, 16 / c->gqa), per16 = (n_tiles + 15) / 16;
+    const int alone = std::min(std::min(per16, 16 * groups), max_wgs / 2 / c->units);
+    int n = std::max(alone, (int)std::sqrt((double)time / 80.0));
+    if (groups == 1) n = std::min(n, std::max(16, per16));
+    if (n > 16 * groups && n <= 20 * groups) n = 16 * groups;
+    return std::max(1, std::min(n, std::min(n_tiles, KVQ_MAX_SPLITS)));
 }
 
 int tiles_of(int n_tokens) { return (n_tokens + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS; }

@@ -141,8 +141,8 @@ struct Cache {
     kvq_config_t cfg{};
     uint8_t* arena = nullptr;
     // supers: allocation blocks of 16 units (a page of raw 16-bit tokens takes 16 units, metadata one)
-    Cache(int page_tokens, int supers, int tier16, int policy = KVQ_POLICY_PAPER, int window = 0, int batch = 1, int kv = 1) {
-        cfg.n_layers = 1; cfg.batch = batch; cfg.n_kv_heads = kv; cfg.n_q_heads = kv; cfg.head_dim = 128; cfg.group = 32;
+    Cache(int page_tokens, int supers, int tier16, int policy = KVQ_POLICY_PAPER, int window = 0, int batch = 1, int kv = 1, int heads = 1) {
+        cfg.n_layers = 1; cfg.batch = batch; cfg.n_kv_heads = kv; cfg.n_q_heads = kv * heads; cfg.head_dim = 128; cfg.group = 32;
         cfg.max_tokens = 1 << 18; cfg.page_tokens = page_tokens; cfg.policy = policy; cfg.window = window;
         const uint64_t budget = 1ull << 50;
         const uint8_t fbit = 2;
@@ -266,6 +266,10 @@ void split_plans() {
     CHECK(wide.append(24 * 32, 16) == KVQ_OK && wide.attend() == KVQ_OK && wide.attend() == KVQ_OK && last.n_splits == 2, "%d splits", last.n_splits);
     Cache one(256, 40, 0);
     CHECK(one.append(32000, 2) == KVQ_OK && one.attend() == KVQ_OK && last.n_splits == 63, "%d splits", last.n_splits);
+    for (int tokens : {256 * 32, 500 * 32}) {  // 16 query heads per KV head
+        Cache heads(256, 70, 0, KVQ_POLICY_PAPER, 0, 1, 1, 16);
+        CHECK(heads.append(tokens, 16) == KVQ_OK && heads.attend() == KVQ_OK && last.n_splits == (tokens + 511) / 512, "%d splits", last.n_splits);
+    }
     // a step on top of 640 tokens of 2 bits and 33 of 16 bits, as the library splits it by itself
     Cache a(64, 64, 0, KVQ_POLICY_PAPER, 64);
     CHECK(a.append(640, 2) == KVQ_OK && a.append(33, 16) == KVQ_OK && a.step() == KVQ_OK && last.app_t_old == 673, "step");
