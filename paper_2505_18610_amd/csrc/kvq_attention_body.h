@@ -817,9 +817,10 @@ __device__ inline float reduce32(float x) {
 // What bounds it is latency: one workgroup per unit, a trip to memory and what depends on it.  Every load is issued before
 // the first wait, and every slot works out the weights of its head's splits by itself from the pairs, which arrive
 // first (a lane takes up to four splits; maximum and denominator are half-wavefront reductions), so that no barrier
-// stands between the loads and the sum; one barrier combines the slot groups.  From the ticket to the stored output 2.15 us
-// with 8 splits, 2.6 with 24 (2.4 and 3.1 with the pairs and the weights passed through LDS behind barriers): 0.2 until the
-// loads are out, 1.0 until maximum and denominator are known, 0.5 for the sum, 0.6 to combine and store.
+// stands between the loads and the sum; one barrier combines the slot groups.  From the ticket to the stored output 2.0 us
+// with 7 or 8 splits, 2.3 with 17 of 4 heads, 2.6 with 24 of 5, 3.0 with 23 of 7 (2.4 with 8 and 3.1 with 24 of 5 with the pairs and
+// the weights passed through LDS behind barriers): 0.2 until the loads are out, 1.0 until maximum and denominator are known,
+// 0.5 for the sum, 0.6 to combine and store.
 // lds: KVQ_MERGE_LDS_FLOATS floats.  Call it with the whole workgroup.
 template <bool AGENT>
 __device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, float* lds) {

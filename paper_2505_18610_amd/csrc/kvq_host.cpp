@@ -837,7 +837,10 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
         // issue and want every unit) or the launch is short (what counts is the length of one range: 8K tokens x 32 units
         // of 4 bits, 43 MB, 15.1 us on all units and 16.5 on three quarters; of 8 bits, 75 MB, 18.5 and 19.1).  A longer
         // launch over wider tiles is bound by HBM, and there three quarters of the units stream measurably faster than all of them
-        // (16-bit blocks of 87 to 160 MB 3 to 4 %, 4-, 8- and 16-bit blocks of 350 MB and more 4 to 7 %).
+        // (16-bit blocks of 87 to 160 MB 3 to 4 %, 4-, 8- and 16-bit blocks of 350 MB and more 4 to 7 %).  Not every block
+        // gains: 32,256 tokens of 8 bits x 16 units (153 MB) take 30.7 us with the 12 splits this gives, 29.6 with 10 or 16
+        // and 28.6 with 14, and 8,192 of 16 bits x 16 units (67 MB) 16.1 with 12 or 16: how the ranges divide into rounds of
+        // eight tiles weighs as much there.
         const TileCensus t = tile_census(c, L, n_tiles);
         int wgs = c->target_workgroups;
         if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);

@@ -66,7 +66,11 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ 
 // PAIR: two wavefronts per string, one for each 16 tokens, two strings per workgroup.  A launch of one or two strings per
 // SIMD (1,024 of them) leaves each alone with some 1,000 to 1,700 vector instructions; shared by two it ends earlier.  Rotated
 // keys, one wavefront against two: 256 strings 6.3 and 5.1 us, 1,024 7.4 and 7.2, 1,536 9.0 and 8.4, 2,560 12.8 and 11.5;
-// from 3,072 on (13.0 and 13.0; 4,096: 15.8 and 17.2) the SIMDs have enough to interleave, so the line is at 2,560.
+// from 3,072 on (13.0 and 13.0; 4,096: 15.8 and 17.2) the SIMDs have enough to interleave, so the line is at 2,560.  Keys that
+// need no preparation, calls in a train, into 8 / 4 / 2 bits: 512 strings and fewer the same (the calls take longer than the
+// kernels), 1,024 4.9 / 4.8 / 4.8 us with one and 4.8 / 4.7 / 4.7 with two, 1,536 6.0 / 6.1 / 6.0 and 5.7 / 5.9 / 5.6, 2,048 6.3 / 6.3
+// / 6.3 and 6.4 / 6.8 / 6.3, 2,560 7.9 / 7.8 / 7.9 and 7.1 / 7.7 / 7.1, 3,072 8.0 / 7.9 / 8.0 and 7.7 / 8.3 / 7.7, 4,096 9.6 / 9.6 / 9.8
+// and 9.7 / 9.8 / 9.1: the same line serves them.
 template <int B, bool PLAIN, bool PAIR>
 __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(uint8_t* __restrict__ arena,
                                                           KvqPageDesc* __restrict__ table,

@@ -34,6 +34,10 @@ SHAPES = {
     "14b-2": ([(32256, 2), (512, 16)], dict(B=8, Hq=40, Hkv=8, P=256)),
     "14b-4": ([(32256, 4), (512, 16)], dict(B=8, Hq=40, Hkv=8, P=256)),
     "14b-8": ([(32256, 8), (512, 16)], dict(B=8, Hq=40, Hkv=8, P=256)),
+    # short launches: 4 x 1,024 tokens of 2 units, 9,001 tokens of 4 units, 764 tokens of 8 units
+    "short-2": ([(1024, 2), (1024, 4), (1024, 8), (1024, 16)], dict(B=1, Hq=8, Hkv=2, P=256)),
+    "short-4": ([(8448, 4), (553, 16)], dict(B=1, Hq=28, Hkv=4, P=128)),
+    "short-8": ([(128, 16), (448, 4), (188, 16)], dict(B=1, Hq=40, Hkv=8, P=64)),
 }
 STAMPS = (("entry", 0), ("inputs staged", 1), ("own range done (wavefront 0)", 2), ("eight wavefronts joined", 6),
           ("wavefront partials merged", 3), ("partial published, ticket drawn", 4), ("split partials merged", 5))
