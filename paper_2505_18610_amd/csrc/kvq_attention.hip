@@ -39,7 +39,7 @@ __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_i16_kernel(con
 // Same thread count as the attention kernel, so both merge variants add in the same order.
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_merge_kernel(const KvqAttnParams P) {
     __shared__ float lds[KVQ_MERGE_LDS_FLOATS];
-    merge_splits<false>(P, blockIdx.x, threadIdx.x, lds);
+    merge_splits<false>(P, blockIdx.x, threadIdx.x, merge_lane(P, blockIdx.x, threadIdx.x), lds);
 }
 
 }  // namespace

@@ -175,6 +175,38 @@ __device__ inline void keep_loaded(const uint32_t (&w)[N]) {
 __device__ inline void keep_loaded(const u32x4& v) { asm volatile("" :: "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w)); }
 #endif
 
+// Reductions over 16, 32 or 64 neighbouring lanes, in every lane, in a fixed order: four steps inside a row of 16 lanes as
+// data-parallel moves, the steps across rows as swaps of rows between two registers (a shuffle through LDS costs several
+// times the latency of either).
+struct Sum { __device__ float operator()(float a, float b) const { return a + b; } };
+struct Max { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+struct Min { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
+struct RowPair { float even, odd; };
+// x of the rows 0 2 (even) and 1 3 (odd), each in both rows of a pair; x of the lower and upper 32 lanes, each in both halves
+__device__ inline RowPair swap_rows(float x) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return RowPair{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ inline RowPair swap_halves(float x) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return RowPair{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+template <class Step> __device__ inline float across_rows(float x) { const RowPair p = swap_rows(x); return Step()(p.even, p.odd); }
+template <class Step> __device__ inline float across_halves(float x) { const RowPair p = swap_halves(x); return Step()(p.even, p.odd); }
+template <class Step>
+__device__ inline float reduce16(float x) {
+    const Step step;
+#define KVQ_DPP(ctrl) __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), ctrl, 0xf, 0xf, true))
+    x = step(x, KVQ_DPP(0xB1));   // quad_perm 1 0 3 2
+    x = step(x, KVQ_DPP(0x4E));   // quad_perm 2 3 0 1
+    x = step(x, KVQ_DPP(0x141));  // row_half_mirror
+    x = step(x, KVQ_DPP(0x140));  // row_mirror
+#undef KVQ_DPP
+    return x;
+}
+template <class Step>
+__device__ inline float reduce32(float x) { return across_rows<Step>(reduce16<Step>(x)); }
+
 struct WaveState {
     float4v o[8];   // out^T accumulators: o[nt][i] = channel 16nt + 4j + i of head n (lane = 16j + n)
     float4v zl;     // quarter 0: zero-point sums of V groups 0..3; quarter 1, element 0: softmax denominator
@@ -219,8 +251,7 @@ __device__ inline void load_q_ops(QOps& Q, const _Float16* q_lds, int lane, int 
             Q.q[grp][v] = __builtin_bit_cast(uint32_t, h);
         }
         if (!Q.have_qsum) {  // sum of q over the group's 32 channels: 8 here, the rest in the other quarters
-            sum += __shfl_xor(sum, 16);
-            sum += __shfl_xor(sum, 32);
+            sum = across_halves<Sum>(across_rows<Sum>(sum));
             sum *= scale_log2;  // the zero-point term then needs no scaling after its MFMA
             _Float16 h = (_Float16)sum;
             _Float16 l = (_Float16)(sum - (float)h);
@@ -454,8 +485,7 @@ __device__ inline void softmax_stage(WaveState& st, float (&s)[TPI][2][4], const
 #pragma unroll
             for (int i = 0; i < 4; ++i) lmax = fmaxf(lmax, s[k][sub][i]);
     if (__any(lmax > st.m)) {
-        float tmax = fmaxf(lmax, __shfl_xor(lmax, 16));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+        const float tmax = across_halves<Max>(across_rows<Max>(lmax));
         // the exact maximum is the reference point: the dominant token then has p = 1 and p * S_v is exact
         float m_new = fmaxf(st.m, tmax);
         float alpha = (st.m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(st.m - m_new);
@@ -765,8 +795,8 @@ __device__ inline void run_chunks(WaveState& st, QOps& Q, const _Float16* q_lds,
 struct AttnShared {
     __attribute__((aligned(16))) _Float16 q[16 * KVQ_D];
     float red_o[KVQ_ATTN_WAVES][16 * KVQ_OPAD];  // partial outputs of the eight wavefronts
-    float red_m[KVQ_ATTN_WAVES][16];
-    float red_l[KVQ_ATTN_WAVES][16];
+    __attribute__((aligned(16))) float red_m[16][KVQ_ATTN_WAVES];  // per head: maxima and sums of the wavefronts
+    __attribute__((aligned(16))) float red_l[16][KVQ_ATTN_WAVES];
     int is_last;
     unsigned claim_ctr;
     u32x4 desc[KVQ_DESC_CACHE];
@@ -787,54 +817,100 @@ struct AttnShared {
 #define KVQ_STAMP(k) do { } while (0)
 #define KVQ_STAMP_ID() do { } while (0)
 #endif
-// Reductions over 16 or 32 neighbouring lanes, in every lane, in a fixed order: four steps inside a row of 16 lanes as
-// data-parallel moves (a shuffle through LDS costs several times their latency), the step across rows as a swizzle.
-struct Sum { __device__ float operator()(float a, float b) const { return a + b; } };
-struct Max { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
-struct Min { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
-template <class Step>
-__device__ inline float reduce16(float x) {
-    const Step step;
-#define KVQ_DPP(ctrl) __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), ctrl, 0xf, 0xf, true))
-    x = step(x, KVQ_DPP(0xB1));   // quad_perm 1 0 3 2
-    x = step(x, KVQ_DPP(0x4E));   // quad_perm 2 3 0 1
-    x = step(x, KVQ_DPP(0x141));  // row_half_mirror
-    x = step(x, KVQ_DPP(0x140));  // row_mirror
-#undef KVQ_DPP
-    return x;
-}
-template <class Step>
-__device__ inline float reduce32(float x) {
-    x = reduce16<Step>(x);
-    return Step()(x, __uint_as_float((uint32_t)__builtin_amdgcn_ds_swizzle((int)__float_as_uint(x), 0x401F)));  // lane ^ 16
-}
-
 #define KVQ_MERGE_LDS_FLOATS ((KVQ_ATTN_THREADS / 32) * (KVQ_MAX_SPLITS + 32 * 4))
 
 // Merge of the split partials of one unit by a workgroup of KVQ_ATTN_THREADS threads.  Threads work in 16 slots
 // of 32 (one head, 4 channels per thread); with fewer than 16 heads the splits of a head are dealt to several
 // slot groups.  Per split the partials hold (max, sum) pairs per head and the un-normalised output rows.
-// What bounds it is latency: one workgroup per unit, a trip to memory and what depends on it.  Every load is issued before
-// the first wait, and every slot works out the weights of its head's splits by itself from the pairs, which arrive
-// first (a lane takes up to four splits; maximum and denominator are half-wavefront reductions), so that no barrier
-// stands between the loads and the sum; one barrier combines the slot groups.  From the ticket to the stored output 2.0 us
-// with 7 or 8 splits, 2.3 with 17 of 4 heads, 2.6 with 24 of 5, 3.0 with 23 of 7 (2.4 with 8 and 3.1 with 24 of 5 with the pairs and
-// the weights passed through LDS behind barriers): 0.2 until the loads are out, 1.0 until maximum and denominator are known,
-// 0.5 for the sum, 0.6 to combine and store.
+// What bounds it is latency: one workgroup per unit, a trip to memory and what depends on it.  Offsets are worked out while
+// the ticket is on its way; every load is issued before the first wait, and every slot works out the weights of its head's
+// splits by itself from the pairs, which arrive first (a lane takes up to four splits; maximum and denominator are
+// half-wavefront reductions), so that no barrier stands between the loads and the sum; one barrier combines the slot groups.
+// The rounds of loads are straight code for each step of their number, and the weights are read together: a branch and an
+// LDS read of its own for each of 16 rounds took 0.8 us, the quotients that place a thread 0.3 us of what stood between the
+// ticket and the output.  Whole launches: 281 tiles x 4 units of 7 heads in 8 splits 14.7 -> 13.6 us, in 16 11.9 -> 10.6;
+// 1,024 tokens of each width x 2 units of 4 heads in 8 splits 12.3 -> 11.4.
 // lds: KVQ_MERGE_LDS_FLOATS floats.  Call it with the whole workgroup.
-template <bool AGENT>
-__device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, float* lds) {
-    const int g = P.gqa, ns = P.n_splits;
+// What a thread does in the merge, worked out while the arrival ticket is on its way.
+struct MergeLane {
+    int slot, head, sgi;    // slot, its head, its slot group (at or beyond P.merge_groups: idle)
+    uint32_t ml_off, o_off; // byte offsets of its first pair and of its first split's channels among the unit's partials
+    size_t out;             // element of the output
+};
+__device__ inline MergeLane merge_lane(const KvqAttnHead& P, int unit, int tid) {
     const int b = div_magic(unit, P.n_kv_heads, P.kv_magic), hk = unit - b * P.n_kv_heads;
-    float* rec_lds = lds + (KVQ_ATTN_THREADS / 32) * KVQ_MAX_SPLITS;  // [slot][32][4]
-    const int slots = KVQ_ATTN_THREADS >> 5;           // 16 >= g
-    const int G = max(1, min(slots / g, ns));          // slot groups sharing the splits of one head
-    const int slot = tid >> 5, d4 = tid & 31;
-    const int sgi = slot / g, head = slot - sgi * g;
-    const bool active = sgi < G;
-    float* const f_lds = lds + slot * KVQ_MAX_SPLITS;  // weights of this slot's head, per split
+    MergeLane t;
+    t.slot = tid >> 5;
+    t.sgi = (int)(((uint32_t)t.slot * P.gqa_magic) >> 16);
+    t.head = t.slot - t.sgi * P.gqa;
+    const bool active = t.sgi < P.merge_groups;
+    t.ml_off = active ? (uint32_t)((tid & 31) * 32 + 2 * t.head) * 4u : 0x80000000u;
+    t.o_off = active ? (uint32_t)((t.sgi * 16 + t.head) * KVQ_D + 4 * (tid & 31)) * 4u : 0x80000000u;
+    t.out = ((size_t)b * P.n_q_heads + hk * P.gqa + t.head) * KVQ_D + 4 * (tid & 31);
+    return t;
+}
+typedef float4v float4v_any __attribute__((aligned(4)));
+typedef half4 half4_any __attribute__((aligned(2)));
+
+// Up to K splits per slot group, all loads of the partial outputs first; what the code branches on is uniform.
+template <int K, int AUX>
+__device__ inline float4v merge_sum(const MergeLane& t, int d4, int ns, int groups, __amdgpu_buffer_rsrc_t slab, const u32x2 (&ml)[4],
+                                    float* f_lds, float* l_out) {
+    const uint32_t step = (uint32_t)groups * (16 * KVQ_D * 4);
+    float4v v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        v[k] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(slab, (int)(t.o_off + k * step), 0, AUX));
+    // ---- the head's common maximum, weights and denominator, by the slot's 32 lanes
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (32 * k < ns) m = d4 + 32 * k < ns ? fmaxf(m, __uint_as_float(ml[k].x)) : m;
+    m = reduce32<Max>(m);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (32 * k < ns) {
+            const float ms = d4 + 32 * k < ns ? __uint_as_float(ml[k].x) : -INFINITY;
+            const float f = (ms == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms - m);
+            f_lds[d4 + 32 * k] = f;
+            l = fmaf(__uint_as_float(ml[k].y), f, l);
+        }
+    wave_lds_sync();  // a slot lies in one wavefront
+    // ---- weighted sum of this thread's splits (further rounds, eight loads at a time, only beyond 16 per slot group)
+    float w[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int sp = t.sgi + k * groups;
+        w[k] = f_lds[min(sp, KVQ_MAX_SPLITS - 1)];
+        w[k] = sp < ns ? w[k] : 0.f;
+    }
+    *l_out = reduce32<Sum>(l);
+    float4v acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc += v[k] * w[k];
+    if constexpr (K == 16) {
+        for (int k0 = K; t.sgi + k0 * groups < ns; k0 += 8) {
+            float4v x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                x[k] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(slab, (int)(t.o_off + (k0 + k) * step), 0, AUX));
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int sp = t.sgi + (k0 + k) * groups;
+                if (sp < ns) acc += x[k] * f_lds[sp];
+            }
+        }
+    }
+    return acc;
+}
+template <bool AGENT>
+__device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, const MergeLane& t, float* lds) {
+    const int g = P.gqa, ns = P.n_splits, groups = P.merge_groups, d4 = tid & 31;
+    float* const rec_lds = lds + (KVQ_ATTN_THREADS / 32) * KVQ_MAX_SPLITS;  // [slot][32][4]
+    float* const f_lds = lds + t.slot * KVQ_MAX_SPLITS;                     // weights of this slot's head, per split
     // The unit's pairs and partial outputs as buffers of ns splits: no branch per lane -- a split index beyond ns is out
-    // of range and reads zeros, and so does an idle thread, whose offset is put out of range.  AGENT: device-scope
+    // of range and reads zeros, and so does an idle thread, whose offset is put out of range (all of an offset goes through
+    // the vector operand: the scalar one takes no part in the range check).  AGENT: device-scope
     // loads (sc1).  A load instruction costs its issue slots whether or not it is in range (16 cycles of the compute unit
     // each), so their number follows the split count in steps.
     constexpr int AUX = AGENT ? 16 : 0;
@@ -842,76 +918,36 @@ __device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, flo
         P.part_ml + (size_t)unit * ns * 32, 0, ns * 32 * (int)sizeof(float), 0x00020000);
     const __amdgpu_buffer_rsrc_t slab = __builtin_amdgcn_make_buffer_rsrc(
         P.part_o + (size_t)unit * ns * 16 * KVQ_D, 0, ns * 16 * KVQ_D * (int)sizeof(float), 0x00020000);
-    u32x2 ml[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        ml[k] = u32x2{0u, 0u};
-        const uint32_t off = active ? (uint32_t)((d4 + 32 * k) * 32 + 2 * head) * 4u : 0x80000000u;
-        if (32 * k < ns) ml[k] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(pairs, (int)off, 0, AUX));
-    }
-    const int per_slot = (ns + G - 1) / G;             // splits per slot group
-    float4v v[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int sp = sgi + k * G;
-        const uint32_t off = active ? (uint32_t)((sp * 16 + head) * KVQ_D + 4 * d4) * 4u : 0x80000000u;
-        v[k] = float4v{0.f, 0.f, 0.f, 0.f};
-        if (k < 2 || (k < 4 && per_slot > 2) || (k < 8 && per_slot > 4) || per_slot > 8)
-            v[k] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(slab, (int)off, 0, AUX));
-    }
-    // ---- the head's common maximum, weights and denominator, by the slot's 32 lanes
-    float m = -INFINITY, l = 0.f;
+    u32x2 ml[4] = {};
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        if (d4 + 32 * k < ns) m = fmaxf(m, __uint_as_float(ml[k].x));
-    m = reduce32<Max>(m);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (d4 + 32 * k < ns) {
-            const float ms = __uint_as_float(ml[k].x);
-            const float f = (ms == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms - m);
-            f_lds[d4 + 32 * k] = f;
-            l = fmaf(__uint_as_float(ml[k].y), f, l);
-        }
-    }
-    l = reduce32<Sum>(l);
-    wave_lds_sync();  // a slot lies in one wavefront
-    // ---- weighted sum of this thread's splits (further rounds, eight loads at a time, only beyond 16 * G splits)
-    float4v acc = {0.f, 0.f, 0.f, 0.f};
-    if (active) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int sp = sgi + k * G;
-            if (sp < ns) acc += v[k] * f_lds[sp];
-        }
-        for (int k0 = 16; k0 < per_slot; k0 += 8) {
-            float4v w[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                w[k] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(
-                    slab, (((sgi + (k0 + k) * G) * 16 + head) * KVQ_D + 4 * d4) * 4, 0, AUX));
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int sp = sgi + (k0 + k) * G;
-                if (sp < ns) acc += w[k] * f_lds[sp];
-            }
-        }
-    }
-    if (G > 1) {  // combine the slot groups in a fixed order
-        if (active && sgi > 0) *reinterpret_cast<float4v*>(rec_lds + (size_t)(slot * 32 + d4) * 4) = acc;
+        if (32 * k < ns) ml[k] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(pairs, (int)(t.ml_off + k * 32 * 32 * 4), 0, AUX));
+    float4v acc;
+    float l;
+    if (P.merge_rounds <= 2) acc = merge_sum<2, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    else if (P.merge_rounds <= 4) acc = merge_sum<4, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    else if (P.merge_rounds <= 8) acc = merge_sum<8, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    else acc = merge_sum<16, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    const float inv = 1.0f / l;
+    if (groups > 1) {  // combine the slot groups in a fixed order
+        if (t.sgi > 0 && t.sgi < groups) *reinterpret_cast<float4v*>(rec_lds + (size_t)(t.slot * 32 + d4) * 4) = acc;
         __syncthreads();
-        if (active && sgi == 0)
-            for (int k = 1; k < G; ++k) acc += *reinterpret_cast<const float4v*>(rec_lds + (size_t)((k * g + head) * 32 + d4) * 4);
-    }
-    if (active && sgi == 0) {
-        const float inv = 1.0f / l;
-        const size_t oi = ((size_t)b * P.n_q_heads + hk * g + head) * KVQ_D + 4 * d4;
+        if (t.sgi == 0) {
+            const float4v* rec = reinterpret_cast<const float4v*>(rec_lds + (size_t)((g + t.head) * 32 + d4) * 4);
+            float4v r[3];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float r = acc[i] * inv;
-            if (P.out_fp32) static_cast<float*>(P.out)[oi + i] = r;
-            else static_cast<_Float16*>(P.out)[oi + i] = (_Float16)r;
+            for (int k = 0; k < 3; ++k)
+                if (k + 1 < groups) r[k] = rec[(size_t)k * g * 32];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (k + 1 < groups) acc += r[k];
+            for (int k = 3; k + 1 < groups; ++k) acc += rec[(size_t)k * g * 32];
         }
+    }
+    if (t.sgi == 0) {
+        acc *= inv;
+        if (P.out_fp32) *reinterpret_cast<float4v_any*>(static_cast<float*>(P.out) + t.out) = acc;
+        else *reinterpret_cast<half4_any*>(static_cast<_Float16*>(P.out) + t.out) = half4{(_Float16)acc[0], (_Float16)acc[1], (_Float16)acc[2], (_Float16)acc[3]};
     }
 }
 
@@ -1025,7 +1061,8 @@ __device__ inline void store_new_token(const KvqAttnHead& P, const AttnShared& s
         }
     }
     if (P.app_page >= 0 && unit == 0 && !which && lane == 0)  // nobody reads this entry in this launch
-        const_cast<KvqPageDesc*>(P.table)[P.app_page] = P.app_desc;
+        reinterpret_cast<u32x4*>(const_cast<KvqPageDesc*>(P.table))[P.app_page] =
+            u32x4{P.app_desc.code_off256, P.app_desc.meta_off256, P.app_desc.bits, P.app_desc.int16};
     if (I16 && lane < 8) {  // S of the four groups, then Z
         const int g = lane & 3, z = lane >> 2;
         uint16_t* m = reinterpret_cast<uint16_t*>(meta + 512 * which + 256 * z);
@@ -1036,10 +1073,10 @@ __device__ inline void store_new_token(const KvqAttnHead& P, const AttnShared& s
 // End of a workgroup's range: merge of its eight wavefront partials through LDS, then either the output (one split),
 // the partial for the separate merge kernel, or the fused merge of the unit's split partials.
 template <bool I16, bool APPEND>
-__device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShared& sh, WaveState& st, int split, int unit) {
+__device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShared& sh, WaveState& st, int split, int unit,
+                                                 int tid) {
     // the thread index is taken afresh, opaque to the compiler: nothing derived from it stays in a register across
     // the streaming loop for the sake of this epilogue
-    int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane >> 4, n = lane & 15;
@@ -1049,9 +1086,11 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
 
     set_accumulator_exponent(st, 0);
     // ---- wavefront epilogue: add the zero-point term, fetch the denominator, leave the partial in LDS
-    const float l_w = __shfl(st.zl[0], 16 + n);
+    const RowPair zl0 = swap_rows(st.zl[0]);
+    const float l_w = swap_halves(zl0.odd).even;  // of lanes 16 .. 31
     {
-        const float z0 = __shfl(st.zl[0], n), z1 = __shfl(st.zl[1], n), z2 = __shfl(st.zl[2], n), z3 = __shfl(st.zl[3], n);
+        const float z0 = swap_halves(zl0.even).even, z1 = swap_halves(swap_rows(st.zl[1]).even).even,
+                    z2 = swap_halves(swap_rows(st.zl[2]).even).even, z3 = swap_halves(swap_rows(st.zl[3]).even).even;  // of lanes 0 .. 15
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             st.o[0][i] += z0; st.o[1][i] += z0;
@@ -1060,7 +1099,7 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
             st.o[6][i] += z3; st.o[7][i] += z3;
         }
     }
-    if (j == 0) { sh.red_m[wave][n] = st.m; sh.red_l[wave][n] = l_w; }
+    if (j == 0) { sh.red_m[n][wave] = st.m; sh.red_l[n][wave] = l_w; }
     if (n < g) {
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt)
@@ -1076,39 +1115,45 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
     const bool fused = !direct && P.fused_merge;
 
     // ---- merge the eight wavefront partials: thread t takes the pairs of elements t, t + 512 of the
-    // [head][64 channel pairs] block; common maximum, weights and a fixed-order sum, one pass over LDS
+    // [head][64 channel pairs] block; common maximum, weights and a fixed-order sum, one pass over LDS, all its reads first
+    // (what a thread beyond the block's pairs reads exists and is not used)
     const int n_pairs = g * (KVQ_D / 2);
     float2v acc[2], ml[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
+        acc[r] = ml[r] = float2v{0.f, 0.f};
+        if (r * KVQ_ATTN_THREADS >= n_pairs) continue;
         const int pr = tid + r * KVQ_ATTN_THREADS;
-        acc[r] = float2v{0.f, 0.f};
-        ml[r] = float2v{-INFINITY, 0.f};
-        if (pr < n_pairs) {
-            const int head = pr >> 6, d = 2 * (pr & 63);
-            float M = -INFINITY;
-            for (int w = 0; w < KVQ_ATTN_WAVES; ++w) M = fmaxf(M, sh.red_m[w][head]);
-            if (appends) M = fmaxf(M, sh.new_score[head]);
-            float2v a = {0.f, 0.f};
-            float L = 0.f;
-            for (int w = 0; w < KVQ_ATTN_WAVES; ++w) {
-                const float mw = sh.red_m[w][head];
-                const float f = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mw - M);
-                const float2v o2 = *reinterpret_cast<const float2v*>(&red_o[w][head * KVQ_OPAD + d]);
-                a[0] = fmaf(o2[0], f, a[0]);
-                a[1] = fmaf(o2[1], f, a[1]);
-                L = fmaf(sh.red_l[w][head], f, L);
-            }
-            if (appends) {
-                const float f = __builtin_amdgcn_exp2f(sh.new_score[head] - M);
-                const float2v v2 = *reinterpret_cast<const float2v*>(&sh.new_x[1][d]);
-                a[0] = fmaf(v2[0], f, a[0]);
-                a[1] = fmaf(v2[1], f, a[1]);
-                L += f;
-            }
-            acc[r] = a;
-            ml[r] = float2v{M, L};
+        const int head = pr >> 6, d = 2 * (pr & 63);
+        float4v mw[2], lw[2];
+        float2v o2[KVQ_ATTN_WAVES];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) mw[h] = reinterpret_cast<const float4v*>(sh.red_m[head])[h];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) lw[h] = reinterpret_cast<const float4v*>(sh.red_l[head])[h];
+#pragma unroll
+        for (int w = 0; w < KVQ_ATTN_WAVES; ++w) o2[w] = *reinterpret_cast<const float2v*>(&red_o[w][head * KVQ_OPAD + d]);
+        float M = fmaxf(fmaxf(fmaxf(mw[0][0], mw[0][1]), fmaxf(mw[0][2], mw[0][3])), fmaxf(fmaxf(mw[1][0], mw[1][1]), fmaxf(mw[1][2], mw[1][3])));
+        if (appends) M = fmaxf(M, sh.new_score[head]);
+        float2v a = {0.f, 0.f};
+        float L = 0.f;
+#pragma unroll
+        for (int w = 0; w < KVQ_ATTN_WAVES; ++w) {
+            const float x = mw[w >> 2][w & 3];
+            const float f = (x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(x - M);
+            a[0] = fmaf(o2[w][0], f, a[0]);
+            a[1] = fmaf(o2[w][1], f, a[1]);
+            L = fmaf(lw[w >> 2][w & 3], f, L);
         }
+        if (appends) {
+            const float f = __builtin_amdgcn_exp2f(sh.new_score[head] - M);
+            const float2v v2 = *reinterpret_cast<const float2v*>(&sh.new_x[1][d]);
+            a[0] = fmaf(v2[0], f, a[0]);
+            a[1] = fmaf(v2[1], f, a[1]);
+            L += f;
+        }
+        acc[r] = a;
+        ml[r] = float2v{M, L};
     }
     KVQ_STAMP(3);
     float* po = P.part_o + ((size_t)unit * ns + split) * 16 * KVQ_D;
@@ -1147,6 +1192,9 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
             __hip_atomic_store(reinterpret_cast<unsigned long long*>(pml + 2 * (pr >> 6)),
                                __builtin_bit_cast(unsigned long long, ml[r]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    MergeLane lane_of_merge = merge_lane(P, unit, tid);
+    asm volatile("" : "+v"(lane_of_merge.slot), "+v"(lane_of_merge.sgi), "+v"(lane_of_merge.head), "+v"(lane_of_merge.ml_off),
+                      "+v"(lane_of_merge.o_off), "+v"(lane_of_merge.out));  // not put off until the ticket is there
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     int& is_last = sh.is_last;
@@ -1157,7 +1205,7 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
     __syncthreads();
     KVQ_STAMP(4);
     if (!is_last) return;
-    merge_splits<true>(P, unit, tid, &sh.red_o[0][0]);
+    merge_splits<true>(P, unit, tid, lane_of_merge, &sh.red_o[0][0]);
     if (tid == 0) __hip_atomic_store(&P.counters[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     KVQ_STAMP(5);
 }
@@ -1291,7 +1339,7 @@ __device__ __forceinline__ void attention_body(const KvqAttnHead& P, const int t
     else stream_range<false, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
 
     KVQ_STAMP(2);
-    finish_workgroup<I16, APPEND>(P, sh, st, split, unit);
+    finish_workgroup<I16, APPEND>(P, sh, st, split, unit, (int)threadIdx.x);
 }
 
 }  // namespace

@@ -871,6 +871,9 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     p.n_kv_heads = c->cfg.n_kv_heads;
     p.kv_magic = p.n_kv_heads > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)p.n_kv_heads - 1) / (uint64_t)p.n_kv_heads) : 0u;
     p.n_splits = n_splits;
+    p.merge_groups = std::max(1, std::min(16 / c->gqa, n_splits));
+    p.merge_rounds = (n_splits + p.merge_groups - 1) / p.merge_groups;
+    p.gqa_magic = 65536u / (uint32_t)c->gqa + 1u;
     p.out_fp32 = out_is_fp32 ? 1 : 0;
     p.fused_merge = c->fused_merge;
     p.deterministic = c->deterministic;

@@ -60,6 +60,9 @@ struct KvqAttnHead {
     int32_t deterministic;     // 1: static chunk-to-wavefront assignment (bit-reproducible summation order)
     int32_t int16_tier;        // 1: 16-bit pages hold integer codes in byte planes (selects the kernel)
     float scale_log2;          // softmax scale * log2(e)
+    int32_t merge_groups;      // split merge: slot groups that share the splits of a head, splits of a group,
+    int32_t merge_rounds;
+    uint32_t gqa_magic;        // 65536 / gqa + 1
     // a one-token append into the 16-bit tier done by the workgroup of a unit's last split (app_t_old < 0: none)
     int32_t app_t_old;         // tokens before the append
     KvqPageDesc app_desc;      // page of the new token

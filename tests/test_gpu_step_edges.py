@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 # gqa g leaves 16 // g slot groups: 16 splits per group in the first round of loads, eight more in each further one; a lane
 # takes the (max, sum) pairs of four splits 32 apart
-@pytest.mark.parametrize("g", [1, 3, 7, 16])
+@pytest.mark.parametrize("g", [1, 3, 5, 7, 16])
 def test_merge_of_any_split_count(g):
     T, P = 128 * 32 - 5, 64
     oc, gc = make_pair(1, 1, 2 * g, 2, T, P)
@@ -27,6 +27,25 @@ def test_merge_of_any_split_count(g):
                 gc.kvq_cache_set_option(kq.KVQ_OPT_SPLITS, splits)
                 gc.kvq_cache_set_option(kq.KVQ_OPT_FUSED_MERGE, fused)
                 check_attention(oc, gc, 0, q)
+    gc.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("splits", [1, 7])
+def test_outputs_that_start_at_any_element(dtype, splits):
+    oc, gc = make_pair(1, 1, 10, 2, 480, 32)
+    K, V = kvq_synth.make_kv(74, 0, 1, 2, 0, 480)
+    append_both(oc, gc, 0, K, V, 8)
+    q = kvq_synth.make_q(74, 0, 1, 10, 479)
+    want = oc.attention(0, q)
+    gc.kvq_cache_set_option(kq.KVQ_OPT_SPLITS, splits)
+    for off in (0, 1, 2, 3):
+        buf = torch.full((q.size + 8,), -7.0, dtype=dtype, device="cuda")
+        out = buf[off:off + q.size].view(q.shape)
+        gc.kvq_decode_attention(0, dev(q), out)
+        ma, rel = attention_errors(out.float().cpu().numpy(), want)
+        assert ma <= MAX_ABS + (1e-3 if dtype == torch.float16 else 0.0) and rel <= REL_L2
+        assert (buf[:off] == -7.0).all() and (buf[off + q.size:] == -7.0).all()
     gc.close()
 
 
