@@ -1199,14 +1199,14 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
     __syncthreads();
     int& is_last = sh.is_last;
     if (tid == 0) {
-        const uint32_t old = __hip_atomic_fetch_add(&P.counters[unit], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t old = __hip_atomic_fetch_add(&P.counters[unit * KVQ_COUNTER_STRIDE], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         is_last = (old == (uint32_t)ns - 1u) ? 1 : 0;
     }
     __syncthreads();
     KVQ_STAMP(4);
     if (!is_last) return;
     merge_splits<true>(P, unit, tid, lane_of_merge, &sh.red_o[0][0]);
-    if (tid == 0) __hip_atomic_store(&P.counters[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) __hip_atomic_store(&P.counters[unit * KVQ_COUNTER_STRIDE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     KVQ_STAMP(5);
 }
 

@@ -177,7 +177,7 @@ Regions layout_regions(const kvq_config_t* c) {
     r.jobs_off = off;      off = align_up(off + max_pages * sizeof(KvqRequantJob), 256);
     r.part_o_off = off;    off = align_up(off + units * KVQ_MAX_SPLITS * 16 * KVQ_D * sizeof(float), 256);
     r.part_ml_off = off;   off = align_up(off + units * KVQ_MAX_SPLITS * 32 * sizeof(float), 256);
-    r.counters_off = off;  off = align_up(off + units * sizeof(uint32_t), 256);
+    r.counters_off = off;  off = align_up(off + units * KVQ_COUNTER_STRIDE * sizeof(uint32_t), 256);
     r.flags_off = off;     off = align_up(off + 64, 256);
     r.reparam_off = off;   off = align_up(off + (uint64_t)c->n_layers * 2 * c->n_kv_heads * KVQ_D * sizeof(float), 256);
     r.pages_off = align_up(off, 4096);
@@ -1079,7 +1079,7 @@ kvq_status_t kvq_decode_attention_static(kvq_cache_t* c, int32_t layer, const vo
     // start at zero (a kernel leaves them there, but a launch that failed half-way would not): a fill kernel, which a
     // caller may also capture into a graph.
     if (p.n_splits > 1 && p.fused_merge &&
-        kvq_launch_fill_u32(p.counters, 0u, (size_t)c->units, s) != hipSuccess)
+        kvq_launch_fill_u32(p.counters, 0u, (size_t)c->units * KVQ_COUNTER_STRIDE, s) != hipSuccess)
         return KVQ_E_HIP;
     return kvq_launch_attention(p, c->units, s) == hipSuccess ? KVQ_OK : KVQ_E_HIP;
 }

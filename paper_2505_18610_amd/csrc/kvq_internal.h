@@ -36,6 +36,11 @@ struct KvqJobArgs {
     KvqRequantJob jobs[KVQ_JOBS_BY_ARG];
 };
 
+// Every unit's arrival counter has 64 bytes of its own.  Tickets of workgroups that end at about the same time are atomics at
+// the device's point of coherence, which takes those on one line in turn, some 12 ns each: with the counters of all units
+// packed into one line 256 workgroups waited up to 3 us for theirs (2,560 tiles of 2 bits x 8 units in 32 splits 21.6 -> 19.5
+// us, 64 tiles of 4 bits x 8 units in 32 splits 9.7 -> 7.7; 128 and 256 bytes apart are no better than 64).
+#define KVQ_COUNTER_STRIDE 16  // in counters
 struct KvqAttnHead {
     const uint8_t* arena;
     const KvqPageDesc* table;  // this block's page table
@@ -44,7 +49,7 @@ struct KvqAttnHead {
     void* out;                 // [batch, n_q_heads, 128] fp16 or fp32
     float* part_o;             // [unit][split][16][128] un-normalised partial outputs
     float* part_ml;            // [unit][split][16] pairs (running max in log2 units, sum)
-    uint32_t* counters;        // [unit] arrival counters of the fused merge (kept at zero between launches)
+    uint32_t* counters;        // [unit * KVQ_COUNTER_STRIDE] arrival counters of the fused merge (kept at zero between launches)
     const uint32_t* v_mark;    // equal to v_epoch: some V scale of the cache is >= 256 (set by the quantizing kernels)
     uint32_t v_epoch;
     int32_t n_tokens;          // tokens read from the cache (without the one this launch appends)
@@ -126,12 +131,13 @@ struct KvqBatchMap {
 };
 
 // Static scratch of kvq_decode_attention_static (kvq_attention.hip): room for the partials of KVQ_STATIC_MAX_WGS
-// workgroups (units * splits of one launch) and the arrival counters of KVQ_STATIC_MAX_UNITS units.
+// workgroups (units * splits of one launch) and their arrival counters (a launch of more than one split per unit has at most
+// half as many units as workgroups).
 #define KVQ_STATIC_MAX_WGS 512
 #define KVQ_STATIC_MAX_UNITS 4096
 #define KVQ_STATIC_PART_O_BYTES ((size_t)KVQ_STATIC_MAX_WGS * 16 * KVQ_D * sizeof(float))
 #define KVQ_STATIC_PART_ML_BYTES ((size_t)KVQ_STATIC_MAX_WGS * 32 * sizeof(float))
-#define KVQ_STATIC_COUNTER_BYTES ((size_t)KVQ_STATIC_MAX_UNITS * sizeof(uint32_t))
+#define KVQ_STATIC_COUNTER_BYTES ((size_t)(KVQ_STATIC_MAX_WGS / 2) * KVQ_COUNTER_STRIDE * sizeof(uint32_t))
 #define KVQ_STATIC_SCRATCH_BYTES (KVQ_STATIC_PART_O_BYTES + KVQ_STATIC_PART_ML_BYTES + KVQ_STATIC_COUNTER_BYTES)
 // Device address of the scratch array on the current device (looked up once per device, no allocation).
 hipError_t kvq_static_scratch(unsigned char** ptr);

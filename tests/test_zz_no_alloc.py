@@ -81,3 +81,15 @@ def test_static_scratch_rejects_launches_beyond_its_size():
     torch.cuda.synchronize()
     mx, rl = attention_errors(out.cpu().numpy(), oc.attention(0, q))
     assert mx <= MAX_ABS and rl <= REL_L2, (mx, rl)
+
+
+def test_static_scratch_holds_the_counters_of_as_many_units_as_share_it():
+    oc, gc, q = _build(905, 32, 8, 8, 32, ((64, 8),))       # 256 units x 2 splits = 512 workgroups
+    gc.kvq_cache_set_option(kq.KVQ_OPT_SPLITS, 2)
+    gc.kvq_cache_set_option(kq.KVQ_OPT_DETERMINISTIC, 1)
+    want = oc.attention(0, q)
+    for _ in range(2):
+        a, b = _both(gc, q, 5.0)
+        assert np.array_equal(a, b)
+        mx, rl = attention_errors(b, want)
+        assert mx <= MAX_ABS and rl <= REL_L2, (mx, rl)
