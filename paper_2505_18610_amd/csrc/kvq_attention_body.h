@@ -849,8 +849,13 @@ __device__ inline MergeLane merge_lane(const KvqAttnHead& P, int unit, int tid) 
     t.out = ((size_t)b * P.n_q_heads + hk * P.gqa + t.head) * KVQ_D + 4 * (tid & 31);
     return t;
 }
+// Four channels of the output from element `at` on (outputs may start at any element).
 typedef float4v float4v_any __attribute__((aligned(4)));
 typedef half4 half4_any __attribute__((aligned(2)));
+__device__ inline void store_out(const KvqAttnHead& P, size_t at, float4v x) {
+    if (P.out_fp32) *reinterpret_cast<float4v_any*>(static_cast<float*>(P.out) + at) = x;
+    else *reinterpret_cast<half4_any*>(static_cast<_Float16*>(P.out) + at) = half4{(_Float16)x[0], (_Float16)x[1], (_Float16)x[2], (_Float16)x[3]};
+}
 
 // Up to K splits per slot group, all loads of the partial outputs first; what the code branches on is uniform.
 template <int K, int AUX>
@@ -944,11 +949,7 @@ __device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, con
             for (int k = 3; k + 1 < groups; ++k) acc += rec[(size_t)k * g * 32];
         }
     }
-    if (t.sgi == 0) {
-        acc *= inv;
-        if (P.out_fp32) *reinterpret_cast<float4v_any*>(static_cast<float*>(P.out) + t.out) = acc;
-        else *reinterpret_cast<half4_any*>(static_cast<_Float16*>(P.out) + t.out) = half4{(_Float16)acc[0], (_Float16)acc[1], (_Float16)acc[2], (_Float16)acc[3]};
-    }
+    if (t.sgi == 0) store_out(P, t.out, acc * inv);
 }
 
 static_assert(KVQ_ATTN_WAVES * 16 * KVQ_OPAD >= KVQ_MERGE_LDS_FLOATS, "the wavefront slab doubles as scratch of the split merge");
@@ -1084,20 +1085,18 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
     const int b = div_magic(unit, P.n_kv_heads, P.kv_magic), hk = unit - b * P.n_kv_heads;
     float (*const red_o)[16 * KVQ_OPAD] = sh.red_o;
 
-    set_accumulator_exponent(st, 0);
-    // ---- wavefront epilogue: add the zero-point term, fetch the denominator, leave the partial in LDS
+    // ---- wavefront epilogue: true values (the exponent taken off, an exact power of two) with the zero-point term added,
+    // denominator; the partial goes to LDS
     const RowPair zl0 = swap_rows(st.zl[0]);
     const float l_w = swap_halves(zl0.odd).even;  // of lanes 16 .. 31
     {
         const float z0 = swap_halves(zl0.even).even, z1 = swap_halves(swap_rows(st.zl[1]).even).even,
                     z2 = swap_halves(swap_rows(st.zl[2]).even).even, z3 = swap_halves(swap_rows(st.zl[3]).even).even;  // of lanes 0 .. 15
+        const float f = __builtin_ldexpf(1.0f, -st.oexp), z[4] = {z0, z1, z2, z3};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            st.o[0][i] += z0; st.o[1][i] += z0;
-            st.o[2][i] += z1; st.o[3][i] += z1;
-            st.o[4][i] += z2; st.o[5][i] += z2;
-            st.o[6][i] += z3; st.o[7][i] += z3;
-        }
+        for (int nt = 0; nt < 8; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st.o[nt][i] = fmaf(st.o[nt][i], f, z[nt >> 1]);
     }
     if (j == 0) { sh.red_m[n][wave] = st.m; sh.red_l[n][wave] = l_w; }
     if (n < g) {
@@ -1114,83 +1113,63 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
     const bool direct = (ns == 1);
     const bool fused = !direct && P.fused_merge;
 
-    // ---- merge the eight wavefront partials: thread t takes the pairs of elements t, t + 512 of the
-    // [head][64 channel pairs] block; common maximum, weights and a fixed-order sum, one pass over LDS, all its reads first
-    // (what a thread beyond the block's pairs reads exists and is not used)
-    const int n_pairs = g * (KVQ_D / 2);
-    float2v acc[2], ml[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        acc[r] = ml[r] = float2v{0.f, 0.f};
-        if (r * KVQ_ATTN_THREADS >= n_pairs) continue;
-        const int pr = tid + r * KVQ_ATTN_THREADS;
-        const int head = pr >> 6, d = 2 * (pr & 63);
-        float4v mw[2], lw[2];
-        float2v o2[KVQ_ATTN_WAVES];
+    // ---- merge the eight wavefront partials: thread t takes four channels of head t / 32; common maximum, weights and a
+    // fixed-order sum, one pass over LDS, all its reads first.  (Wavefronts whose two heads do not exist have nothing to do: with
+    // two channels a thread and two rounds beyond eight heads, twice the wavefronts shared the vector units with this.)
+    const int head = tid >> 5, d = 4 * (tid & 31);
+    float4v acc = {0.f, 0.f, 0.f, 0.f};
+    float M = -INFINITY, L = 0.f;
+    if (2 * wave < g) {
+        float4v mw[2], lw[2], o4[KVQ_ATTN_WAVES];
 #pragma unroll
         for (int h = 0; h < 2; ++h) mw[h] = reinterpret_cast<const float4v*>(sh.red_m[head])[h];
 #pragma unroll
         for (int h = 0; h < 2; ++h) lw[h] = reinterpret_cast<const float4v*>(sh.red_l[head])[h];
 #pragma unroll
-        for (int w = 0; w < KVQ_ATTN_WAVES; ++w) o2[w] = *reinterpret_cast<const float2v*>(&red_o[w][head * KVQ_OPAD + d]);
-        float M = fmaxf(fmaxf(fmaxf(mw[0][0], mw[0][1]), fmaxf(mw[0][2], mw[0][3])), fmaxf(fmaxf(mw[1][0], mw[1][1]), fmaxf(mw[1][2], mw[1][3])));
+        for (int w = 0; w < KVQ_ATTN_WAVES; ++w) o4[w] = *reinterpret_cast<const float4v*>(&red_o[w][head * KVQ_OPAD + d]);
+        M = fmaxf(fmaxf(fmaxf(mw[0][0], mw[0][1]), fmaxf(mw[0][2], mw[0][3])), fmaxf(fmaxf(mw[1][0], mw[1][1]), fmaxf(mw[1][2], mw[1][3])));
         if (appends) M = fmaxf(M, sh.new_score[head]);
-        float2v a = {0.f, 0.f};
-        float L = 0.f;
 #pragma unroll
         for (int w = 0; w < KVQ_ATTN_WAVES; ++w) {
             const float x = mw[w >> 2][w & 3];
             const float f = (x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(x - M);
-            a[0] = fmaf(o2[w][0], f, a[0]);
-            a[1] = fmaf(o2[w][1], f, a[1]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = fmaf(o4[w][i], f, acc[i]);
             L = fmaf(lw[w >> 2][w & 3], f, L);
         }
         if (appends) {
             const float f = __builtin_amdgcn_exp2f(sh.new_score[head] - M);
-            const float2v v2 = *reinterpret_cast<const float2v*>(&sh.new_x[1][d]);
-            a[0] = fmaf(v2[0], f, a[0]);
-            a[1] = fmaf(v2[1], f, a[1]);
+            const float4v v = *reinterpret_cast<const float4v*>(&sh.new_x[1][d]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = fmaf(v[i], f, acc[i]);
             L += f;
         }
-        acc[r] = a;
-        ml[r] = float2v{M, L};
     }
     KVQ_STAMP(3);
-    float* po = P.part_o + ((size_t)unit * ns + split) * 16 * KVQ_D;
-    float* pml = P.part_ml + ((size_t)unit * ns + split) * 32;
+    float* const po = P.part_o + ((size_t)unit * ns + split) * 16 * KVQ_D;
+    float* const pml = P.part_ml + ((size_t)unit * ns + split) * 32;
     if (!fused) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int pr = tid + r * KVQ_ATTN_THREADS;
-            if (pr >= n_pairs) continue;
-            const int head = pr >> 6, d = 2 * (pr & 63);
-            if (direct) {
-                const float inv = 1.0f / ml[r][1];
-                const float r0 = acc[r][0] * inv, r1 = acc[r][1] * inv;
-                const size_t oi = ((size_t)b * P.n_q_heads + hk * g + head) * KVQ_D + d;
-                if (P.out_fp32) *reinterpret_cast<float2v*>(static_cast<float*>(P.out) + oi) = float2v{r0, r1};
-                else *reinterpret_cast<half2v*>(static_cast<_Float16*>(P.out) + oi) = half2v{(_Float16)r0, (_Float16)r1};
-            } else {  // the merge kernel that follows reads these
-                *reinterpret_cast<float2v*>(po + 2 * pr) = acc[r];
-                if (d == 0) *reinterpret_cast<float2v*>(pml + 2 * head) = ml[r];
-            }
+        if (head >= g) return;
+        if (direct) {
+            store_out(P, ((size_t)b * P.n_q_heads + hk * g + head) * KVQ_D + d, acc * (1.0f / L));
+        } else {  // the merge kernel that follows reads these
+            *reinterpret_cast<float4v*>(po + 4 * tid) = acc;
+            if (d == 0) *reinterpret_cast<float2v*>(pml + 2 * head) = float2v{M, L};
         }
         return;
     }
 
-    // ---- fused merge of the split partials: every workgroup publishes its partial with device-scope stores, waits
+    // ---- fused merge of the split partials: every workgroup publishes its partial with device-scope stores (sc1), waits
     // until they have been performed, and one thread bumps the unit's arrival counter (device-scope atomic); the
     // workgroup that draws the last ticket reads all partials back with device-scope loads and writes the output.
     // The counter is left at zero for the next launch.
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int pr = tid + r * KVQ_ATTN_THREADS;
-        if (pr >= n_pairs) continue;
-        __hip_atomic_store(reinterpret_cast<unsigned long long*>(po + 2 * pr), __builtin_bit_cast(unsigned long long, acc[r]),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((pr & 63) == 0)
-            __hip_atomic_store(reinterpret_cast<unsigned long long*>(pml + 2 * (pr >> 6)),
-                               __builtin_bit_cast(unsigned long long, ml[r]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (head < g) {
+        const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(po, 0, 16 * KVQ_D * (int)sizeof(float), 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc), to, 16 * tid, 0, 16);
+        if (d == 0) {
+            const __amdgpu_buffer_rsrc_t pair = __builtin_amdgcn_make_buffer_rsrc(pml, 0, 32 * (int)sizeof(float), 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, float2v{M, L}), pair, 8 * head, 0, 16);
+        }
     }
     MergeLane lane_of_merge = merge_lane(P, unit, tid);
     asm volatile("" : "+v"(lane_of_merge.slot), "+v"(lane_of_merge.sgi), "+v"(lane_of_merge.head), "+v"(lane_of_merge.ml_off),
