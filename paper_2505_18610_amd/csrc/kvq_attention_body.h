@@ -460,9 +460,10 @@ __device__ inline void accumulate_tile(WaveState& st, const uint32_t (&vw)[2 * c
 // Online softmax over the TPI*32 scores of a stage (log2 domain).  The running maximum st.m is equal in the
 // four lane quarters of a head column; the cross-quarter reduction and the rescaling of the accumulators run
 // only when some lane sees a score above it, which becomes rare after the first tiles.
+// fresh (wavefront-uniform): nothing has been accumulated yet, there is nothing to rescale.
 template <int B, int TPI>
 __device__ inline void softmax_stage(WaveState& st, float (&s)[TPI][2][4], const int (&tok0)[TPI], int n_tokens,
-                                     int lane, uint32_t (&pop)[TPI][4]) {
+                                     int lane, uint32_t (&pop)[TPI][4], const bool fresh = false) {
     const int j = lane >> 4;
     bool ragged = false;
 #pragma unroll
@@ -484,7 +485,9 @@ __device__ inline void softmax_stage(WaveState& st, float (&s)[TPI][2][4], const
         for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
             for (int i = 0; i < 4; ++i) lmax = fmaxf(lmax, s[k][sub][i]);
-    if (__any(lmax > st.m)) {
+    if (fresh) {
+        st.m = across_halves<Max>(across_rows<Max>(lmax));
+    } else if (__any(lmax > st.m)) {
         const float tmax = across_halves<Max>(across_rows<Max>(lmax));
         // the exact maximum is the reference point: the dominant token then has p = 1 and p * S_v is exact
         float m_new = fmaxf(st.m, tmax);
@@ -932,6 +935,7 @@ __device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, con
     if (P.merge_rounds <= 2) acc = merge_sum<2, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
     else if (P.merge_rounds <= 4) acc = merge_sum<4, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
     else if (P.merge_rounds <= 8) acc = merge_sum<8, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    else if (P.merge_rounds <= 12) acc = merge_sum<12, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
     else acc = merge_sum<16, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
     const float inv = 1.0f / l;
     if (groups > 1) {  // combine the slot groups in a fixed order
@@ -1073,7 +1077,8 @@ __device__ inline void store_new_token(const KvqAttnHead& P, const AttnShared& s
 
 // End of a workgroup's range: merge of its eight wavefront partials through LDS, then either the output (one split),
 // the partial for the separate merge kernel, or the fused merge of the unit's split partials.
-template <bool I16, bool APPEND>
+// SCORED: the scores of an appended token are there already.
+template <bool I16, bool APPEND, bool SCORED = false>
 __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShared& sh, WaveState& st, int split, int unit,
                                                  int tid) {
     // the thread index is taken afresh, opaque to the compiler: nothing derived from it stays in a register across
@@ -1105,7 +1110,7 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
             *reinterpret_cast<float4v*>(&red_o[wave][n * KVQ_OPAD + 16 * nt + 4 * j]) = st.o[nt];
     }
     const bool appends = APPEND && P.app_t_old >= 0 && split == ns - 1;
-    if (appends) score_new_token(sh, P.scale_log2, wave, lane);  // here it hides in the wait for the slowest wavefront
+    if (appends && !SCORED) score_new_token(sh, P.scale_log2, wave, lane);  // here it hides in the wait for the slowest wavefront
     __syncthreads();  // the eight wavefronts of the workgroup have joined
     if (appends && wave < 2) store_new_token<I16>(P, sh, unit, wave, lane);
     KVQ_STAMP(6);

@@ -774,6 +774,7 @@ namespace {
 // the attention kernel (in units of kTileTime), how many of them are 2 bits wide, and the bytes of one (sequence, KV head).
 struct TileCensus {
     int n2 = 0, n_all = 0;
+    int narrowest = 0;  // the least time of a tile
     uint64_t cost = 0, time = 0, bytes = 0;
 };
 TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
@@ -783,6 +784,7 @@ TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
         if (nt <= 0) break;
         const int b = L.pages[i].bits;
         t.n_all += nt;
+        t.narrowest = t.narrowest ? std::min(t.narrowest, kTileTime[cost_index(b)]) : kTileTime[cost_index(b)];
         if (b == 2) t.n2 += nt;
         t.cost += (uint64_t)nt * (uint64_t)c->tile_cost[cost_index(b)];
         t.time += (uint64_t)nt * (uint64_t)kTileTime[cost_index(b)];
@@ -791,22 +793,53 @@ TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
     return t;
 }
 
-// Most splits of one (sequence, KV head) that pay.  A range of up to 20 tiles is left to one workgroup, whose eight
-// wavefronts take two or three tiles each: publishing and merging partials costs 2.5 us, more than halving such a range
-// saves (10 tiles: 6.9 us in one split, 8.7 at best in several; 20 tiles of 16 bits 9.1 and 9.0; 32 tiles 10.3 and 9.5).
-// Beyond that a split saves its share of the range's time (0.9 us per 1,000 units of kTileTime) and costs about 0.07 us of
-// the merge, which is least at sqrt(time / 80) splits: 24 tiles of mixed widths 9.3 us with 8 splits (11.0 with two of
-// 12 tiles, the former bound of 16 tiles per split), 79 tiles of 16 bits 10.6 us with 16 (11.9 with 5), 128 tiles of 2 bits
-// 10.8 us with 12 (11.5 with 8), 128K tokens of 2 bits 21.6 us with 64 and 22.9 with 128.
-// A unit or two by themselves take one split per 16 tiles if that is more, as long as half of the compute units stay idle
-// (max_wgs / 2) and the merge issues all its loads in one round: 1,000 tiles of 2 bits and 4 query heads per KV head 13.2 us
-// with 63 splits and 14.8 with 35 in one unit, 13.5 and 14.6 in two, 15.2 and 14.9 in four.
-// More than eight query heads per KV head leave the merge one slot group, which loads 16 splits a round: beyond 16 splits a
-// range of such a unit keeps 16 tiles (16 heads: 256 tiles of 16 bits x 8 units 14.3 us with 16 splits and 15.7 with 31, 500 tiles x
-// one unit 13.9 with 32 and 14.8 with 43).  A count a little above the 16 of every slot group, which cost one round of the
-// merge's loads, is brought down to it (4 heads, 1,500 tiles of 8 bits x 3 units 15.7 us with 64 splits and 16.3 with 68; 8 heads,
-// 1,000 tiles of 2 bits 14.9 with 32 and 15.8 with 35).
-int useful_splits(const kvq_cache_t* c, uint64_t time, int n_tiles, int max_wgs) {
+// Tiles of the longest of n ranges of the same time.
+uint64_t longest_range(const TileCensus& t, int n) {
+    const uint64_t per = (uint64_t)n * (uint64_t)std::max(t.narrowest, 1);
+    return std::min<uint64_t>((t.time + per - 1) / per, (uint64_t)t.n_all);
+}
+// Loads of partial outputs a thread of the split merge issues for n splits, in the steps that merge_splits has.
+int merge_loads(int gqa, int n) {
+    const int groups = std::max(1, std::min(16 / gqa, n)), rounds = (n + groups - 1) / groups;
+    for (int k : {2, 4, 8, 12, 16})
+        if (rounds <= k) return k;
+    return 16 + (rounds - 16 + 7) / 8 * 8;
+}
+// Splits of one (sequence, KV head) that take least, at most max_splits: as many as make ranges of some 4, 8, 16, ... tiles, or
+// max_splits.  A launch whose splits are short is a chain of latencies; what the split count changes of it, in us:
+//   the range    0.7 per 1,000 units of its tile time (what a compute unit needs to fetch and expand its tiles), and 0.8 for
+//                every eight tiles beyond the first (the wavefronts take another one)
+//   the merge    1.8 for publishing, ticket and the last workgroup's trip to memory, 0.02 per split (tickets on one counter come
+//                in turn), 0.06 per load a thread issues, 0.7 for every further round of eight beyond 16
+// Fitted to launches of 1, 2, 4, ... 128 units of 8 to 1,024 tiles at each width in 1 to 64 splits (5 query heads per KV head;
+// 320 launches): the choice is 1.1 % slower than the best count tried, 14 % at worst.  48 tiles of 4 bits x 8 units take 6.6 us in 12
+// splits, 7.2 in 8, 8.2 in 4; 128 tiles x 1 unit 7.2 in 32, 7.4 in 16, 8.3 in 8; 12 tiles of 4 bits 6.1 in one and 6.0 in three;
+// 16 query heads per KV head, 512 tiles of 16 bits x 1 unit 11.1 in 32, 12.7 in 48 and 14.3 in 16 or 64.
+int planned_splits(const kvq_cache* c, const TileCensus& t, int n_tiles, int max_splits) {
+    max_splits = std::max(1, std::min(max_splits, std::min(n_tiles, KVQ_MAX_SPLITS)));
+    int best = 1;
+    double least = 0.0;
+    for (int range : {0, 256, 128, 64, 32, 24, 16, 8, 4, 1}) {
+        int n = range ? std::max(1, (int)longest_range(t, range)) : 1;  // (the two are each other's quotient)
+        const bool most = range == 1 || n >= max_splits;
+        if (most) n = max_splits;
+        double us = 0.7e-3 * (double)t.time / n + 0.8 * ((int)(longest_range(t, n) + 7) / 8 - 1);
+        if (n > 1) {
+            const int loads = merge_loads(c->gqa, n);
+            us += 1.8 + 0.02 * n + 0.06 * loads + (loads > 16 ? 0.7 * ((loads - 16) / 8) : 0.0);
+        }
+        if (range == 0 || us < least) { least = us; best = n; }
+        if (most && range) break;
+    }
+    return best;
+}
+
+// Most splits of one (sequence, KV head) that pay in a batch, whose ranges are streamed whatever their length: none up to 20
+// tiles, beyond that sqrt(time / 80), or one per 16 tiles for a unit or two by themselves (max_wgs / 2) as long as the
+// merge issues all its loads in one round.  More than eight query heads per KV head leave the merge one slot group, which loads
+// 16 splits a round: beyond 16 splits a range of such a unit keeps 16 tiles.  A count a little above the 16 of every slot group,
+// which cost one round of the merge's loads, is brought down to it.
+int useful_batch_splits(const kvq_cache* c, uint64_t time, int n_tiles, int max_wgs) {
     if (n_tiles <= 20) return 1;
     const int groups = std::max(1, 16 / c->gqa), per16 = (n_tiles + 15) / 16;
     const int alone = std::min(std::min(per16, 16 * groups), max_wgs / 2 / c->units);
@@ -843,15 +876,20 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
         // eight tiles weighs as much there.
         const TileCensus t = tile_census(c, L, n_tiles);
         int wgs = c->target_workgroups;
-        if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs) wgs = std::max(c->units, wgs * 3 / 4);
-        n_splits = std::min(wgs / c->units, useful_splits(c, t.time, n_tiles, wgs));
-        // two halves of a range that one workgroup takes in a few rounds do not pay for the merge, unless they are long reads:
-        // 128 units x 21 tiles of 8 bits 9.3 us in one and 10.6 in two, x 28 10.6 and 11.5, x 22 of 16 bits (360 KB) 11.7 and
-        // 12.2; 86 units x 24 of 16 bits (393 KB) 11.3 and 11.0, x 32 13.9 and 12.2
+        // Where three quarters do not divide into the units, 128 of them, one workgroup a unit would leave half of the compute units
+        // idle: 48 tiles of 16 bits 17.4 us in two splits and 20.0 in one, 128 of 4 bits 18.7 and 23.0.
+        if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs && wgs * 3 / 4 / c->units * c->units * 8 >= wgs * 5)
+            wgs = wgs * 3 / 4;
+        n_splits = planned_splits(c, t, n_tiles, wgs / c->units);
+        // two halves of a range that one workgroup takes in a few rounds stay one, unless they are long reads: 128 units x 20 or 24
+        // tiles of 8, 4 or 2 bits take the same in one and in two, 24 of 16 bits (393 KB) 11.3 and 10.2 us
         if (n_splits == 2 && n_tiles <= 32 && t.bytes <= 375000) n_splits = 1;
     }
     n_splits = std::max(1, std::min(n_splits, std::min(KVQ_MAX_SPLITS, n_tiles)));
     plan_splits(c, L, n_tiles, n_splits);
+    int longest = 0;
+    for (int i = 0; i < n_splits; ++i) longest = std::max(longest, L.split_begin[i + 1] - L.split_begin[i]);
+    p.short_ranges = longest <= KVQ_SHORT_TILES ? 1 : 0;
 
     p.arena = c->arena;
     p.table = c->table_dev(layer);
@@ -985,7 +1023,7 @@ kvq_status_t batch_attention(kvq_cache_t* const* caches, int32_t n, int32_t laye
         if (L.T == 0) return KVQ_E_STATE;
         const int n_tiles = tiles_read(L, app[(size_t)i]);
         const TileCensus t = tile_census(c, L, n_tiles);
-        share[(size_t)i] = BatchShare{t.cost, c->units, useful_splits(c, t.time, n_tiles, c->target_workgroups), 1};
+        share[(size_t)i] = BatchShare{t.cost, c->units, useful_batch_splits(c, t.time, n_tiles, c->target_workgroups), 1};
     }
     deal_workgroups(share, caches[0]->target_workgroups);
     std::vector<KvqAttnParams> params((size_t)n);

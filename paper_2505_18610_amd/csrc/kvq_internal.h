@@ -63,6 +63,7 @@ struct KvqAttnHead {
     int32_t out_fp32;
     int32_t fused_merge;
     int32_t deterministic;     // 1: static chunk-to-wavefront assignment (bit-reproducible summation order)
+    int32_t short_ranges;      // 1: no range is longer than KVQ_SHORT_TILES (selects the kernel)
     int32_t int16_tier;        // 1: 16-bit pages hold integer codes in byte planes (selects the kernel)
     float scale_log2;          // softmax scale * log2(e)
     int32_t merge_groups;      // split merge: slot groups that share the splits of a head, splits of a group,
@@ -78,6 +79,12 @@ struct KvqAttnHead {
     const float* app_rinv;     // [n_kv_heads][128] reciprocal reparameterization factors, or null
     int32_t app_gspan;         // quantization group / 32 (integer 16-bit tier: the new token is quantized, Eq. 1-2)
 };
+// A launch none of whose ranges is longer takes the kernels for short ranges (kvq_attention_short.hip), two tiles to a
+// wavefront; beyond that the streaming kernels, which overlap the loads of later tiles with the arithmetic of earlier ones,
+// catch up: blocks in turn, 600 MB of them, ranges of 24 tiles of 4 bits x 64 units 13.5 us and 12.4 streaming, of 17 tiles of
+// 4 and 16 bits x 4 units 11.6 and 10.6, of 24 tiles of 16 bits x 64 units 20.3 and 21.1, of 32 tiles of 2 bits x 32 units 13.2 and
+// 12.6; ranges of 16 tiles: 4 bits x 8 units 8.6 and 9.6.
+#define KVQ_SHORT_TILES 16
 struct KvqAttnParams : KvqAttnHead {
     int32_t split_begin[KVQ_MAX_SPLITS + 1];  // tile index where each split starts
 };
@@ -144,6 +151,7 @@ hipError_t kvq_static_scratch(unsigned char** ptr);
 
 // kvq_attention.hip
 hipError_t kvq_launch_attention(const KvqAttnParams& p, int units, hipStream_t s);
+hipError_t kvq_launch_attention_short(const KvqAttnParams& p, int units, hipStream_t s);  // kernel only, no merge
 hipError_t kvq_launch_merge(const KvqAttnParams& p, int units, hipStream_t s);
 hipError_t kvq_launch_attention_i16_append(const KvqAttnParams& p, int units, hipStream_t s);  // kernel only, no merge
 // kvq_attention_batch.hip: the bare kernel launch kvq_launch_attention_batch wraps

@@ -2,7 +2,7 @@
 // the device wall clock (100 MHz) when thread 0 of a workgroup passes a numbered point, into a static device array
 // that kvq_phase_stamps_read copies out.  paper_2505_18610_amd/phase_table.py turns the stamps of launches inside
 // back-to-back trains into the per-phase table kept under profiles/.  The stamps cost about 1.5 us per launch.
-//   0 workgroup entry          1 q and page descriptors staged     2 thread 0's wavefront has finished its range
+//   0 workgroup entry          1 q and page descriptors staged (short ranges: page entries there)     2 thread 0's wavefront has finished its range
 //   6 all eight wavefronts joined                                   3 wavefront partials merged (LDS)
 //   4 partial published and arrival ticket drawn                    5 split partials merged (last workgroup of a unit)
 //   7 hardware ids: XCC_ID << 32 | HW_ID

@@ -123,7 +123,10 @@ def main(names):
         cache, arena, q, out = _build_cache(kq_s, torch, tiers, L=L, arena=arena, **kw)
         t_stamped = _train_us(torch, cache, q, out, L)
         lib = kq_s.load_library()
-        lib.kvq_phase_stamps_read.argtypes = [ctypes.c_void_p]
+        # the kernels for short ranges stamp an array of their own
+        readers = (lib.kvq_phase_stamps_read, lib.kvq_phase_stamps_read_short)
+        for read in readers:
+            read.argtypes = [ctypes.c_void_p]
         rows = {label: [] for label, _ in STAMPS}
         per_wg = {"range (staged -> own range done)": [], "wait for the other wavefronts": [], "LDS merge": [],
                   "publish + ticket": [], "merge of the splits (last workgroup)": []}
@@ -131,9 +134,12 @@ def main(names):
             for i in range(8 + rep % L):                      # a train; its last launch is the one read
                 cache.kvq_decode_attention(i % L, q, out)
             torch.cuda.synchronize()
-            buf = (ctypes.c_ulonglong * (1024 * 8))()
-            assert lib.kvq_phase_stamps_read(buf) == 0
-            a = np.frombuffer(buf, dtype=np.uint64).reshape(1024, 8).astype(np.int64)
+            stamps = []
+            for read in readers:
+                buf = (ctypes.c_ulonglong * (1024 * 8))()
+                assert read(buf) == 0
+                stamps.append(np.frombuffer(buf, dtype=np.uint64).reshape(1024, 8).astype(np.int64))
+            a = max(stamps, key=lambda x: x[:, 0].max())      # the launch was one kernel's
             a = a[a[:, 0] > a[:, 0].max() - 100000]           # this launch's workgroups (others: stale rows of earlier shapes)
             wgs = a.shape[0]
             t0 = a[:, 0].min()

@@ -30,6 +30,49 @@ def test_merge_of_any_split_count(g):
     gc.close()
 
 
+# 16 tiles a range is the most the kernels for short ranges take: one or two tiles a wavefront, of one width or two, of one page or
+# two neighbouring ones (pages of one and of three tiles), with and without queries scaled by factors and V scales of 256 and more
+@pytest.mark.parametrize("tier16", [0, 1])
+@pytest.mark.parametrize("page", [32, 96])
+@pytest.mark.parametrize("scaled", [False, True])
+def test_ranges_around_the_longest_short_one(page, tier16, scaled):
+    B, Hkv, g = 1, 2, 5
+    for tiles in (1, 2, 8, 9, 15, 16, 17, 33):
+        T = 32 * tiles - 7
+        oc, gc = make_pair(1, B, g * Hkv, Hkv, T + 40, page, policy=1, tier16=tier16)
+        if scaled:
+            lam = (1.0 + np.random.default_rng(5).random((Hkv, 128)) * 3.0).astype(np.float32)
+            oc.set_reparam(0, lam)
+            gc.kvq_cache_set_reparam(0, dev(lam))
+        K, V = kvq_synth.make_kv(75, 0, B, Hkv, 0, T + 40)
+        v_size = 600.0 if scaled else 1.0
+        V = (V.astype(np.float32) * v_size).astype(np.float16)
+        t = 0
+        for i in range(T // page):  # widths change from page to page, now and then not
+            append_both(oc, gc, 0, K[:, :, t:t + page], V[:, :, t:t + page], (2, 4, 4, 8, 16, 2, 2)[i % 7])
+            t += page
+        if t < T:
+            append_both(oc, gc, 0, K[:, :, t:T], V[:, :, t:T], 16)
+        q = kvq_synth.make_q(75, 0, B, g * Hkv, T - 1)
+        for splits in (1, 2, 3, 0):
+            if splits > tiles:
+                continue
+            gc.kvq_cache_set_option(kq.KVQ_OPT_SPLITS, splits)
+            out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+            gc.kvq_decode_attention(0, dev(q), out)
+            ma, rel = attention_errors(out.cpu().numpy(), oc.attention(0, q))
+            assert ma <= MAX_ABS * v_size and rel <= REL_L2, (tiles, splits)
+            for _ in range(2 if splits else 9):  # steps of one token, across tiles
+                k, v = K[:, :, T:T + 1], V[:, :, T:T + 1]
+                oc.append(0, k, v, 0)
+                gc.kvq_append_decode_attention(0, dev(k), dev(v), dev(q), out)
+                T += 1
+                ma, rel = attention_errors(out.cpu().numpy(), oc.attention(0, q))
+                assert ma <= MAX_ABS * v_size and rel <= REL_L2, (tiles, splits, T)
+        assert_same_cache(oc, gc, 0)
+        gc.close()
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("splits", [1, 7])
 def test_outputs_that_start_at_any_element(dtype, splits):
