@@ -11,6 +11,14 @@ namespace kvq_dev {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// Quotients by launch constants: n / d = mulhi(n, magic), magic = ceil(2^32 / d), exact for n < 2^22, d <= 2^10 and for
+// n, d < 2^16.  (A division of scalars is some thirty dependent instructions, several of which stood in front of the first load.)
+__device__ inline int div_magic(int n, int d, uint32_t magic) { return d == 1 ? n : (int)__umulhi((uint32_t)n, magic); }
+// Tells the compiler that a pointer which comes out of registers points to global memory: unlike a kernel argument's it
+// would be generic, every access a flat one, and behind flat loads every wait is a wait for all loads in flight.
+template <class T>
+__device__ inline T* as_global(T* p) { return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p; }
+
 __device__ inline float h2f(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
 __device__ inline uint16_t f2h_rn(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }  // RNE
 
@@ -96,7 +104,8 @@ struct NewRows {
     __device__ uint64_t row(int tok) const { return (uint64_t)max(0, min(tok - t_old, n_new - 1)); }
 };
 
-// One wavefront writes the new tokens that fall into one K tile of a 16-bit page.  code: the tile; tok0: its first token.
+// One wavefront writes the new tokens that fall into one K tile of a 16-bit page.  code_at: called behind the loads of the
+// rows, gives the tile's address; tok0: its first token.
 // A tile that holds no older token is written in full with streaming stores (it is read much later; slots of tokens that
 // are not there yet are zero, so partially filled tiles stay well defined); otherwise only the new tokens' 16-byte chunks
 // are stored.  rope: table of the new tokens, fp32 [n_new][128], or null; rinv_head: the 128 reciprocal reparameterization
@@ -104,7 +113,8 @@ struct NewRows {
 // A lane holds all four channel groups of its two tokens, so the rotation's partner channels are its own registers and
 // eight angles serve two groups; all loads are issued before the arithmetic.  (With the angles read one by one and the
 // partner read again, 8,192 new tokens x 32 units took 271 us with rotation against 56 without.)
-__device__ inline void append16_k_tile(uint8_t* code, const NewRows& rows, int tok0, int lane, const float* rope,
+template <class Code>
+__device__ inline void append16_k_tile(Code code_at, const NewRows& rows, int tok0, int lane, const float* rope,
                                        const float* rinv_head) {
     const int j = lane >> 4, n = lane & 15;
     u32x4 v[2][4];
@@ -117,14 +127,18 @@ __device__ inline void append16_k_tile(uint8_t* code, const NewRows& rows, int t
 #pragma unroll
         for (int grp = 0; grp < 4; ++grp) v[sub][grp] = rows.load(off + 64u * grp);
     }
+    Angles8 a[2][2];
     if (rope) {
-        Angles8 a[2][2];
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
             const float* row = rope + rows.row(tok0 + 8 * (n >> 2) + 4 * sub + (n & 3)) * KVQ_D;
 #pragma unroll
             for (int p = 0; p < 2; ++p) a[sub][p] = load_angles8(row, 32 * p + 8 * j);
         }
+    }
+    __builtin_amdgcn_sched_barrier(0);  // all of these loads first
+    uint8_t* const code = code_at();
+    if (rope) {
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
@@ -170,9 +184,11 @@ __device__ inline void append16_k_tile(uint8_t* code, const NewRows& rows, int t
 // A tile that holds older tokens gets the new ones' values one by one, straight from the input: there are few as a rule, one
 // in a decode step, and the trip through LDS only makes the chain longer (kernel of 1 / 8 / 24 tokens x 8 units 2.6 / 3.3 / 3.6
 // us, through LDS 4.7 / 4.8 / 4.6; 1 / 8 / 24 x 600 units 3.0 / 4.6 / 7.2 and 5.1 / 5.2 / 8.0).
-__device__ inline void append16_v_tile(uint8_t* code, const NewRows& rows, int tok0, int lane, uint8_t* lds, bool stream) {
+template <class Code>
+__device__ inline void append16_v_tile(Code code_at, const NewRows& rows, int tok0, int lane, uint8_t* lds, bool stream) {
     const int j = lane >> 4, n = lane & 15;
     if (tok0 < rows.t_old) {
+        uint8_t* const code = code_at();
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             if (rows.has(tok0 + 8 * j + i)) {
@@ -193,6 +209,8 @@ __device__ inline void append16_v_tile(uint8_t* code, const NewRows& rows, int t
 #pragma unroll
         for (int c = 0; c < 8; ++c) v[c] = rows.load(rows.offset(tok0 + 4 * c + j) + 16u * n);
     }
+    __builtin_amdgcn_sched_barrier(0);
+    uint8_t* const code = code_at();
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         const int tl = 4 * c + j;

@@ -12,10 +12,6 @@ constexpr int kHeadDwords = sizeof(KvqAttnHead) / 4, kBlockDwords = sizeof(KvqAt
 static_assert(kBlockDwords - kHeadDwords == KVQ_MAX_SPLITS + 1 + (KVQ_MAX_SPLITS + 1) % 2, "split_begin follows the head (padded to 8 bytes)");
 static_assert(kHeadDwords <= 64 && kBlockDwords <= KVQ_ATTN_THREADS && sizeof(KvqAttnHead) % 8 == 0, "one dword per lane, one per thread");
 struct HeadWords { uint32_t w[kHeadDwords]; };
-// Tells the compiler that a pointer which comes out of registers points to global memory: unlike a kernel argument's it
-// would be generic, every access a flat one, and behind flat loads every wait is a wait for all loads in flight.
-template <class T>
-__device__ inline T* as_global(T* p) { return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p; }
 
 template <bool I16>
 __device__ __forceinline__ void batch_body(const KvqAttnParams* __restrict__ params, const KvqBatchMap& map, AttnShared& sh,

@@ -562,9 +562,8 @@ __device__ inline void compute_stage(WaveState& st, const QOps& Q, const Stage<B
     if constexpr (B < 16) wave_lds_sync();
 }
 
-// Quotients by launch constants: n / d = mulhi(n, magic), magic = ceil(2^32 / d), exact for n < 2^22, d <= 2^10 and for
-// n, d < 2^16.  (A division of scalars is some thirty dependent instructions, several of which stood in front of the first load.)
-__device__ inline int div_magic(int n, int d, uint32_t magic) { return d == 1 ? n : (int)__umulhi((uint32_t)n, magic); }
+using kvq_dev::div_magic;
+using kvq_dev::as_global;
 
 // A claimed chunk, resolved to addresses; every member is wavefront-uniform (scalar registers).
 struct Claim {

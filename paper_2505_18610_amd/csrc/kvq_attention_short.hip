@@ -15,9 +15,6 @@
 
 namespace {
 
-template <class T>
-__device__ inline T* as_global(T* p) { return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p; }
-
 // The parameters, all read at once: left alone the compiler reads them one by one where they are used first, each a trip of
 // its own to the constant cache.  (A pointer that has gone through the registers of an asm is generic to the compiler, every
 // access a flat one, behind which every wait is a wait for all loads: hence as_global.)

@@ -11,6 +11,8 @@
 namespace {
 
 using namespace kvq_q;
+using kvq_dev::div_magic;
+using kvq_dev::as_global;
 
 // Work of the append kernels: one wavefront per string, a (tile, K | V) of one (sequence, KV head) unit; the WAVES
 // wavefronts of a workgroup take neighbouring strings of a unit and share nothing.  PLAIN instantiations serve keys that
@@ -18,44 +20,87 @@ using namespace kvq_q;
 // the bulk of the general kernels' registers.
 // by_unit: the units of a string follow one another in the grid instead of the strings of a unit.  The table rows of the
 // string's tokens, 512 bytes a token and as much as its keys and values in one unit, are then read by all units at about
-// the same time and come from the caches.  For the 16-bit tiers and at least 98,304 rows of all units together: 8,192
-// rotated tokens x 32 units 59 instead of 74 us (raw fp16), 78 instead of 88 (integer tier), 2,048 x 64 34 instead of 44 and
-// 48 instead of 52; 2,048 x 32 (65,536 rows) 22 instead of 21 and 32 instead of 30.  Into 8, 4 and 2 bits, where the
-// arithmetic weighs more, it loses 3 to 7 % at every size.
+// the same time and come from the caches.  For the 16-bit tiers and at least 98,304 rows of all units together.  Rotated keys,
+// raw fp16 / integer tier, with and without: 4,096 x 32 26.1 / 33.7 instead of 27.6 / 36.1 us, 2,048 x 64 26.2 / 33.8 and 29.0 /
+// 37.4, 2,048 x 48 (98,304 rows) 21.3 / 24.3 and 21.0 / 25.6; 2,048 x 32 (65,536) 15.3 / 18.9 and 15.5 / 18.1, 8,192 x 8 17.7 /
+// 21.8 and 15.2 / 19.4.  Into 8, 4 and 2 bits, where the arithmetic weighs more, it loses 3 to 7 % at every size.
+// What a launch's kernels need, read at once at their start: left alone the compiler reads the arguments one by one where they
+// are used first, each a trip to the constant cache or beyond, and three quotients and the lookup of the page entry stood in
+// front of the rows as well.  Now rows and angles are asked for first and the page entry behind them, needed only for the stores.
+// Kernel times before and after: 1,024 tokens x 16 units, rotated, into 8 / 4 bits 6.76 / 6.84 and 6.32 / 6.48 us; 2,500 x 8 at
+// 16 bits 6.88 and 6.64; 2,048 x 32, rotated and scaled, into 8 / 4 / 2 bits 15.4 / 15.0 / 14.9 and 13.3 / 13.3 / 13.1 and into the
+// integer tier 24.5 and 20.9; keys that need no preparation 1 to 3 % (64 units x 2,048 at 16 bits 21.8 and 22.1).
+struct AppendArgs {
+    uint8_t* arena;
+    KvqPageDesc* table;
+    const uint16_t *k, *v;
+    const float *rinv, *rope;
+    uint32_t* v_word;
+    int32_t t_old, n_new, tpp;
+    uint32_t tpp_magic;
+    int32_t tile0, n_strings, by_unit, n_kv_heads;
+    uint32_t kv_magic, v_epoch;
+    int32_t gspan;
+    int32_t stream_v;  // see append16_v_tile
+    KvqAppendPages pages;
+};
+struct AppendString {  // one wavefront's string
+    int which, unit, tile, page;
+    uint64_t tslot;
+    const float* rinv_head;
+};
+template <bool PLAIN>
+__device__ __forceinline__ void read_append_args(const AppendArgs& args, AppendArgs& A) {
+    uint8_t* arena = args.arena;
+    KvqPageDesc* table = args.table;
+    const uint16_t *k = args.k, *v = args.v;
+    const float *rinv = args.rinv, *rope = args.rope;
+    uint32_t* word = args.v_word;
+    A.t_old = args.t_old; A.n_new = args.n_new; A.tpp = args.tpp; A.tpp_magic = args.tpp_magic; A.tile0 = args.tile0;
+    A.n_strings = args.n_strings; A.by_unit = args.by_unit; A.n_kv_heads = args.n_kv_heads; A.kv_magic = args.kv_magic;
+    A.v_epoch = args.v_epoch; A.gspan = args.gspan; A.stream_v = args.stream_v;
+    asm volatile("" : "+s"(arena), "+s"(table), "+s"(k), "+s"(v), "+s"(word), "+s"(A.t_old), "+s"(A.n_new), "+s"(A.tpp), "+s"(A.tpp_magic),
+                      "+s"(A.tile0), "+s"(A.n_strings), "+s"(A.v_epoch), "+s"(A.gspan), "+s"(A.stream_v));
+    if constexpr (!PLAIN) asm volatile("" : "+s"(rinv), "+s"(rope), "+s"(A.by_unit), "+s"(A.n_kv_heads), "+s"(A.kv_magic));
+    A.arena = as_global(arena); A.table = as_global(table); A.k = as_global(k); A.v = as_global(v);
+    A.rinv = as_global(rinv); A.rope = as_global(rope); A.v_word = as_global(word);
+}
 template <bool PLAIN, int WAVES>
-__device__ inline bool append_work(int n_strings, int by_unit, int wave, int* string, int* unit) {
+__device__ __forceinline__ bool append_string(const AppendArgs& A, int wave, AppendString& t) {
     int s = blockIdx.x;
-    *unit = blockIdx.y;
-    if (!PLAIN && by_unit) { const int q = s / by_unit; *unit = s - q * by_unit; s = q; }
-    *string = s * WAVES + wave;
-    return *string < n_strings;
+    t.unit = blockIdx.y;
+    if (!PLAIN && A.by_unit) { const int q = s / A.by_unit; t.unit = s - q * A.by_unit; s = q; }
+    const int string = s * WAVES + wave;
+    t.which = string & 1;
+    t.tile = A.tile0 + (string >> 1);
+    t.page = div_magic(t.tile, A.tpp, A.tpp_magic);
+    t.tslot = (uint64_t)t.unit * A.tpp + (t.tile - t.page * A.tpp);
+    t.rinv_head = nullptr;
+    if (!PLAIN && A.rinv) t.rinv_head = A.rinv + (t.unit - div_magic(t.unit, A.n_kv_heads, A.kv_magic) * A.n_kv_heads) * KVQ_D;
+    return string < A.n_strings;
 }
 
-// Append into the 16-bit tier: the new rows are copied into the tile layout.  stream_v: see append16_v_tile.
+// Append into the 16-bit tier: the new rows are copied into the tile layout.
 template <bool PLAIN>
-__global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ arena,
-                                                          KvqPageDesc* __restrict__ table,
-                                                          const uint16_t* __restrict__ k_in,
-                                                          const uint16_t* __restrict__ v_in, int t_old,
-                                                          int n_new, int tpp, int tile0, const KvqAppendPages ap,
-                                                          int stream_v,
-                                                          const float* __restrict__ rinv, int n_kv_heads,
-                                                          const float* __restrict__ rope, int n_strings, int by_unit) {
+__global__ __launch_bounds__(64) void kvq_append16_kernel(const AppendArgs args) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[32 * 256];
     const int lane = threadIdx.x;
-    int string, unit;
-    write_fresh_pages(table, ap, lane);
-    if (!append_work<PLAIN, 1>(n_strings, by_unit, 0, &string, &unit)) return;
-    const int which = string & 1;
-    const int tile = tile0 + (string >> 1);
-    const int page = tile / tpp, tip = tile - page * tpp;
-    const KvqPageDesc pd = append_desc(table, ap, page);
-    const uint64_t tslot = (uint64_t)unit * tpp + tip;
-    uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * 16);
-    const kvq_dev::NewRows rows((which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D, t_old, n_new);
-    if (which) kvq_dev::append16_v_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, lds, stream_v);  // (wavefront-uniform)
-    else if (PLAIN) kvq_dev::append16_k_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, nullptr, nullptr);
-    else kvq_dev::append16_k_tile(code, rows, tile * KVQ_TILE_TOKENS, lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
+    AppendArgs A;
+    read_append_args<PLAIN>(args, A);
+    AppendString t;
+    const bool mine = append_string<PLAIN, 1>(A, 0, t);
+    if (mine) {
+        const kvq_dev::NewRows rows((t.which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, A.t_old, A.n_new);
+        const int tok0 = t.tile * KVQ_TILE_TOKENS;
+        // the page entry is looked up behind the loads of the rows
+        const auto code = [&]() {
+            const KvqPageDesc pd = append_desc(A.table, args.pages, t.page);
+            return A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + t.which) * (512u * 16);
+        };
+        if (t.which) kvq_dev::append16_v_tile(code, rows, tok0, lane, lds, A.stream_v);  // (wavefront-uniform)
+        else kvq_dev::append16_k_tile(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head);
+    }
+    write_fresh_pages(A.table, args.pages, lane);
 }
 
 // Quantizing append (B = 8, 4, 2), built on the row-owner core.
@@ -72,37 +117,46 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(uint8_t* __restrict__ 
 // / 6.3 and 6.4 / 6.8 / 6.3, 2,560 7.9 / 7.8 / 7.9 and 7.1 / 7.7 / 7.1, 3,072 8.0 / 7.9 / 8.0 and 7.7 / 8.3 / 7.7, 4,096 9.6 / 9.6 / 9.8
 // and 9.7 / 9.8 / 9.1: the same line serves them.
 template <int B, bool PLAIN, bool PAIR>
-__global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(uint8_t* __restrict__ arena,
-                                                          KvqPageDesc* __restrict__ table,
-                                                          const uint16_t* __restrict__ k_in,
-                                                          const uint16_t* __restrict__ v_in, int t_old,
-                                                          int n_new, int tpp, int tile0, const KvqAppendPages ap,
-                                                          const KvqVMark mark, int gspan,
-                                                          const float* __restrict__ rinv, int n_kv_heads,
-                                                          const float* __restrict__ rope, int n_strings, int by_unit) {
+__global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(const AppendArgs args) {
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[KVQ_APPEND_WG_WAVES][KVQ_LDS_CODES];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* const lds = lds_all[PAIR ? wave >> 1 : wave];
     const int lane = threadIdx.x & 63, j = lane >> 4, n = lane & 15;
-    int string, unit;
-    if (wave == 0) write_fresh_pages(table, ap, lane);
+    AppendArgs A;
+    read_append_args<PLAIN>(args, A);
+    AppendString t;
     // (the number of strings is even: with pairs every workgroup has two, K and V of one tile)
-    if (!append_work<PLAIN, PAIR ? 2 : KVQ_APPEND_WG_WAVES>(n_strings, by_unit, PAIR ? wave >> 1 : wave, &string, &unit)) return;
-    const int which = string & 1;
-    const int tile = tile0 + (string >> 1);
-    const int page = tile / tpp, tip = tile - page * tpp;
-    const KvqPageDesc pd = append_desc(table, ap, page);
-    const uint64_t tslot = (uint64_t)unit * tpp + tip;
-    uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * B);
-    uint8_t* meta = arena + (uint64_t)pd.meta_off256 * 256u + tslot * KVQ_META_TILE_BYTES;
-    const int tok0 = tile * KVQ_TILE_TOKENS;
-    const kvq_dev::NewRows rows((which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D, t_old, n_new);
+    const bool mine = append_string<PLAIN, PAIR ? 2 : KVQ_APPEND_WG_WAVES>(A, PAIR ? wave >> 1 : wave, t);
+    if (wave == 0) write_fresh_pages(A.table, args.pages, lane);
+    if (!mine) return;
+    const int which = t.which, t_old = A.t_old, gspan = A.gspan;
+    const KvqVMark mark{A.v_word, A.v_epoch};
+    const int tok0 = t.tile * KVQ_TILE_TOKENS;
+    const kvq_dev::NewRows rows((which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, t_old, A.n_new);
     const int grp = lane & 3;
     constexpr int PASSES = PAIR ? 1 : 2;
     const int pass0 = PAIR ? wave & 1 : 0;
     uint32_t w[PASSES][16];
     load_owner_rows(w, rows, tok0 + 16 * pass0, lane);
-    if (!PLAIN && !which) prepare_owner_keys(w, rows, tok0 + 16 * pass0, rows.all(tok0), lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
+    const bool rotates = !PLAIN && !which && A.rope;
+    OwnerAngles angles;
+    if (rotates) load_owner_angles(angles, rows, tok0 + 16 * pass0 + (lane >> 2), lane, A.rope);
+    __builtin_amdgcn_sched_barrier(0);  // all of these loads first
+    const KvqPageDesc pd = append_desc(A.table, args.pages, t.page);
+    uint8_t* code = A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + which) * (512u * B);
+    uint8_t* meta = A.arena + (uint64_t)pd.meta_off256 * 256u + t.tslot * KVQ_META_TILE_BYTES;
+    if (rotates) {
+#pragma unroll
+        for (int pass = 0; pass < PASSES; ++pass) {
+            const int tok = tok0 + 16 * (pass0 + pass) + (lane >> 2);
+            if (pass) load_owner_angles(angles, rows, tok, lane, A.rope);
+            rotate_owner_keys(w[pass], angles, rows.has(tok), rows.all(tok0), lane);
+        }
+    }
+    if (!PLAIN && !which && t.rinv_head) {
+#pragma unroll
+        for (int pass = 0; pass < PASSES; ++pass) scale_owner_keys(w[pass], lane, t.rinv_head);
+    }
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
         const int tl = 16 * (pass0 + pass) + (lane >> 2);
@@ -164,32 +218,40 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
 // Append into the integer 16-bit tier: Eq. 1-2 with 2^16 - 1 levels by the same owner lanes; the high and the low
 // bytes of the codes then travel through LDS and into the tile's two byte planes like two 8-bit tiles.
 template <bool PLAIN>
-__global__ __launch_bounds__(64) void kvq_append_i16_kernel(uint8_t* __restrict__ arena,
-                                                            KvqPageDesc* __restrict__ table,
-                                                            const uint16_t* __restrict__ k_in,
-                                                            const uint16_t* __restrict__ v_in, int t_old,
-                                                            int n_new, int tpp, int tile0, const KvqAppendPages ap,
-                                                            int gspan, const float* __restrict__ rinv,
-                                                            int n_kv_heads, const float* __restrict__ rope,
-                                                            int n_strings, int by_unit) {
+__global__ __launch_bounds__(64) void kvq_append_i16_kernel(const AppendArgs args) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][KVQ_LDS_CODES];
     const int lane = threadIdx.x, j = lane >> 4, n = lane & 15;
-    int string, unit;
-    write_fresh_pages(table, ap, lane);
-    if (!append_work<PLAIN, 1>(n_strings, by_unit, 0, &string, &unit)) return;
-    const int which = string & 1;
-    const int tile = tile0 + (string >> 1);
-    const int page = tile / tpp, tip = tile - page * tpp;
-    const KvqPageDesc pd = append_desc(table, ap, page);
-    const uint64_t tslot = (uint64_t)unit * tpp + tip;
-    uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * 16);
-    uint8_t* meta = arena + (uint64_t)pd.meta_off256 * 256u + tslot * KVQ_META_TILE_BYTES;
-    const int tok0 = tile * KVQ_TILE_TOKENS;
-    const kvq_dev::NewRows rows((which ? v_in : k_in) + (uint64_t)unit * n_new * KVQ_D, t_old, n_new);
+    AppendArgs A;
+    read_append_args<PLAIN>(args, A);
+    AppendString t;
+    const bool mine = append_string<PLAIN, 1>(A, 0, t);
+    write_fresh_pages(A.table, args.pages, lane);
+    if (!mine) return;
+    const int which = t.which, t_old = A.t_old, gspan = A.gspan;
+    const int tok0 = t.tile * KVQ_TILE_TOKENS;
+    const kvq_dev::NewRows rows((which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, t_old, A.n_new);
     const int grp = lane & 3;
     uint32_t w[2][16];
     load_owner_rows(w, rows, tok0, lane);
-    if (!PLAIN && !which) prepare_owner_keys(w, rows, tok0, rows.all(tok0), lane, rope, rinv ? rinv + (unit % n_kv_heads) * KVQ_D : nullptr);
+    const bool rotates = !PLAIN && !which && A.rope;
+    OwnerAngles angles;
+    if (rotates) load_owner_angles(angles, rows, tok0 + (lane >> 2), lane, A.rope);
+    __builtin_amdgcn_sched_barrier(0);  // all of these loads first
+    const KvqPageDesc pd = append_desc(A.table, args.pages, t.page);
+    uint8_t* code = A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + which) * (512u * 16);
+    uint8_t* meta = A.arena + (uint64_t)pd.meta_off256 * 256u + t.tslot * KVQ_META_TILE_BYTES;
+    if (rotates) {
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            const int tok = tok0 + 16 * pass + (lane >> 2);
+            if (pass) load_owner_angles(angles, rows, tok, lane, A.rope);
+            rotate_owner_keys(w[pass], angles, rows.has(tok), rows.all(tok0), lane);
+        }
+    }
+    if (!PLAIN && !which && t.rinv_head) {
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) scale_owner_keys(w[pass], lane, t.rinv_head);
+    }
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         const int tl = 16 * pass + (lane >> 2);
@@ -748,29 +810,35 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     // 2,000 16.0 and 16.0, from buffers in turn 18.9 and 15.8.
     const int stream_v = !plain || (int64_t)units * n_new * (2 * 256) > (192 << 20);
     const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 ? units : 0;
-#define KVQ_APPEND_LAUNCH(kernel_, waves_, per_, extra_)                                                                     \
+    AppendArgs A;
+    A.arena = arena; A.table = table; A.k = k; A.v = v; A.rinv = rinv; A.rope = rope; A.v_word = mark.word; A.v_epoch = mark.epoch;
+    A.t_old = t_old; A.n_new = n_new; A.tpp = tiles_per_page; A.tile0 = tile0; A.n_strings = n_strings; A.by_unit = by_unit;
+    A.n_kv_heads = n_kv_heads; A.gspan = gspan; A.stream_v = stream_v;
+    const auto magic = [](int d) { return d > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; };
+    A.tpp_magic = magic(tiles_per_page);
+    A.kv_magic = magic(n_kv_heads);
+    A.pages = ap;
+#define KVQ_APPEND_LAUNCH(kernel_, waves_, per_)                                                                           \
     do {                                                                                                                 \
         const int n_wg = (n_strings + waves_ - 1) / waves_;                                                              \
         const dim3 grid = by_unit ? dim3((unsigned)n_wg * (unsigned)units) : dim3(n_wg, units);                          \
-        hipLaunchKernelGGL((kernel_), grid, dim3(64 * waves_ * per_), 0, s, arena, table, k, v, t_old, n_new, tiles_per_page, \
-                           tile0, ap, extra_, rinv, n_kv_heads, rope, n_strings, by_unit);                               \
+        hipLaunchKernelGGL((kernel_), grid, dim3(64 * waves_ * per_), 0, s, A);                                          \
     } while (0)
-#define KVQ_MARK mark, gspan
     switch (bits + (int16 && bits == 16 ? 1 : 0)) {
         case 17:
-            if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 1, 1, gspan);
-            else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, 1, gspan);
+            if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 1, 1);
+            else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, 1);
             break;
         case 16:
-            if (plain) KVQ_APPEND_LAUNCH(kvq_append16_kernel<true>, 1, 1, stream_v);
-            else KVQ_APPEND_LAUNCH(kvq_append16_kernel<false>, 1, 1, stream_v);
+            if (plain) KVQ_APPEND_LAUNCH(kvq_append16_kernel<true>, 1, 1);
+            else KVQ_APPEND_LAUNCH(kvq_append16_kernel<false>, 1, 1);
             break;
 #define KVQ_APPEND_CASE(b_)                                                                                              \
         case b_:                                                                                                         \
-            if (plain && pair) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true, true>), 2, 2, KVQ_MARK);                \
-            else if (plain) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true, false>), KVQ_APPEND_WG_WAVES, 1, KVQ_MARK); \
-            else if (pair) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false, true>), 2, 2, KVQ_MARK);                   \
-            else KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false, false>), KVQ_APPEND_WG_WAVES, 1, KVQ_MARK);          \
+            if (plain && pair) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true, true>), 2, 2);                           \
+            else if (plain) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true, false>), KVQ_APPEND_WG_WAVES, 1);           \
+            else if (pair) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false, true>), 2, 2);                              \
+            else KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false, false>), KVQ_APPEND_WG_WAVES, 1);                     \
             break;
         KVQ_APPEND_CASE(8)
         KVQ_APPEND_CASE(4)
@@ -778,7 +846,6 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
         default: return hipErrorInvalidValue;
     }
 #undef KVQ_APPEND_CASE
-#undef KVQ_MARK
 #undef KVQ_APPEND_LAUNCH
     return hipGetLastError();
 }

@@ -113,47 +113,39 @@ __device__ inline void load_owner_rows(uint32_t (&w)[PASSES][16], const kvq_dev:
         }
     }
 }
-// Rotation and reparameterization of the owners' keys, as configured.  The owner of the channels +- 64 of the same token is
-// the lane two further in the quad, so the partner channels are a data-parallel move away; a lane reads the 32 angles of
-// its channels with 16-byte loads.  (With the partner read again from memory and the angles one by one, 8,192 new tokens
-// x 32 units into 8, 4 or 2 bits took 166 to 172 us with rotation, 45 to 52 without.)
-template <int PASSES>
-__device__ inline void prepare_owner_keys(uint32_t (&w)[PASSES][16], const kvq_dev::NewRows& rows, int tok0, bool all_new, int lane,
-                                          const float* rope, const float* rinv_head) {
+// Rotation and reparameterization of the owners' keys of one pass, as configured.  The owner of the channels +- 64 of the same
+// token is the lane two further in the quad, so the partner channels are a data-parallel move away; a lane reads the 32 angles of
+// its channels with 16-byte loads, which the callers issue together with the rows.  (With the partner read again from memory and
+// the angles one by one, 8,192 new tokens x 32 units into 8, 4 or 2 bits took 166 to 172 us with rotation, 45 to 52 without.)
+struct OwnerAngles { kvq_dev::Angles8 a[4]; };
+__device__ inline void load_owner_angles(OwnerAngles& a, const kvq_dev::NewRows& rows, int tok, int lane, const float* rope) {
+    const float* row = rope + rows.row(tok) * KVQ_D;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) a.a[c] = kvq_dev::load_angles8(row, 32 * (lane & 1) + 8 * c);
+}
+__device__ inline void rotate_owner_keys(uint32_t (&w)[16], const OwnerAngles& a, bool isnew, bool all_new, int lane) {
     const int grp = lane & 3;
 #pragma unroll
-    for (int pass = 0; pass < PASSES; ++pass) {
-        const int tok = tok0 + 16 * pass + (lane >> 2);
-        const bool isnew = rows.has(tok);
-        if (rope) {
-            const float* row = rope + rows.row(tok) * KVQ_D;
-            kvq_dev::Angles8 a[4];
+    for (int c = 0; c < 4; ++c) {
+        u32x4 own = {w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]}, partner;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) a[c] = kvq_dev::load_angles8(row, 32 * (grp & 1) + 8 * c);
+        for (int e = 0; e < 4; ++e)  // quad_perm 2 3 0 1
+            partner[e] = (uint32_t)__builtin_amdgcn_mov_dpp((int)own[e], 0x4E, 0xf, 0xf, true);
+        own = kvq_dev::rope8(own, partner, a.a[c], grp >= 2 ? 0u : 0x80008000u);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                u32x4 own = {w[pass][4 * c], w[pass][4 * c + 1], w[pass][4 * c + 2], w[pass][4 * c + 3]}, partner;
+        for (int e = 0; e < 4; ++e) w[4 * c + e] = own[e];
+    }
+    if (!all_new) {  // (uniform) the zeros of tokens that are not new: a rotated one may be negative
+        asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                for (int e = 0; e < 4; ++e)  // quad_perm 2 3 0 1
-                    partner[e] = (uint32_t)__builtin_amdgcn_mov_dpp((int)own[e], 0x4E, 0xf, 0xf, true);
-                own = kvq_dev::rope8(own, partner, a[c], grp >= 2 ? 0u : 0x80008000u);
+        for (int e = 0; e < 16; ++e) w[e] = isnew ? w[e] : 0u;
+    }
+}
+__device__ inline void scale_owner_keys(uint32_t (&w)[16], int lane, const float* rinv_head) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[pass][4 * c + e] = own[e];
-            }
-            if (!all_new) {  // (uniform) the zeros of tokens that are not new: a rotated one may be negative
-                asm volatile("" ::: "memory");  // keeps this a branch
-#pragma unroll
-                for (int e = 0; e < 16; ++e) w[pass][e] = isnew ? w[pass][e] : 0u;
-            }
-        }
-        if (rinv_head) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const u32x4 v = kvq_dev::scale_keys8(u32x4{w[pass][4 * c], w[pass][4 * c + 1], w[pass][4 * c + 2], w[pass][4 * c + 3]},
-                                                     rinv_head + 32 * grp + 8 * c);
-                w[pass][4 * c] = v.x; w[pass][4 * c + 1] = v.y; w[pass][4 * c + 2] = v.z; w[pass][4 * c + 3] = v.w;
-            }
-        }
+    for (int c = 0; c < 4; ++c) {
+        const u32x4 v = kvq_dev::scale_keys8(u32x4{w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]}, rinv_head + 32 * (lane & 3) + 8 * c);
+        w[4 * c] = v.x; w[4 * c + 1] = v.y; w[4 * c + 2] = v.z; w[4 * c + 3] = v.w;
     }
 }
 

@@ -163,3 +163,27 @@ def test_one_long_append_writes_what_its_pieces_write(bits, tier16, rope):
         gc.close()
         arenas.append(arena)
     assert torch.equal(*arenas)
+
+
+@pytest.mark.parametrize("P,B,H", [(96, 3, 5), (224, 2, 3), (32, 2, 7), (1056, 1, 1)])
+@pytest.mark.parametrize("bits,tier16", [(16, 0), (16, 1), (8, 0)])
+def test_pages_and_heads_of_every_quotient(bits, tier16, P, B, H):
+    """Page, tile in the page and reparameterization row come from multiplied quotients; calls that start in later pages, with a
+    second page in sight, and factors that differ from head to head.  Bit for bit the oracle's."""
+    T = 2 * P + 75
+    K, V = kvq_synth.make_kv(85, 0, B, H, 0, T, rope_base=None)
+    cos, sin = kvq_synth.rope_tables(np.arange(T), 1.0e4)
+    table = np.concatenate([cos, sin], 1).astype(np.float32)
+    Krot = rope_rotate_keys(K, cos, sin)
+    lam = calibrate_lambda(Krot[:, :, :64], 0.5)
+    oc, gc = make_pair(1, B, H, H, T, P, tier16=tier16)
+    oc.set_reparam(0, lam)
+    gc.kvq_cache_set_reparam(0, torch.from_numpy(lam).cuda())
+    t = 0
+    for n in (P - 1, 2, P + 9, T - 2 * P - 10):
+        oc.append(0, Krot[:, :, t:t + n], V[:, :, t:t + n], bits)
+        gc.kvq_quantize_append_rope(0, view(K[:, :, t:t + n], 0), view(V[:, :, t:t + n], 0), view(table[t:t + n], 0), bits)
+        t += n
+    assert t == T
+    assert_same_cache(oc, gc, 0)
+    gc.close()
