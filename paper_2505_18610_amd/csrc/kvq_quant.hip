@@ -107,15 +107,21 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(const AppendArgs args)
 // Four wavefronts per workgroup, each with a string and LDS of its own: 1 to 2 % faster on bulk appends than one-wavefront
 // workgroups (a quarter of the workgroups to dispatch).
 #define KVQ_APPEND_WG_WAVES 4
-#define KVQ_PAIR_MAX_STRINGS 2560
 // PAIR: two wavefronts per string, one for each 16 tokens, two strings per workgroup.  A launch of one or two strings per
-// SIMD (1,024 of them) leaves each alone with some 1,000 to 1,700 vector instructions; shared by two it ends earlier.  Rotated
-// keys, one wavefront against two: 256 strings 6.3 and 5.1 us, 1,024 7.4 and 7.2, 1,536 9.0 and 8.4, 2,560 12.8 and 11.5;
-// from 3,072 on (13.0 and 13.0; 4,096: 15.8 and 17.2) the SIMDs have enough to interleave, so the line is at 2,560.  Keys that
-// need no preparation, calls in a train, into 8 / 4 / 2 bits: 512 strings and fewer the same (the calls take longer than the
-// kernels), 1,024 4.9 / 4.8 / 4.8 us with one and 4.8 / 4.7 / 4.7 with two, 1,536 6.0 / 6.1 / 6.0 and 5.7 / 5.9 / 5.6, 2,048 6.3 / 6.3
-// / 6.3 and 6.4 / 6.8 / 6.3, 2,560 7.9 / 7.8 / 7.9 and 7.1 / 7.7 / 7.1, 3,072 8.0 / 7.9 / 8.0 and 7.7 / 8.3 / 7.7, 4,096 9.6 / 9.6 / 9.8
-// and 9.7 / 9.8 / 9.1: the same line serves them.
+// SIMD (1,024 of them) leaves each alone with some 1,000 to 1,700 vector instructions; shared by two it ends earlier, and with half
+// the registers for its rows (88 instead of 112 with angles) more of it fits on a SIMD.  What a pair costs: factors are read twice,
+// and each wavefront gathers the whole string's codes to store half of them (into 2 bits, one chunk a lane, one stores all).
+// kvq_pair_strings draws the line.  Time of one wavefront per string over that of two, calls in a train, rotated keys into 8 / 4 / 2
+// bits: 1,536 strings 1.06 / 1.07 / 1.13, 1,984 1.07 / 1.05 / 1.11, 2,048 1.05 / 0.95 / 1.05, 2,560 1.22 / 1.13 / 1.22, 2,944 1.22 /
+// 1.12 / 1.23, 3,072 1.02 / 0.96 / 1.07, 4,096 1.00 / 0.98 / 1.08, 5,120 1.10 / 1.08 / 1.18, 16,384 1.05 / 0.97 / 1.13, 32,768 1.04 /
+// 0.97 / 1.11; scaled as well: 1,984 1.05 / 1.01 / 1.05, 2,048 0.99 / 0.91 / 0.96, 2,560 1.09 / 1.05 / 1.10, 2,944 1.09 / 1.06 / 1.11,
+// 3,072 0.94 / 0.91 / 0.97, 4,096 0.88 / 0.85 / 0.93, 32,768 0.90 / 0.85 / 0.89; neither: 1,984 1.14 / 1.08 / 1.15, 2,048 1.08 / 0.95 /
+// 1.06, 2,944 1.12 / 1.04 / 1.15, 4,096 1.00 / 0.97 / 1.07, 5,120 0.96 / 0.97 / 1.06, 32,768 1.07 / 0.90 / 0.99.  (16 units x 1,024
+// tokens are 1,024 strings; the first size takes 7.0 us, the last 67.)
+static bool kvq_pair_strings(int bits, int64_t strings, bool rotated, bool scaled) {
+    if (bits == 4 || scaled) return strings < 2048 || (strings >= 2560 && strings < 3072);  // from 2,560 on a third string per SIMD
+    return bits == 2 || rotated || strings < 4608;
+}
 template <int B, bool PLAIN, bool PAIR>
 __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(const AppendArgs args) {
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[KVQ_APPEND_WG_WAVES][KVQ_LDS_CODES];
@@ -801,7 +807,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     const bool plain = !rinv && !rope;
     const uint16_t* k = static_cast<const uint16_t*>(k_in);
     const uint16_t* v = static_cast<const uint16_t*>(v_in);
-    const bool pair = (int64_t)n_strings * units <= KVQ_PAIR_MAX_STRINGS;
+    const bool pair = kvq_pair_strings(bits, (int64_t)n_strings * units, rope != nullptr, rinv != nullptr);
     // How the 16-bit tier's V rows are read: new values have usually just been written and lie in the caches, which streaming
     // loads make less of.  128 units x 2,000 tokens (131 MB of keys and values) 43 us with plain loads of V and 51 with streaming
     // ones, 64 x 2,000 21 and 25, 32 x 2,000 10.9 and 12.6 (from 230 MB of buffers in turn 13.4 and 13.0), 600 x 50 12.1 and 13.0,

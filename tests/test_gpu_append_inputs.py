@@ -69,8 +69,8 @@ def test_page_entries_of_long_appends(pages, first):
 @pytest.mark.parametrize("bits", [8, 4, 2])
 @pytest.mark.parametrize("B,H,T", [(1, 1, 1), (5, 8, 1024), (5, 8, 1025), (4, 16, 1280)])
 def test_strings_shared_by_two_wavefronts(bits, B, H, T):
-    """Up to 2,560 strings (two per tile and unit) are quantized by two wavefronts each: the last such launch, one tile more, and a
-    launch beyond; a second append continues the partly filled tile."""
+    """Strings (two per tile and unit) quantized by two wavefronts each or by one, depending on their number: 2,560 of them, one tile
+    more, and twice as many; a second append continues the partly filled tile."""
     K, V = kvq_synth.make_kv(83, 0, B, H, 0, T + 6)
     oc, gc = make_pair(1, B, H, H, T + 6, 64)
     append_both(oc, gc, 0, K[:, :, :T], V[:, :, :T], bits)
@@ -187,3 +187,29 @@ def test_pages_and_heads_of_every_quotient(bits, tier16, P, B, H):
     assert t == T
     assert_same_cache(oc, gc, 0)
     gc.close()
+
+
+@pytest.mark.parametrize("bits", [8, 4, 2])
+@pytest.mark.parametrize("reparam", [False, True])
+@pytest.mark.parametrize("T", [480, 511, 608, 640, 736, 768, 1152, 2300])
+def test_prepared_keys_of_every_number_of_strings(bits, reparam, T):
+    """64 units x T rotated tokens at once (four strings a token: the sizes at which one or two wavefronts take a string, from 1,920
+    to 9,216) and in pieces of 96 tokens, which two wavefronts share: the same arena, byte for byte."""
+    B, H, P = 8, 8, 64
+    g = torch.Generator(device="cuda").manual_seed(86)
+    k, v = (torch.randn((B, H, T, 128), device="cuda", generator=g).half() for _ in range(2))
+    table = torch.randn((T, 128), device="cuda", generator=g)
+    lam = 1 + torch.rand((H, 128), device="cuda", generator=g)
+    cfg = kq.KvqConfig(1, B, H, H, T, page_tokens=P)
+    arenas = []
+    for step in (T, 96):
+        arena = torch.zeros(kq.kvq_arena_bytes(cfg, T * B * H * 640 + (64 << 20)), dtype=torch.uint8, device="cuda")
+        gc = kq.KvqCache(cfg, [1 << 50], [2], arena=arena)
+        if reparam:
+            gc.kvq_cache_set_reparam(0, lam)
+        for t in range(0, T, step):
+            gc.kvq_quantize_append_rope(0, *(x[:, :, t:t + step].contiguous() for x in (k, v)), table[t:t + step].contiguous(), bits)
+        torch.cuda.synchronize()
+        gc.close()
+        arenas.append(arena)
+    assert torch.equal(*arenas)
