@@ -698,10 +698,13 @@ __global__ void kvq_reparam_store_kernel(const float* __restrict__ lambda, float
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) { const float l = lambda[i]; dst[i] = l; dst[n + i] = 1.0f / l; }
 }
-// Eq. 8, first half: acc[h][i] = max over sequences and tokens of |K|.  acc holds float bit patterns of non-negative
-// values, whose unsigned order is their order.  256 threads: 16 lanes x 16 bytes read one row of 128 channels, a workgroup 16
-// rows at a time, eight loads in flight per lane; the 16 row groups meet in LDS and 128 atomics go out whose result nobody
-// waits for (looking first whether a channel exceeds what is there costs 20 us: the look is a trip to memory at the end of
+// Eq. 8: lambda[h][i] = max(max over sequences and tokens of |K|, floor)^alpha, pow in fp64, rounded to fp32.  Every workgroup raises
+// its own maxima and an atomic maximum joins them: lambda holds float bit patterns of non-negative values, whose unsigned order is
+// their order, and the rounded power keeps the order of its arguments (alpha >= 0; of two different fp16 magnitudes the powers are
+// further apart than fp64 errs, or so near to 1 that both round to it), so the joined result is the power of the joint maximum.  A
+// third launch that raised the maxima in place took 2.4 us and more.  256 threads: 16 lanes x 16 bytes read one row of 128 channels,
+// a workgroup 16 rows at a time, eight loads in flight per lane; the 16 row groups meet in LDS and 128 atomics go out whose result
+// nobody waits for (looking first whether a channel exceeds what is there costs 20 us: the look is a trip to memory at the end of
 // every workgroup, the atomics are not).
 //   FLAT = false: grid.x = (sequence, KV head) units, grid.y = slices of a unit's tokens
 //   FLAT = true:  grid.x = KV heads, grid.y = slices of a head's rows, the tokens of all its sequences in turn; a row's place
@@ -709,13 +712,15 @@ __global__ void kvq_reparam_store_kernel(const float* __restrict__ lambda, float
 // Bound by the one read of the keys.  32 sequences x 8 heads x 2,048 tokens (134 MB): 24 us over keys read for the first
 // time, 5.6 TB/s, and 21 over the same ones again, which the last-level cache partly holds (82 with 2-byte loads, a 64-bit
 // division per row and 1,024 slices per head).  The stepping costs the long sequences 2 to 3 %; on short ones a workgroup per unit
-// pays its atomics for few rows.  Whole calls over 134 MB of 8 heads, FLAT = false and true: 2,048 tokens a sequence 26.3
-// and 26.8 us, 512 26.9 and 27.4, 256 28.0 and 28.4, 128 32.5 and 29.6, 64 49 and 28, 16 159 and 29, 1 token 2,453 and 28 (64
-// heads, 268 MB: 512 46.7 and 46.4, 256 47.4 and 46.0, 128 49.7 and 46.8): the line is at 256 tokens.
+// pays its atomics and powers for few rows.  Whole calls, three launches before and two now: 134 MB of 8 heads 24.6 and 23.2 us over
+// the same keys, 26.3 and 24.5 from memory, 33 MB 11.4 and 7.9, 16 MB of one head 24.6 and 13.7, small ones 9 to 11 and 7.5 to 8.  Whole
+// calls over 134 MB of 8 heads, FLAT = false and true: 2,048 tokens a sequence 22.0 and 22.3 us, 512 23.2 and 23.1, 256 23.5 and 23.8,
+// 128 24.0 and 24.2, 64 31.8 and 23.7, 16 81.6 and 24.5; from memory 256 tokens 25.0 and 26.2; 64 heads, 268 MB: 512 42.3 and 41.5,
+// 256 42.7 and 41.4, 128 43.5 and 41.7, 64 48.0 and 42.2: the line is at 256 tokens.
 template <bool FLAT>
 __global__ __launch_bounds__(256) void kvq_absmax_kernel(const uint16_t* __restrict__ k, int n_kv_heads, int n_tokens,
                                                          int n_rows, int slice_rows, int step_seqs, int step_tokens,
-                                                         uint32_t* __restrict__ acc) {
+                                                         float alpha, float floor_, uint32_t* __restrict__ acc) {
     __shared__ __attribute__((aligned(16))) uint32_t part[16][KVQ_D / 2];
     const int c8 = threadIdx.x & 15, rg = threadIdx.x >> 4, head = FLAT ? blockIdx.x : blockIdx.x % n_kv_heads;
     const int r0 = blockIdx.y * slice_rows, r1 = r0 + min(slice_rows, n_rows - r0);
@@ -758,19 +763,14 @@ __global__ __launch_bounds__(256) void kvq_absmax_kernel(const uint16_t* __restr
     }
     *reinterpret_cast<u32x4*>(&part[rg][4 * c8]) = u32x4{m[0], m[1], m[2], m[3]};
     __syncthreads();
-    if (threadIdx.x < KVQ_D / 2) {
-        uint32_t w = part[0][threadIdx.x];
+    if (threadIdx.x < KVQ_D) {
+        const _Float16* const col = reinterpret_cast<const _Float16*>(&part[0][0]) + threadIdx.x;
+        _Float16 w = col[0];
 #pragma unroll
-        for (int r = 1; r < 16; ++r) w = pk_max_u(w, part[r][threadIdx.x]);
-        uint32_t* dst = acc + head * KVQ_D + 2 * threadIdx.x;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) atomicMax(dst + h, __float_as_uint(h2f((uint16_t)(w >> (16 * h)))));
+        for (int r = 1; r < 16; ++r) w = __builtin_elementwise_max(w, col[r * KVQ_D]);
+        const float lam = (float)pow((double)fmaxf((float)w, floor_), (double)alpha);
+        atomicMax(acc + head * KVQ_D + threadIdx.x, __float_as_uint(lam));
     }
-}
-// Eq. 8, second half, in place: lambda = max(absmax, floor)^alpha, pow in fp64, rounded to fp32.
-__global__ void kvq_lambda_pow_kernel(float* __restrict__ lam, int n, float alpha, float floor_) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) lam[i] = (float)pow((double)fmaxf(lam[i], floor_), (double)alpha);
 }
 
 // Plain streaming read (16 bytes per lane, 4 non-temporal loads in flight): the practical HBM read ceiling of the device,
@@ -940,15 +940,14 @@ hipError_t kvq_launch_calibrate(const void* k, int batch, int n_kv_heads, int n_
         const int want = std::max(1, (1024 + units - 1) / units);
         const int slice = std::max(128, ((n_tokens + want - 1) / want + 15) / 16 * 16);
         hipLaunchKernelGGL(kvq_absmax_kernel<false>, dim3(units, (n_tokens + slice - 1) / slice), dim3(256), 0, s, keys, n_kv_heads,
-                           n_tokens, n_tokens, slice, 0, 16, acc);
+                           n_tokens, n_tokens, slice, 0, 16, alpha, floor_, acc);
     } else {
         // (with more heads than workgroups are wanted, slices of about 2,048 rows, so that the last ones idle little)
         const int64_t want = std::max<int64_t>((1024 + n_kv_heads - 1) / n_kv_heads, std::min<int64_t>(1024, (rows + 2047) / 2048));
         const int slice = (int)std::max<int64_t>(128, ((rows + want - 1) / want + 15) / 16 * 16);
         hipLaunchKernelGGL(kvq_absmax_kernel<true>, dim3(n_kv_heads, (unsigned)((rows + slice - 1) / slice)), dim3(256), 0, s, keys,
-                           n_kv_heads, n_tokens, (int)rows, slice, 16 / n_tokens, 16 % n_tokens, acc);
+                           n_kv_heads, n_tokens, (int)rows, slice, 16 / n_tokens, 16 % n_tokens, alpha, floor_, acc);
     }
-    hipLaunchKernelGGL(kvq_lambda_pow_kernel, dim3((n + 255) / 256), dim3(256), 0, s, lambda, n, alpha, floor_);
     return hipGetLastError();
 }
 

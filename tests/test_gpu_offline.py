@@ -79,6 +79,22 @@ def test_calibration_over_many_sequences_or_heads(B, H, T):
     assert torch.equal(lam, K.abs_().amax(dim=(0, 2)).float())
 
 
+@pytest.mark.parametrize("alpha", [0.0, 1e-30, 1e-14, 0.3, 1.0, 4.0])
+@pytest.mark.parametrize("B,H,T", [(5, 3, 700), (40, 3, 20)])
+def test_the_power_of_the_maximum_is_the_maximum_of_the_powers(B, H, T, alpha):
+    """Every workgroup raises its own maxima: the same bits as from one row that holds the maxima, below the floor and at infinity too."""
+    K = torch.randn((B, H, T, 128), generator=torch.Generator("cuda").manual_seed(63), device="cuda", dtype=torch.float16)
+    K[..., 0], K[..., 1] = 0.0, 6e-8
+    K[2, 1, 11, 5] = float("inf")
+    lam, want = (torch.full((H, 128), -1.0, device="cuda") for _ in range(2))
+    kq.kvq_calibrate_lambda(K, alpha, lam)
+    kq.kvq_calibrate_lambda(K.abs().amax(dim=(0, 2)).reshape(1, H, 1, 128), alpha, want)
+    assert torch.equal(lam, want)
+    # floor and alpha as fp32 holds them; pow in fp64 rounded to fp32: one ulp
+    floor, power = (float(np.float32(x)) for x in (1e-5, alpha))
+    assert torch.allclose(lam.double(), K.abs().amax(dim=(0, 2)).double().clamp(min=floor) ** power, rtol=1.2e-7, atol=0)
+
+
 def test_calibration_time_does_not_depend_on_how_the_tokens_are_cut_into_sequences():
     """131,072 tokens of 8 heads as 64 sequences and as 131,072."""
     K = torch.randn((131072, 8, 1, 128), dtype=torch.float16, device="cuda")
