@@ -6,6 +6,8 @@
 // every lane quantizes the 64 slots it will later feed to the matrix cores.
 #include "kvq_quant_dev.h"
 
+#include <type_traits>
+
 #include <algorithm>
 
 namespace {
@@ -529,11 +531,14 @@ __device__ inline void unpack8(const uint32_t* str, int p, uint32_t* w0, uint32_
 }
 // Byte codes of one tile string -> LDS [32 tokens][128 channels]; the columns of row t are rotated by 32 (t / 8), which
 // puts the four lane quarters of a V string, whose rows are 8 apart, into different banks.
-template <int B>
-__device__ inline void rows_of_string(uint8_t* lds, const uint8_t* code, int which, int lane) {
+// behind: called once the loads of the codes are issued.
+template <int B, class Behind>
+__device__ inline void rows_of_string(uint8_t* lds, const uint8_t* code, int which, int lane, Behind behind) {
     const int j = lane >> 4, n = lane & 15;
     uint32_t str[2 * B];
     load_chunks_stream<B>(code, lane, str);
+    __builtin_amdgcn_sched_barrier(0);
+    behind();
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
         uint32_t w[2];
@@ -550,10 +555,13 @@ __device__ inline void rows_of_string(uint8_t* lds, const uint8_t* code, int whi
     }
 }
 // The same for raw fp16 values: [32 tokens][128 channels] halves, rows rotated by 64 bytes per 8 tokens.
-__device__ inline void rows_of_raw(uint8_t* lds, const uint8_t* code, int which, int lane) {
+template <class Behind>
+__device__ inline void rows_of_raw(uint8_t* lds, const uint8_t* code, int which, int lane, Behind behind) {
     const int j = lane >> 4, n = lane & 15;
     uint32_t in[32];
     load_chunks_stream<16>(code, lane, in);
+    __builtin_amdgcn_sched_barrier(0);
+    behind();
     if (!which) {
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
@@ -576,118 +584,153 @@ __device__ inline void rows_of_raw(uint8_t* lds, const uint8_t* code, int which,
 //   L1 = false: (x_hat - x)^2
 //   L1 = true:  |g * (x_hat - x)| (g = 1 if no gradient tensor [unit][token][128] fp32 is given), the terms of the
 //               sensitivity of Sec. 3.2, Eq. 5
-// fp32 inside a lane's 32 elements of a row, fp64 beyond; the host adds the workgroups up in order.
+// fp32 over 32 elements of a lane (eight tokens x 4 channels), fp64 beyond; the host adds the workgroups up in order.
 //
 // Bound by the references and gradients (4 + 8 bytes per cached token and channel against at most 2 of codes), which are
-// rows while the codes are tiles: every wavefront turns one tile string to rows in LDS and then reads both with 16-byte
-// loads, a lane taking 32 consecutive channels of a token like the quantizers' owner lanes (16 lanes to a row instead
-// needs more registers and measured 12 % slower; streaming loads twice as slow, a lane's four loads share a line).  A
-// fixed number of workgroups strides over the strings and leaves two numbers each, without atomics.  64 units x 2,048
-// tokens at 4 bits with gradients (219 MB): 41 us, 5.3 TB/s; with 2- and 4-byte loads in the codes' own order and an fp64
-// atomic per tile on two addresses 304 us.
+// rows while the codes are tiles: every wavefront turns one tile string to rows in LDS and then reads both row by row, 32
+// lanes to a token and 4 channels a lane, so that a load instruction covers whole lines (512 bytes of references, 1 KiB of
+// gradients) and can stream.  Six tokens of every lane are on their way at any time, the first six from behind the loads of
+// the codes on: with eight the kernel would spill at four wavefronts per SIMD, which is also what the LDS holds.  (With a
+// lane taking 32 channels of a token a load instruction touched 64 lines, four instructions one after the other the same
+// ones, and nothing was asked for before the codes were in LDS.)  A fixed number of workgroups strides over the strings and
+// leaves two numbers each, without atomics.  Whole calls, of which launch and synchronization are some 11 us, before and
+// now: 64 units x 2,048 tokens at 4 bits with gradients (219 MB) 48.1 and 45.9 us, without 36.1 and 32.5, 128 x 4,096 (880 MB)
+// 158 and 142 (6.7 TB/s) and 69 and 65; the integer tier with gradients 57 and 55; streaming loads against plain ones 142 and 155.
 #define KVQ_ERR_WAVES 4
-template <bool L1>
-__global__ __launch_bounds__(64 * KVQ_ERR_WAVES) void kvq_error_kernel(const uint8_t* __restrict__ arena,
+#define KVQ_ERR_AHEAD 6
+enum { KVQ_ERR_SQ, KVQ_ERR_L1, KVQ_ERR_L1_GRAD, KVQ_ERR_L1_ONE_GRAD };  // (one: K or V comes without gradients)
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+struct ErrorStep { uint32_t units, tiles; };  // from a wavefront's string to its next
+template <int MODE>
+__global__ __launch_bounds__(64 * KVQ_ERR_WAVES) __attribute__((amdgpu_waves_per_eu(4))) void kvq_error_kernel(const uint8_t* __restrict__ arena,
                                                        const KvqPageDesc* __restrict__ table,
                                                        const uint16_t* __restrict__ k_ref,
                                                        const uint16_t* __restrict__ v_ref,
                                                        const float* __restrict__ gk, const float* __restrict__ gv,
-                                                       int n_tokens, int tpp, int n_tiles, int64_t n_strings,
-                                                       double* __restrict__ partial) {
+                                                       int n_tokens, int tpp, uint32_t tpp_magic, int n_tiles, int units,
+                                                       ErrorStep step, double* __restrict__ partial) {
     __shared__ __attribute__((aligned(16))) uint8_t rows[KVQ_ERR_WAVES][32 * 256];
+    __shared__ f32x2 metas[KVQ_ERR_WAVES][128];  // [token][group]: scale, zero point
     __shared__ double sums[KVQ_ERR_WAVES];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int which = wave & 1, grp = lane & 3;  // a wavefront's strings are all of K or all of V: the stride is even
+    constexpr int AHEAD = KVQ_ERR_AHEAD, ROWS = KVQ_TILE_TOKENS / 2;
+    const int thread_lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int which = wave & 1;  // a wavefront's strings are all of K or all of V: the stride is even
     uint8_t* const lds = rows[wave];
+    f32x2* const meta = metas[wave];
     const uint16_t* const ref = which ? v_ref : k_ref;
     const float* const grad = which ? gv : gk;
+    const uint32_t first = (uint32_t)(blockIdx.x * (KVQ_ERR_WAVES / 2) + (wave >> 1));
+    int unit = (int)(first / (uint32_t)n_tiles), tile = (int)(first - (uint32_t)unit * (uint32_t)n_tiles);
     double total = 0.0;
-    for (int64_t s = (int64_t)blockIdx.x * KVQ_ERR_WAVES + wave; s < n_strings; s += (int64_t)gridDim.x * KVQ_ERR_WAVES) {
-        const int64_t r = s >> 1;
-        const int unit = (int)(r / n_tiles), tile = (int)(r - (int64_t)unit * n_tiles);
-        const int page = tile / tpp, tip = tile - page * tpp;
+    while (unit < units) {
+        int lane = thread_lane;
+        asm("" : "+v"(lane));  // addresses in LDS are made anew for each string: kept across strings they would take half the registers
+        const int half = lane >> 5, c4 = 4 * (lane & 31);
+        const int page = div_magic(tile, tpp, tpp_magic), tip = tile - page * tpp;
         const KvqPageDesc pd = table[page];
         const uint64_t tslot = (uint64_t)unit * tpp + tip;
         const uint8_t* code = arena + (uint64_t)pd.code_off256 * 256u + (tslot * 2 + which) * (512u * pd.bits);
-        const uint16_t* meta = reinterpret_cast<const uint16_t*>(arena + (uint64_t)pd.meta_off256 * 256u +
-                                                                 tslot * KVQ_META_TILE_BYTES) + (which ? 256 : 0);
+        const uint32_t* meta_in = reinterpret_cast<const uint32_t*>(arena + (uint64_t)pd.meta_off256 * 256u +
+                                                                    tslot * KVQ_META_TILE_BYTES) + (which ? 128 : 0);
+        const uint64_t tile_row = (uint64_t)unit * n_tokens + (uint64_t)tile * KVQ_TILE_TOKENS;
+        const int left = n_tokens - tile * KVQ_TILE_TOKENS;
+        // (buffers that end with the last token: what lies beyond reads as zeros)
+        const auto ref_tile = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(ref + tile_row * KVQ_D), 0,
+                                                                min(left, KVQ_TILE_TOKENS) * (KVQ_D * 2), 0x00020000);
+        const bool weighs = MODE == KVQ_ERR_L1_GRAD || (MODE == KVQ_ERR_L1_ONE_GRAD && grad);
+        const auto grad_tile = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(weighs ? grad + tile_row * KVQ_D : nullptr), 0,
+                                                                 weighs ? min(left, KVQ_TILE_TOKENS) * (KVQ_D * 4) : 0, 0x00020000);
+        const float no_weight = weighs ? 0.0f : 1.0f;  // (gradients that are not there read as zeros)
+        u32x2 x[AHEAD];
+        u32x4 g[AHEAD];
+        const auto load = [&](int i) {
+            x[i % AHEAD] = __builtin_amdgcn_raw_buffer_load_b64(ref_tile, 8 * lane + 512 * i, 0, 2);
+            if (MODE >= KVQ_ERR_L1_GRAD) g[i % AHEAD] = __builtin_amdgcn_raw_buffer_load_b128(grad_tile, 16 * lane + 1024 * i, 0, 2);
+        };
         const bool raw = pd.bits == 16 && !pd.int16;
+        const auto behind_codes = [&]() {
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) load(i);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const uint32_t ms = raw ? 0u : meta_in[lane], mz = raw ? 0u : meta_in[64 + lane];
         switch (pd.bits) {
-            case 2: rows_of_string<2>(lds, code, which, lane); break;
-            case 4: rows_of_string<4>(lds, code, which, lane); break;
-            case 8: rows_of_string<8>(lds, code, which, lane); break;
+            case 2: rows_of_string<2>(lds, code, which, lane, behind_codes); break;
+            case 4: rows_of_string<4>(lds, code, which, lane, behind_codes); break;
+            case 8: rows_of_string<8>(lds, code, which, lane, behind_codes); break;
             default:
                 if (raw) {
-                    rows_of_raw(lds, code, which, lane);
+                    rows_of_raw(lds, code, which, lane, behind_codes);
                 } else {  // byte planes: high bytes, then low bytes
-                    rows_of_string<8>(lds, code, which, lane);
-                    rows_of_string<8>(lds + 4096, code + 512u * 8, which, lane);
+                    rows_of_string<8>(lds, code, which, lane, [] {});
+                    rows_of_string<8>(lds + 4096, code + 512u * 8, which, lane, behind_codes);
                 }
         }
+        if (!raw) {
+            int put[2];  // where the lane's two entries of the tile's metadata go
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int at = 2 * lane + e, v = at & 31;  // (kvq_vmeta_index the other way)
+                put[e] = which ? ((v >> 3) * 8 + ((v & 7) >> 1) + 4 * (v & 1)) * 4 + (at >> 5) : at;
+            }
+            meta[put[0]] = f32x2{h2f((uint16_t)ms), h2f((uint16_t)mz)};
+            meta[put[1]] = f32x2{h2f((uint16_t)(ms >> 16)), h2f((uint16_t)(mz >> 16))};
+        }
         wave_sync_lds();
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            const int t = 16 * pass + (lane >> 2), tok = tile * KVQ_TILE_TOKENS + t;
-            const uint64_t row = ((uint64_t)unit * n_tokens + min(tok, n_tokens - 1)) * KVQ_D + 32 * grp;
-            uint32_t x[16];
-            float g[32];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const u32x4 v = load16_any(ref + row + 8 * c);
-                x[4 * c] = v.x; x[4 * c + 1] = v.y; x[4 * c + 2] = v.z; x[4 * c + 3] = v.w;
-            }
-            if (L1 && grad) {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const u32x4 v = load16_any(grad + row + 4 * c);
-                    g[4 * c] = __uint_as_float(v.x); g[4 * c + 1] = __uint_as_float(v.y);
-                    g[4 * c + 2] = __uint_as_float(v.z); g[4 * c + 3] = __uint_as_float(v.w);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 32; ++e) g[e] = 1.0f;
-            }
+        // x_hat - x = code * S + (Z - x): the difference of two fp16 numbers is exact in fp32 and the fused
+        // multiply-add rounds once, so large codes times large scales lose nothing before the subtraction
+        const auto sum_up = [&](auto kind) {  // 0: bytes, 1: byte planes, 2: raw
+            constexpr int KIND = decltype(kind)::value;
             float acc[4] = {0.f, 0.f, 0.f, 0.f};
-            // x_hat - x = code * S + (Z - x): the difference of two fp16 numbers is exact in fp32 and the fused
-            // multiply-add rounds once, so large codes times large scales lose nothing before the subtraction
-            if (raw) {
-                const u32x4* hp = reinterpret_cast<const u32x4*>(lds + t * 256 + ((64 * grp + 64 * (t >> 3)) & 255));
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const u32x4 h = hp[c];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int sh = 16 * (e & 1);
-                        const float dx = h2f((uint16_t)(h[e >> 1] >> sh)) - h2f((uint16_t)(x[4 * c + (e >> 1)] >> sh));
-                        acc[e & 3] += L1 ? fabsf(g[8 * c + e] * dx) : dx * dx;
-                    }
+            for (int i = 0; i < ROWS; ++i) {
+                const int t = 2 * i + half;
+                f32x2 sz = {0.f, 0.f};
+                u32x2 b;
+                if (KIND == 2) {
+                    b = *reinterpret_cast<const u32x2*>(lds + half * 256 + ((2 * c4 + 64 * (i >> 2)) & 255) + 512 * i);
+                } else {
+                    sz = meta[4 * half + (c4 >> 5) + 8 * i];
+                    const uint8_t* const at = lds + half * 128 + ((c4 + 32 * (i >> 2)) & 127) + 256 * i;
+                    b.x = *reinterpret_cast<const uint32_t*>(at);
+                    b.y = KIND == 1 ? *reinterpret_cast<const uint32_t*>(at + 4096) : 0u;
                 }
-            } else {
-                const int mi = which ? kvq_vmeta_index(t, grp) : t * 4 + grp;
-                const float S = h2f(meta[mi]), Z = h2f(meta[mi + 128]);
-                const int at = t * 128 + ((32 * grp + 32 * (t >> 3)) & 127);
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const u32x4 b = reinterpret_cast<const u32x4*>(lds + at)[c];
-                    u32x4 lo = {0u, 0u, 0u, 0u};
-                    if (pd.int16) lo = reinterpret_cast<const u32x4*>(lds + 4096 + at)[c];
-                    const float hi_weight = pd.int16 ? 256.0f : 1.0f;
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const float cd = fmaf((float)((b[e >> 2] >> (8 * (e & 3))) & 0xffu), hi_weight,
-                                              (float)((lo[e >> 2] >> (8 * (e & 3))) & 0xffu));  // exact
-                        const float dx = fmaf(cd, S, Z - h2f((uint16_t)(x[8 * c + (e >> 1)] >> (16 * (e & 1)))));
-                        acc[e & 3] += L1 ? fabsf(g[16 * c + e] * dx) : dx * dx;
+                for (int e = 0; e < 4; ++e) {
+                    const float xe = h2f((uint16_t)(x[i % AHEAD][e >> 1] >> (16 * (e & 1))));
+                    float dx;
+                    if (KIND == 2) {
+                        dx = h2f((uint16_t)(b[e >> 1] >> (16 * (e & 1)))) - xe;
+                    } else {
+                        float cd = (float)((b.x >> (8 * e)) & 0xffu);
+                        if (KIND == 1) cd = fmaf(cd, 256.0f, (float)((b.y >> (8 * e)) & 0xffu));  // exact
+                        dx = fmaf(cd, sz.x, sz.y - xe);
                     }
+                    if (t >= left) dx = 0.0f;
+                    if (MODE == KVQ_ERR_SQ) acc[e] = fmaf(dx, dx, acc[e]);
+                    else if (MODE == KVQ_ERR_L1) acc[e] += fabsf(dx);
+                    else acc[e] = fmaf(fabsf(__uint_as_float(g[i % AHEAD][e])) + (MODE == KVQ_ERR_L1_ONE_GRAD ? no_weight : 0.0f), fabsf(dx), acc[e]);
+                }
+                if (i + AHEAD < ROWS) load(i + AHEAD);
+                if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (left alone, all rows are read from LDS first)
+                if (i % 8 == 7) {  // 32 elements
+                    total += (double)((acc[0] + acc[1]) + (acc[2] + acc[3]));
+                    acc[0] = acc[1] = acc[2] = acc[3] = 0.f;
                 }
             }
-            if (tok < n_tokens) total += (double)((acc[0] + acc[1]) + (acc[2] + acc[3]));
-        }
+        };
+        if (raw) sum_up(std::integral_constant<int, 2>());
+        else if (pd.int16) sum_up(std::integral_constant<int, 1>());
+        else sum_up(std::integral_constant<int, 0>());
         wave_sync_lds();
+        unit += (int)step.units;
+        tile += (int)step.tiles;
+        if (tile >= n_tiles) { tile -= n_tiles; ++unit; }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
-    if (lane == 0) sums[wave] = total;
+    if (thread_lane == 0) sums[wave] = total;
     __syncthreads();
     if (threadIdx.x < 2) partial[2 * blockIdx.x + threadIdx.x] = sums[threadIdx.x] + sums[threadIdx.x + 2];
 }
@@ -897,12 +940,20 @@ hipError_t kvq_launch_error(bool l1, const uint8_t* arena, const KvqPageDesc* ta
                             const void* v_ref, const float* gk, const float* gv, int n_tokens, int tiles_per_page,
                             int units, double* partial, hipStream_t s) {
     const int n_tiles = (n_tokens + KVQ_TILE_TOKENS - 1) / KVQ_TILE_TOKENS;
-    const int64_t n_strings = 2ll * n_tiles * units;
-    const dim3 grid(kvq_error_workgroups(n_tokens, units)), block(64 * KVQ_ERR_WAVES);
+    const int wgs = kvq_error_workgroups(n_tokens, units);
+    const dim3 grid(wgs), block(64 * KVQ_ERR_WAVES);
     const uint16_t* k = static_cast<const uint16_t*>(k_ref);
     const uint16_t* v = static_cast<const uint16_t*>(v_ref);
-    if (l1) hipLaunchKernelGGL(kvq_error_kernel<true>, grid, block, 0, s, arena, table, k, v, gk, gv, n_tokens, tiles_per_page, n_tiles, n_strings, partial);
-    else hipLaunchKernelGGL(kvq_error_kernel<false>, grid, block, 0, s, arena, table, k, v, gk, gv, n_tokens, tiles_per_page, n_tiles, n_strings, partial);
+    const uint32_t stride = (uint32_t)wgs * (KVQ_ERR_WAVES / 2);  // in tiles (a tile takes two wavefronts; 2^31 of them hold 4 TB)
+    const ErrorStep step{stride / (uint32_t)n_tiles, stride % (uint32_t)n_tiles};
+    const uint32_t magic = tiles_per_page > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)tiles_per_page - 1) / (uint64_t)tiles_per_page) : 0u;
+#define KVQ_ERR_LAUNCH(mode_) \
+    hipLaunchKernelGGL(kvq_error_kernel<mode_>, grid, block, 0, s, arena, table, k, v, gk, gv, n_tokens, tiles_per_page, magic, n_tiles, units, step, partial)
+    if (!l1) KVQ_ERR_LAUNCH(KVQ_ERR_SQ);
+    else if (!gk && !gv) KVQ_ERR_LAUNCH(KVQ_ERR_L1);
+    else if (!gk || !gv) KVQ_ERR_LAUNCH(KVQ_ERR_L1_ONE_GRAD);
+    else KVQ_ERR_LAUNCH(KVQ_ERR_L1_GRAD);
+#undef KVQ_ERR_LAUNCH
     return hipGetLastError();
 }
 

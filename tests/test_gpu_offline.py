@@ -55,6 +55,27 @@ def test_errors_against_the_oracle(B, Hkv, P, tiers, tier16):
     gc.close()
 
 
+@pytest.mark.parametrize("bits,tier16", [(16, 0), (16, 1), (8, 0), (2, 0)])
+@pytest.mark.parametrize("T", [1, 7, 32, 45, 129])
+def test_sensitivity_with_gradients_of_one_tensor(T, bits, tier16):
+    """Gradients of K alone and of V alone weigh that tensor, ones the other: the sums that two calls give."""
+    B, H = 2, 3
+    g = torch.Generator("cuda").manual_seed(64)
+    K, V, Kr, Vr = (torch.randn((B, H, T, 128), generator=g, device="cuda").half() for _ in range(4))
+    gk, gv = (torch.randn((B, H, T, 128), generator=g, device="cuda") for _ in range(2))
+    _, gc = make_pair(1, B, H, H, T, 96, tier16=tier16)
+    gc.kvq_quantize_append(0, K, V, bits)
+    both, none = gc.kvq_cache_sensitivity(0, Kr, Vr, gk, gv), gc.kvq_cache_sensitivity(0, Kr, Vr)
+    assert tuple(gc.kvq_cache_sensitivity(0, Kr, Vr, gk, None)) == (both[0], none[1])
+    assert tuple(gc.kvq_cache_sensitivity(0, Kr, Vr, None, gv)) == (none[0], both[1])
+    if bits == 16 and not tier16:  # raw values: the terms themselves
+        d = [(a.double() - b.double()).abs() for a, b in ((K, Kr), (V, Vr))]
+        # 8 fp32 terms per accumulator and their sum, each rounded at most twice: 10 x 2^-24
+        assert np.allclose(none, [float(x.sum()) for x in d], rtol=1e-6, atol=0)
+        assert np.allclose(both, [float((x * y.double().abs()).sum()) for x, y in zip(d, (gk, gv))], rtol=1e-6, atol=0)
+    gc.close()
+
+
 @pytest.mark.parametrize("B,Hkv,T", [(1, 1, 1), (1, 2, 15), (2, 1, 129), (3, 4, 257), (1, 8, 4097), (40, 32, 17),
                                      (300, 3, 1), (1000, 2, 3), (77, 1, 16), (33, 2, 31), (2, 1100, 3)])
 def test_calibration_at_slice_edges(B, Hkv, T):
