@@ -96,7 +96,15 @@ hipError_t kvq_launch_attention_batch(const KvqAttnParams* params_dev, const Kvq
         wgs += params_host[i].n_splits * units[i];
     }
     for (int i = n; i <= KVQ_MAX_BATCH_CACHES; ++i) map.wg_begin[i] = wgs;
-    hipError_t e = kvq_launch_attention_batch_kernel(params_dev, map, params_host[0].int16_tier != 0, s);
+    const bool int16 = params_host[0].int16_tier != 0;
+    // One launch, one kernel: that for short ranges where every cache's are.  Calls in a train, streaming kernel and this one, four
+    // sequences of 300 tokens x 8 units 9.1 -> 7.2 us, 100 to 2,000 x 8 11.9 -> 9.4, 3,500 x 8 of 4 / 16 bits (14 tiles a range) 13.2 -> 11.9
+    // and 17.7 -> 15.6, 32 of 500 x 8 (16 tiles) 15.5 -> 14.3 and 19.4 -> 18.0; with ranges of 20 tiles in it, 32 of 640 x 8 of 8 bits, it
+    // took 17.2 and streaming 16.9.
+    bool short_ranges = true;
+    for (int i = 0; i < n; ++i) short_ranges = short_ranges && params_host[i].short_ranges;
+    hipError_t e = short_ranges ? kvq_launch_attention_short_batch(params_dev, map, int16, s)
+                                : kvq_launch_attention_batch_kernel(params_dev, map, int16, s);
     for (int i = 0; i < n && e == hipSuccess; ++i)
         if (params_host[i].n_splits > 1 && !params_host[i].fused_merge) e = kvq_launch_merge(params_host[i], units[i], s);
     return e;

@@ -10,8 +10,8 @@
 // 4.9).  Launches in a train, streaming kernels and these: 764 tokens of 4 and 16 bits x 8 units 8.6 -> 6.7 us, with an appended
 // token 8.5 -> 6.7, 2,500 tokens of 16 bits x 8 units 9.3 -> 6.5, one tile x one unit 5.1 -> 3.9; with 16-bit codes 764 tokens
 // 9.5 -> 7.6.  The loads are streaming ones here too: plain ones are 0.4 us faster on blocks that lie in the L2 caches, but
-// 0.2 us slower on blocks that come from memory.
-#include "kvq_attention_body.h"
+// 0.2 us slower on blocks that come from memory.  A batch has two kernels more, which find their parameters as the streaming ones do.
+#include "kvq_attention_batch.h"
 
 namespace {
 
@@ -140,10 +140,8 @@ __device__ __forceinline__ void short_tiles(WaveState& st, QOps& Q, u32x4 (&qraw
 }
 
 template <bool I16, bool APPEND>
-__device__ __forceinline__ void short_body(const KvqAttnParams& params, AttnShared& sh) {
-    const int split = blockIdx.x, unit = blockIdx.y;
-    const int t_begin = params.split_begin[split], t_end = params.split_begin[split + 1];
-    const KvqAttnHead P = read_head(params);
+__device__ __forceinline__ void short_range(const KvqAttnHead& P, const int t_begin, const int t_end, const int split, const int unit,
+                                            AttnShared& sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane >> 4, n = lane & 15;
     const int b = div_magic(unit, P.n_kv_heads, P.kv_magic), hk = unit - b * P.n_kv_heads;
@@ -239,6 +237,22 @@ __device__ __forceinline__ void short_body(const KvqAttnParams& params, AttnShar
     finish_workgroup<I16, APPEND, true>(P, sh, st, split, unit, 64 * wave + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (uint32_t)zero)));
 }
 
+template <bool I16, bool APPEND>
+__device__ __forceinline__ void short_body(const KvqAttnParams& params, AttnShared& sh) {
+    const int split = blockIdx.x, unit = blockIdx.y;
+    const int t_begin = params.split_begin[split], t_end = params.split_begin[split + 1];
+    const KvqAttnHead P = read_head(params);
+    short_range<I16, APPEND>(P, t_begin, t_end, split, unit, sh);
+}
+// A ragged batch all of whose ranges are short.
+template <bool I16>
+__device__ __forceinline__ void short_batch_body(const KvqAttnParams* __restrict__ params, const KvqBatchMap& map, AttnShared& sh,
+                                                 uint32_t (&block)[kBlockDwords]) {
+    BatchWork work;
+    const KvqAttnHead P = batch_work(params, map, block, work);
+    short_range<I16, true>(P, work.t_begin, work.t_end, work.split, work.unit, sh);
+}
+
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
     short_body<false, false>(P, sh);
@@ -256,8 +270,27 @@ __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_i16_appe
     short_body<true, true>(P, sh);
 }
 
+__global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_batch_kernel(const KvqAttnParams* __restrict__ params,
+                                                                                     const KvqBatchMap map) {
+    __shared__ AttnShared sh;
+    __shared__ uint32_t block[kBlockDwords];
+    short_batch_body<false>(params, map, sh, block);
+}
+__global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_batch_i16_kernel(const KvqAttnParams* __restrict__ params,
+                                                                                         const KvqBatchMap map) {
+    __shared__ AttnShared sh;
+    __shared__ uint32_t block[kBlockDwords];
+    short_batch_body<true>(params, map, sh, block);
+}
+
 }  // namespace
 
+hipError_t kvq_launch_attention_short_batch(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16, hipStream_t s) {
+    const dim3 grid(map.wg_begin[map.n]), block(KVQ_ATTN_THREADS);
+    if (int16) hipLaunchKernelGGL(kvq_attention_short_batch_i16_kernel, grid, block, 0, s, params_dev, map);
+    else hipLaunchKernelGGL(kvq_attention_short_batch_kernel, grid, block, 0, s, params_dev, map);
+    return hipGetLastError();
+}
 hipError_t kvq_launch_attention_short(const KvqAttnParams& p, int units, hipStream_t s) {
     const dim3 grid(p.n_splits, units), block(KVQ_ATTN_THREADS);
     const bool append = p.app_t_old >= 0;

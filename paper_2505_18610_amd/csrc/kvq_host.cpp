@@ -834,7 +834,7 @@ int planned_splits(const kvq_cache* c, const TileCensus& t, int n_tiles, int max
     return best;
 }
 
-// Most splits of one (sequence, KV head) that pay in a batch, whose ranges are streamed whatever their length: none up to 20
+// Most splits of one (sequence, KV head) that pay in a batch, most of whose launches stream their ranges: none up to 20
 // tiles, beyond that sqrt(time / 80), or one per 16 tiles for a unit or two by themselves (max_wgs / 2) as long as the
 // merge issues all its loads in one round.  More than eight query heads per KV head leave the merge one slot group, which loads
 // 16 splits a round: beyond 16 splits a range of such a unit keeps 16 tiles.  A count a little above the 16 of every slot group,

@@ -154,7 +154,8 @@ hipError_t kvq_launch_attention(const KvqAttnParams& p, int units, hipStream_t s
 hipError_t kvq_launch_attention_short(const KvqAttnParams& p, int units, hipStream_t s);  // kernel only, no merge
 hipError_t kvq_launch_merge(const KvqAttnParams& p, int units, hipStream_t s);
 hipError_t kvq_launch_attention_i16_append(const KvqAttnParams& p, int units, hipStream_t s);  // kernel only, no merge
-// kvq_attention_batch.hip: the bare kernel launch kvq_launch_attention_batch wraps
+// kvq_attention_batch.hip, kvq_attention_short.hip: the bare kernel launches kvq_launch_attention_batch wraps
+hipError_t kvq_launch_attention_short_batch(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16, hipStream_t s);
 hipError_t kvq_launch_attention_batch_kernel(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16,
                                              hipStream_t s);
 // params_dev: the n parameter blocks in device memory (in stream order); params_host: the same blocks on the host;

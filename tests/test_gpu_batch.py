@@ -172,6 +172,51 @@ def test_full_size_ragged_batch_sampled_sequences():
         c.close()
 
 
+# Batches none of whose ranges has more than 16 tiles take kernels of their own: batches on both sides of that line, of sequences that
+# are one range (up to 20 tiles) or several, and with scaled queries and V scales of 256 and more
+@pytest.mark.parametrize("tier16", [0, TIER16_INT16])
+@pytest.mark.parametrize("tiles", [(1, 16), (15, 17, 3), (16, 21, 100), (2, 16, 9, 40, 64), (20, 600)])
+def test_batches_around_the_longest_short_range(tiles, tier16):
+    Hq, Hkv = 10, 2
+    built = []
+    for i, n in enumerate(tiles):
+        P, T, v_size = (32, 96)[i % 2], 32 * n - 5, 600.0 if i % 3 == 2 else 1.0
+        oc, gc = make_pair(1, 1, Hq, Hkv, T + 40, P, policy=POLICY_OLDEST_FIRST, tier16=tier16)
+        if i % 3 == 1:
+            lam = (1.0 + np.random.default_rng(5).random((Hkv, 128)) * 3.0).astype(np.float32)
+            oc.set_reparam(0, lam)
+            gc.kvq_cache_set_reparam(0, dev(lam))
+        K, V = kvq_synth.make_kv(420 + i, 0, 1, Hkv, 0, T + 40)
+        V = (V.astype(np.float32) * v_size).astype(np.float16)
+        t = 0
+        for j, bits in zip(range(T // P), (2, 4, 4, 8, 16) * (T // P)):
+            append_both(oc, gc, 0, K[:, :, t:t + P], V[:, :, t:t + P], bits)
+            t += P
+        append_both(oc, gc, 0, K[:, :, t:T], V[:, :, t:T], 16)
+        built.append((oc, gc, K, V, T, v_size))
+    ocs, gcs = [b[0] for b in built], [b[1] for b in built]
+    outs = [torch.empty((1, Hq, 128), dtype=torch.float32, device="cuda") for _ in built]
+
+    def check(want, what):
+        torch.cuda.synchronize()
+        for o, w, b in zip(outs, want, built):
+            mx, rl = attention_errors(o.cpu().numpy(), w)
+            assert mx <= MAX_ABS * b[5] and rl <= REL_L2, (what, mx, rl)
+
+    for step in range(8):  # into the next tile
+        ks = [b[2][:, :, b[4] + step:b[4] + step + 1] for b in built]
+        vs = [b[3][:, :, b[4] + step:b[4] + step + 1] for b in built]
+        qs = [kvq_synth.make_q(420 + i, 0, 1, Hq, b[4] + step) for i, b in enumerate(built)]
+        if step % 3 == 0:
+            kq.kvq_decode_attention_batch(gcs, 0, [dev(q) for q in qs], outs)
+            check([oc.attention(0, q) for oc, q in zip(ocs, qs)], step)
+        want = decode_step_batch(ocs, 0, ks, vs, qs)
+        kq.kvq_append_decode_attention_batch(gcs, 0, [dev(k) for k in ks], [dev(v) for v in vs], [dev(q) for q in qs], outs)
+        check(want, step)
+    for oc, gc in zip(ocs, gcs):
+        assert_same_cache(oc, gc, 0)
+
+
 def test_maximum_batch_of_64_caches():
     """The largest batch the entry points take: 64 caches (1 or 2 sequences each, 2 KV heads) of 1 ... ~700 tokens in
     every mix of widths, three decode steps in one launch each; every cache stays bit-identical to its oracle and every
