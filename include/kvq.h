@@ -273,7 +273,8 @@ kvq_status_t kvq_cache_set_reparam(kvq_cache_t* cache, int32_t layer, const floa
  * token positions of the calibration keys (magnitudes; maxima below 1e-5 count as 1e-5), pow in fp64 rounded to
  * fp32.  k_calib_dev: device, fp16 [batch, n_kv_heads, n_tokens, 128], keys as they would be appended (rotated; for
  * the paper's calibration with positional interpolation, Eq. 10, rotated at positions s * m).  lambda_dev: device,
- * fp32 [n_kv_heads][128], written.  0 <= alpha <= 4.  Needs no cache; enqueues three small kernels on the stream. */
+ * fp32 [n_kv_heads][128], written.  0 <= alpha <= 4.  Needs no cache; enqueues two
+ * kernels on the stream. */
 kvq_status_t kvq_calibrate_lambda(const void* k_calib_dev, int32_t batch, int32_t n_kv_heads, int32_t n_tokens,
                                   float alpha, float* lambda_dev, void* hip_stream);
 
