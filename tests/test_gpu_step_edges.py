@@ -30,6 +30,12 @@ def test_merge_of_any_split_count(g):
     gc.close()
 
 
+@pytest.mark.parametrize("g", [9, 12])
+def test_merge_beyond_the_first_rounds_with_idle_slots(g):
+    """One slot group of 9 or 12 heads: the other slots have no split of their own, also in the rounds beyond the sixteenth."""
+    test_merge_of_any_split_count(g)
+
+
 # 16 tiles a range is the most the kernels for short ranges take: one or two tiles a wavefront, of one width or two, of one page or
 # two neighbouring ones (pages of one and of three tiles), with and without queries scaled by factors and V scales of 256 and more
 @pytest.mark.parametrize("tier16", [0, 1])
