@@ -148,10 +148,15 @@ __device__ __forceinline__ void short_range(const KvqAttnHead& P, const int t_be
     KVQ_STAMP(0);
     KVQ_STAMP_ID();
     uint32_t mark = scalar_load(P.v_mark);
-    // ---- the tiles of this wavefront
-    const int per_wave = (t_end - t_begin + KVQ_ATTN_WAVES - 1) / KVQ_ATTN_WAVES;
-    int t = t_begin + wave * per_wave;
-    const int t_hi = min(t + per_wave, t_end);
+    // ---- the tiles of this wavefront: two where there are more than eight, but of 10 to 12 the first wavefronts take two and the
+    // others one: wavefronts w and w + 4 share a SIMD, and six wavefronts of two tiles would give the first SIMDs four tiles where
+    // three do (12 tiles of 4 bits x 256 units 8.0 -> 7.0 us, of 8 bits 9.1 -> 8.3, of 2 bits x 8 units 6.4 -> 5.6; streaming 7.6, 8.9 and
+    // 7.1).  Of 9 or of 13 and more the fullest SIMD has three or four tiles either way, and byte planes, whose second tile follows the
+    // first, take longer spread (9 tiles x 256 units 9.8 and 10.9 us).
+    const int n_tiles = t_end - t_begin, spread = n_tiles > 9 && n_tiles < 13 ? n_tiles - KVQ_ATTN_WAVES : 0;
+    const int per_wave = spread ? 1 : (n_tiles + KVQ_ATTN_WAVES - 1) / KVQ_ATTN_WAVES;
+    int t = t_begin + wave * per_wave + min(wave, spread);
+    const int t_hi = min(t + per_wave + (wave < spread ? 1 : 0), t_end);
     const int tpp = P.tiles_per_page;
     const u32x4* const table = reinterpret_cast<const u32x4*>(P.table);
     // page entries of the tile t and the one behind it, which may lie in the next page

@@ -79,6 +79,68 @@ def test_ranges_around_the_longest_short_one(page, tier16, scaled):
         gc.close()
 
 
+# of 10 to 12 tiles the first wavefronts take two and the others one
+@pytest.mark.parametrize("tier16", [0, 1])
+@pytest.mark.parametrize("tiles", [10, 11, 12, 13])
+def test_ranges_whose_tiles_are_spread_over_the_wavefronts(tiles, tier16):
+    T, page, g = 32 * tiles - 7, 96, 5
+    oc, gc = make_pair(1, 1, 2 * g, 2, T + 40, page, policy=1, tier16=tier16)
+    K, V = kvq_synth.make_kv(76, 0, 1, 2, 0, T + 40)
+    widths = (4, 2, 16) if tiles % 2 else (8, 8, 4)
+    t = 0
+    for i in range(T // page):
+        append_both(oc, gc, 0, K[:, :, t:t + page], V[:, :, t:t + page], widths[i % 3])
+        t += page
+    append_both(oc, gc, 0, K[:, :, t:T], V[:, :, t:T], 16)
+    q = kvq_synth.make_q(76, 0, 1, 2 * g, T - 1)
+    gc.kvq_cache_set_option(kq.KVQ_OPT_SPLITS, 1)
+    check_attention(oc, gc, 0, q)
+    out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    for _ in range(9):  # into the next tile
+        k, v = K[:, :, T:T + 1], V[:, :, T:T + 1]
+        oc.append(0, k, v, 0)
+        gc.kvq_append_decode_attention(0, dev(k), dev(v), dev(q), out)
+        T += 1
+        ma, rel = attention_errors(out.cpu().numpy(), oc.attention(0, q))
+        assert ma <= MAX_ABS and rel <= REL_L2, T
+    assert_same_cache(oc, gc, 0)
+    gc.close()
+
+
+def _us_per_launch(tiles, bits, units, n=40):
+    gc = make_pair(1, 1, 4 * units, units, 32 * tiles, 64)[1]
+    k = torch.randn((1, units, 32 * tiles, 128), device="cuda").half()
+    gc.kvq_quantize_append(0, k, k, bits)
+    gc.kvq_cache_set_option(kq.KVQ_OPT_SPLITS, 1)
+    q = torch.randn((1, 4 * units, 128), device="cuda").half()
+    out = torch.empty((1, 4 * units, 128), device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        gc.kvq_decode_attention(0, q, out, stream=side)
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            for _ in range(n):
+                gc.kvq_decode_attention(0, q, out, stream=side)
+    times = []
+    for _ in range(12):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        graph.replay()
+        start.record()
+        graph.replay()
+        end.record()
+        torch.cuda.synchronize()
+        times.append(start.elapsed_time(end) * 1000 / n)
+    gc.close()
+    return min(times)
+
+
+def test_no_simd_takes_more_tiles_of_a_short_range_than_it_has_to():
+    """12 tiles are three for each SIMD, 16 four: 5.6 and 6.6 us.  (Two a wavefront from the first on, the first SIMDs take four: 6.4.)"""
+    assert _us_per_launch(12, 2, 8) < 0.93 * _us_per_launch(16, 2, 8)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("splits", [1, 7])
 def test_outputs_that_start_at_any_element(dtype, splits):
