@@ -113,15 +113,19 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(const AppendArgs args)
 // SIMD (1,024 of them) leaves each alone with some 1,000 to 1,700 vector instructions; shared by two it ends earlier, and with half
 // the registers for its rows (88 instead of 112 with angles) more of it fits on a SIMD.  What a pair costs: factors are read twice,
 // and each wavefront gathers the whole string's codes to store half of them (into 2 bits, one chunk a lane, one stores all).
-// kvq_pair_strings draws the line.  Time of one wavefront per string over that of two, calls in a train, rotated keys into 8 / 4 / 2
-// bits: 1,536 strings 1.06 / 1.07 / 1.13, 1,984 1.07 / 1.05 / 1.11, 2,048 1.05 / 0.95 / 1.05, 2,560 1.22 / 1.13 / 1.22, 2,944 1.22 /
-// 1.12 / 1.23, 3,072 1.02 / 0.96 / 1.07, 4,096 1.00 / 0.98 / 1.08, 5,120 1.10 / 1.08 / 1.18, 16,384 1.05 / 0.97 / 1.13, 32,768 1.04 /
-// 0.97 / 1.11; scaled as well: 1,984 1.05 / 1.01 / 1.05, 2,048 0.99 / 0.91 / 0.96, 2,560 1.09 / 1.05 / 1.10, 2,944 1.09 / 1.06 / 1.11,
-// 3,072 0.94 / 0.91 / 0.97, 4,096 0.88 / 0.85 / 0.93, 32,768 0.90 / 0.85 / 0.89; neither: 1,984 1.14 / 1.08 / 1.15, 2,048 1.08 / 0.95 /
-// 1.06, 2,944 1.12 / 1.04 / 1.15, 4,096 1.00 / 0.97 / 1.07, 5,120 0.96 / 0.97 / 1.06, 32,768 1.07 / 0.90 / 0.99.  (16 units x 1,024
-// tokens are 1,024 strings; the first size takes 7.0 us, the last 67.)
+// kvq_pair_strings draws the line: by how the 1,024 SIMDs fill, in steps of 1,024 strings with one wavefront each and of 512 with two.
+// Time of two wavefronts per string over that of one, launches in a train, 16 units x 32 to 110 tiles, over the same input, which the
+// caches hold / over inputs in turn from memory:
+//   into 8 / 4 / 2 bits            2,080 to 2,560 strings                       2,624 to 3,008                               3,136 to 3,520
+//   neither rotated nor scaled     0.90, 0.98, 0.87 / 0.88 to 1.01, 0.95, 0.86  0.96, 1.06, 0.95 / 1.07, 1.00, 0.92  0.91, 1.03, 0.89 / 0.96, 0.93, 0.87
+//   rotated                        0.85, 0.90, 0.83 / 0.83 to 0.93, 0.89, 0.82  0.91, 0.98, 0.87 / 1.02, 0.94, 0.88  0.90, 0.94, 0.85 / 0.90, 0.91, 0.86
+//   scaled                         0.96, 0.99, 0.93 / 0.94, 0.98, 0.90          1.19, 1.21, 1.09 / 1.21, 1.14, 1.05  1.13, 1.17, 1.06 / 1.03, 1.09, 1.03
+//   both                           0.95, 0.98, 0.92 / 0.92, 0.95, 0.89          1.02, 1.05, 0.99 / 1.04, 1.00, 0.97  1.00, 1.03, 0.95 / 0.98, 0.97, 0.93
+// 2,048 and 3,072 fill the SIMDs without a rest either way: 1.03 to 1.30 / 0.98 to 1.25 of 4 bits or scaled.  Below 1,600 all but one of
+// these gain, up to 26 %.  3,500 to 40,000 strings: 8 bits 0.90 to 1.05 / 0.92 to 0.98, 4 bits 0.92 to 1.07 / 0.92 to 0.99, scaled ones from
+// memory 1.00 to 1.07, rotated ones by how often the table is read.
 static bool kvq_pair_strings(int bits, int64_t strings, bool rotated, bool scaled) {
-    if (bits == 4 || scaled) return strings < 2048 || (strings >= 2560 && strings < 3072);  // from 2,560 on a third string per SIMD
+    if (bits == 4 || scaled) return strings != 2048 && strings < (scaled && !rotated ? 2561 : 3072);
     return bits == 2 || rotated || strings < 4608;
 }
 template <int B, bool PLAIN, bool PAIR>
