@@ -871,9 +871,16 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     A.tpp_magic = magic(tiles_per_page);
     A.kv_magic = magic(n_kv_heads);
     A.pages = ap;
+    // A row of the table is read by the L2 of every XCD that a string with its tokens runs on.  Workgroups go to the eight XCDs in
+    // turn, so these are 8 / gcd(8, workgroups of a unit) of them, for an odd number all eight: with two wavefronts per string, a
+    // workgroup a tile, 4 n + 3 tiles then took longer than with one, half as many workgroups.  Up to three idle workgroups a unit make
+    // it a multiple of four.  One wavefront each / two / now, over the same input and from memory: into 8 bits 52 units x 191 tiles 43.0,
+    // 55.6, 39.6 and 56.2, 58.1, 52.4 us, 47 x 127 29.2, 30.3, 26.2 and 37.2, 35.0, 34.0; into 2 bits 39 x 255 41.2, 50.1, 37.1 and 48.6, 49.2, 43.1.
+    // Up to 120 workgroups, some two MB of rows, the caches hold them all the same, and three idle ones are too large a part.
+    const auto workgroups = [&](int n) { return rope && bits < 16 && n > 120 ? (n + 3) / 4 * 4 : n; };
 #define KVQ_APPEND_LAUNCH(kernel_, waves_, per_)                                                                           \
     do {                                                                                                                 \
-        const int n_wg = (n_strings + waves_ - 1) / waves_;                                                              \
+        const int n_wg = workgroups((n_strings + waves_ - 1) / waves_);                                                  \
         const dim3 grid = by_unit ? dim3((unsigned)n_wg * (unsigned)units) : dim3(n_wg, units);                          \
         hipLaunchKernelGGL((kernel_), grid, dim3(64 * waves_ * per_), 0, s, A);                                          \
     } while (0)

@@ -213,3 +213,52 @@ def test_prepared_keys_of_every_number_of_strings(bits, reparam, T):
         gc.close()
         arenas.append(arena)
     assert torch.equal(*arenas)
+
+
+@pytest.mark.parametrize("bits", [8, 4, 2])
+@pytest.mark.parametrize("tiles", [121, 122, 123, 124, 127])
+def test_rotated_keys_of_idle_workgroups(bits, tiles):
+    """Beyond 120 workgroups a unit up to three idle ones follow: the same arena as from calls of 32 tokens, byte for byte."""
+    B, H, T = 1, 3, 32 * tiles - 9
+    g = torch.Generator(device="cuda").manual_seed(87)
+    k, v = (torch.randn((B, H, T, 128), device="cuda", generator=g).half() for _ in range(2))
+    table = torch.randn((T, 128), device="cuda", generator=g)
+    cfg = kq.KvqConfig(1, B, H, H, T, page_tokens=96)
+    arenas = []
+    for step in (T, 32):
+        arena = torch.zeros(kq.kvq_arena_bytes(cfg, T * B * H * 640 + (64 << 20)), dtype=torch.uint8, device="cuda")
+        gc = kq.KvqCache(cfg, [1 << 50], [2], arena=arena)
+        for t in range(0, T, step):
+            gc.kvq_quantize_append_rope(0, *(x[:, :, t:t + step].contiguous() for x in (k, v)), table[t:t + step].contiguous(), bits)
+        torch.cuda.synchronize()
+        gc.close()
+        arenas.append(arena)
+    assert torch.equal(*arenas)
+
+
+def test_time_of_rotated_appends_does_not_depend_on_the_number_of_tiles_beyond_their_work():
+    """191 and 192 tiles x 52 units: with every row of the table read by all eight L2 caches 191 took 1.3 times as long."""
+    H, L = 52, 8
+    k, v = (torch.randn((1, H, 192 * 32, 128), device="cuda").half() for _ in range(2))
+    table = torch.randn((192 * 32, 128), device="cuda")
+    cfg = kq.KvqConfig(L, 1, H, H, 192 * 32, page_tokens=256)
+    arena = torch.empty(kq.kvq_arena_bytes(cfg, L * 192 * 32 * H * 300 + (64 << 20)), dtype=torch.uint8, device="cuda")
+    gc = kq.KvqCache(cfg, [1 << 50] * L, [2] * L, arena=arena)
+
+    def best(tiles):
+        T = 32 * tiles
+        kk, vv = k.view(-1)[:H * T * 128].view(1, H, T, 128), v.view(-1)[:H * T * 128].view(1, H, T, 128)
+        times = []
+        for _ in range(6):
+            gc.kvq_cache_reset(-1)
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for layer in range(L):
+                gc.kvq_quantize_append_rope(layer, kk, vv, table[:T], 8)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+
+    assert best(191) < 1.15 * best(192)
+    gc.close()
