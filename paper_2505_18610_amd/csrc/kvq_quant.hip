@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(const AppendArgs args)
         const int tok0 = t.tile * KVQ_TILE_TOKENS;
         // the page entry is looked up behind the loads of the rows
         const auto code = [&]() {
-            const KvqPageDesc pd = append_desc(A.table, args.pages, t.page);
+            const KvqPageDesc pd = append_desc<false>(A.table, args.pages, t.page);
             return A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + t.which) * (512u * 16);
         };
         if (t.which) kvq_dev::append16_v_tile(code, rows, tok0, lane, lds, A.stream_v);  // (wavefront-uniform)
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
     OwnerAngles angles;
     if (rotates) load_owner_angles(angles, rows, tok0 + 16 * pass0 + (lane >> 2), lane, A.rope);
     __builtin_amdgcn_sched_barrier(0);  // all of these loads first
-    const KvqPageDesc pd = append_desc(A.table, args.pages, t.page);
+    const KvqPageDesc pd = append_desc<PLAIN>(A.table, args.pages, t.page);
     uint8_t* code = A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + which) * (512u * B);
     uint8_t* meta = A.arena + (uint64_t)pd.meta_off256 * 256u + t.tslot * KVQ_META_TILE_BYTES;
     if (rotates) {
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64) void kvq_append_i16_kernel(const AppendArgs arg
     OwnerAngles angles;
     if (rotates) load_owner_angles(angles, rows, tok0 + (lane >> 2), lane, A.rope);
     __builtin_amdgcn_sched_barrier(0);  // all of these loads first
-    const KvqPageDesc pd = append_desc(A.table, args.pages, t.page);
+    const KvqPageDesc pd = append_desc<PLAIN>(A.table, args.pages, t.page);
     uint8_t* code = A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + which) * (512u * 16);
     uint8_t* meta = A.arena + (uint64_t)pd.meta_off256 * 256u + t.tslot * KVQ_META_TILE_BYTES;
     if (rotates) {
