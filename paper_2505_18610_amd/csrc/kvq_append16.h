@@ -113,7 +113,9 @@ struct NewRows {
 // A lane holds all four channel groups of its two tokens, so the rotation's partner channels are its own registers and
 // eight angles serve two groups; all loads are issued before the arithmetic.  (With the angles read one by one and the
 // partner read again, 8,192 new tokens x 32 units took 271 us with rotation against 56 without.)
-template <class Code>
+// LATE: the last eight angles are asked for behind the lookup of the page, which saves the registers for one more wavefront on every
+// SIMD and costs 2 to 4 % where that does not matter.
+template <bool LATE, class Code>
 __device__ inline void append16_k_tile(Code code_at, const NewRows& rows, int tok0, int lane, const float* rope,
                                        const float* rinv_head) {
     const int j = lane >> 4, n = lane & 15;
@@ -133,12 +135,14 @@ __device__ inline void append16_k_tile(Code code_at, const NewRows& rows, int to
         for (int sub = 0; sub < 2; ++sub) {
             const float* row = rope + rows.row(tok0 + 8 * (n >> 2) + 4 * sub + (n & 3)) * KVQ_D;
 #pragma unroll
-            for (int p = 0; p < 2; ++p) a[sub][p] = load_angles8(row, 32 * p + 8 * j);
+            for (int p = 0; p < 2; ++p)
+                if (!LATE || !sub || !p) a[sub][p] = load_angles8(row, 32 * p + 8 * j);
         }
     }
     __builtin_amdgcn_sched_barrier(0);  // all of these loads first
     uint8_t* const code = code_at();
     if (rope) {
+        if (LATE) a[1][1] = load_angles8(rope + rows.row(tok0 + 8 * (n >> 2) + 4 + (n & 3)) * KVQ_D, 32 + 8 * j);
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub)
 #pragma unroll

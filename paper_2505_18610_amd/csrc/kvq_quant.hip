@@ -82,8 +82,11 @@ __device__ __forceinline__ bool append_string(const AppendArgs& A, int wave, App
     return string < A.n_strings;
 }
 
-// Append into the 16-bit tier: the new rows are copied into the tile layout.
-template <bool PLAIN>
+// Append into the 16-bit tier: the new rows are copied into the tile layout.  FIVE: with 92 registers five wavefronts fit on a SIMD,
+// otherwise, with 104, four.  Prepared keys of 4,097 to 4,608 and 5,121 to 5,632 strings, the odd steps of half a wavefront a SIMD beyond
+// four, end earlier with five (16 units x 136 tiles, rotated and scaled, 17.0 us and 19.0, x 164 20.9 and 21.9), those between and beyond
+// with four (x 156 20.6 and 19.4, 8,192 strings and more 2 to 4 %).
+template <bool PLAIN, bool FIVE>
 __global__ __launch_bounds__(64) void kvq_append16_kernel(const AppendArgs args) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[32 * 256];
     const int lane = threadIdx.x;
@@ -100,7 +103,7 @@ __global__ __launch_bounds__(64) void kvq_append16_kernel(const AppendArgs args)
             return A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + t.which) * (512u * 16);
         };
         if (t.which) kvq_dev::append16_v_tile(code, rows, tok0, lane, lds, A.stream_v);  // (wavefront-uniform)
-        else kvq_dev::append16_k_tile(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head);
+        else kvq_dev::append16_k_tile<FIVE>(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head);
     }
     write_fresh_pages(A.table, args.pages, lane);
 }
@@ -854,7 +857,8 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     const bool plain = !rinv && !rope;
     const uint16_t* k = static_cast<const uint16_t*>(k_in);
     const uint16_t* v = static_cast<const uint16_t*>(v_in);
-    const bool pair = kvq_pair_strings(bits, (int64_t)n_strings * units, rope != nullptr, rinv != nullptr);
+    const int64_t strings = (int64_t)n_strings * units;
+    const bool pair = kvq_pair_strings(bits, strings, rope != nullptr, rinv != nullptr);
     // How the 16-bit tier's V rows are read: new values have usually just been written and lie in the caches, which streaming
     // loads make less of.  128 units x 2,000 tokens (131 MB of keys and values) 43 us with plain loads of V and 51 with streaming
     // ones, 64 x 2,000 21 and 25, 32 x 2,000 10.9 and 12.6 (from 230 MB of buffers in turn 13.4 and 13.0), 600 x 50 12.1 and 13.0,
@@ -862,6 +866,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     // MB) 86 and 85, from buffers in turn 102 and 94.  Beside keys that are prepared, streaming is the better or the same: 32 x
     // 2,000 16.0 and 16.0, from buffers in turn 18.9 and 15.8.
     const int stream_v = !plain || (int64_t)units * n_new * (2 * 256) > (192 << 20);
+    const bool five = strings > 4096 && strings <= 5632 && (strings + 511) / 512 % 2 == 1;  // see kvq_append16_kernel
     const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 ? units : 0;
     AppendArgs A;
     A.arena = arena; A.table = table; A.k = k; A.v = v; A.rinv = rinv; A.rope = rope; A.v_word = mark.word; A.v_epoch = mark.epoch;
@@ -890,8 +895,9 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
             else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, 1);
             break;
         case 16:
-            if (plain) KVQ_APPEND_LAUNCH(kvq_append16_kernel<true>, 1, 1);
-            else KVQ_APPEND_LAUNCH(kvq_append16_kernel<false>, 1, 1);
+            if (plain) KVQ_APPEND_LAUNCH((kvq_append16_kernel<true, false>), 1, 1);
+            else if (five) KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, true>), 1, 1);
+            else KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, false>), 1, 1);
             break;
 #define KVQ_APPEND_CASE(b_)                                                                                              \
         case b_:                                                                                                         \

@@ -236,6 +236,35 @@ def test_rotated_keys_of_idle_workgroups(bits, tiles):
     assert torch.equal(*arenas)
 
 
+@pytest.mark.parametrize("rope,reparam", [(True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("tiles", [32, 33, 36, 37, 40, 41, 44, 45])
+def test_prepared_keys_into_16_bits_of_every_number_of_strings(tiles, rope, reparam):
+    """64 units x 32 to 45 tiles are 4,096 to 5,760 strings, between which two kernels take turns: the same arena as from pieces of 96
+    tokens, byte for byte."""
+    B, H, T, P = 8, 8, 32 * tiles - 5, 64
+    g = torch.Generator(device="cuda").manual_seed(88)
+    k, v = (torch.randn((B, H, T, 128), device="cuda", generator=g).half() for _ in range(2))
+    table = torch.randn((T, 128), device="cuda", generator=g)
+    lam = 1 + torch.rand((H, 128), device="cuda", generator=g)
+    cfg = kq.KvqConfig(1, B, H, H, T, page_tokens=P)
+    arenas = []
+    for step in (T, 96):
+        arena = torch.zeros(kq.kvq_arena_bytes(cfg, T * B * H * 640 + (64 << 20)), dtype=torch.uint8, device="cuda")
+        gc = kq.KvqCache(cfg, [1 << 50], [2], arena=arena)
+        if reparam:
+            gc.kvq_cache_set_reparam(0, lam)
+        for t in range(0, T, step):
+            kk, vv = (x[:, :, t:t + step].contiguous() for x in (k, v))
+            if rope:
+                gc.kvq_quantize_append_rope(0, kk, vv, table[t:t + step].contiguous(), 16)
+            else:
+                gc.kvq_quantize_append(0, kk, vv, 16)
+        torch.cuda.synchronize()
+        gc.close()
+        arenas.append(arena)
+    assert torch.equal(*arenas)
+
+
 def test_time_of_rotated_appends_does_not_depend_on_the_number_of_tiles_beyond_their_work():
     """191 and 192 tiles x 52 units: with every row of the table read by all eight L2 caches 191 took 1.3 times as long."""
     H, L = 52, 8
