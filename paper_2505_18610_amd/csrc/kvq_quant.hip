@@ -899,16 +899,16 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
             else if (five) KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, true>), 1, 1);
             else KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, false>), 1, 1);
             break;
-#define KVQ_APPEND_CASE(b_)                                                                                              \
+#define KVQ_APPEND_CASE(b_, plain_alone_)                                                                                \
         case b_:                                                                                                         \
             if (plain && pair) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true, true>), 2, 2);                           \
-            else if (plain) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, true, false>), KVQ_APPEND_WG_WAVES, 1);           \
+            else if (plain) plain_alone_;                                                                                \
             else if (pair) KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false, true>), 2, 2);                              \
             else KVQ_APPEND_LAUNCH((kvq_append_q_kernel<b_, false, false>), KVQ_APPEND_WG_WAVES, 1);                     \
             break;
-        KVQ_APPEND_CASE(8)
-        KVQ_APPEND_CASE(4)
-        KVQ_APPEND_CASE(2)
+        KVQ_APPEND_CASE(8, KVQ_APPEND_LAUNCH((kvq_append_q_kernel<8, true, false>), KVQ_APPEND_WG_WAVES, 1))
+        KVQ_APPEND_CASE(4, KVQ_APPEND_LAUNCH((kvq_append_q_kernel<4, true, false>), KVQ_APPEND_WG_WAVES, 1))
+        KVQ_APPEND_CASE(2, return hipErrorInvalidValue)  // (kvq_pair_strings: such strings are always shared)
         default: return hipErrorInvalidValue;
     }
 #undef KVQ_APPEND_CASE

@@ -62,3 +62,10 @@ def test_wavefronts_that_the_launch_rules_count_on(kernels):
         assert per_simd(f"kvq_append_q_kernel<{bits}, false, true>", 4) == 5
     for mode in range(4):
         assert per_simd(f"kvq_error_kernel<{mode}>", 4) == 4
+
+
+def test_no_kernel_that_no_launch_reaches(kernels):
+    """Strings into 2 bits that need no preparation are always shared by two wavefronts."""
+    assert {n for n in kernels if n.startswith("kvq_append_q_kernel")} == {
+        f"kvq_append_q_kernel<{bits}, {plain}, {pair}>" for bits in (8, 4, 2) for plain in ("true", "false") for pair in ("true", "false")
+        if (bits, plain, pair) != (2, "true", "false")}
