@@ -103,6 +103,20 @@ __device__ __forceinline__ void short_tiles(WaveState& st, QOps& Q, u32x4 (&qraw
     asm volatile("" : "+s"(n));
     // (opaque: the operands of all widths would be arranged in front of the loads)
     asm volatile("" : "+v"(qraw[0]), "+v"(qraw[1]), "+v"(qraw[2]), "+v"(qraw[3]));
+#ifdef KVQ_NO_ARITHMETIC  // every load issued and waited for in the same order, no tile computed on (kvq_attention_body.h)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if (k == 1 && n < 2) break;
+        keep_loaded(kw[k]);
+        if constexpr (has_meta<B>()) keep_loaded(m[k]);
+        if (W == 16 && k == 0 && n > 1) {
+            if (B == KVQ_I16) load_k(1);
+            else load_v(1);
+        }
+        keep_loaded(vw[k]);
+        if (B == KVQ_I16 && k == 0 && n > 1) load_v(1);
+    }
+#else
     arrange_q<q_class<B>()>(Q, qraw);
     if constexpr (has_meta<B>()) sum_q(Q, qraw, lane, scale_log2);
     if (fresh) st.oexp = v_exponent<B>(st.safe_v);
@@ -137,6 +151,7 @@ __device__ __forceinline__ void short_tiles(WaveState& st, QOps& Q, u32x4 (&qraw
         }
     }
     if constexpr (has_meta<B>()) wave_lds_sync();
+#endif
 }
 
 template <bool I16, bool APPEND>

@@ -69,3 +69,21 @@ def test_no_kernel_that_no_launch_reaches(kernels):
     assert {n for n in kernels if n.startswith("kvq_append_q_kernel")} == {
         f"kvq_append_q_kernel<{bits}, {plain}, {pair}>" for bits in (8, 4, 2) for plain in ("true", "false") for pair in ("true", "false")
         if (bits, plain, pair) != (2, "true", "false")}
+
+
+def test_the_build_without_arithmetic_has_none(tmp_path):
+    """libkvq_noarith.so times loads, join and merge alone: not one of its attention kernels multiplies on the matrix cores."""
+    from paper_2505_18610_amd.build import NOARITH_LIB
+    tool = os.path.join(LLVM, "llvm-objdump")
+    if not (os.path.exists(tool) and os.path.exists(NOARITH_LIB)):
+        pytest.skip("no llvm-objdump, or the measurement build is not there")
+
+    def products(lib):
+        n = 0
+        for i, code in enumerate(code_objects(lib)):
+            path = tmp_path / f"object{i}"
+            path.write_bytes(code)
+            n += subprocess.run([tool, "-d", str(path)], capture_output=True, text=True, check=True).stdout.count("v_mfma_")
+        return n
+
+    assert products(kq.library_path()) > 0 and products(NOARITH_LIB) == 0
