@@ -230,6 +230,8 @@ __device__ inline uint32_t pack_rn(float a, float b) {  // two floats -> packed 
     return __builtin_bit_cast(uint32_t, h);
 }
 
+// SHUFFLE: the sums go through LDS instead of row swaps, which byte planes have no registers to spare for.
+template <bool SHUFFLE>
 __device__ inline void load_q_ops(QOps& Q, const _Float16* q_lds, int lane, int cls, float scale_log2) {
     const int j = lane >> 4, n = lane & 15;
     const _Float16* row = q_lds + n * KVQ_D;
@@ -251,7 +253,12 @@ __device__ inline void load_q_ops(QOps& Q, const _Float16* q_lds, int lane, int 
             Q.q[grp][v] = __builtin_bit_cast(uint32_t, h);
         }
         if (!Q.have_qsum) {  // sum of q over the group's 32 channels: 8 here, the rest in the other quarters
-            sum = across_halves<Sum>(across_rows<Sum>(sum));
+            if (SHUFFLE) {
+                sum += __shfl_xor(sum, 16);
+                sum += __shfl_xor(sum, 32);
+            } else {
+                sum = across_halves<Sum>(across_rows<Sum>(sum));
+            }
             sum *= scale_log2;  // the zero-point term then needs no scaling after its MFMA
             _Float16 h = (_Float16)sum;
             _Float16 l = (_Float16)(sum - (float)h);
@@ -692,7 +699,7 @@ __device__ inline void run_chunks(WaveState& st, QOps& Q, const _Float16* q_lds,
         load_string<2 * W>(cur.code + 512u * W, c.lane_off, vw);
         // the query operands are arranged afresh at the start of every run, also when the last run had the same
         // arrangement: carried from run to run they would occupy 16 registers across the dispatch in between
-        load_q_ops(Q, q_lds, lane, q_class<B>(), c.scale_log2);
+        load_q_ops<B == KVQ_I16>(Q, q_lds, lane, q_class<B>(), c.scale_log2);
         for (;;) {
             float s[1][2][4];
             uint32_t pop[1][4];
@@ -747,7 +754,7 @@ __device__ inline void run_chunks(WaveState& st, QOps& Q, const _Float16* q_lds,
         Stage<B, TPI> sg[N];
         issue_stage<B, TPI>(sg[0], c, c.next);
         advance_begin(c);
-        load_q_ops(Q, q_lds, lane, B, c.scale_log2);  // afresh in every run, see above
+        load_q_ops<false>(Q, q_lds, lane, B, c.scale_log2);  // afresh in every run, see above
         advance_end(c);
         int n_live = 1, head = 0;
         // (the run is left by jumps, not by flags: a flag-guarded chain of steps would give the control-flow
@@ -1096,12 +1103,17 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
 
     // ---- wavefront epilogue: true values (the exponent taken off, an exact power of two) with the zero-point term added,
     // denominator; the partial goes to LDS
+    // (Row swaps in the streaming kernels of the raw tier, shuffles elsewhere: the former have the compiler copy the accumulators once
+    // more where the widths' paths meet, the latter cost narrow tiles more than that.  Swaps and shuffles, 235 units x 21 tiles of the integer
+    // tier 18.6 and 18.3 us, 193 x 17 14.4 and 14.0, 270 x 8 of 2 bits 9.0 and 8.9; 230 x 20 of 2 bits streamed 7.9 and 8.1.)
+    constexpr bool SHUFFLE = I16 || SCORED;
     const RowPair zl0 = swap_rows(st.zl[0]);
-    const float l_w = swap_halves(zl0.odd).even;  // of lanes 16 .. 31
+    const float l_w = SHUFFLE ? __shfl(st.zl[0], 16 + n) : swap_halves(zl0.odd).even;  // of lanes 16 .. 31
     {
-        const float z0 = swap_halves(zl0.even).even, z1 = swap_halves(swap_rows(st.zl[1]).even).even,
-                    z2 = swap_halves(swap_rows(st.zl[2]).even).even, z3 = swap_halves(swap_rows(st.zl[3]).even).even;  // of lanes 0 .. 15
-        const float f = __builtin_ldexpf(1.0f, -st.oexp), z[4] = {z0, z1, z2, z3};
+        float z[4];  // of lanes 0 .. 15
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = SHUFFLE ? __shfl(st.zl[e], n) : swap_halves(swap_rows(st.zl[e]).even).even;
+        const float f = __builtin_ldexpf(1.0f, -st.oexp);
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt)
 #pragma unroll
