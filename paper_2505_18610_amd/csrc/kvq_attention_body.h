@@ -868,7 +868,7 @@ __device__ inline void store_out(const KvqAttnHead& P, size_t at, float4v x) {
 
 // Up to K splits per slot group, all loads of the partial outputs first; what the code branches on is uniform.
 template <int K, int AUX>
-__device__ inline float4v merge_sum(const MergeLane& t, int d4, int ns, int groups, int rounds, __amdgpu_buffer_rsrc_t slab, const u32x2 (&ml)[4],
+__device__ inline float4v merge_sum(const MergeLane& t, int d4, int ns, int groups, __amdgpu_buffer_rsrc_t slab, const u32x2 (&ml)[4],
                                     float* f_lds, float* l_out) {
     const uint32_t step = (uint32_t)groups * (16 * KVQ_D * 4);
     float4v v[K];
@@ -903,11 +903,12 @@ __device__ inline float4v merge_sum(const MergeLane& t, int d4, int ns, int grou
 #pragma unroll
     for (int k = 0; k < K; ++k) acc += v[k] * w[k];
     if constexpr (K == 16) {
-        // The number of rounds is uniform and idle slots stay out.  (Each lane counting to its own end, the loop ran under a mask
-        // that changed from round to round: 128 splits of 2,790 tiles of 16 bits x 2 units of 12 heads 35.2 us, now 33.0; 88 of 6,164 of 2
-        // bits x one unit 27.2 and 25.5.)
-        if (t.sgi < groups) {
-            for (int k0 = K; k0 < rounds; k0 += 8) {
+        // The number of rounds is a wavefront's, that of its first slot, and idle wavefronts stay out.  (Each lane counting to its own end,
+        // the loop ran under a mask that changed from round to round: 128 splits of 2,790 tiles of 16 bits x 2 units of 12 heads 35.2 us, now
+        // 33.0; 88 of 6,164 of 2 bits x one unit 27.2 and 25.5.)
+        const int first = __builtin_amdgcn_readfirstlane(t.sgi);
+        if (first < groups) {
+            for (int k0 = K; first + k0 * groups < ns; k0 += 8) {
                 float4v x[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
@@ -943,11 +944,11 @@ __device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, con
         if (32 * k < ns) ml[k] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(pairs, (int)(t.ml_off + k * 32 * 32 * 4), 0, AUX));
     float4v acc;
     float l;
-    if (P.merge_rounds <= 2) acc = merge_sum<2, AUX>(t, d4, ns, groups, P.merge_rounds, slab, ml, f_lds, &l);
-    else if (P.merge_rounds <= 4) acc = merge_sum<4, AUX>(t, d4, ns, groups, P.merge_rounds, slab, ml, f_lds, &l);
-    else if (P.merge_rounds <= 8) acc = merge_sum<8, AUX>(t, d4, ns, groups, P.merge_rounds, slab, ml, f_lds, &l);
-    else if (P.merge_rounds <= 12) acc = merge_sum<12, AUX>(t, d4, ns, groups, P.merge_rounds, slab, ml, f_lds, &l);
-    else acc = merge_sum<16, AUX>(t, d4, ns, groups, P.merge_rounds, slab, ml, f_lds, &l);
+    if (P.merge_rounds <= 2) acc = merge_sum<2, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    else if (P.merge_rounds <= 4) acc = merge_sum<4, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    else if (P.merge_rounds <= 8) acc = merge_sum<8, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    else if (P.merge_rounds <= 12) acc = merge_sum<12, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
+    else acc = merge_sum<16, AUX>(t, d4, ns, groups, slab, ml, f_lds, &l);
     const float inv = 1.0f / l;
     if (groups > 1) {  // combine the slot groups in a fixed order
         if (t.sgi > 0 && t.sgi < groups) *reinterpret_cast<float4v*>(rec_lds + (size_t)(t.slot * 32 + d4) * 4) = acc;
