@@ -168,12 +168,11 @@ __device__ __forceinline__ void short_range(const KvqAttnHead& P, const int t_be
     // three do (12 tiles of 4 bits x 256 units 8.0 -> 7.0 us, of 8 bits 9.1 -> 8.3, of 2 bits x 8 units 6.4 -> 5.6; streaming 7.6, 8.9 and
     // 7.1).  Of 9 or of 13 and more the fullest SIMD has three or four tiles either way, and byte planes, whose second tile follows the
     // first, take longer spread (9 tiles x 256 units 9.8 and 10.9 us).
-    const int n_tiles = t_end - t_begin, per_wave = (n_tiles + KVQ_ATTN_WAVES - 1) / KVQ_ATTN_WAVES;
-    int t = t_begin + wave * per_wave, t_hi = min(t + per_wave, t_end);
-    if ((unsigned)(n_tiles - 10) < 3u) {
-        t = t_begin + wave + min(wave, n_tiles - KVQ_ATTN_WAVES);
-        t_hi = t + 1 + (wave < n_tiles - KVQ_ATTN_WAVES ? 1 : 0);
-    }
+    const int n_tiles = t_end - t_begin;
+    // (wavefronts that take two, a digit for each number of tiles from 1 to 16; as compares and selects they cost steps 1 %)
+    const int twos = (int)(0x8888432800000000ull >> (4 * ((n_tiles - 1) & 15))) & 15;
+    int t = t_begin + wave + min(wave, twos);
+    const int t_hi = min(t + 1 + (wave < twos ? 1 : 0), t_end);
     const int tpp = P.tiles_per_page;
     const u32x4* const table = reinterpret_cast<const u32x4*>(P.table);
     // page entries of the tile t and the one behind it, which may lie in the next page
