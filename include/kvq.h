@@ -282,7 +282,8 @@ kvq_status_t kvq_calibrate_lambda(const void* k_calib_dev, int32_t batch, int32_
  * to compare the bit-width shrinking strategies of Sec. 4.3.1): sq_err_host[0] = sum over all cached K elements of
  * (K_hat - K)^2 with K_hat = code * S + Z (raw value in the 16-bit tier), sq_err_host[1] the same for V.
  * k_ref_dev, v_ref_dev: device, fp16 [batch, n_kv_heads, n_tokens, 128] with n_tokens the block's current length.
- * sq_err_host: host, 2 doubles.  Squares are added in fp32 over 32 channels of a token and in fp64 beyond.
+ * sq_err_host: host, 2 doubles.  Squares are added in fp32 over 32 elements (4 channels of every second one of 16 tokens)
+ * and in fp64 beyond.
  * Enqueues on the stream, then waits for it (like kvq_cache_export_segment).  KVQ_E_STATE on an empty block or an
  * accounting-only cache. */
 kvq_status_t kvq_cache_sq_error(kvq_cache_t* cache, int32_t layer, const void* k_ref_dev, const void* v_ref_dev,
@@ -293,8 +294,8 @@ kvq_status_t kvq_cache_sq_error(kvq_cache_t* cache, int32_t layer, const void* k
  * value in the 16-bit tier); s_{i,b} of Eq. 5 is their sum for block i held at width b.  k_ref_dev, v_ref_dev as in
  * kvq_cache_sq_error; gk_dev, gv_dev: device, fp32 [batch, n_kv_heads, n_tokens, 128], the gradients of the loss with
  * respect to K and V, or NULL for all-ones (no model at hand: plain L1 reconstruction error).  For a block with
- * reparameterization the stored keys are K Lambda^-1: pass references in that space.  fp32 over 32 channels of a token,
- * fp64 beyond.  Enqueues on the stream, then waits for it. */
+ * reparameterization the stored keys are K Lambda^-1: pass references in that space.  fp32 over 32 elements (4 channels of
+ * every second one of 16 tokens), fp64 beyond.  Enqueues on the stream, then waits for it. */
 kvq_status_t kvq_cache_sensitivity(kvq_cache_t* cache, int32_t layer, const void* k_ref_dev, const void* v_ref_dev,
                                    const float* gk_dev, const float* gv_dev, double* s_host, void* hip_stream);
 

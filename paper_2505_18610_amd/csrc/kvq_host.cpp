@@ -812,9 +812,10 @@ int merge_loads(int gqa, int n) {
 //   the merge    1.8 for publishing, ticket and the last workgroup's trip to memory, 0.02 per split (tickets on one counter come
 //                in turn), 0.06 per load a thread issues, 0.7 for every further round of eight beyond 16
 // Fitted to launches of 1, 2, 4, ... 128 units of 8 to 1,024 tiles at each width in 1 to 64 splits (5 query heads per KV head;
-// 320 launches): the choice is 1.1 % slower than the best count tried, 14 % at worst.  48 tiles of 4 bits x 8 units take 6.6 us in 12
-// splits, 7.2 in 8, 8.2 in 4; 128 tiles x 1 unit 7.2 in 32, 7.4 in 16, 8.3 in 8; 12 tiles of 4 bits 6.1 in one and 6.0 in three;
-// 16 query heads per KV head, 512 tiles of 16 bits x 1 unit 11.1 in 32, 12.7 in 48 and 14.3 in 16 or 64.
+// 320 launches, when a further round took a little longer than now): the choice is 1.1 % slower than the best count tried, 14 % at
+// worst.  48 tiles of 4 bits x 8 units take 6.7 us in 12 splits, 7.3 in 8, 7.7 in 4; 128 tiles x 1 unit 7.3 in 32, 7.5 in 16, 8.9 in 8; 12
+// tiles of 4 bits 5.6 in one and 6.6 in three; 16 query heads per KV head, 512 tiles of 16 bits x 1 unit 12.6 in 32, 13.2 in 48, 14.0 in 64
+// and 15.7 in 16.
 int planned_splits(const kvq_cache* c, const TileCensus& t, int n_tiles, int max_splits) {
     max_splits = std::max(1, std::min(max_splits, std::min(n_tiles, KVQ_MAX_SPLITS)));
     int best = 1;
@@ -839,6 +840,11 @@ int planned_splits(const kvq_cache* c, const TileCensus& t, int n_tiles, int max
 // merge issues all its loads in one round.  More than eight query heads per KV head leave the merge one slot group, which loads
 // 16 splits a round: beyond 16 splits a range of such a unit keeps 16 tiles.  A count a little above the 16 of every slot group,
 // which cost one round of the merge's loads, is brought down to it.
+// Measured in launches of one cache on the streaming kernels with the merge they had then (us): 10 tiles 6.9 in one split and 8.7 at best
+// in several, 20 of 16 bits 9.1 and 9.0, 32 10.3 and 9.5, 24 of mixed widths 9.3 in eight and 11.0 in two, 79 of 16 bits 10.6 in 16 and 11.9
+// in five, 128 of 2 bits 10.8 in 12 and 11.5 in eight; 1,000 of 2 bits, 4 heads, one unit 13.2 in 63 and 14.8 in 35, four units 15.2 and 14.9;
+// 16 heads, 256 of 16 bits x 8 units 14.3 in 16 and 15.7 in 31; 1,500 of 8 bits x 3 units 15.7 in 64 and 16.3 in 68.  (Ranges of 17 to 20 tiles,
+// which this leaves whole, keep a batch from the kernels for short ranges.)
 int useful_batch_splits(const kvq_cache* c, uint64_t time, int n_tiles, int max_wgs) {
     if (n_tiles <= 20) return 1;
     const int groups = std::max(1, 16 / c->gqa), per16 = (n_tiles + 15) / 16;
@@ -876,8 +882,11 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
         // eight tiles weighs as much there.
         const TileCensus t = tile_census(c, L, n_tiles);
         int wgs = c->target_workgroups;
-        // Where three quarters do not divide into the units, 128 of them, one workgroup a unit would leave half of the compute units
-        // idle: 48 tiles of 16 bits 17.4 us in two splits and 20.0 in one, 128 of 4 bits 18.7 and 23.0.
+        // Where the splits that three quarters give a unit leave three eighths of the compute units idle or more (39, 49 to 53, 65 to 79
+        // and 97 to 128 units), all of them take part.  With three quarters and with all, 4 heads: 39 units x 900 tiles of 4 bits 36.8 and 34.3
+        // us, 51 x 700 37.1 and 34.9, 65 x 600 44.1 and 36.5, 76 x 500 38.9 and 36.6, 97 x 400 52.5 and 37.4, 112 x 400 52.7 and 42.9, 128 x 300
+        // 41.9 and 37.2; 39 x 200 of 16 bits 24.8 and 24.0, 51 x 150 24.4 and 23.8, 65 x 120 26.4 and 24.4, 76 x 100 24.1 and 23.5, 97 x 80 29.6
+        // and 23.6, 112 x 64 25.0 and 22.4, 128 x 64 25.9 and 25.3.
         if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs && wgs * 3 / 4 / c->units * c->units * 8 >= wgs * 5)
             wgs = wgs * 3 / 4;
         n_splits = planned_splits(c, t, n_tiles, wgs / c->units);

@@ -588,9 +588,9 @@ __device__ inline void rows_of_raw(uint8_t* lds, const uint8_t* code, int which,
 
 // Over a block's stored tokens, with x_hat = code * S + Z (or the raw value of a 16-bit tile) and x the reference fp16
 // tensor [unit][token][128]: partial[2 * workgroup + which] = sum over the workgroup's share of K (which = 0), V (1) of
-//   L1 = false: (x_hat - x)^2
-//   L1 = true:  |g * (x_hat - x)| (g = 1 if no gradient tensor [unit][token][128] fp32 is given), the terms of the
-//               sensitivity of Sec. 3.2, Eq. 5
+//   KVQ_ERR_SQ: (x_hat - x)^2
+//   KVQ_ERR_L1, _L1_GRAD, _L1_ONE_GRAD: |g * (x_hat - x)|, the terms of the sensitivity of Sec. 3.2, Eq. 5, with gradient tensors
+//               [unit][token][128] fp32 for none, both or one of K and V (g = 1 where there is none)
 // fp32 over 32 elements of a lane (eight tokens x 4 channels), fp64 beyond; the host adds the workgroups up in order.
 //
 // Bound by the references and gradients (4 + 8 bytes per cached token and channel against at most 2 of codes), which are
@@ -600,9 +600,9 @@ __device__ inline void rows_of_raw(uint8_t* lds, const uint8_t* code, int which,
 // the codes on: with eight the kernel would spill at four wavefronts per SIMD, which is also what the LDS holds.  (With a
 // lane taking 32 channels of a token a load instruction touched 64 lines, four instructions one after the other the same
 // ones, and nothing was asked for before the codes were in LDS.)  A fixed number of workgroups strides over the strings and
-// leaves two numbers each, without atomics.  Whole calls, of which launch and synchronization are some 11 us, before and
-// now: 64 units x 2,048 tokens at 4 bits with gradients (219 MB) 48.1 and 45.9 us, without 36.1 and 32.5, 128 x 4,096 (880 MB)
-// 158 and 142 (6.7 TB/s) and 69 and 65; the integer tier with gradients 57 and 55; streaming loads against plain ones 142 and 155.
+// leaves two numbers each, without atomics.  Whole calls, of which launch and synchronization are some 11 us, with a lane's 32
+// channels and now: 64 units x 2,048 tokens at 4 bits with gradients (219 MB) 53.2 and 47.9 us, without 31.0 and 27.3, 128 x 4,096 (880 MB)
+// 157 and 142 and 69 and 65; the integer tier with gradients 57 and 55; streaming loads against plain ones 142 and 155.
 #define KVQ_ERR_WAVES 4
 #define KVQ_ERR_AHEAD 6
 enum { KVQ_ERR_SQ, KVQ_ERR_L1, KVQ_ERR_L1_GRAD, KVQ_ERR_L1_ONE_GRAD };  // (one: K or V comes without gradients)

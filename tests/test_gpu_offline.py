@@ -116,6 +116,25 @@ def test_the_power_of_the_maximum_is_the_maximum_of_the_powers(B, H, T, alpha):
     assert torch.allclose(lam.double(), K.abs().amax(dim=(0, 2)).double().clamp(min=floor) ** power, rtol=1.2e-7, atol=0)
 
 
+@pytest.mark.parametrize("bits", [0x7e00, 0xfe00, 0x7c01, 0xffff])
+@pytest.mark.parametrize("B,H,T", [(5, 3, 700), (40, 3, 20)])
+def test_calibration_passes_over_what_is_no_number(B, H, T, bits):
+    """NaN of either kind and sign, in the row group, slice and sequence that hold a channel's maximum and elsewhere: the maximum of the rest."""
+    K = torch.randn((B, H, T, 128), generator=torch.Generator("cuda").manual_seed(65), device="cuda", dtype=torch.float16)
+    K[3, 1, 7, 20] = 50.0
+    rest = K.clone()
+    at = ((3, 1, 7 + 8, 20), (3, 1, 6, 20), (0, 1, 0, 20), (B - 1, 2, T - 1, 127), (2, 0, 5, 0))
+    for i in at:
+        K.view(torch.int16)[i] = bits - 0x10000 if bits >= 0x8000 else bits
+        rest[i] = 0.0
+    K.view(torch.int16)[:, 2, :, 64] = 0x7e00  # a channel without a number: the floor
+    rest[:, 2, :, 64] = 0.0
+    lam, want = (torch.full((H, 128), -1.0, device="cuda") for _ in range(2))
+    kq.kvq_calibrate_lambda(K, 0.5, lam)
+    kq.kvq_calibrate_lambda(rest, 0.5, want)
+    assert torch.equal(lam, want)
+
+
 def test_calibration_time_does_not_depend_on_how_the_tokens_are_cut_into_sequences():
     """131,072 tokens of 8 heads as 64 sequences and as 131,072."""
     K = torch.randn((131072, 8, 1, 128), dtype=torch.float16, device="cuda")
