@@ -83,6 +83,10 @@ struct Page {
     uint32_t meta_unit = 0; // valid when the page has metadata (bits < 16, or the integer 16-bit tier)
 };
 
+struct Run {  // neighbouring pages of one width
+    int page_end, bits;
+};
+
 struct Layer {
     uint64_t budget = 0;
     int fbit = 2;
@@ -90,8 +94,14 @@ struct Layer {
     bool reparam = false;  // keys stored as K / lambda, queries multiplied by lambda (Sec. 3.3)
     bool poisoned = false; // an enqueue failed after the host tables had been updated: unusable until kvq_cache_reset
     std::vector<Page> pages;
-    // split plan cache of kvq_decode_attention
+    // the pages as runs of one width, of the state runs_version; see runs_of
+    std::vector<Run> runs;
+    uint64_t runs_version = ~0ull;
+    // what the split count was worked out from and the count itself; split plan cache of kvq_decode_attention
+    uint64_t count_key[3] = {};
+    int count_splits = 1;
     int plan_tiles = -1, plan_splits = 0;
+    bool plan_side_by_side = false;
     uint64_t version = 0, plan_version = ~0ull;
     int32_t split_begin[KVQ_MAX_SPLITS + 1];
 };
@@ -385,41 +395,85 @@ void build_segments(const kvq_cache* c, const Layer& L, std::vector<kvq_segment_
 // bytes).
 int cost_index(int bits) { return bits == 16 ? 3 : bits == 8 ? 2 : bits == 4 ? 1 : 0; }
 
-// Cost-balanced split of the tile range (n_splits <= n_tiles, or one split of nothing).  The last range is never empty: the
-// workgroup that holds the last tile is the one that stores the token a launch appends, behind its own reads of that tile.
-void plan_splits(kvq_cache* c, Layer& L, int n_tiles, int n_splits) {
-    if (L.plan_tiles == n_tiles && L.plan_splits == n_splits && L.plan_version == L.version) return;
+// Tiles of the longest of n ranges of the same number of tiles, as plan_splits cuts them for the kernels for short ranges.
+int longest_even(int n_tiles, int n, int tpp) {
+    const int k = (n_tiles + n - 1) / n;
+    return n > 1 && tpp % 2 == 0 ? (k + 1) & ~1 : k;
+}
+// Launch plans look at widths only, of which a block of thousands of pages has a few runs.  An append extends them, a page that goes
+// down makes them stale.  (131,000 tokens in pages of 32, a step a launch: looking at every page cost the host 7 of 31 us.)
+const std::vector<Run>& runs_of(Layer& L) {
+    if (L.runs_version != L.version) {
+        L.runs.clear();
+        for (size_t i = 0; i < L.pages.size(); ++i) {
+            if (L.runs.empty() || L.runs.back().bits != L.pages[i].bits) L.runs.push_back(Run{(int)i + 1, L.pages[i].bits});
+            else L.runs.back().page_end = (int)i + 1;
+        }
+        L.runs_version = L.version;
+    }
+    return L.runs;
+}
+
+// Ranges of about the same sum of cost[cost_index(width)], none of more than `most` tiles, written to split_begin.
+void cut_by_cost(const kvq_cache* c, Layer& L, int n_tiles, int n_splits, const uint64_t (&costs)[4], int most) {
     const int tpp = c->tpp;
+    const std::vector<Run>& runs = runs_of(L);
+    const auto tiles_to = [&](const Run& r) { return (int)std::min<int64_t>((int64_t)r.page_end * tpp, n_tiles); };
     uint64_t total = 0;
-    for (size_t i = 0; i < L.pages.size(); ++i) {
-        int nt = std::min(tpp, n_tiles - (int)i * tpp);
-        if (nt <= 0) break;
-        int b = L.pages[i].bits;
-        total += (uint64_t)nt * (uint64_t)c->tile_cost[cost_index(b)];
+    int done = 0;
+    for (const Run& r : runs) {
+        total += (uint64_t)(tiles_to(r) - done) * costs[cost_index(r.bits)];
+        done = tiles_to(r);
     }
     int sp = 1;
     L.split_begin[0] = 0;
     uint64_t cum = 0;
-    for (size_t i = 0; i < L.pages.size() && sp < n_splits; ++i) {
-        int nt = std::min(tpp, n_tiles - (int)i * tpp);
+    done = 0;
+    for (size_t i = 0; i < runs.size() && sp < n_splits; ++i) {
+        const int nt = tiles_to(runs[i]) - done;
         if (nt <= 0) break;
-        uint64_t cost = (uint64_t)c->tile_cost[cost_index(L.pages[i].bits)];
-        uint64_t page_end = cum + cost * nt;
+        const uint64_t cost = costs[cost_index(runs[i].bits)], run_end = cum + cost * (uint64_t)nt;
         while (sp < n_splits) {
             uint64_t target = (total * sp + n_splits - 1) / n_splits;
-            if (target > page_end) break;
+            if (target > run_end) break;
             uint64_t k = target <= cum ? 0 : (target - cum + cost - 1) / cost;
             if ((tpp & 1) == 0) k = std::min<uint64_t>((k + 1) & ~1ull, (uint64_t)nt);  // chunks are tile pairs
+            int64_t at = std::min<int64_t>((int64_t)done + (int64_t)k, (int64_t)L.split_begin[sp - 1] + most);
+            int64_t least = n_tiles - (int64_t)(n_splits - sp) * most;  // (what the later ranges can take)
+            if ((tpp & 1) == 0) least = (least + 1) & ~1ll;
+            at = std::max(at, least);
             // at least one tile is left for every later range: what this cuts off an even boundary is a range of one tile
-            L.split_begin[sp] = std::min((int)i * tpp + (int)k, n_tiles - (n_splits - sp));
+            L.split_begin[sp] = (int)std::min<int64_t>(at, n_tiles - (n_splits - sp));
             ++sp;
         }
-        cum = page_end;
+        cum = run_end;
+        done += nt;
     }
     while (sp <= n_splits) L.split_begin[sp++] = n_tiles;
+}
+int longest_of(const Layer& L, int n_splits) {
+    int longest = 0;
+    for (int i = 0; i < n_splits; ++i) longest = std::max(longest, L.split_begin[i + 1] - L.split_begin[i]);
+    return longest;
+}
+
+// Split of the tile range (n_splits <= n_tiles, or one split of nothing), balanced by tile costs.  The last range is never empty: the
+// workgroup that holds the last tile is the one that stores the token a launch appends, behind its own reads of that tile.
+// side_by_side: a light launch for the kernels for short ranges, which take a range's tiles side by side, so that how many there are counts
+// beside how wide they are: every tile costs as much as a 16-bit one more, and no range gets a tile more for a SIMD than equal ones
+// would have (4 x 1,024 tokens of 2, 4, 8 and 16 bits x 2 units in 32 splits 7.2 us without this and 6.7).  Forty drawn blocks of
+// several widths, best of all split counts, with 0, 60, 120, 200, 300, 500 and infinitely many of the default units more: 3.9, 2.0, 1.6, 1.1, 0.9,
+// 0.9 and 0.9 % slower on average than the best of these.
+void plan_splits(kvq_cache* c, Layer& L, int n_tiles, int n_splits, bool side_by_side) {
+    if (L.plan_tiles == n_tiles && L.plan_splits == n_splits && L.plan_side_by_side == side_by_side && L.plan_version == L.version) return;
     L.plan_tiles = n_tiles;
     L.plan_splits = n_splits;
+    L.plan_side_by_side = side_by_side;
     L.plan_version = L.version;
+    uint64_t costs[4];
+    const uint64_t more = side_by_side ? (uint64_t)c->tile_cost[3] : 0u;
+    for (int i = 0; i < 4; ++i) costs[i] = (uint64_t)c->tile_cost[i] + more;
+    cut_by_cost(c, L, n_tiles, n_splits, costs, side_by_side ? (longest_even(n_tiles, n_splits, c->tpp) + 3) & ~3 : n_tiles);
 }
 
 }  // namespace
@@ -638,6 +692,10 @@ kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, 
     for (const Page& p : bl.fresh) L.pages.push_back(p);
     for (size_t i = 0; i < L.pages.size(); ++i) L.pages[i].n = pl.cnt[i];
     L.T = T;
+    if (L.runs_version == L.version && !L.runs.empty() && L.runs.back().bits == e) {  // new pages have the width e
+        L.runs.back().page_end = (int)L.pages.size();
+        L.runs_version = L.version + 1;
+    }
     L.version++;
     // From here on the host tables count the new tokens: a failing enqueue leaves the block unusable (poisoned).
     if (!c->dry && defer && n_new == 1 && e == 16) {
@@ -771,21 +829,22 @@ kvq_status_t kvq_progressive_requant(kvq_cache_t* c, int32_t layer, int32_t segm
 namespace {
 
 // What the block's tiles cost by the weights of KVQ_OPT_TILE_COST_* (relative, in a scale the caller chooses) and what they take
-// the attention kernel (in units of kTileTime), how many of them are 2 bits wide, and the bytes of one (sequence, KV head).
+// the attention kernel (in units of kTileTime), how many of them are 2 and 16 bits wide, and the bytes of one (sequence, KV head).
 struct TileCensus {
-    int n2 = 0, n_all = 0;
-    int narrowest = 0;  // the least time of a tile
+    int n2 = 0, n16 = 0, n_all = 0;
+    int narrowest = 0, widest = 0;  // the least and the most time of a tile
     uint64_t cost = 0, time = 0, bytes = 0;
 };
-TileCensus tile_census(const kvq_cache_t* c, const Layer& L, int n_tiles) {
+TileCensus tile_census(const kvq_cache_t* c, Layer& L, int n_tiles) {
     TileCensus t;
-    for (size_t i = 0; i < L.pages.size(); ++i) {
-        const int nt = std::min(c->tpp, n_tiles - (int)i * c->tpp);
+    for (const Run& r : runs_of(L)) {
+        const int nt = (int)std::min<int64_t>((int64_t)r.page_end * c->tpp, n_tiles) - t.n_all, b = r.bits;
         if (nt <= 0) break;
-        const int b = L.pages[i].bits;
         t.n_all += nt;
         t.narrowest = t.narrowest ? std::min(t.narrowest, kTileTime[cost_index(b)]) : kTileTime[cost_index(b)];
+        t.widest = std::max(t.widest, kTileTime[cost_index(b)]);
         if (b == 2) t.n2 += nt;
+        if (b == 16) t.n16 += nt;
         t.cost += (uint64_t)nt * (uint64_t)c->tile_cost[cost_index(b)];
         t.time += (uint64_t)nt * (uint64_t)kTileTime[cost_index(b)];
         t.bytes += (uint64_t)nt * (2u * kvq_tile_code_bytes(b) + (c->has_meta(b) ? KVQ_META_TILE_BYTES : 0u));
@@ -805,18 +864,61 @@ int merge_loads(int gqa, int n) {
         if (rounds <= k) return k;
     return 16 + (rounds - 16 + 7) / 8 * 8;
 }
-// Splits of one (sequence, KV head) that take least, at most max_splits: as many as make ranges of some 4, 8, 16, ... tiles, or
-// max_splits.  A launch whose splits are short is a chain of latencies; what the split count changes of it, in us:
+// Splits of one (sequence, KV head) that take least, at most max_splits: as many as make ranges of some 1, 2, 4, ... tiles, or
+// max_splits.  A launch whose splits are short is a chain of latencies; what the split count changes of it, in us, tile times in units
+// of 1,000:
+//   the range    of up to 16 tiles: 0.25 x its time, for every further tile of a SIMD (beyond 4, 8, 12) 0.05 + 2.8 x a tile's time -- the
+//                first time the widest tile's, then the mean one's -- and 0.2 beyond 12; of more tiles, which are streamed: 2.6,
+//                0.57 per eight tiles and 0.26 x its time
+//   the merge    2.0 (behind streamed ranges 1.8) for publishing, ticket and the last workgroup's trip to memory, 0.007 (0.004) per
+//                split (tickets on one counter come in turn), twice that beyond 64, 0.16 (0.14) per load a thread issues, 0.7 (0.77) for
+//                every further round of eight beyond 16, and 0.35 behind short ranges that take more than half of the compute
+//                units (more than eight query heads per KV head leave one slot group, which loads 16 splits a round: beyond 16
+//                splits a range of such a unit keeps 16 tiles, 512 tiles of 16 bits x 1 unit 12.6 in 32 and 13.2 in 48)
+// Up to eight tiles, and up to 12 unless they are wide, one workgroup takes all.
+// Fitted to launches of 1, 2, 4, ... 128 units of 3 to 4,000 tiles (2, 4 or 8 bits with four tiles of 16, all of 16, 2 / 4 / 16) in 1 to
+// 128 splits, 1 to 8 query heads per KV head, over blocks in turn from memory: 600 shapes.  How much slower the choice is than the best
+// count tried, on average, with the model for byte planes below, ranges cut by cost, and with this one, cut as plan_splits does: up to
+// 12 tiles 1.6 and 0.5 %, 13 to 16 4.9 and 1.1, 17 to 64 3.4 and 1.2, 65 to 256 3.5 and 0.8, beyond 3.8 and 1.4.  64 units x 12 tiles of 4 bits 7.8 us in four splits and 5.9 in one,
+// 16 x 32 of 2, 4 and 16 bits 7.7 in 12 and 6.9 in eight, 1 x 320 of 4 bits 9.6 in 52 and 8.5 in 32.
+int planned_splits(const kvq_cache* c, const TileCensus& t, int n_tiles, int max_splits) {
+    max_splits = std::max(1, std::min(max_splits, std::min(n_tiles, KVQ_MAX_SPLITS)));
+    if (n_tiles <= 8 || max_splits == 1) return 1;
+    if (16 / c->gqa == 1) max_splits = std::min(max_splits, std::max(16, (n_tiles + 15) / 16));
+    const double total = 1e-3 * (double)t.time, mean = total / n_tiles;
+    if (n_tiles <= 12 && mean <= 0.25) return 1;
+    const double first = 0.05 + 2.8e-3 * t.widest, next = 0.05 + 2.8 * mean;
+    int best = 1;
+    double least = 0.0;
+    for (int range : {0, 256, 192, 128, 96, 64, 48, 40, 32, 24, 20, 16, 14, 12, 10, 8, 7, 6, 5, 4, 3, 2, 1}) {
+        int n = range ? (n_tiles + range - 1) / range : 1;
+        const bool most = range == 1 || n >= max_splits;
+        if (most) n = max_splits;
+        const int tiles = longest_even(n_tiles, n, c->tpp);
+        const bool few = tiles <= KVQ_SHORT_TILES;
+        double us = few ? first * (tiles > 4) + next * ((tiles > 8) + (tiles > 12)) + 0.2 * (tiles > 12) + 0.25 * total / n
+                        : 2.6 + 0.57 / 8 * tiles + 0.26 * total / n;
+        if (n > 1) {
+            const int loads = merge_loads(c->gqa, n), more = std::max(0, loads - 16) / 8, per = n + std::max(0, n - 64);
+            us += few ? 2.0 + 0.007 * per + 0.16 * std::min(loads, 16) + 0.7 * more + (2 * n * c->units > c->target_workgroups ? 0.35 : 0.0)
+                      : 1.8 + 0.004 * per + 0.14 * std::min(loads, 16) + 0.77 * more;
+        }
+        if (range == 0 || us < least) { least = us; best = n; }
+        if (most && range) break;
+    }
+    return best;
+}
+
+// The same for a block of byte planes, whose tiles hold a wavefront up so long that ranges are better cut by time: as many splits as
+// make ranges of some 4, 8, 16, ... tiles, or max_splits.  A launch whose splits are short is a chain of latencies; what the split count changes of it, in us:
 //   the range    0.7 per 1,000 units of its tile time (what a compute unit needs to fetch and expand its tiles), and 0.8 for
 //                every eight tiles beyond the first (the wavefronts take another one)
 //   the merge    1.8 for publishing, ticket and the last workgroup's trip to memory, 0.02 per split (tickets on one counter come
 //                in turn), 0.06 per load a thread issues, 0.7 for every further round of eight beyond 16
 // Fitted to launches of 1, 2, 4, ... 128 units of 8 to 1,024 tiles at each width in 1 to 64 splits (5 query heads per KV head;
 // 320 launches, when a further round took a little longer than now): the choice is 1.1 % slower than the best count tried, 14 % at
-// worst.  48 tiles of 4 bits x 8 units take 6.7 us in 12 splits, 7.3 in 8, 7.7 in 4; 128 tiles x 1 unit 7.3 in 32, 7.5 in 16, 8.9 in 8; 12
-// tiles of 4 bits 5.6 in one and 6.6 in three; 16 query heads per KV head, 512 tiles of 16 bits x 1 unit 12.6 in 32, 13.2 in 48, 14.0 in 64
-// and 15.7 in 16.
-int planned_splits(const kvq_cache* c, const TileCensus& t, int n_tiles, int max_splits) {
+// worst.
+int planned_splits_planes(const kvq_cache* c, const TileCensus& t, int n_tiles, int max_splits) {
     max_splits = std::max(1, std::min(max_splits, std::min(n_tiles, KVQ_MAX_SPLITS)));
     int best = 1;
     double least = 0.0;
@@ -871,6 +973,7 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     const int n_tokens = app && app->active ? app->t_old : L.T;
     const int n_tiles = app ? tiles_read(L, *app) : tiles_of(L.T);
     int n_splits = c->splits_override > 0 ? c->splits_override : batch_splits;
+    bool side_by_side = false;
     if (n_splits <= 0) {
         // One workgroup per compute unit when a good part of the tiles is 2 bits wide (those are bound by vector
         // issue and want every unit) or the launch is short (what counts is the length of one range: 8K tokens x 32 units
@@ -889,16 +992,25 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
         // and 23.6, 112 x 64 25.0 and 22.4, 128 x 64 25.9 and 25.3.
         if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs && wgs * 3 / 4 / c->units * c->units * 8 >= wgs * 5)
             wgs = wgs * 3 / 4;
-        n_splits = planned_splits(c, t, n_tiles, wgs / c->units);
-        // two halves of a range that one workgroup takes in a few rounds stay one, unless they are long reads: 128 units x 20 or 24
-        // tiles of 8, 4 or 2 bits take the same in one and in two, 24 of 16 bits (393 KB) 11.3 and 10.2 us
-        if (n_splits == 2 && n_tiles <= 32 && t.bytes <= 375000) n_splits = 1;
+        // (as long as the tiles of each width are as many as last time, so are the splits)
+        const bool planes = c->int16() && t.n16 > 0;
+        const uint64_t key[3] = {t.time, (uint64_t)n_tiles << 32 | (uint32_t)t.n16, (uint64_t)t.widest << 32 | (uint32_t)(wgs / c->units)};
+        if (std::memcmp(L.count_key, key, sizeof key) != 0) {
+            L.count_splits = (planes ? planned_splits_planes : planned_splits)(c, t, n_tiles, wgs / c->units);
+            std::memcpy(L.count_key, key, sizeof key);
+        }
+        n_splits = L.count_splits;
+        // two halves of a range of wide tiles that one workgroup takes in a few rounds stay one, unless they are long reads: 128 units x 20
+        // or 24 tiles of 8 bits take the same in one and in two and 32 of them 12.2 and 12.6 us, 24 of 16 bits (393 KB) 11.3 and 10.2, 24 of 2 bits 10.3 and 8.5
+        if (n_splits == 2 && n_tiles <= 32 && (planes || t.narrowest >= kTileTime[2]) && t.bytes <= 375000) n_splits = 1;
+        // (heavy launches in few splits are better cut by time: 32 units x 2,146 tokens of 8 and 16 bits, 28 MB, in eight splits 10.0 us with
+        // ranges of the same cost and 10.8 side by side, 2,042 of 2 and 16 bits, 19 MB, 9.8 and 10.4; in more than 16 splits a unit drawn
+        // blocks of 300 and more tiles are 3 % faster side by side on average)
+        side_by_side = !planes && (t.bytes * (uint64_t)c->units <= 16000000u || n_splits > 16) && longest_even(n_tiles, n_splits, c->tpp) <= KVQ_SHORT_TILES;
     }
     n_splits = std::max(1, std::min(n_splits, std::min(KVQ_MAX_SPLITS, n_tiles)));
-    plan_splits(c, L, n_tiles, n_splits);
-    int longest = 0;
-    for (int i = 0; i < n_splits; ++i) longest = std::max(longest, L.split_begin[i + 1] - L.split_begin[i]);
-    p.short_ranges = longest <= KVQ_SHORT_TILES ? 1 : 0;
+    plan_splits(c, L, n_tiles, n_splits, side_by_side);
+    p.short_ranges = longest_of(L, n_splits) <= KVQ_SHORT_TILES ? 1 : 0;
 
     p.arena = c->arena;
     p.table = c->table_dev(layer);
@@ -1028,7 +1140,7 @@ kvq_status_t batch_attention(kvq_cache_t* const* caches, int32_t n, int32_t laye
     std::vector<BatchShare> share((size_t)n);
     for (int i = 0; i < n; ++i) {
         kvq_cache_t* c = caches[i];
-        const Layer& L = c->layers[(size_t)layer];
+        Layer& L = c->layers[(size_t)layer];
         if (L.T == 0) return KVQ_E_STATE;
         const int n_tiles = tiles_read(L, app[(size_t)i]);
         const TileCensus t = tile_census(c, L, n_tiles);

@@ -275,6 +275,40 @@ void split_plans() {
     CHECK(a.append(640, 2) == KVQ_OK && a.append(33, 16) == KVQ_OK && a.step() == KVQ_OK && last.app_t_old == 673, "step");
 }
 
+// A plan knows the pages as they are, however they came about: after random appends, shrinks and emptyings it is that of a
+// block built at once with the same widths.  And ranges that are cut for the kernels for short ranges give no SIMD a tile more
+// than equal ones would.
+void plans_follow_the_pages() {
+    std::mt19937 rng(11);
+    const auto R = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+    for (int round = 0; round < 40; ++round) {
+        const int page = 32 * R(1, 4), units = 1 << R(0, 2), tier16 = R(0, 3) == 0;
+        Cache a(page, 60, tier16, KVQ_POLICY_PAPER, 0, 1, units, R(1, 8));
+        for (int step = 0; step < 20; ++step) {
+            const int bits[4] = {2, 4, 8, 16};
+            switch (R(0, 5)) {
+                case 0: kvq_progressive_requant(a.c, 0, R(0, 2), 0, nullptr, nullptr); break;
+                case 1: if (R(0, 9) == 0) kvq_cache_reset(a.c, -1); break;
+                case 2: a.step(); break;
+                default: if (a.tokens() < 25 * page) a.append(R(1, 3) * page - a.tokens() % page, a.tokens() % page ? 0 : bits[R(0, 3)]);
+            }
+            if (a.tokens() == 0 || a.attend() != KVQ_OK) continue;
+            const std::vector<int32_t> got(last.split_begin, last.split_begin + last.n_splits + 1);
+            kvq_segment_info_t segs[64];
+            int m = 0;
+            kvq_cache_describe(a.c, 0, segs, 64, &m, nullptr, nullptr, nullptr);
+            Cache b(page, 60, tier16, KVQ_POLICY_PAPER, 0, 1, units, a.cfg.n_q_heads / units);
+            for (int k = 0; k < m; ++k) CHECK(b.append(segs[k].token_end - segs[k].token_begin, segs[k].bits) == KVQ_OK, "segment %d of %d", k, m);
+            CHECK(b.attend() == KVQ_OK, "attention");
+            const std::vector<int32_t> fresh(last.split_begin, last.split_begin + last.n_splits + 1);
+            CHECK(got == fresh, "round %d, step %d: %zu ranges, %zu in a fresh block", round, step, got.size() - 1, fresh.size() - 1);
+            const int n = last.n_splits, n_tiles = (a.tokens() + 31) / 32, even = (n_tiles + n - 1) / n + 1;
+            if (!tier16 && n > 16 && even <= 16)
+                for (int i = 0; i < n; ++i) CHECK(got[(size_t)i + 1] - got[(size_t)i] <= (even + 3) / 4 * 4, "range %d of %d tiles in %d: %d", i, n_tiles, n, got[(size_t)i + 1] - got[(size_t)i]);
+        }
+    }
+}
+
 // The tile costs are relative: their scale changes neither how many splits a launch takes nor where they lie.
 void tile_costs_are_relative() {
     for (int narrow : {8, 30, 200}) {
@@ -389,6 +423,7 @@ const std::map<std::string, std::function<void()>> scenarios = {
     {"batch_failing_launch", batch_failing_launch},
     {"failed_block_is_refused", failed_block_is_refused},
     {"split_plans", split_plans},
+    {"plans_follow_the_pages", plans_follow_the_pages},
     {"tile_costs_are_relative", tile_costs_are_relative},
     {"batch_shares", batch_shares},
 };
