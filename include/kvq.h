@@ -174,11 +174,11 @@ kvq_status_t kvq_decode_attention_static(kvq_cache_t* cache, int32_t layer, cons
 
 /* One decode step of a block in one launch: kvq_quantize_append_rope of one token (n_new = 1, entry_bits = 0; k_dev,
  * v_dev: fp16 [batch, n_kv_heads, 1, 128]; cos_sin_dev: fp32 [1][128] or NULL for keys that already carry RoPE)
- * followed by kvq_decode_attention over the block including that token.  When the token enters the 16-bit tier
- * (a window is configured, the policy is OLDEST_FIRST, or the block is still at 16 bits) the attention kernel itself rotates,
- * with KVQ_TIER16_INT16 quantizes (Eq. 1-2, 2^16 - 1 levels), attends to and stores it, so that the small append launch
- * and its gap disappear; otherwise the two kernels are launched one after the other.  Bookkeeping, budget check, page allocation and window evictions are those of kvq_quantize_append; the
- * cache contents afterwards are bit-identical to the two separate calls, the outputs equal up to summation order.
+ * followed by kvq_decode_attention over the block including that token.  The attention kernel itself rotates, quantizes
+ * (Eq. 1-2, below 16 bits and with KVQ_TIER16_INT16), attends to and stores the token, so that the small append launch and
+ * its gap disappear.  Bookkeeping, budget check, page allocation and window evictions are those of kvq_quantize_append; the
+ * cache contents afterwards are bit-identical to the two separate calls, the outputs equal up to summation order and the
+ * rounding of the new token's probability.
  * Errors of the append part leave the cache unchanged and nothing is computed. */
 kvq_status_t kvq_append_decode_attention(kvq_cache_t* cache, int32_t layer, const void* k_dev, const void* v_dev,
                                          const float* cos_sin_dev, const void* q_dev, void* out_dev,

@@ -21,19 +21,19 @@ unsigned char* g_scratch_ptr[kMaxDevices];  // device address of `scratch` per d
 // grid = (splits, units); 512 threads = 8 wavefronts, one workgroup per compute unit.
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    attention_body<false, false, false>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
+    attention_body<false, false, 0>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
 }
 
 // The same with a one-token append into the raw fp16 tier in front (kvq_append_decode_attention).
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_append_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    attention_body<false, false, true>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
+    attention_body<false, false, KVQ_APPEND_16>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
 }
 
 // The same for a cache whose 16-bit tier holds integer codes in byte planes (KVQ_TIER16_INT16).
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_i16_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    attention_body<true, false, false>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
+    attention_body<true, false, 0>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
 }
 
 // Same thread count as the attention kernel, so both merge variants add in the same order.
@@ -75,6 +75,7 @@ hipError_t kvq_launch_merge(const KvqAttnParams& p, int units, hipStream_t s) {
 
 hipError_t kvq_launch_attention(const KvqAttnParams& p, int units, hipStream_t s) {
     if (p.short_ranges) { hipError_t e0 = kvq_launch_attention_short(p, units, s); if (e0 != hipSuccess) return e0; }
+    else if (p.app_t_old >= 0 && p.app_desc.bits < 16) { hipError_t e0 = kvq_launch_attention_append_narrow(p, units, s); if (e0 != hipSuccess) return e0; }
     else if (p.int16_tier && p.app_t_old >= 0) { hipError_t e0 = kvq_launch_attention_i16_append(p, units, s); if (e0 != hipSuccess) return e0; }
     else if (p.int16_tier) hipLaunchKernelGGL(kvq_attention_i16_kernel, dim3(p.n_splits, units), dim3(KVQ_ATTN_THREADS), 0, s, p);
     else if (p.app_t_old >= 0) hipLaunchKernelGGL(kvq_attention_append_kernel, dim3(p.n_splits, units), dim3(KVQ_ATTN_THREADS), 0, s, p);

@@ -10,7 +10,7 @@ __device__ __forceinline__ void batch_body(const KvqAttnParams* __restrict__ par
                                            uint32_t (&block)[kBlockDwords]) {
     BatchWork work;
     const KvqAttnHead P = batch_work(params, map, block, work);
-    attention_body<I16, true, true>(P, work.t_begin, work.t_end, sh, work.split, work.unit);
+    attention_body<I16, true, KVQ_APPEND_16>(P, work.t_begin, work.t_end, sh, work.split, work.unit);
 }
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_batch_kernel(const KvqAttnParams* __restrict__ params,
                                                                                const KvqBatchMap map) {

@@ -811,9 +811,9 @@ struct AttnShared {
     u32x4 desc[KVQ_DESC_CACHE];
     __attribute__((aligned(16))) uint8_t meta[KVQ_ATTN_WAVES * KVQ_WAVE_LDS_BYTES];
     // the token a fused append adds: K, V
-    __attribute__((aligned(16))) uint16_t new_bits[2][KVQ_D];  // as stored: fp16 values, or codes of the integer tier
+    __attribute__((aligned(16))) uint16_t new_bits[2][KVQ_D];  // as stored: fp16 values, or codes
     __attribute__((aligned(16))) float new_x[2][KVQ_D];        // what attention sees of it: the value, or code * S + Z
-    uint16_t new_sz[2][KVQ_NGRP][2];                           // (S, Z) of its groups (integer tier)
+    uint16_t new_sz[2][KVQ_NGRP][2];                           // (S, Z) of its groups (where it is quantized)
     float new_score[16];                                       // its score per head, log2 units
 };
 
@@ -970,6 +970,8 @@ __device__ inline void merge_splits(const KvqAttnHead& P, int unit, int tid, con
 
 static_assert(KVQ_ATTN_WAVES * 16 * KVQ_OPAD >= KVQ_MERGE_LDS_FLOATS, "the wavefront slab doubles as scratch of the split merge");
 
+#define KVQ_APPEND_16 1
+#define KVQ_APPEND_NARROW 2  // kernels of their own: with the width looked at in the other ones a generation's steps took 0.7 % longer
 // ---- A one-token append fused into the launch (kvq_append_decode_attention).  The workgroup of a unit's last split does
 // it.  The token is never read back from the cache: its rows wait in LDS from the staging phase on, its score and its V
 // row enter the merge of the wavefront partials as a ninth partial of one token, and its elements are stored behind the
@@ -978,9 +980,9 @@ static_assert(KVQ_ATTN_WAVES * 16 * KVQ_OPAD >= KVQ_MERGE_LDS_FLOATS, "the wavef
 // nothing of it.  (Written at the start, waited for and read back with its tile, the token cost 3 to 4 us of every step.)
 
 // K (which = 0) or V (1) row of the new token -> LDS, one wavefront, two channels per lane: rotation and
-// reparameterization exactly as the append kernels carry them out (kvq_append16.h), in the integer tier Eq. 1-2 with
-// 2^16 - 1 levels (kvq_quant_dev.h).
-template <bool I16>
+// reparameterization exactly as the append kernels carry them out (kvq_append16.h), in the integer tier and the widths below
+// 16 bits Eq. 1-2 (kvq_quant_dev.h).
+template <bool I16, int APPEND>
 __device__ inline void stage_new_token(const KvqAttnHead& P, AttnShared& sh, int unit, int hk, int which, int lane) {
     uint32_t w;
     __builtin_memcpy(&w, static_cast<const uint16_t*>(which ? P.app_v : P.app_k) + (size_t)unit * KVQ_D + 2 * lane, 4);
@@ -994,7 +996,8 @@ __device__ inline void stage_new_token(const KvqAttnHead& P, AttnShared& sh, int
         w = kvq_dev::scale_pair(w, r[0], r[1]);
     }
     float x0 = mixf(w, 0), x1 = mixf(w, 1);
-    if constexpr (I16) {
+    if constexpr (I16 || APPEND == KVQ_APPEND_NARROW) {
+        const int levels = APPEND == KVQ_APPEND_NARROW ? (1 << P.app_desc.bits) - 1 : 65535;
         float mn = reduce16<Min>(fminf(x0, x1)), mx = reduce16<Max>(fmaxf(x0, x1));
         for (int o = 16; o < 16 * P.app_gspan; o <<= 1) {  // a group of 32, 64 or 128 channels is 16, 32 or 64 lanes
             mn = fminf(mn, __shfl_xor(mn, o));
@@ -1002,8 +1005,8 @@ __device__ inline void stage_new_token(const KvqAttnHead& P, AttnShared& sh, int
         }
         uint16_t S, Z;
         float Sf;
-        kvq_q::group_params(mn, mx, 65535, &S, &Z, &Sf);
-        const uint32_t c0 = kvq_q::code_of(x0, mn, Sf, 65535), c1 = kvq_q::code_of(x1, mn, Sf, 65535);
+        kvq_q::group_params(mn, mx, levels, &S, &Z, &Sf);
+        const uint32_t c0 = kvq_q::code_of(x0, mn, Sf, levels), c1 = kvq_q::code_of(x1, mn, Sf, levels);
         w = c0 | (c1 << 16);
         const float Zf = kvq_dev::h2f(Z);
         x0 = fmaf((float)c0, Sf, Zf);
@@ -1026,23 +1029,66 @@ __device__ inline void score_new_token(AttnShared& sh, float scale_log2, int wav
     if ((lane & 31) == 0) sh.new_score[head] = s * scale_log2;
 }
 
+// Code of the new token's K or V into the tile of a page of 8, 4 or 2 bits.  K: 8 channels of a token are a piece of a lane's string.
+// V: 8 tokens of a channel are, so that a byte of 4 or 2 bits holds older tokens too, which keep their bits (each byte is one lane's).
+__device__ inline void store_new_codes(const AttnShared& sh, uint8_t* code, int t, int which, int bits, int lane) {
+    int ln, slot;
+    if (!which) {
+        const int ch = 8 * (lane & 15);
+        kvq_k_slot(t, ch, &ln, &slot);
+        const u32x4 c = *reinterpret_cast<const u32x4*>(&sh.new_bits[0][ch]);
+        uint8_t* const at = code + kvq_tile_byte(ln, (uint32_t)(slot * bits) / 8u);
+        const uint32_t lo = __builtin_amdgcn_perm(c.y, c.x, 0x06040200u), hi = __builtin_amdgcn_perm(c.w, c.z, 0x06040200u);  // a byte each
+        if (lane < 16) {
+            uint32_t w0, w1;
+            if (bits == 8) *reinterpret_cast<u32x2*>(at) = u32x2{lo, hi};
+            else if (bits == 4) { kvq_q::pack8<4>(lo, hi, &w0, &w1); *reinterpret_cast<uint32_t*>(at) = w0; }
+            else { kvq_q::pack8<2>(lo, hi, &w0, &w1); *reinterpret_cast<uint16_t*>(at) = (uint16_t)w0; }
+        }
+        return;
+    }
+    uint8_t* at[2];
+    uint32_t old[2];
+    int shift = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        kvq_v_slot(t, lane + 64 * h, &ln, &slot);
+        at[h] = code + kvq_tile_byte(ln, (uint32_t)(slot * bits) / 8u);
+        old[h] = *at[h];
+        shift = slot * bits & 7;  // the same for both
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t field = ((1u << bits) - 1u) << shift;
+        *at[h] = (uint8_t)((old[h] & ~field) | ((uint32_t)sh.new_bits[1][lane + 64 * h] << shift));
+    }
+}
 // The new token's K (which = 0) or V (1) elements -> its tile, one wavefront.  A tile that it starts is zeroed first, codes
-// and (integer tier) metadata, so that the slots of tokens to come are well defined, as the append kernels leave them.
-template <bool I16>
+// and metadata, so that the slots of tokens to come are well defined, as the append kernels leave them.
+template <bool I16, int APPEND>
 __device__ inline void store_new_token(const KvqAttnHead& P, const AttnShared& sh, int unit, int which, int lane) {
     const int tile = P.app_t_old / KVQ_TILE_TOKENS, t = P.app_t_old - tile * KVQ_TILE_TOKENS;
     const int tip = tile - (tile / P.tiles_per_page) * P.tiles_per_page;
     const uint64_t tslot = (uint64_t)unit * P.tiles_per_page + tip;
-    uint8_t* const code = const_cast<uint8_t*>(P.arena) + (uint64_t)P.app_desc.code_off256 * 256u + (tslot * 2 + which) * (512u * 16);
+    constexpr bool narrow = APPEND == KVQ_APPEND_NARROW, quantized = I16 || narrow;
+    const int bits = narrow ? (int)P.app_desc.bits : 16;
+    uint8_t* const code = const_cast<uint8_t*>(P.arena) + (uint64_t)P.app_desc.code_off256 * 256u + (tslot * 2 + which) * (512u * bits);
     uint8_t* const meta = const_cast<uint8_t*>(P.arena) + (uint64_t)P.app_desc.meta_off256 * 256u + tslot * KVQ_META_TILE_BYTES;
     if (t == 0) {
         const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int c = 0; c < 8; ++c) *reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16) = zero;
-        if (I16 && lane < 32) *reinterpret_cast<u32x4*>(meta + 512 * which + lane * 16) = zero;
+        for (int c = 0; c < (narrow ? 4 : 8); ++c)
+            if (!narrow || 2 * c < bits) *reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16) = zero;
+        if (quantized && lane < 32) *reinterpret_cast<u32x4*>(meta + 512 * which + lane * 16) = zero;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the elements below go to addresses other lanes have just zeroed
     }
-    if (!which) {  // lane = 4 grp + j: channels 32 grp + 8 j .. + 7 are consecutive slots of one lane's string
+    if constexpr (narrow) {
+        store_new_codes(sh, code, t, which, bits, lane);
+        if (lane == 0 && which)
+#pragma unroll
+            for (int g = 0; g < KVQ_NGRP; ++g)
+                kvq_q::note_large_v_scale(KvqVMark{const_cast<uint32_t*>(P.v_mark), P.v_epoch}, 1, sh.new_sz[1][g][0]);
+    } else if (!which) {  // lane = 4 grp + j: channels 32 grp + 8 j .. + 7 are consecutive slots of one lane's string
         int ln, slot;
         const int ch = 8 * ((lane & 3) + 4 * ((lane >> 2) & 3));
         kvq_k_slot(t, ch, &ln, &slot);
@@ -1080,7 +1126,7 @@ __device__ inline void store_new_token(const KvqAttnHead& P, const AttnShared& s
     if (P.app_page >= 0 && unit == 0 && !which && lane == 0)  // nobody reads this entry in this launch
         reinterpret_cast<u32x4*>(const_cast<KvqPageDesc*>(P.table))[P.app_page] =
             u32x4{P.app_desc.code_off256, P.app_desc.meta_off256, P.app_desc.bits, P.app_desc.int16};
-    if (I16 && lane < 8) {  // S of the four groups, then Z
+    if (quantized && lane < 8) {  // S of the four groups, then Z
         const int g = lane & 3, z = lane >> 2;
         uint16_t* m = reinterpret_cast<uint16_t*>(meta + 512 * which + 256 * z);
         m[which ? kvq_vmeta_index(t, g) : t * 4 + g] = sh.new_sz[which][g][z];
@@ -1090,7 +1136,7 @@ __device__ inline void store_new_token(const KvqAttnHead& P, const AttnShared& s
 // End of a workgroup's range: merge of its eight wavefront partials through LDS, then either the output (one split),
 // the partial for the separate merge kernel, or the fused merge of the unit's split partials.
 // SCORED: the scores of an appended token are there already.
-template <bool I16, bool APPEND, bool SCORED = false>
+template <bool I16, int APPEND, bool SCORED = false>
 __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShared& sh, WaveState& st, int split, int unit,
                                                  int tid) {
     // the thread index is taken afresh, opaque to the compiler: nothing derived from it stays in a register across
@@ -1129,7 +1175,11 @@ __device__ __forceinline__ void finish_workgroup(const KvqAttnHead& P, AttnShare
     const bool appends = APPEND && P.app_t_old >= 0 && split == ns - 1;
     if (appends && !SCORED) score_new_token(sh, P.scale_log2, wave, lane);  // here it hides in the wait for the slowest wavefront
     __syncthreads();  // the eight wavefronts of the workgroup have joined
-    if (appends && wave < 2) store_new_token<I16>(P, sh, unit, wave, lane);
+    if constexpr (APPEND == KVQ_APPEND_NARROW) {  // (reads older codes: the last two wavefronts have no heads to merge as a rule)
+        if (appends && wave >= KVQ_ATTN_WAVES - 2) store_new_token<I16, APPEND>(P, sh, unit, wave & 1, lane);
+    } else if constexpr (APPEND != 0) {
+        if (appends && wave < 2) store_new_token<I16, APPEND>(P, sh, unit, wave, lane);
+    }
     KVQ_STAMP(6);
 
     const bool direct = (ns == 1);
@@ -1288,8 +1338,9 @@ __device__ __forceinline__ void stream_range(const KvqAttnHead& P, AttnShared& s
 // one kind only, so each kernel carries the code of one.
 // BATCH: the workgroup's (split, unit) come from the caller (ragged batch); else they are the workgroup's grid indices,
 // read where they are needed (handing them in as values costs the single-cache kernels scalar registers they lack).
-// APPEND: the kernel can carry out a one-token append into the 16-bit tier (P.app_t_old >= 0) and attend to that token too.
-template <bool I16, bool BATCH, bool APPEND>
+// APPEND: the kernel can carry out a one-token append (P.app_t_old >= 0) into the 16-bit tier, KVQ_APPEND_16, or into a narrower page,
+// KVQ_APPEND_NARROW, and attend to that token too.
+template <bool I16, bool BATCH, int APPEND>
 __device__ __forceinline__ void attention_body(const KvqAttnHead& P, const int t_begin, const int t_end, AttnShared& sh,
                                                const int split_in = 0, const int unit_in = 0) {
     const int split = BATCH ? split_in : (int)blockIdx.x, unit = BATCH ? unit_in : (int)blockIdx.y;
@@ -1331,7 +1382,7 @@ __device__ __forceinline__ void attention_body(const KvqAttnHead& P, const int t
     }
     // waves 4 and 5 have nothing else to stage
     if (APPEND && P.app_t_old >= 0 && split == P.n_splits - 1 && (wave == 4 || wave == 5))
-        stage_new_token<I16>(P, sh, unit, hk, wave & 1, lane);
+        stage_new_token<I16, APPEND>(P, sh, unit, hk, wave & 1, lane);
     if (tid == 0) sh.claim_ctr = KVQ_ATTN_WAVES;  // the first chunk of every wavefront is fixed, the counter starts behind them
     __syncthreads();
     KVQ_STAMP(1);

@@ -7,7 +7,7 @@ namespace {
 
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_i16_append_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    attention_body<true, false, true>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
+    attention_body<true, false, KVQ_APPEND_16>(P, P.split_begin[blockIdx.x], P.split_begin[blockIdx.x + 1], sh);
 }
 
 }  // namespace

@@ -154,7 +154,7 @@ __device__ __forceinline__ void short_tiles(WaveState& st, QOps& Q, u32x4 (&qraw
 #endif
 }
 
-template <bool I16, bool APPEND>
+template <bool I16, int APPEND>
 __device__ __forceinline__ void short_range(const KvqAttnHead& P, const int t_begin, const int t_end, const int split, const int unit,
                                             AttnShared& sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -200,7 +200,7 @@ __device__ __forceinline__ void short_range(const KvqAttnHead& P, const int t_be
     // hold anyway, its scores.
     if (APPEND && P.app_t_old >= 0 && split == P.n_splits - 1 && wave >= KVQ_ATTN_WAVES - 2) {
         const int which = wave & 1;
-        stage_new_token<I16>(P, sh, unit, hk, which, lane);
+        stage_new_token<I16, APPEND>(P, sh, unit, hk, which, lane);
         if (!which) {
             wave_lds_sync();
             float s = 0.f;
@@ -258,7 +258,7 @@ __device__ __forceinline__ void short_range(const KvqAttnHead& P, const int t_be
     finish_workgroup<I16, APPEND, true>(P, sh, st, split, unit, 64 * wave + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (uint32_t)zero)));
 }
 
-template <bool I16, bool APPEND>
+template <bool I16, int APPEND>
 __device__ __forceinline__ void short_body(const KvqAttnParams& params, AttnShared& sh) {
     const int split = blockIdx.x, unit = blockIdx.y;
     const int t_begin = params.split_begin[split], t_end = params.split_begin[split + 1];
@@ -271,24 +271,33 @@ __device__ __forceinline__ void short_batch_body(const KvqAttnParams* __restrict
                                                  uint32_t (&block)[kBlockDwords]) {
     BatchWork work;
     const KvqAttnHead P = batch_work(params, map, block, work);
-    short_range<I16, true>(P, work.t_begin, work.t_end, work.split, work.unit, sh);
+    short_range<I16, KVQ_APPEND_16>(P, work.t_begin, work.t_end, work.split, work.unit, sh);
 }
 
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    short_body<false, false>(P, sh);
+    short_body<false, 0>(P, sh);
 }
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_append_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    short_body<false, true>(P, sh);
+    short_body<false, KVQ_APPEND_16>(P, sh);
 }
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_i16_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    short_body<true, false>(P, sh);
+    short_body<true, 0>(P, sh);
 }
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_i16_append_kernel(const KvqAttnParams P) {
     __shared__ AttnShared sh;
-    short_body<true, true>(P, sh);
+    short_body<true, KVQ_APPEND_16>(P, sh);
+}
+
+__global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_append_narrow_kernel(const KvqAttnParams P) {
+    __shared__ AttnShared sh;
+    short_body<false, KVQ_APPEND_NARROW>(P, sh);
+}
+__global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_i16_append_narrow_kernel(const KvqAttnParams P) {
+    __shared__ AttnShared sh;
+    short_body<true, KVQ_APPEND_NARROW>(P, sh);
 }
 
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_batch_kernel(const KvqAttnParams* __restrict__ params,
@@ -315,7 +324,10 @@ hipError_t kvq_launch_attention_short_batch(const KvqAttnParams* params_dev, con
 hipError_t kvq_launch_attention_short(const KvqAttnParams& p, int units, hipStream_t s) {
     const dim3 grid(p.n_splits, units), block(KVQ_ATTN_THREADS);
     const bool append = p.app_t_old >= 0;
-    if (p.int16_tier && append) hipLaunchKernelGGL(kvq_attention_short_i16_append_kernel, grid, block, 0, s, p);
+    if (append && p.app_desc.bits < 16) {
+        if (p.int16_tier) hipLaunchKernelGGL(kvq_attention_short_i16_append_narrow_kernel, grid, block, 0, s, p);
+        else hipLaunchKernelGGL(kvq_attention_short_append_narrow_kernel, grid, block, 0, s, p);
+    } else if (p.int16_tier && append) hipLaunchKernelGGL(kvq_attention_short_i16_append_kernel, grid, block, 0, s, p);
     else if (p.int16_tier) hipLaunchKernelGGL(kvq_attention_short_i16_kernel, grid, block, 0, s, p);
     else if (append) hipLaunchKernelGGL(kvq_attention_short_append_kernel, grid, block, 0, s, p);
     else hipLaunchKernelGGL(kvq_attention_short_kernel, grid, block, 0, s, p);

@@ -572,7 +572,7 @@ void kvq_cache_destroy(kvq_cache_t* c) {
 
 namespace {
 
-// What a deferred single-token append into the 16-bit tier leaves for the attention launch to do.
+// What a deferred single-token append leaves for the attention launch to do.
 struct DeferredAppend {
     bool active = false;
     int t_old = 0;
@@ -682,7 +682,8 @@ kvq_status_t reserve_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl,
 // not launched but described in *defer.  The caller must then launch the attention with it, or mark the block unusable: the
 // token, and the table entry of a page that it starts, are written by that launch and by nothing else.
 kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, AppendBlocks& bl, const void* k_dev,
-                           const void* v_dev, int32_t n_new, const float* cos_sin_dev, hipStream_t s, DeferredAppend* defer) {
+                           const void* v_dev, int32_t n_new, const float* cos_sin_dev, hipStream_t s, DeferredAppend* defer,
+                           bool defer_narrow) {
     Layer& L = c->layers[(size_t)layer];
     const int P = c->cfg.page_tokens, e = pl.e;
     const size_t old_pages = L.pages.size();
@@ -698,7 +699,7 @@ kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, 
     }
     L.version++;
     // From here on the host tables count the new tokens: a failing enqueue leaves the block unusable (poisoned).
-    if (!c->dry && defer && n_new == 1 && e == 16) {
+    if (!c->dry && defer && n_new == 1 && (e == 16 || defer_narrow)) {
         defer->active = true;
         defer->t_old = t_old;
         defer->desc = c->desc(L.pages[(size_t)(t_old / P)]);
@@ -749,7 +750,7 @@ kvq_status_t append_impl(kvq_cache_t* c, int32_t layer, const void* k_dev, const
     kvq_status_t st = plan_append(c, layer, n_new, entry_bits, pl);
     if (st == KVQ_OK) st = reserve_append(c, layer, pl, bl, as_stream(hip_stream));
     if (st != KVQ_OK) return st;
-    return commit_append(c, layer, pl, bl, k_dev, v_dev, n_new, cos_sin_dev, as_stream(hip_stream), defer);
+    return commit_append(c, layer, pl, bl, k_dev, v_dev, n_new, cos_sin_dev, as_stream(hip_stream), defer, true);
 }
 
 }  // namespace
@@ -1199,7 +1200,7 @@ kvq_status_t batch_impl(kvq_cache_t* const* caches, int32_t n, int32_t layer, co
         while (st == KVQ_OK && done < n) {
             const int i = done++;
             st = commit_append(caches[i], layer, plans[(size_t)i], blocks[(size_t)i], k_dev[i], v_dev[i], 1,
-                               cos_sin_dev ? cos_sin_dev[i] : nullptr, s, &app[(size_t)i]);
+                               cos_sin_dev ? cos_sin_dev[i] : nullptr, s, &app[(size_t)i], false);
         }
         if (st != KVQ_OK)
             for (int i = done; i < held; ++i) release_append(caches[i], blocks[(size_t)i]);

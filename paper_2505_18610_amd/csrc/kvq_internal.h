@@ -69,7 +69,7 @@ struct KvqAttnHead {
     int32_t merge_groups;      // split merge: slot groups that share the splits of a head, splits of a group,
     int32_t merge_rounds;
     uint32_t gqa_magic;        // 65536 / gqa + 1
-    // a one-token append into the 16-bit tier done by the workgroup of a unit's last split (app_t_old < 0: none)
+    // a one-token append done by the workgroup of a unit's last split (app_t_old < 0: none)
     int32_t app_t_old;         // tokens before the append
     KvqPageDesc app_desc;      // page of the new token
     int32_t app_page;          // the table entry the launch has to write (the token starts the page), or -1
@@ -77,7 +77,7 @@ struct KvqAttnHead {
     const void* app_v;
     const float* app_rope;     // [1][128] cos | sin of the new position, or null
     const float* app_rinv;     // [n_kv_heads][128] reciprocal reparameterization factors, or null
-    int32_t app_gspan;         // quantization group / 32 (integer 16-bit tier: the new token is quantized, Eq. 1-2)
+    int32_t app_gspan;         // quantization group / 32 (integer tier and below 16 bits: the new token is quantized, Eq. 1-2)
 };
 // A launch none of whose ranges is longer takes the kernels for short ranges (kvq_attention_short.hip), two tiles to a
 // wavefront; beyond that the streaming kernels, which overlap the loads of later tiles with the arithmetic of earlier ones,
@@ -154,6 +154,7 @@ hipError_t kvq_launch_attention(const KvqAttnParams& p, int units, hipStream_t s
 hipError_t kvq_launch_attention_short(const KvqAttnParams& p, int units, hipStream_t s);  // kernel only, no merge
 hipError_t kvq_launch_merge(const KvqAttnParams& p, int units, hipStream_t s);
 hipError_t kvq_launch_attention_i16_append(const KvqAttnParams& p, int units, hipStream_t s);  // kernel only, no merge
+hipError_t kvq_launch_attention_append_narrow(const KvqAttnParams& p, int units, hipStream_t s);  // kernel only, no merge
 // kvq_attention_batch.hip, kvq_attention_short.hip: the bare kernel launches kvq_launch_attention_batch wraps
 hipError_t kvq_launch_attention_short_batch(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16, hipStream_t s);
 hipError_t kvq_launch_attention_batch_kernel(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16,
