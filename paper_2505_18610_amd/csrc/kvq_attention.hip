@@ -86,6 +86,44 @@ hipError_t kvq_launch_attention(const KvqAttnParams& p, int units, hipStream_t s
     return e;
 }
 
+// The parameter blocks as kernel arguments.
+static bool pack_batch_args(const KvqAttnParams* params, const KvqBatchMap& map, int n, KvqBatchArgs& a) {
+    if (!kvq_batch_fits_args(params, n)) return false;
+    a.n = n;
+    for (int i = 0; i <= KVQ_BATCH_ARG_CACHES; ++i) a.wg_begin[i] = map.wg_begin[i < n ? i : n];
+    int at = 0;
+    for (int i = 0; i < n; ++i) {
+        const KvqAttnParams& p = params[i];
+        KvqBatchCache& c = a.cache[i];
+        bool ok = true;
+        const auto offset = [&](const void* x) {
+            if (!x) return 0u;
+            const uint64_t d = (uint64_t)(static_cast<const uint8_t*>(x) - p.arena);
+            ok = ok && d % 16 == 0 && d / 16 <= 0xffffffffull && d != 0;
+            return (uint32_t)(d / 16);
+        };
+        const uint64_t table = (uint64_t)(reinterpret_cast<const uint8_t*>(p.table) - p.arena);  // (the first block's is the arena's start)
+        c.arena = p.arena; c.q = p.q; c.out = p.out; c.app_k = p.app_k; c.app_v = p.app_v; c.app_rope = p.app_rope;
+        c.table16 = (uint32_t)(table / 16);
+        ok = ok && table % 16 == 0 && table / 16 <= 0xffffffffull;
+        c.lambda16 = offset(p.lambda); c.part_o16 = offset(p.part_o); c.part_ml16 = offset(p.part_ml);
+        c.counters16 = offset(p.counters); c.v_mark16 = offset(p.v_mark);
+        ok = ok && (!p.app_rinv || (p.lambda && p.app_rinv == p.lambda + (size_t)p.n_kv_heads * KVQ_D));
+        c.v_epoch = p.v_epoch; c.n_tokens = p.n_tokens; c.tiles_per_page = p.tiles_per_page; c.tpp_magic = p.tpp_magic;
+        c.gqa = p.gqa; c.n_q_heads = p.n_q_heads; c.n_kv_heads = p.n_kv_heads; c.kv_magic = p.kv_magic;
+        c.n_splits = p.n_splits; c.merge_groups = p.merge_groups; c.merge_rounds = p.merge_rounds; c.gqa_magic = p.gqa_magic;
+        c.scale_log2 = p.scale_log2;
+        c.flags = (p.out_fp32 ? 1u : 0u) | (p.fused_merge ? 2u : 0u) | (p.deterministic ? 4u : 0u) | (p.app_rinv ? 8u : 0u) |
+                  (p.app_desc.int16 ? 16u : 0u) | (uint32_t)p.app_gspan << 8;
+        c.split_at = at;
+        c.app_t_old = p.app_t_old; c.app_page = p.app_page;
+        c.app_code_off256 = p.app_desc.code_off256; c.app_meta_off256 = p.app_desc.meta_off256;
+        for (int k = 0; k <= p.n_splits; ++k) a.split_begin[at++] = p.split_begin[k];
+        if (!ok) return false;
+    }
+    return true;
+}
+
 hipError_t kvq_launch_attention_batch(const KvqAttnParams* params_dev, const KvqAttnParams* params_host,
                                       const int* units, int n, hipStream_t s) {
     if (n < 1 || n > KVQ_MAX_BATCH_CACHES) return hipErrorInvalidValue;
@@ -104,8 +142,14 @@ hipError_t kvq_launch_attention_batch(const KvqAttnParams* params_dev, const Kvq
     // took 17.2 and streaming 16.9.
     bool short_ranges = true;
     for (int i = 0; i < n; ++i) short_ranges = short_ranges && params_host[i].short_ranges;
-    hipError_t e = short_ranges ? kvq_launch_attention_short_batch(params_dev, map, int16, s)
-                                : kvq_launch_attention_batch_kernel(params_dev, map, int16, s);
+    hipError_t e;
+    if (!params_dev) {
+        KvqBatchArgs args;
+        if (!pack_batch_args(params_host, map, n, args)) return hipErrorInvalidValue;
+        e = short_ranges ? kvq_launch_attention_short_batch(args, int16, s) : kvq_launch_attention_batch_kernel(args, int16, s);
+    } else {
+        e = short_ranges ? kvq_launch_attention_short_batch(params_dev, map, int16, s) : kvq_launch_attention_batch_kernel(params_dev, map, int16, s);
+    }
     for (int i = 0; i < n && e == hipSuccess; ++i)
         if (params_host[i].n_splits > 1 && !params_host[i].fused_merge) e = kvq_launch_merge(params_host[i], units[i], s);
     return e;

@@ -12,6 +12,20 @@ __device__ __forceinline__ void batch_body(const KvqAttnParams* __restrict__ par
     const KvqAttnHead P = batch_work(params, map, block, work);
     attention_body<I16, true, KVQ_APPEND_16>(P, work.t_begin, work.t_end, sh, work.split, work.unit);
 }
+template <bool I16>
+__device__ __forceinline__ void batch_body(const KvqBatchArgs& args, AttnShared& sh) {
+    BatchWork work;
+    const KvqAttnHead P = batch_work<false>(args, work);
+    attention_body<I16, true, KVQ_APPEND_16>(P, work.t_begin, work.t_end, sh, work.split, work.unit);
+}
+__global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_batch_args_kernel(const KvqBatchArgs args) {
+    __shared__ AttnShared sh;
+    batch_body<false>(args, sh);
+}
+__global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_batch_args_i16_kernel(const KvqBatchArgs args) {
+    __shared__ AttnShared sh;
+    batch_body<true>(args, sh);
+}
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_batch_kernel(const KvqAttnParams* __restrict__ params,
                                                                                const KvqBatchMap map) {
     __shared__ AttnShared sh;
@@ -27,6 +41,12 @@ __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_batch_i16_kern
 
 }  // namespace
 
+hipError_t kvq_launch_attention_batch_kernel(const KvqBatchArgs& args, bool int16, hipStream_t s) {
+    const dim3 grid(args.wg_begin[args.n]), block(KVQ_ATTN_THREADS);
+    if (int16) hipLaunchKernelGGL(kvq_attention_batch_args_i16_kernel, grid, block, 0, s, args);
+    else hipLaunchKernelGGL(kvq_attention_batch_args_kernel, grid, block, 0, s, args);
+    return hipGetLastError();
+}
 hipError_t kvq_launch_attention_batch_kernel(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16,
                                              hipStream_t s) {
     const int wgs = map.wg_begin[map.n];

@@ -300,6 +300,20 @@ __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_i16_appe
     short_body<true, KVQ_APPEND_NARROW>(P, sh);
 }
 
+template <bool I16>
+__device__ __forceinline__ void short_batch_body(const KvqBatchArgs& args, AttnShared& sh) {
+    BatchWork work;
+    const KvqAttnHead P = batch_work<true>(args, work);
+    short_range<I16, KVQ_APPEND_16>(P, work.t_begin, work.t_end, work.split, work.unit, sh);
+}
+__global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_batch_args_kernel(const KvqBatchArgs args) {
+    __shared__ AttnShared sh;
+    short_batch_body<false>(args, sh);
+}
+__global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_batch_args_i16_kernel(const KvqBatchArgs args) {
+    __shared__ AttnShared sh;
+    short_batch_body<true>(args, sh);
+}
 __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_batch_kernel(const KvqAttnParams* __restrict__ params,
                                                                                      const KvqBatchMap map) {
     __shared__ AttnShared sh;
@@ -315,6 +329,12 @@ __global__ __launch_bounds__(KVQ_ATTN_THREADS) void kvq_attention_short_batch_i1
 
 }  // namespace
 
+hipError_t kvq_launch_attention_short_batch(const KvqBatchArgs& args, bool int16, hipStream_t s) {
+    const dim3 grid(args.wg_begin[args.n]), block(KVQ_ATTN_THREADS);
+    if (int16) hipLaunchKernelGGL(kvq_attention_short_batch_args_i16_kernel, grid, block, 0, s, args);
+    else hipLaunchKernelGGL(kvq_attention_short_batch_args_kernel, grid, block, 0, s, args);
+    return hipGetLastError();
+}
 hipError_t kvq_launch_attention_short_batch(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16, hipStream_t s) {
     const dim3 grid(map.wg_begin[map.n]), block(KVQ_ATTN_THREADS);
     if (int16) hipLaunchKernelGGL(kvq_attention_short_batch_i16_kernel, grid, block, 0, s, params_dev, map);

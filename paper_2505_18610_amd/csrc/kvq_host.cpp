@@ -1155,13 +1155,14 @@ kvq_status_t batch_attention(kvq_cache_t* const* caches, int32_t n, int32_t laye
                                            cos_sin_dev ? cos_sin_dev[i] : nullptr, share[(size_t)i].splits, params[(size_t)i]);
         if (st != KVQ_OK) return st;
     }
-    // The kernel reads the parameter blocks straight from the pinned staging ring of the first cache (host memory the
-    // device can address): a copy into the arena would be a separate transfer between two kernels on the stream, which
-    // costs more than the workgroups' first reads travelling over the host link.
+    // Parameter blocks of up to 16 caches travel in the kernel arguments.  Those of more the kernel reads straight from the pinned
+    // staging ring of the first cache (host memory the device can address): a copy into the arena would be a separate transfer
+    // between two kernels on the stream, which costs more than the workgroups' first reads travelling over the host link.
     kvq_cache_t* lead = caches[0];
     const KvqAttnParams* params_dev = nullptr;
-    kvq_status_t st = stage(lead, params.data(), params.size() * sizeof(KvqAttnParams), s,
-                            reinterpret_cast<const void**>(&params_dev));
+    kvq_status_t st = KVQ_OK;
+    if (!kvq_batch_fits_args(params.data(), n))
+        st = stage(lead, params.data(), params.size() * sizeof(KvqAttnParams), s, reinterpret_cast<const void**>(&params_dev));
     std::vector<int> units((size_t)n);
     for (int i = 0; i < n; ++i) units[(size_t)i] = caches[i]->units;
     if (st == KVQ_OK && kvq_launch_attention_batch(params_dev, params.data(), units.data(), n, s) != hipSuccess) st = KVQ_E_HIP;

@@ -137,6 +137,43 @@ struct KvqBatchMap {
     int32_t wg_begin[KVQ_MAX_BATCH_CACHES + 1];  // first workgroup of every cache; [n] = grid size
 };
 
+// A batch of few caches has its parameters in the kernel arguments instead: what differs from cache to cache, pointers into the arena as
+// offsets in units of 16 bytes (0: none), and the ranges of all caches one after the other.
+#define KVQ_BATCH_ARG_CACHES 16
+#define KVQ_BATCH_ARG_SPLITS 320
+struct KvqBatchCache {
+    const uint8_t* arena;
+    const void *q, *app_k, *app_v;
+    void* out;
+    const float* app_rope;
+    uint32_t table16, lambda16, part_o16, part_ml16, counters16, v_mark16;
+    uint32_t v_epoch;
+    int32_t n_tokens, tiles_per_page;
+    uint32_t tpp_magic;
+    int32_t gqa, n_q_heads, n_kv_heads;
+    uint32_t kv_magic;
+    int32_t n_splits, merge_groups, merge_rounds;
+    uint32_t gqa_magic;
+    float scale_log2;
+    uint32_t flags;       // bit 0: out_fp32, 1: fused_merge, 2: deterministic, 3: reciprocal factors for the new token, 4: its page's int16; from bit 8 on its gspan
+    int32_t split_at;     // where the cache's ranges begin in split_begin
+    int32_t app_t_old, app_page;
+    uint32_t app_code_off256, app_meta_off256;
+};
+struct KvqBatchArgs {
+    int32_t n;
+    int32_t wg_begin[KVQ_BATCH_ARG_CACHES + 1];  // first workgroup of every cache; entries from n on hold the grid size
+    KvqBatchCache cache[KVQ_BATCH_ARG_CACHES];
+    int32_t split_begin[KVQ_BATCH_ARG_SPLITS];
+};
+static_assert(sizeof(KvqBatchArgs) <= 3840, "kernel arguments end at 4 KiB");
+// Whether the parameters of these caches fit (their parameter blocks need not be in device-visible memory then).
+inline bool kvq_batch_fits_args(const KvqAttnParams* p, int n) {
+    int ranges = 0;
+    for (int i = 0; i < n; ++i) ranges += p[i].n_splits + 1;
+    return n <= KVQ_BATCH_ARG_CACHES && ranges <= KVQ_BATCH_ARG_SPLITS;
+}
+
 // Static scratch of kvq_decode_attention_static (kvq_attention.hip): room for the partials of KVQ_STATIC_MAX_WGS
 // workgroups (units * splits of one launch) and their arrival counters (a launch of more than one split per unit has at most
 // half as many units as workgroups).
@@ -157,9 +194,12 @@ hipError_t kvq_launch_attention_i16_append(const KvqAttnParams& p, int units, hi
 hipError_t kvq_launch_attention_append_narrow(const KvqAttnParams& p, int units, hipStream_t s);  // kernel only, no merge
 // kvq_attention_batch.hip, kvq_attention_short.hip: the bare kernel launches kvq_launch_attention_batch wraps
 hipError_t kvq_launch_attention_short_batch(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16, hipStream_t s);
+hipError_t kvq_launch_attention_short_batch(const KvqBatchArgs& args, bool int16, hipStream_t s);
 hipError_t kvq_launch_attention_batch_kernel(const KvqAttnParams* params_dev, const KvqBatchMap& map, bool int16,
                                              hipStream_t s);
-// params_dev: the n parameter blocks in device memory (in stream order); params_host: the same blocks on the host;
+hipError_t kvq_launch_attention_batch_kernel(const KvqBatchArgs& args, bool int16, hipStream_t s);
+// params_dev: the n parameter blocks in device memory (in stream order), or null where they fit the kernel arguments
+// (kvq_batch_fits_args); params_host: the same blocks on the host;
 // units[i]: (sequence, KV head) units of cache i
 hipError_t kvq_launch_attention_batch(const KvqAttnParams* params_dev, const KvqAttnParams* params_host,
                                       const int* units, int n, hipStream_t s);
