@@ -3,11 +3,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
-#include <new>
-#include <set>
+#include <cstdlib>
 #include <limits>
+#include <memory>
+#include <new>
 #include <vector>
 
 #include "../../include/kvq.h"
@@ -19,6 +21,7 @@ namespace {
 constexpr int kMaxOrder = 4;  // allocation blocks of 1, 2, 4, 8, 16 units; a unit is one metadata block
 constexpr int kRingSegments = 4;
 constexpr uint64_t kRingSegmentBytes = 1u << 20;  // the pinned staging ring: 4 segments of 1 MiB
+constexpr uint64_t kNoSum = 0x7ff0dead0000beefull;  // a signalling NaN
 
 // Markers of the staging ring: one HIP event per segment, recorded on the cache's stream.
 struct RingEvents {
@@ -33,25 +36,72 @@ int order_of_bits(int bits) { return bits == 16 ? 4 : bits == 8 ? 3 : bits == 4 
 constexpr int kTileTime[4] = {100, 145, 250, 300};
 bool valid_bits(int b) { return b == 16 || b == 8 || b == 4 || b == 2; }
 
+// A set of numbers below n that finds its smallest: a bit for each, and a bit per word of the level below on the levels above.
+class NumberSet {
+public:
+    bool init(uint64_t n, bool full) {
+        levels_.clear();
+        for (uint64_t bits = n;;) {
+            const uint64_t words = std::max<uint64_t>(1, (bits + 63) / 64);
+            levels_.emplace_back(static_cast<uint64_t*>(std::calloc(words, sizeof(uint64_t))));  // (pages of zeros cost nothing until written)
+            if (!levels_.back()) return false;
+            if (full) {
+                std::memset(levels_.back().get(), 0xff, (size_t)(bits / 64) * sizeof(uint64_t));
+                if (bits % 64) levels_.back()[(size_t)(bits / 64)] = (1ull << (bits % 64)) - 1;
+            }
+            if (words == 1) return true;
+            bits = words;
+        }
+    }
+    bool empty() const { return levels_.back()[0] == 0; }
+    uint32_t smallest() const {
+        uint64_t i = 0;
+        for (size_t l = levels_.size(); l-- > 0;) i = i * 64 + (uint64_t)__builtin_ctzll(levels_[l][i]);
+        return (uint32_t)i;
+    }
+    bool has(uint32_t i) const { return levels_[0][i / 64] >> (i % 64) & 1; }
+    void add(uint32_t i) {
+        for (auto& words : levels_) {
+            const uint64_t old = words[i / 64];
+            words[i / 64] = old | 1ull << (i % 64);
+            if (old) return;
+            i /= 64;
+        }
+    }
+    void remove(uint32_t i) {
+        for (auto& words : levels_) {
+            if (words[i / 64] &= ~(1ull << (i % 64))) return;
+            i /= 64;
+        }
+    }
+
+private:
+    struct Free { void operator()(uint64_t* p) const { std::free(p); } };
+    std::vector<std::unique_ptr<uint64_t[], Free>> levels_;
+};
+
 // Buddy allocator in units.  Code blocks need 2^order units (2-bit: 2, 4-bit: 4, 8-bit: 8, 16-bit: 16),
 // metadata blocks one unit, so every size is a power of two and freed space coalesces without compaction.
+// (With the free blocks in std::set a prompt of 16,000 tokens that is shrunk twice spent 55 of the host's 137 us here, and more than a
+// launch takes on most calls.)
 class Buddy {
 public:
-    void init(uint32_t n_super) {
-        for (auto& f : free_) f.clear();
-        for (uint32_t i = 0; i < n_super; ++i) free_[kMaxOrder].insert(i << kMaxOrder);
-        total_ = (uint64_t)n_super << kMaxOrder;
-        free_units_ = total_;
+    bool init(uint32_t n_super) {
+        for (int o = 0; o <= kMaxOrder; ++o)
+            if (!free_[o].init((uint64_t)n_super << (kMaxOrder - o), o == kMaxOrder)) return false;
+        free_units_ = (uint64_t)n_super << kMaxOrder;
+        return true;
     }
     bool alloc(int order, uint32_t* off) {
         int o = order;
         while (o <= kMaxOrder && free_[o].empty()) ++o;
         if (o > kMaxOrder) return false;
-        uint32_t blk = *free_[o].begin();
-        free_[o].erase(free_[o].begin());
+        uint32_t blk = free_[o].smallest();
+        free_[o].remove(blk);
+        blk <<= o;
         while (o > order) {
             --o;
-            free_[o].insert(blk + (1u << o));
+            free_[o].add((blk >> o) + 1);
         }
         free_units_ -= 1u << order;
         *off = blk;
@@ -59,21 +109,19 @@ public:
     }
     void release(uint32_t off, int order) {
         free_units_ += 1u << order;
-        while (order < kMaxOrder) {
-            uint32_t buddy = off ^ (1u << order);
-            auto it = free_[order].find(buddy);
-            if (it == free_[order].end()) break;
-            free_[order].erase(it);
-            off = std::min(off, buddy);
+        uint32_t blk = off >> order;
+        while (order < kMaxOrder && free_[order].has(blk ^ 1)) {
+            free_[order].remove(blk ^ 1);
+            blk >>= 1;
             ++order;
         }
-        free_[order].insert(off);
+        free_[order].add(blk);
     }
     uint64_t free_units() const { return free_units_; }
 
 private:
-    std::set<uint32_t> free_[kMaxOrder + 1];
-    uint64_t total_ = 0, free_units_ = 0;
+    NumberSet free_[kMaxOrder + 1];
+    uint64_t free_units_ = 0;
 };
 
 struct Page {
@@ -95,8 +143,8 @@ struct Layer {
     bool poisoned = false; // an enqueue failed after the host tables had been updated: unusable until kvq_cache_reset
     std::vector<Page> pages;
     // the pages as runs of one width, of the state runs_version; see runs_of
-    std::vector<Run> runs;
-    uint64_t runs_version = ~0ull;
+    mutable std::vector<Run> runs;
+    mutable uint64_t runs_version = ~0ull;
     // what the split count was worked out from and the count itself; split plan cache of kvq_decode_attention
     uint64_t count_key[3] = {};
     int count_splits = 1;
@@ -125,6 +173,8 @@ struct kvq_cache {
     uint8_t* ring_dev = nullptr;  // the same pinned memory as the device addresses it
     KvqStagingRing<RingEvents, kRingSegments> ring_ctl;
     RingEvents ring_events;
+    uint64_t* sums = nullptr;   // behind the ring: 2 sums for each workgroup of the error kernel, kNoSum between calls
+    bool sums_at_rest = false;
     bool device_ready = false;
     bool enqueue_failed = false;  // a block was left unusable since the device's counters were last cleared
     int splits_override = 0;
@@ -242,22 +292,39 @@ kvq_status_t upload_table(kvq_cache* c, int layer, int first, int last, hipStrea
     return upload(c, c->table_dev(layer) + first, d.data(), d.size() * sizeof(KvqPageDesc), s);
 }
 
+// Accounting and launch plans look at widths only, of which a block of thousands of pages has a few runs.  An append extends them, a page that goes
+// down makes them stale.  (131,000 tokens in pages of 32, a step a launch: looking at every page cost the host 7 of 31 us.)
+const std::vector<Run>& runs_of(const Layer& L) {
+    if (L.runs_version != L.version) {
+        L.runs.clear();
+        for (size_t i = 0; i < L.pages.size(); ++i) {
+            if (L.runs.empty() || L.runs.back().bits != L.pages[i].bits) L.runs.push_back(Run{(int)i + 1, L.pages[i].bits});
+            else L.runs.back().page_end = (int)i + 1;
+        }
+        L.runs_version = L.version;
+    }
+    return L.runs;
+}
+
+// (every page but the last is full)
 uint64_t bytes_used(const kvq_cache* c, const Layer& L) {
     uint64_t u = 0;
-    for (const Page& p : L.pages) u += (uint64_t)p.n * c->units * c->bpth(p.bits);
+    int64_t t = 0;
+    for (const Run& r : runs_of(L)) {
+        const int64_t end = std::min<int64_t>((int64_t)r.page_end * c->cfg.page_tokens, L.T);
+        u += (uint64_t)(end - t) * c->units * c->bpth(r.bits);
+        t = end;
+    }
     return u;
 }
 
 // Width of the block's bulk: smallest width among pages after the sink (16 if there is none).
-int current_bits(const kvq_cache* c, const std::vector<int>& bits) {
-    int first = c->cfg.n_sink / c->cfg.page_tokens, b = 16;
-    for (size_t i = (size_t)first; i < bits.size(); ++i) b = std::min(b, bits[i]);
-    return b;
-}
 int current_bits(const kvq_cache* c, const Layer& L) {
-    std::vector<int> bits(L.pages.size());
-    for (size_t i = 0; i < bits.size(); ++i) bits[i] = L.pages[i].bits;
-    return current_bits(c, bits);
+    const int first = c->cfg.n_sink / c->cfg.page_tokens;
+    int b = 16;
+    for (const Run& r : runs_of(L))
+        if (r.page_end > first) b = std::min(b, r.bits);
+    return b;
 }
 
 // Sink pages and pages overlapping the most recent `window` tokens are never lowered.
@@ -400,20 +467,6 @@ int longest_even(int n_tiles, int n, int tpp) {
     const int k = (n_tiles + n - 1) / n;
     return n > 1 && tpp % 2 == 0 ? (k + 1) & ~1 : k;
 }
-// Launch plans look at widths only, of which a block of thousands of pages has a few runs.  An append extends them, a page that goes
-// down makes them stale.  (131,000 tokens in pages of 32, a step a launch: looking at every page cost the host 7 of 31 us.)
-const std::vector<Run>& runs_of(Layer& L) {
-    if (L.runs_version != L.version) {
-        L.runs.clear();
-        for (size_t i = 0; i < L.pages.size(); ++i) {
-            if (L.runs.empty() || L.runs.back().bits != L.pages[i].bits) L.runs.push_back(Run{(int)i + 1, L.pages[i].bits});
-            else L.runs.back().page_end = (int)i + 1;
-        }
-        L.runs_version = L.version;
-    }
-    return L.runs;
-}
-
 // Ranges of about the same sum of cost[cost_index(width)], none of more than `most` tiles, written to split_begin.
 void cut_by_cost(const kvq_cache* c, Layer& L, int n_tiles, int n_splits, const uint64_t (&costs)[4], int most) {
     const int tpp = c->tpp;
@@ -523,7 +576,7 @@ kvq_status_t kvq_cache_create(const kvq_config_t* cfg, const uint64_t* block_bud
     if (arena_bytes < c->pages_off + super) { delete c; return KVQ_E_OOM; }
     uint64_t n_super = (arena_bytes - c->pages_off) / super;
     if ((c->pages_off + n_super * super) / 256 > 0xffffffffull) { delete c; return KVQ_E_INVALID; }
-    c->buddy.init((uint32_t)n_super);
+    if (!c->buddy.init((uint32_t)n_super)) { delete c; return KVQ_E_OOM; }
     c->layers.resize((size_t)cfg->n_layers);
     for (int i = 0; i < cfg->n_layers; ++i) {
         c->layers[(size_t)i].budget = block_budget_bytes_host[i];
@@ -531,7 +584,7 @@ kvq_status_t kvq_cache_create(const kvq_config_t* cfg, const uint64_t* block_bud
     }
     if (!c->dry) {
         c->ring_ctl.init(kRingSegmentBytes);
-        if (hipHostMalloc(reinterpret_cast<void**>(&c->ring), c->ring_ctl.total_bytes(), hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(reinterpret_cast<void**>(&c->ring), c->ring_ctl.total_bytes() + 2 * KVQ_ERR_MAX_WGS * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
             delete c;
             return KVQ_E_HIP;
         }
@@ -549,6 +602,9 @@ kvq_status_t kvq_cache_create(const kvq_config_t* cfg, const uint64_t* block_bud
             delete c;
             return KVQ_E_HIP;
         }
+        c->sums = reinterpret_cast<uint64_t*>(c->ring + c->ring_ctl.total_bytes());
+        std::fill_n(c->sums, 2 * KVQ_ERR_MAX_WGS, kNoSum);
+        c->sums_at_rest = true;
         int dev = 0;
         hipDeviceProp_t prop;
         if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess &&
@@ -580,11 +636,11 @@ struct DeferredAppend {
     KvqPageDesc desc{};
 };
 
-// Bookkeeping of an append, worked out without touching the cache: entry width, page widths and fill counts
-// afterwards, the window pages the append evicts and the width they go to.
+// Bookkeeping of an append, worked out without touching the cache: entry width, tokens and pages afterwards, the window pages
+// the append evicts and the width they go to.
 struct AppendPlan {
-    int e = 16, T = 0, bcur = 16;
-    std::vector<int> bits, cnt, evicted;
+    int e = 16, T = 0, n_pages = 0, bcur = 16;
+    std::vector<int> evicted;
 };
 
 kvq_status_t plan_append(const kvq_cache_t* c, int32_t layer, int32_t n_new, int32_t entry_bits, AppendPlan& pl) {
@@ -598,31 +654,21 @@ kvq_status_t plan_append(const kvq_cache_t* c, int32_t layer, int32_t n_new, int
     if (L.T % P != 0 && L.pages.back().bits != e) return KVQ_E_STATE;
     const bool evict = entry_bits == 0 && cfg.policy == KVQ_POLICY_PAPER && cfg.window > 0;
     pl.e = e;
-    pl.bits.resize(L.pages.size());
-    pl.cnt.resize(L.pages.size());
-    for (size_t i = 0; i < L.pages.size(); ++i) { pl.bits[i] = L.pages[i].bits; pl.cnt[i] = L.pages[i].n; }
-    int T = L.T, left = n_new;
-    while (left) {
-        if (T % P == 0) { pl.bits.push_back(e); pl.cnt.push_back(0); }
-        int take = std::min(left, P - pl.cnt.back());
-        pl.cnt.back() += take; T += take; left -= take;
-    }
-    pl.T = T;
+    const int T = pl.T = L.T + n_new;
+    pl.n_pages = (int)(((int64_t)T + P - 1) / P);
     pl.evicted.clear();
     pl.bcur = 16;
-    if (evict) {
-        pl.bcur = current_bits(c, pl.bits);
-        if (pl.bcur < 16) {
-            for (;;) {
-                int i = (int)pl.bits.size(), first = cfg.n_sink / P;
-                while (i > first && pl.bits[(size_t)i - 1] == 16) --i;  // start of the trailing 16-bit run
-                if (i < (int)pl.bits.size() && T - i * P >= cfg.window + P) { pl.bits[(size_t)i] = pl.bcur; pl.evicted.push_back(i); }
-                else break;
-            }
+    uint64_t used = bytes_used(c, L) + (uint64_t)n_new * c->units * c->bpth(e);
+    if (evict) pl.bcur = current_bits(c, L);  // (the new pages have 16 bits)
+    if (pl.bcur < 16) {
+        const int first = cfg.n_sink / P;
+        int i = std::max((int)L.pages.size(), first);
+        while (i > first && L.pages[(size_t)i - 1].bits == 16) --i;  // start of the trailing 16-bit run
+        for (; i < pl.n_pages && (int64_t)T - (int64_t)i * P >= (int64_t)cfg.window + P; ++i) {
+            pl.evicted.push_back(i);
+            used -= (uint64_t)P * c->units * (c->bpth(16) - c->bpth(pl.bcur));
         }
     }
-    uint64_t used = 0;
-    for (size_t i = 0; i < pl.bits.size(); ++i) used += (uint64_t)pl.cnt[i] * c->units * c->bpth(pl.bits[i]);
     if (used > L.budget) return KVQ_E_BUDGET;
     return KVQ_OK;
 }
@@ -657,7 +703,7 @@ void release_append(kvq_cache_t* c, AppendBlocks& bl) {
 
 // Takes the blocks of a planned append; on an error none is held.
 kvq_status_t reserve_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, AppendBlocks& bl, hipStream_t s) {
-    for (size_t i = c->layers[(size_t)layer].pages.size(); i < pl.bits.size(); ++i) {
+    for (int i = (int)c->layers[(size_t)layer].pages.size(); i < pl.n_pages; ++i) {
         Page p;
         p.bits = pl.e;
         const bool ok = c->buddy.alloc(order_of_bits(p.bits), &p.code_unit);
@@ -691,7 +737,7 @@ kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, 
     kvq_status_t st = KVQ_OK;
     const int t_old = L.T, T = pl.T;
     for (const Page& p : bl.fresh) L.pages.push_back(p);
-    for (size_t i = 0; i < L.pages.size(); ++i) L.pages[i].n = pl.cnt[i];
+    for (size_t i = (size_t)(t_old / P); i < L.pages.size(); ++i) L.pages[i].n = std::min(P, T - (int)i * P);
     L.T = T;
     if (L.runs_version == L.version && !L.runs.empty() && L.runs.back().bits == e) {  // new pages have the width e
         L.runs.back().page_end = (int)L.pages.size();
@@ -1426,19 +1472,43 @@ kvq_status_t cache_error(kvq_cache_t* c, int32_t layer, bool l1, const void* k_r
     const Layer& L = c->layers[(size_t)layer];
     if (L.T == 0 || L.poisoned) return KVQ_E_STATE;
     hipStream_t s = as_stream(hip_stream);
-    // The workgroups store their sums straight into the pinned staging ring, where the host adds them up behind the
-    // synchronization this call makes anyway: no accumulators to clear, no copy back.
-    const int wgs = kvq_error_workgroups(L.T, c->units);
-    c->ring_events.stream = s;
-    const int64_t at = c->ring_ctl.reserve(c->ring_events, (uint64_t)wgs * 2 * sizeof(double), 256);
-    if (at < 0) return KVQ_E_HIP;
+    // The workgroups store their sums straight into pinned memory, where the host adds them up as they come: no accumulators to
+    // clear, no copy back, and no wait for the end of the kernel, whose completion signal reaches the host some 5 us behind the last
+    // sum.  A sum that is not there yet reads as a NaN no sum can be (its quiet bit is clear: arithmetic gives quiet ones).  All that a
+    // workgroup reads it has read before it stores, so that with the last sum the inputs are the caller's again.  What keeps the host
+    // waiting longer than a millisecond, work in front of the kernel as a rule, or an error, is left to the stream's synchronization.
+    // Whole calls with the synchronization and now: 16 units x 137 tokens 16.9 and 11.5 us, 64 x 2,048 with gradients 50.7 and 42.1.
+    const int n = 2 * kvq_error_workgroups(L.T, c->units);
+    if (!c->sums_at_rest) std::fill_n(c->sums, 2 * KVQ_ERR_MAX_WGS, kNoSum);
+    c->sums_at_rest = false;
     if (kvq_launch_error(l1, c->arena, c->table_dev(layer), k_ref_dev, v_ref_dev, gk_dev, gv_dev, L.T, c->tpp, c->units,
-                         reinterpret_cast<double*>(c->ring_dev + at), s) != hipSuccess)
+                         reinterpret_cast<double*>(c->ring_dev + c->ring_ctl.total_bytes()), s) != hipSuccess)
         return KVQ_E_HIP;
-    if (hipStreamSynchronize(s) != hipSuccess) return KVQ_E_HIP;
-    const double* partial = reinterpret_cast<const double*>(c->ring + at);
-    out_host[0] = out_host[1] = 0.0;
-    for (int i = 0; i < wgs; ++i) { out_host[0] += partial[2 * i]; out_host[1] += partial[2 * i + 1]; }
+    bool waited = false;
+    const auto start = std::chrono::steady_clock::now();
+    const auto sum_at = [&](int i, uint64_t* bits) {
+        for (int spins = 0; (*bits = __atomic_load_n(&c->sums[i], __ATOMIC_ACQUIRE)) == kNoSum; ++spins) {
+            if (waited) return false;  // the stream is done and the sum is not there
+            if (spins % 64 != 63 || std::chrono::steady_clock::now() - start < std::chrono::milliseconds(1)) continue;
+            if (hipStreamSynchronize(s) != hipSuccess) return false;
+            waited = true;
+        }
+        return true;
+    };
+    uint64_t bits;
+    for (int i = n - 1; i >= 0; i -= 64)  // (a look here and there first: what is added up then is there as a rule, line behind line)
+        if (!sum_at(i, &bits)) return KVQ_E_HIP;
+    double sum[2] = {0.0, 0.0};
+    for (int i = 0; i < n; ++i) {
+        if (!sum_at(i, &bits)) return KVQ_E_HIP;
+        double x;
+        std::memcpy(&x, &bits, sizeof x);
+        sum[i & 1] += x;
+    }
+    std::fill_n(c->sums, n, kNoSum);
+    c->sums_at_rest = true;
+    out_host[0] = sum[0];
+    out_host[1] = sum[1];
     return KVQ_OK;
 }
 }  // namespace
