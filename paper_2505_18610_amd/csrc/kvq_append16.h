@@ -115,25 +115,27 @@ struct NewRows {
 // partner read again, 8,192 new tokens x 32 units took 271 us with rotation against 56 without.)
 // LATE: the last eight angles are asked for behind the lookup of the page, which saves the registers for one more wavefront on every
 // SIMD and costs 2 to 4 % where that does not matter.
-template <bool LATE, class Code>
+// SUBS: the lane's tokens that are taken, both of them or, with first_sub, one.
+template <bool LATE, int SUBS, class Code>
 __device__ inline void append16_k_tile(Code code_at, const NewRows& rows, int tok0, int lane, const float* rope,
-                                       const float* rinv_head) {
+                                       const float* rinv_head, int first_sub) {
     const int j = lane >> 4, n = lane & 15;
-    u32x4 v[2][4];
-    bool isnew[2];
+    const int tok1 = tok0 + 8 * (n >> 2) + (n & 3) + 4 * first_sub;
+    u32x4 v[SUBS][4];
+    bool isnew[SUBS];
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-        const int tok = tok0 + 8 * (n >> 2) + 4 * sub + (n & 3);
+    for (int sub = 0; sub < SUBS; ++sub) {
+        const int tok = tok1 + 4 * sub;
         isnew[sub] = rows.has(tok);
         const uint32_t off = rows.offset(tok) + 16u * j;
 #pragma unroll
         for (int grp = 0; grp < 4; ++grp) v[sub][grp] = rows.load(off + 64u * grp);
     }
-    Angles8 a[2][2];
+    Angles8 a[SUBS][2];
     if (rope) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            const float* row = rope + rows.row(tok0 + 8 * (n >> 2) + 4 * sub + (n & 3)) * KVQ_D;
+        for (int sub = 0; sub < SUBS; ++sub) {
+            const float* row = rope + rows.row(tok1 + 4 * sub) * KVQ_D;
 #pragma unroll
             for (int p = 0; p < 2; ++p)
                 if (!LATE || !sub || !p) a[sub][p] = load_angles8(row, 32 * p + 8 * j);
@@ -142,9 +144,9 @@ __device__ inline void append16_k_tile(Code code_at, const NewRows& rows, int to
     __builtin_amdgcn_sched_barrier(0);  // all of these loads first
     uint8_t* const code = code_at();
     if (rope) {
-        if (LATE) a[1][1] = load_angles8(rope + rows.row(tok0 + 8 * (n >> 2) + 4 + (n & 3)) * KVQ_D, 32 + 8 * j);
+        if (LATE) a[SUBS - 1][1] = load_angles8(rope + rows.row(tok1 + 4 * (SUBS - 1)) * KVQ_D, 32 + 8 * j);
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 const u32x4 lo = rope8(v[sub][p], v[sub][p + 2], a[sub][p], 0x80008000u);
@@ -154,30 +156,29 @@ __device__ inline void append16_k_tile(Code code_at, const NewRows& rows, int to
         if (!rows.all(tok0)) {  // (uniform) the zeros of tokens that are not new: a rotated one may be negative
             asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
+            for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
                 for (int grp = 0; grp < 4; ++grp) v[sub][grp] = isnew[sub] ? v[sub][grp] : u32x4{0u, 0u, 0u, 0u};
         }
     }
     if (rinv_head) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
             for (int grp = 0; grp < 4; ++grp) v[sub][grp] = scale_keys8(v[sub][grp], rinv_head + 32 * grp + 8 * j);
     }
+    uint8_t* const to = code + first_sub * 4096 + lane * 16;
     if (tok0 < rows.t_old) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < SUBS; ++sub)
             if (isnew[sub]) {
 #pragma unroll
-                for (int grp = 0; grp < 4; ++grp)
-                    *reinterpret_cast<u32x4*>(code + ((sub * 4 + grp) * 64 + lane) * 16) = v[sub][grp];
+                for (int grp = 0; grp < 4; ++grp) *reinterpret_cast<u32x4*>(to + (sub * 4 + grp) * 1024) = v[sub][grp];
             }
         return;
     }
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
-        __builtin_nontemporal_store(v[c >> 2][c & 3], reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16));
+    for (int c = 0; c < 4 * SUBS; ++c) __builtin_nontemporal_store(v[c >> 2][c & 3], reinterpret_cast<u32x4*>(to + c * 1024));
 }
 
 // The same for a V tile.  A tile of new tokens only goes through LDS: the rows are read with 16-byte loads (a wavefront
@@ -188,53 +189,58 @@ __device__ inline void append16_k_tile(Code code_at, const NewRows& rows, int to
 // A tile that holds older tokens gets the new ones' values one by one, straight from the input: there are few as a rule, one
 // in a decode step, and the trip through LDS only makes the chain longer (kernel of 1 / 8 / 24 tokens x 8 units 2.6 / 3.3 / 3.6
 // us, through LDS 4.7 / 4.8 / 4.6; 1 / 8 / 24 x 600 units 3.0 / 4.6 / 7.2 and 5.1 / 5.2 / 8.0).
-template <class Code>
-__device__ inline void append16_v_tile(Code code_at, const NewRows& rows, int tok0, int lane, uint8_t* lds, bool stream) {
+// CHUNKS: eight, the whole tile, or four: the 64 channels from 16 first_chunk on (a wavefront instruction covers 128 bytes of each
+// of eight rows; lds: 4 KiB).
+template <int CHUNKS, class Code>
+__device__ inline void append16_v_tile(Code code_at, const NewRows& rows, int tok0, int lane, uint8_t* lds, bool stream, int first_chunk) {
     const int j = lane >> 4, n = lane & 15;
     if (tok0 < rows.t_old) {
         uint8_t* const code = code_at();
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             if (rows.has(tok0 + 8 * j + i)) {
-                const uint32_t off = rows.offset(tok0 + 8 * j + i) + 2u * n;
-                uint16_t x[8];
+                const uint32_t off = rows.offset(tok0 + 8 * j + i) + 2u * n + 32u * first_chunk;
+                uint16_t x[CHUNKS];
 #pragma unroll
-                for (int c = 0; c < 8; ++c) x[c] = rows.load_half(off + 32u * c);
+                for (int c = 0; c < CHUNKS; ++c) x[c] = rows.load_half(off + 32u * c);
 #pragma unroll
-                for (int c = 0; c < 8; ++c) *reinterpret_cast<uint16_t*>(code + (c * 64 + lane) * 16 + 2 * i) = x[c];
+                for (int c = 0; c < CHUNKS; ++c)
+                    *reinterpret_cast<uint16_t*>(code + ((first_chunk + c) * 64 + lane) * 16 + 2 * i) = x[c];
             }
         return;
     }
-    u32x4 v[8];
+    constexpr int PITCH = 32 * CHUNKS, LANES = 2 * CHUNKS, ROWS = 64 / LANES;  // bytes and lanes of a row, rows of an instruction
+    const int row = lane / LANES, piece = 16 * (lane % LANES);
+    u32x4 v[CHUNKS];
     if (stream) {
 #pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = rows.load_stream(rows.offset(tok0 + 4 * c + j) + 16u * n);
+        for (int c = 0; c < CHUNKS; ++c) v[c] = rows.load_stream(rows.offset(tok0 + ROWS * c + row) + piece + 32 * first_chunk);
     } else {
 #pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = rows.load(rows.offset(tok0 + 4 * c + j) + 16u * n);
+        for (int c = 0; c < CHUNKS; ++c) v[c] = rows.load(rows.offset(tok0 + ROWS * c + row) + piece + 32 * first_chunk);
     }
     __builtin_amdgcn_sched_barrier(0);
     uint8_t* const code = code_at();
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const int tl = 4 * c + j;
-        *reinterpret_cast<u32x4*>(lds + tl * 256 + ((n * 16 + 32 * (tl >> 3)) & 255)) = v[c];
+    for (int c = 0; c < CHUNKS; ++c) {
+        const int tl = ROWS * c + row;
+        *reinterpret_cast<u32x4*>(lds + tl * PITCH + ((piece + 32 * (tl >> 3)) & (PITCH - 1))) = v[c];
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {  // chunk c of the lane's string = channel block nt = c, tokens 8j + 0..7
+    for (int c = 0; c < CHUNKS; ++c) {  // a chunk of the lane's string = a channel block, tokens 8j + 0..7
         uint32_t w[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int r0 = 8 * j + 2 * e, r1 = r0 + 1;      // same group of 8 rows: same rotation
-            const int col = ((16 * c + n) * 2 + 32 * j) & 255;
-            const uint32_t lo = *reinterpret_cast<const uint16_t*>(lds + r0 * 256 + col);
-            const uint32_t hi = *reinterpret_cast<const uint16_t*>(lds + r1 * 256 + col);
+            const int col = ((16 * c + n) * 2 + 32 * j) & (PITCH - 1);
+            const uint32_t lo = *reinterpret_cast<const uint16_t*>(lds + r0 * PITCH + col);
+            const uint32_t hi = *reinterpret_cast<const uint16_t*>(lds + r1 * PITCH + col);
             w[e] = lo | (hi << 16);
         }
-        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(code + (c * 64 + lane) * 16));
+        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(code + ((first_chunk + c) * 64 + lane) * 16));
     }
 }
 

@@ -22,10 +22,12 @@ using kvq_dev::as_global;
 // the bulk of the general kernels' registers.
 // by_unit: the units of a string follow one another in the grid instead of the strings of a unit.  The table rows of the
 // string's tokens, 512 bytes a token and as much as its keys and values in one unit, are then read by all units at about
-// the same time and come from the caches.  For the 16-bit tiers and at least 98,304 rows of all units together.  Rotated keys,
-// raw fp16 / integer tier, with and without: 4,096 x 32 26.1 / 33.7 instead of 27.6 / 36.1 us, 2,048 x 64 26.2 / 33.8 and 29.0 /
-// 37.4, 2,048 x 48 (98,304 rows) 21.3 / 24.3 and 21.0 / 25.6; 2,048 x 32 (65,536) 15.3 / 18.9 and 15.5 / 18.1, 8,192 x 8 17.7 /
-// 21.8 and 15.2 / 19.4.  Into 8, 4 and 2 bits, where the arithmetic weighs more, it loses 3 to 7 % at every size.
+// the same time and come from the caches.  For the 16-bit tiers and at least 98,304 rows of all units together.
+// Rotated keys into the raw tier, with and without, over the same input / from memory, for 64 units and more and at least 98,304 rows:
+// 2,048 x 64 25.6 and 27.7 / 27.5 and 30.4 us, 4,096 x 128 84 and 90 / 99 and 103; 4,096 x 32 25.5 and 24.5 / 27.2 and 27.0, 2,048 x 48 20.5
+// and 19.2 / 21.8 and 21.4, 1,024 x 64 (65,536 rows) 14.4 and 14.5 / 15.9 and 17.6, 8,192 x 8 17.9 and 14.3 / 17.5 and 18.7.  Into the integer
+// tier, at least 98,304 rows: 4,096 x 32 33.7 and 36.1, 2,048 x 64 33.8 and 37.4, 2,048 x 48 24.3 and 25.6; 2,048 x 32 18.9 and 18.1.
+// Into 8, 4 and 2 bits, where the arithmetic weighs more, it loses 3 to 7 % at every size.
 // What a launch's kernels need, read at once at their start: left alone the compiler reads the arguments one by one where they
 // are used first, each a trip to the constant cache or beyond, and three quotients and the lookup of the page entry stood in
 // front of the rows as well.  Now rows and angles are asked for first and the page entry behind them, needed only for the stores.
@@ -82,30 +84,55 @@ __device__ __forceinline__ bool append_string(const AppendArgs& A, int wave, App
     return string < A.n_strings;
 }
 
-// Append into the 16-bit tier: the new rows are copied into the tile layout.  FIVE: with 92 registers five wavefronts fit on a SIMD,
-// otherwise, with 104, four.  Prepared keys of 4,097 to 4,608 and 5,121 to 5,632 strings, the odd steps of half a wavefront a SIMD beyond
-// four, end earlier with five (16 units x 136 tiles, rotated and scaled, 17.0 us and 19.0, x 164 20.9 and 21.9), those between and beyond
-// with four (x 156 20.6 and 19.4, 8,192 strings and more 2 to 4 %).
+// Append into the 16-bit tier: the new rows are copied into the tile layout.  A workgroup is a tile, its first wavefront the keys and
+// its second the values.  Workgroups go to the eight XCDs in turn: with one string each, keys and values in turn, all keys, which
+// are rotated and scaled, were on every other XCD and the others had little to do.  One wavefront a workgroup and now: 1,024 tokens x
+// 16 units rotated 6.1 and 5.1 us, 2,500 x 8 7.0 and 6.0, 1,024 x 32 9.3 and 7.5, 2,048 x 32 15.4 and 14.3, neither rotated nor scaled
+// 2,500 x 8 4.4 and 4.2, 4,096 x 128 96 and 86.
+// FIVE: with 92 registers five wavefronts fit on a SIMD, otherwise, with 104, four.  Scaled keys of 4,097 to 4,608 and 5,121 to 5,632
+// strings, the odd steps of half a wavefront a SIMD beyond four, end earlier with five (16 units x 144 tiles 16.4 us and 17.8, from memory
+// 18.1 and 19.4; x 164 19.1 and 19.2, 19.2 and 20.1); 4,992 strings are alike, and keys that are only rotated lose 1 to 4 % of it.
 template <bool PLAIN, bool FIVE>
-__global__ __launch_bounds__(64) void kvq_append16_kernel(const AppendArgs args) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[32 * 256];
-    const int lane = threadIdx.x;
+__global__ __launch_bounds__(128) void kvq_append16_kernel(const AppendArgs args) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[32 * 256];  // of the wavefront with the values
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     AppendArgs A;
     read_append_args<PLAIN>(args, A);
     AppendString t;
-    const bool mine = append_string<PLAIN, 1>(A, 0, t);
-    if (mine) {
-        const kvq_dev::NewRows rows((t.which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, A.t_old, A.n_new);
-        const int tok0 = t.tile * KVQ_TILE_TOKENS;
-        // the page entry is looked up behind the loads of the rows
-        const auto code = [&]() {
-            const KvqPageDesc pd = append_desc<false>(A.table, args.pages, t.page);
-            return A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + t.which) * (512u * 16);
-        };
-        if (t.which) kvq_dev::append16_v_tile(code, rows, tok0, lane, lds, A.stream_v);  // (wavefront-uniform)
-        else kvq_dev::append16_k_tile<FIVE>(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head);
-    }
-    write_fresh_pages(A.table, args.pages, lane);
+    append_string<PLAIN, 2>(A, wave, t);  // (the number of strings is even)
+    const kvq_dev::NewRows rows((t.which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, A.t_old, A.n_new);
+    const int tok0 = t.tile * KVQ_TILE_TOKENS;
+    // the page entry is looked up behind the loads of the rows
+    const auto code = [&]() {
+        const KvqPageDesc pd = append_desc<false>(A.table, args.pages, t.page);
+        return A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + t.which) * (512u * 16);
+    };
+    if (t.which) kvq_dev::append16_v_tile<8>(code, rows, tok0, lane, lds, A.stream_v, 0);  // (wavefront-uniform)
+    else kvq_dev::append16_k_tile<FIVE, 2>(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head, 0);
+    if (wave == 1) write_fresh_pages(A.table, args.pages, lane);
+}
+// The same with two wavefronts per string, which share nothing: of keys each takes 16 tokens, of values 64 channels.  For launches
+// that leave SIMDs without a wavefront otherwise, where the chain of one is what counts: up to 512 strings, up to 1,024 of keys that need
+// no preparation.  One wavefront per string and two, over the same input / from memory: prepared, 1 token x 8 units 3.4 and 3.0 us, 256 x
+// 8 3.8 and 3.6 / 3.9 and 3.6, 700 x 8 alike, 1,500 x 8 5.2 and 5.0 / 5.5 and 5.5, 1,024 x 16 5.4 and 5.5 / 5.9 and 5.8, rotated only 5.1 and
+// 5.2 / 5.2 and 5.8; unprepared 256 x 8 2.9 and 2.9 / 3.5 and 2.9, 1,024 x 16 3.8 and 4.0 / 5.6 and 4.6, 1,536 x 16 4.3 and 4.8 / 6.4 and 5.6.
+template <bool PLAIN>
+__global__ __launch_bounds__(256) void kvq_append16_pair_kernel(const AppendArgs args) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][32 * 128];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
+    AppendArgs A;
+    read_append_args<PLAIN>(args, A);
+    AppendString t;
+    append_string<PLAIN, 2>(A, wave >> 1, t);
+    const kvq_dev::NewRows rows((t.which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, A.t_old, A.n_new);
+    const int tok0 = t.tile * KVQ_TILE_TOKENS;
+    const auto code = [&]() {
+        const KvqPageDesc pd = append_desc<false>(A.table, args.pages, t.page);
+        return A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + t.which) * (512u * 16);
+    };
+    if (t.which) kvq_dev::append16_v_tile<4>(code, rows, tok0, lane, lds[half], A.stream_v, 4 * half);
+    else kvq_dev::append16_k_tile<false, 1>(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head, half);
+    if (wave == 3) write_fresh_pages(A.table, args.pages, lane);
 }
 
 // Quantizing append (B = 8, 4, 2), built on the row-owner core.
@@ -866,8 +893,9 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     // MB) 86 and 85, from buffers in turn 102 and 94.  Beside keys that are prepared, streaming is the better or the same: 32 x
     // 2,000 16.0 and 16.0, from buffers in turn 18.9 and 15.8.
     const int stream_v = !plain || (int64_t)units * n_new * (2 * 256) > (192 << 20);
-    const bool five = strings > 4096 && strings <= 5632 && (strings + 511) / 512 % 2 == 1;  // see kvq_append16_kernel
-    const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 ? units : 0;
+    const bool few = strings <= (plain ? 1024 : 512);  // see kvq_append16_pair_kernel
+    const bool five = rinv && strings > 4096 && strings <= 5632 && (strings + 511) / 512 % 2 == 1;  // see kvq_append16_kernel
+    const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 && (int16 || units >= 64) ? units : 0;
     AppendArgs A;
     A.arena = arena; A.table = table; A.k = k; A.v = v; A.rinv = rinv; A.rope = rope; A.v_word = mark.word; A.v_epoch = mark.epoch;
     A.t_old = t_old; A.n_new = n_new; A.tpp = tiles_per_page; A.tile0 = tile0; A.n_strings = n_strings; A.by_unit = by_unit;
@@ -895,9 +923,11 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
             else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, 1);
             break;
         case 16:
-            if (plain) KVQ_APPEND_LAUNCH((kvq_append16_kernel<true, false>), 1, 1);
-            else if (five) KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, true>), 1, 1);
-            else KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, false>), 1, 1);
+            if (plain && few) KVQ_APPEND_LAUNCH(kvq_append16_pair_kernel<true>, 2, 2);
+            else if (plain) KVQ_APPEND_LAUNCH((kvq_append16_kernel<true, false>), 2, 1);
+            else if (few) KVQ_APPEND_LAUNCH(kvq_append16_pair_kernel<false>, 2, 2);
+            else if (five) KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, true>), 2, 1);
+            else KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, false>), 2, 1);
             break;
 #define KVQ_APPEND_CASE(b_, plain_alone_)                                                                                \
         case b_:                                                                                                         \
