@@ -22,12 +22,12 @@ using kvq_dev::as_global;
 // the bulk of the general kernels' registers.
 // by_unit: the units of a string follow one another in the grid instead of the strings of a unit.  The table rows of the
 // string's tokens, 512 bytes a token and as much as its keys and values in one unit, are then read by all units at about
-// the same time and come from the caches.  For the 16-bit tiers and at least 98,304 rows of all units together.
-// Rotated keys into the raw tier, with and without, over the same input / from memory, for 64 units and more and at least 98,304 rows:
-// 2,048 x 64 25.6 and 27.7 / 27.5 and 30.4 us, 4,096 x 128 84 and 90 / 99 and 103; 4,096 x 32 25.5 and 24.5 / 27.2 and 27.0, 2,048 x 48 20.5
+// the same time and come from the caches.  For the raw 16-bit tier, 64 units and more and at least 98,304 rows of all units together.
+// Rotated keys, with and without, over the same input / from memory: 2,048 x 64 25.6 and 27.7 / 27.5 and 30.4 us, 4,096 x 128 84
+// and 90 / 99 and 103; 4,096 x 32 25.5 and 24.5 / 27.2 and 27.0, 2,048 x 48 20.5
 // and 19.2 / 21.8 and 21.4, 1,024 x 64 (65,536 rows) 14.4 and 14.5 / 15.9 and 17.6, 8,192 x 8 17.9 and 14.3 / 17.5 and 18.7.  Into the integer
-// tier, at least 98,304 rows: 4,096 x 32 33.7 and 36.1, 2,048 x 64 33.8 and 37.4, 2,048 x 48 24.3 and 25.6; 2,048 x 32 18.9 and 18.1.
-// Into 8, 4 and 2 bits, where the arithmetic weighs more, it loses 3 to 7 % at every size.
+// tier it loses: 4,096 x 128 113 and 108 / 112 and 109, 2,048 x 64 25.0 and 24.3 / 32.7 and 31.0, 8,192 x 8 17.9 and 15.1.  Into 8,
+// 4 and 2 bits, where the arithmetic weighs more, it loses 3 to 7 % at every size.
 // What a launch's kernels need, read at once at their start: left alone the compiler reads the arguments one by one where they
 // are used first, each a trip to the constant cache or beyond, and three quotients and the lookup of the page entry stood in
 // front of the rows as well.  Now rows and angles are asked for first and the page entry behind them, needed only for the stores.
@@ -259,53 +259,49 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
 
 // Append into the integer 16-bit tier: Eq. 1-2 with 2^16 - 1 levels by the same owner lanes; the high and the low
 // bytes of the codes then travel through LDS and into the tile's two byte planes like two 8-bit tiles.
+// A workgroup is a tile (see kvq_append16_kernel).  Two wavefronts share a string: each quantizes 16 tokens and then writes one
+// plane; with 90 registers instead of 111 one more of them fits on a SIMD, and the chain of a small launch is half as long.  A
+// workgroup of one string and one wavefront, and now, over the same input / from memory: rotated 64 tokens x 8 units 5.2 and 4.5 us,
+// 1,024 x 16 7.8 and 7.0 / 8.7 and 7.4, 1,280 x 32 13.2 and 10.7 / 14.5 and 11.4, 2,048 x 32 18.0 and 14.8 / 21.1 and 18.3, 2,048 x 64
+// 27.4 and 24.3 / 35.8 and 31.0, 4,096 x 128 116 and 108; rotated and scaled 2,048 x 32 20.2 and 18.0 / 23.0 and 20.0; neither 1,024 x 16
+// 6.6 and 6.2 / 7.0 and 6.7, 2,048 x 32 13.0 and 12.1 / 15.1 and 15.6, 2,048 x 64 23.8 and 22.3 / 31.1 and 28.6.  (A wavefront a string and a
+// tile a workgroup: 3 to 14 % behind that, but for 4,096 strings of scaled keys, 16.5 / 18.3.)
 template <bool PLAIN>
-__global__ __launch_bounds__(64) void kvq_append_i16_kernel(const AppendArgs args) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2][KVQ_LDS_CODES];
-    const int lane = threadIdx.x, j = lane >> 4, n = lane & 15;
+__global__ __launch_bounds__(256) void kvq_append_i16_kernel(const AppendArgs args) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[2][2][KVQ_LDS_CODES];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
+    auto& lds = lds_all[wave >> 1];
+    const int lane = threadIdx.x & 63, j = lane >> 4, n = lane & 15;
     AppendArgs A;
     read_append_args<PLAIN>(args, A);
     AppendString t;
-    const bool mine = append_string<PLAIN, 1>(A, 0, t);
-    write_fresh_pages(A.table, args.pages, lane);
-    if (!mine) return;
+    append_string<PLAIN, 2>(A, wave >> 1, t);  // (the number of strings is even)
+    if (wave == 3) write_fresh_pages(A.table, args.pages, lane);
     const int which = t.which, t_old = A.t_old, gspan = A.gspan;
     const int tok0 = t.tile * KVQ_TILE_TOKENS;
     const kvq_dev::NewRows rows((which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, t_old, A.n_new);
     const int grp = lane & 3;
-    uint32_t w[2][16];
-    load_owner_rows(w, rows, tok0, lane);
+    const int tl = 16 * half + (lane >> 2), tok = tok0 + tl;
+    uint32_t w[1][16];
+    load_owner_rows(w, rows, tok0 + 16 * half, lane);
     const bool rotates = !PLAIN && !which && A.rope;
     OwnerAngles angles;
-    if (rotates) load_owner_angles(angles, rows, tok0 + (lane >> 2), lane, A.rope);
+    if (rotates) load_owner_angles(angles, rows, tok, lane, A.rope);
     __builtin_amdgcn_sched_barrier(0);  // all of these loads first
     const KvqPageDesc pd = append_desc<PLAIN>(A.table, args.pages, t.page);
     uint8_t* code = A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + which) * (512u * 16);
     uint8_t* meta = A.arena + (uint64_t)pd.meta_off256 * 256u + t.tslot * KVQ_META_TILE_BYTES;
-    if (rotates) {
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            const int tok = tok0 + 16 * pass + (lane >> 2);
-            if (pass) load_owner_angles(angles, rows, tok, lane, A.rope);
-            rotate_owner_keys(w[pass], angles, rows.has(tok), rows.all(tok0), lane);
-        }
-    }
-    if (!PLAIN && !which && t.rinv_head) {
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass) scale_owner_keys(w[pass], lane, t.rinv_head);
-    }
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int tl = 16 * pass + (lane >> 2);
-        const int tok = tok0 + tl;
+    if (rotates) rotate_owner_keys(w[0], angles, rows.has(tok), rows.all(tok0), lane);
+    if (!PLAIN && !which && t.rinv_head) scale_owner_keys(w[0], lane, t.rinv_head);
+    {
         uint32_t codes[32];
         uint16_t S, Z;
-        quantize_owner<16>(w[pass], codes, &S, &Z, gspan);
+        quantize_owner<16>(w[0], codes, &S, &Z, gspan);
         scatter_codes<1>(lds[0], which, tl, grp, codes);
         scatter_codes<0>(lds[1], which, tl, grp, codes);
         if (tok >= t_old) store_meta_owner(meta, which, tl, grp, S, Z);
     }
-    wave_sync_lds();
+    __syncthreads();
     uint32_t keep = 0;  // stored tokens keep their bits
     if (!which) {
 #pragma unroll
@@ -316,26 +312,23 @@ __global__ __launch_bounds__(64) void kvq_append_i16_kernel(const AppendArgs arg
         for (int i = 0; i < 8; ++i)
             if (tok0 + 8 * j + i < t_old) keep |= 1u << i;
     }
+    uint32_t str[16];
+    gather_string<8>(lds[half], which, lane, str);
+    uint8_t* dst = code + half * (512u * 8);
+    if (tok0 < t_old && keep) {
+        uint32_t old[16];
+        load_chunks<8>(dst, lane, old);
 #pragma unroll
-    for (int plane = 0; plane < 2; ++plane) {
-        uint32_t str[16];
-        gather_string<8>(lds[plane], which, lane, str);
-        uint8_t* dst = code + plane * (512u * 8);
-        if (tok0 < t_old && keep) {
-            uint32_t old[16];
-            load_chunks<8>(dst, lane, old);
-#pragma unroll
-            for (int d = 0; d < 16; ++d) {
-                uint32_t m = which ? v_token_mask<8>(keep, d) : (((keep >> (d / 8)) & 1u) ? 0xffffffffu : 0u);
-                str[d] = (old[d] & m) | (str[d] & ~m);
-            }
+        for (int d = 0; d < 16; ++d) {
+            uint32_t m = which ? v_token_mask<8>(keep, d) : (((keep >> (d / 8)) & 1u) ? 0xffffffffu : 0u);
+            str[d] = (old[d] & m) | (str[d] & ~m);
         }
-        if (tok0 >= t_old) {
-            store_chunks_stream<8>(dst, lane, str);
-        } else {
-            store_chunks<8>(dst, lane, str);
-            asm volatile("" ::: "memory");  // keeps the two kinds of store apart
-        }
+    }
+    if (tok0 >= t_old) {
+        store_chunks_stream<8>(dst, lane, str);
+    } else {
+        store_chunks<8>(dst, lane, str);
+        asm volatile("" ::: "memory");  // keeps the two kinds of store apart
     }
 }
 
@@ -895,7 +888,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     const int stream_v = !plain || (int64_t)units * n_new * (2 * 256) > (192 << 20);
     const bool few = strings <= (plain ? 1024 : 512);  // see kvq_append16_pair_kernel
     const bool five = rinv && strings > 4096 && strings <= 5632 && (strings + 511) / 512 % 2 == 1;  // see kvq_append16_kernel
-    const int by_unit = !plain && bits == 16 && (int64_t)units * n_new >= 98304 && (int16 || units >= 64) ? units : 0;
+    const int by_unit = !plain && bits == 16 && !int16 && units >= 64 && (int64_t)units * n_new >= 98304 ? units : 0;
     AppendArgs A;
     A.arena = arena; A.table = table; A.k = k; A.v = v; A.rinv = rinv; A.rope = rope; A.v_word = mark.word; A.v_epoch = mark.epoch;
     A.t_old = t_old; A.n_new = n_new; A.tpp = tiles_per_page; A.tile0 = tile0; A.n_strings = n_strings; A.by_unit = by_unit;
@@ -919,8 +912,8 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     } while (0)
     switch (bits + (int16 && bits == 16 ? 1 : 0)) {
         case 17:
-            if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 1, 1);
-            else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 1, 1);
+            if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 2, 2);
+            else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 2, 2);
             break;
         case 16:
             if (plain && few) KVQ_APPEND_LAUNCH(kvq_append16_pair_kernel<true>, 2, 2);
