@@ -15,7 +15,7 @@
  *     No entry point waits for the stream, except the three that copy results to the host
  *     (kvq_cache_export_segment, kvq_cache_sq_error, kvq_cache_sensitivity).  Page table
  *     entries ride in the arguments of the kernels that make the pages.  What is too long for that (appends over more than
- *     128 pages, shrinks of more than 192, the parameter blocks of a ragged batch) travels through a pinned staging ring
+ *     128 pages, shrinks of more than 192, the parameter blocks of large ragged batches) travels through a pinned staging ring
  *     of 4 segments of 1 MiB whose reuse is guarded by one HIP event per segment: a call blocks the host only when it has
  *     run a whole ring ahead of the device, and then only until the oldest segment has been consumed.
  *   - Stream capture: kvq_decode_attention and kvq_decode_attention_static enqueue kernels only and may be captured
@@ -199,8 +199,9 @@ kvq_status_t kvq_append_decode_attention(kvq_cache_t* cache, int32_t layer, cons
  *   is unusable (KVQ_E_STATE until kvq_cache_reset) in the cache whose launch failed and in those whose token the attention
  *   launch was to write; the others hold their new token or, if their append had not begun, are unchanged.
  * The device's workgroups are shared among the caches in proportion to the time their tiles take.  Results per cache
- * are those of the single-cache calls up to floating-point summation order.  The parameter blocks of the launch are
- * read from the pinned staging memory of caches[0]: calls that involve that cache must be issued on one stream. */
+ * are those of the single-cache calls up to floating-point summation order.  The parameter blocks of the launch travel in
+ * the kernel arguments or, of more caches than fit there (16, less where ranges are many), are read from the pinned staging
+ * memory of caches[0]: calls that involve that cache must be issued on one stream. */
 kvq_status_t kvq_decode_attention_batch(kvq_cache_t* const* caches, int32_t n_caches, int32_t layer,
                                         const void* const* q_dev, void* const* out_dev, int32_t out_is_fp32,
                                         float softmax_scale, void* hip_stream);
@@ -284,7 +285,7 @@ kvq_status_t kvq_calibrate_lambda(const void* k_calib_dev, int32_t batch, int32_
  * k_ref_dev, v_ref_dev: device, fp16 [batch, n_kv_heads, n_tokens, 128] with n_tokens the block's current length.
  * sq_err_host: host, 2 doubles.  Squares are added in fp32 over 32 elements (4 channels of every second one of 16 tokens)
  * and in fp64 beyond.
- * Enqueues on the stream, then waits for it (like kvq_cache_export_segment).  KVQ_E_STATE on an empty block or an
+ * Enqueues on the stream, then waits for the kernel's sums.  KVQ_E_STATE on an empty block or an
  * accounting-only cache. */
 kvq_status_t kvq_cache_sq_error(kvq_cache_t* cache, int32_t layer, const void* k_ref_dev, const void* v_ref_dev,
                                 double* sq_err_host, void* hip_stream);
@@ -295,7 +296,7 @@ kvq_status_t kvq_cache_sq_error(kvq_cache_t* cache, int32_t layer, const void* k
  * kvq_cache_sq_error; gk_dev, gv_dev: device, fp32 [batch, n_kv_heads, n_tokens, 128], the gradients of the loss with
  * respect to K and V, or NULL for all-ones (no model at hand: plain L1 reconstruction error).  For a block with
  * reparameterization the stored keys are K Lambda^-1: pass references in that space.  fp32 over 32 elements (4 channels of
- * every second one of 16 tokens), fp64 beyond.  Enqueues on the stream, then waits for it. */
+ * every second one of 16 tokens), fp64 beyond.  Enqueues on the stream, then waits for the kernel's sums. */
 kvq_status_t kvq_cache_sensitivity(kvq_cache_t* cache, int32_t layer, const void* k_ref_dev, const void* v_ref_dev,
                                    const float* gk_dev, const float* gv_dev, double* s_host, void* hip_stream);
 

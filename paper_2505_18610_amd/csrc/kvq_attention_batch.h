@@ -5,7 +5,7 @@
 
 namespace {
 
-// The parameter block of the workgroup's cache lies in host memory.  It is fetched over the link once, a dword per thread, and
+// The parameter block of the workgroup's cache lies in host memory where the arguments do not hold it.  It is fetched over the link once, a dword per thread, and
 // handed out from LDS: the head as scalars (read lane by lane from one register), the range of the split by index.  (Read
 // field by field as the kernel comes to them, the blocks cost two to three dependent trips over the link.)
 constexpr int kHeadDwords = sizeof(KvqAttnHead) / 4, kBlockDwords = sizeof(KvqAttnParams) / 4;

@@ -10,7 +10,7 @@
 // 4.9).  Launches in a train, streaming kernels and these: 764 tokens of 4 and 16 bits x 8 units 8.6 -> 6.7 us, with an appended
 // token 8.5 -> 6.7, 2,500 tokens of 16 bits x 8 units 9.3 -> 6.5, one tile x one unit 5.1 -> 3.9; with 16-bit codes 764 tokens
 // 9.5 -> 7.6.  The loads are streaming ones here too: plain ones are 0.4 us faster on blocks that lie in the L2 caches, but
-// 0.2 us slower on blocks that come from memory.  A batch has two kernels more, which find their parameters as the streaming ones do.
+// 0.2 us slower on blocks that come from memory.  A batch has kernels of its own, which find their parameters as the streaming ones do.
 #include "kvq_attention_batch.h"
 
 namespace {

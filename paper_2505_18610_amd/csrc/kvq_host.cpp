@@ -724,8 +724,8 @@ kvq_status_t reserve_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl,
     return st;
 }
 
-// Carries a planned append out whose blocks have been taken.  defer != nullptr: a one-token append into the 16-bit tier is
-// not launched but described in *defer.  The caller must then launch the attention with it, or mark the block unusable: the
+// Carries a planned append out whose blocks have been taken.  defer != nullptr: a one-token append into the 16-bit tier, with
+// defer_narrow into any width, is not launched but described in *defer.  The caller must then launch the attention with it, or mark the block unusable: the
 // token, and the table entry of a page that it starts, are written by that launch and by nothing else.
 kvq_status_t commit_append(kvq_cache_t* c, int32_t layer, const AppendPlan& pl, AppendBlocks& bl, const void* k_dev,
                            const void* v_dev, int32_t n_new, const float* cos_sin_dev, hipStream_t s, DeferredAppend* defer,

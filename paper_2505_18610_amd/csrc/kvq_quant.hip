@@ -111,11 +111,11 @@ __global__ __launch_bounds__(128) void kvq_append16_kernel(const AppendArgs args
     else kvq_dev::append16_k_tile<FIVE, 2>(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head, 0);
     if (wave == 1) write_fresh_pages(A.table, args.pages, lane);
 }
-// The same with two wavefronts per string, which share nothing: of keys each takes 16 tokens, of values 64 channels.  For launches
-// that leave SIMDs without a wavefront otherwise, where the chain of one is what counts: up to 512 strings, up to 1,024 of keys that need
-// no preparation.  One wavefront per string and two, over the same input / from memory: prepared, 1 token x 8 units 3.4 and 3.0 us, 256 x
-// 8 3.8 and 3.6 / 3.9 and 3.6, 700 x 8 alike, 1,500 x 8 5.2 and 5.0 / 5.5 and 5.5, 1,024 x 16 5.4 and 5.5 / 5.9 and 5.8, rotated only 5.1 and
-// 5.2 / 5.2 and 5.8; unprepared 256 x 8 2.9 and 2.9 / 3.5 and 2.9, 1,024 x 16 3.8 and 4.0 / 5.6 and 4.6, 1,536 x 16 4.3 and 4.8 / 6.4 and 5.6.
+// The same with two wavefronts per string, which share nothing: of keys each takes 16 tokens, of values 64 channels.  For less
+// than 1,024 strings, launches that leave SIMDs without a wavefront otherwise, where the chain of one is what counts.  One wavefront per
+// string and two, over the same input / from memory: rotated and scaled, 64 tokens x 8 units 3.8 and 3.5 us / 3.8 and 3.6, 700 x 8 4.2 and
+// 3.9 / 4.3 and 4.1, 1,500 x 8 5.1 and 4.9 / 5.5 and 5.4, 1,024 x 16 (1,024 strings) 5.6 and 5.4 / 5.6 and 5.9, 1,536 x 16 6.4 and 6.3 / 6.9 and
+// 7.6; neither, 64 x 8 2.9 and 2.7 / 2.9 and 2.8, 1,500 x 8 alike, 1,536 x 16 4.2 and 4.6 / 5.3 and 5.6.
 template <bool PLAIN>
 __global__ __launch_bounds__(256) void kvq_append16_pair_kernel(const AppendArgs args) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][32 * 128];
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
 // workgroup of one string and one wavefront, and now, over the same input / from memory: rotated 64 tokens x 8 units 5.2 and 4.5 us,
 // 1,024 x 16 7.8 and 7.0 / 8.7 and 7.4, 1,280 x 32 13.2 and 10.7 / 14.5 and 11.4, 2,048 x 32 18.0 and 14.8 / 21.1 and 18.3, 2,048 x 64
 // 27.4 and 24.3 / 35.8 and 31.0, 4,096 x 128 116 and 108; rotated and scaled 2,048 x 32 20.2 and 18.0 / 23.0 and 20.0; neither 1,024 x 16
-// 6.6 and 6.2 / 7.0 and 6.7, 2,048 x 32 13.0 and 12.1 / 15.1 and 15.6, 2,048 x 64 23.8 and 22.3 / 31.1 and 28.6.  (A wavefront a string and a
+// 6.6 and 6.2 / 7.0 and 6.7, 2,048 x 32 13.3 and 12.1 / 14.5 and 15.7, 2,048 x 64 23.0 and 22.4 / 29.6 and 28.4.  (A wavefront a string and a
 // tile a workgroup: 3 to 14 % behind that, but for 4,096 strings of scaled keys, 16.5 / 18.3.)
 template <bool PLAIN>
 __global__ __launch_bounds__(256) void kvq_append_i16_kernel(const AppendArgs args) {
@@ -886,7 +886,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     // MB) 86 and 85, from buffers in turn 102 and 94.  Beside keys that are prepared, streaming is the better or the same: 32 x
     // 2,000 16.0 and 16.0, from buffers in turn 18.9 and 15.8.
     const int stream_v = !plain || (int64_t)units * n_new * (2 * 256) > (192 << 20);
-    const bool few = strings <= (plain ? 1024 : 512);  // see kvq_append16_pair_kernel
+    const bool few = strings < 1024;  // see kvq_append16_pair_kernel
     const bool five = rinv && strings > 4096 && strings <= 5632 && (strings + 511) / 512 % 2 == 1;  // see kvq_append16_kernel
     const int by_unit = !plain && bits == 16 && !int16 && units >= 64 && (int64_t)units * n_new >= 98304 ? units : 0;
     AppendArgs A;
