@@ -88,7 +88,7 @@ __device__ __forceinline__ bool append_string(const AppendArgs& A, int wave, App
 // its second the values.  Workgroups go to the eight XCDs in turn: with one string each, keys and values in turn, all keys, which
 // are rotated and scaled, were on every other XCD and the others had little to do.  One wavefront a workgroup and now: 1,024 tokens x
 // 16 units rotated 6.1 and 5.1 us, 2,500 x 8 7.0 and 6.0, 1,024 x 32 9.3 and 7.5, 2,048 x 32 15.4 and 14.3, neither rotated nor scaled
-// 2,500 x 8 4.4 and 4.2, 4,096 x 128 96 and 86.
+// 2,500 x 8 4.4 and 4.1, 1,024 x 32 5.5 and 5.0.
 // FIVE: with 92 registers five wavefronts fit on a SIMD, otherwise, with 104, four.  Scaled keys of 4,097 to 4,608 and 5,121 to 5,632
 // strings, the odd steps of half a wavefront a SIMD beyond four, end earlier with five (16 units x 144 tiles 16.4 us and 17.8, from memory
 // 18.1 and 19.4; x 164 19.1 and 19.2, 19.2 and 20.1); 4,992 strings are alike, and keys that are only rotated lose 1 to 4 % of it.
@@ -110,6 +110,28 @@ __global__ __launch_bounds__(128) void kvq_append16_kernel(const AppendArgs args
     if (t.which) kvq_dev::append16_v_tile<8>(code, rows, tok0, lane, lds, A.stream_v, 0);  // (wavefront-uniform)
     else kvq_dev::append16_k_tile<FIVE, 2>(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head, 0);
     if (wave == 1) write_fresh_pages(A.table, args.pages, lane);
+}
+// The same for keys that need no preparation, two tiles a workgroup, half as many workgroups to dispatch.  For more than 16,384
+// strings.  One tile a workgroup and two, over the same input / from memory: 4,096 tokens x 128 units 87 and 80 us / 105 and 101,
+// 8,192 x 64 84 and 80 / 107 and 106, 16,384 x 64 189 and 188 (one string a workgroup 97 / 105, 84 / 105, 187); 4,096 x 64 (16,384 strings)
+// 39.7 and 39.1 / 54 and 55, 2,048 x 64 20.8 and 20.1 / 29.2 and 30.7.
+__global__ __launch_bounds__(256) void kvq_append16_bulk_kernel(const AppendArgs args) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][32 * 256];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    AppendArgs A;
+    read_append_args<true>(args, A);
+    AppendString t;
+    const bool mine = append_string<true, 4>(A, wave, t);
+    if (wave == 1) write_fresh_pages(A.table, args.pages, lane);
+    if (!mine) return;
+    const kvq_dev::NewRows rows((t.which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, A.t_old, A.n_new);
+    const int tok0 = t.tile * KVQ_TILE_TOKENS;
+    const auto code = [&]() {
+        const KvqPageDesc pd = append_desc<false>(A.table, args.pages, t.page);
+        return A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + t.which) * (512u * 16);
+    };
+    if (t.which) kvq_dev::append16_v_tile<8>(code, rows, tok0, lane, lds[wave >> 1], A.stream_v, 0);
+    else kvq_dev::append16_k_tile<false, 2>(code, rows, tok0, lane, nullptr, nullptr, 0);
 }
 // The same with two wavefronts per string, which share nothing: of keys each takes 16 tokens, of values 64 channels.  For less
 // than 1,024 strings, launches that leave SIMDs without a wavefront otherwise, where the chain of one is what counts.  One wavefront per
@@ -886,6 +908,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     // MB) 86 and 85, from buffers in turn 102 and 94.  Beside keys that are prepared, streaming is the better or the same: 32 x
     // 2,000 16.0 and 16.0, from buffers in turn 18.9 and 15.8.
     const int stream_v = !plain || (int64_t)units * n_new * (2 * 256) > (192 << 20);
+    const bool bulk = strings > 16384;  // see kvq_append16_bulk_kernel
     const bool few = strings < 1024;  // see kvq_append16_pair_kernel
     const bool five = rinv && strings > 4096 && strings <= 5632 && (strings + 511) / 512 % 2 == 1;  // see kvq_append16_kernel
     const int by_unit = !plain && bits == 16 && !int16 && units >= 64 && (int64_t)units * n_new >= 98304 ? units : 0;
@@ -917,6 +940,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
             break;
         case 16:
             if (plain && few) KVQ_APPEND_LAUNCH(kvq_append16_pair_kernel<true>, 2, 2);
+            else if (plain && bulk) KVQ_APPEND_LAUNCH(kvq_append16_bulk_kernel, 4, 1);
             else if (plain) KVQ_APPEND_LAUNCH((kvq_append16_kernel<true, false>), 2, 1);
             else if (few) KVQ_APPEND_LAUNCH(kvq_append16_pair_kernel<false>, 2, 2);
             else if (five) KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, true>), 2, 1);

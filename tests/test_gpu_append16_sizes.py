@@ -9,10 +9,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("tier16", [0, 1])
 @pytest.mark.parametrize("prepared", [False, True])
-@pytest.mark.parametrize("units,T", [(8, 1017), (8, 1050), (8, 2041), (8, 2075), (64, 1535), (64, 1552), (16, 4380)])
+@pytest.mark.parametrize("units,T", [(8, 1017), (8, 1050), (8, 2041), (8, 2075), (64, 1535), (64, 1552), (16, 4380), (64, 4100)])
 def test_one_append_writes_what_its_pieces_write(units, T, prepared, tier16):
     """Seven tokens and then the rest at once, from inside a tile (512 strings and more, 1,024 and more, 98,304 rows and more of 64
-    units, the sizes with five wavefronts a SIMD), or in pieces of 96, which other tests compare with the oracle: the same arena, byte
+    units, the sizes with five wavefronts a SIMD, an odd number of tiles beyond 16,384 strings), or in pieces of 96, which other tests compare with the oracle: the same arena, byte
     for byte."""
     H, P = 8, 64
     B = units // H
