@@ -109,7 +109,7 @@ static bool pack_batch_args(const KvqAttnParams* params, const KvqBatchMap& map,
         c.lambda16 = offset(p.lambda); c.part_o16 = offset(p.part_o); c.part_ml16 = offset(p.part_ml);
         c.counters16 = offset(p.counters); c.v_mark16 = offset(p.v_mark);
         ok = ok && (!p.app_rinv || (p.lambda && p.app_rinv == p.lambda + (size_t)p.n_kv_heads * KVQ_D));
-        c.v_epoch = p.v_epoch; c.n_tokens = p.n_tokens; c.tiles_per_page = p.tiles_per_page; c.tpp_magic = p.tpp_magic;
+        c.v_tag = p.v_tag; c.n_tokens = p.n_tokens; c.tiles_per_page = p.tiles_per_page; c.tpp_magic = p.tpp_magic;
         c.gqa = p.gqa; c.n_q_heads = p.n_q_heads; c.n_kv_heads = p.n_kv_heads; c.kv_magic = p.kv_magic;
         c.n_splits = p.n_splits; c.merge_groups = p.merge_groups; c.merge_rounds = p.merge_rounds; c.gqa_magic = p.gqa_magic;
         c.scale_log2 = p.scale_log2;

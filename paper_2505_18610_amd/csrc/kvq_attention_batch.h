@@ -59,7 +59,7 @@ __device__ __forceinline__ KvqAttnHead batch_work(const KvqBatchArgs& args, Batc
     const uint8_t *arena = b.arena, *q = static_cast<const uint8_t*>(b.q), *k = static_cast<const uint8_t*>(b.app_k), *v = static_cast<const uint8_t*>(b.app_v);
     uint8_t* out = static_cast<uint8_t*>(b.out);
     if constexpr (AT_ONCE) asm volatile("" : "+s"(arena), "+s"(q), "+s"(k), "+s"(v), "+s"(out), "+s"(b.app_rope), "+s"(b.table16), "+s"(b.lambda16), "+s"(b.part_o16),
-                      "+s"(b.part_ml16), "+s"(b.counters16), "+s"(b.v_mark16), "+s"(b.v_epoch), "+s"(b.n_tokens), "+s"(b.tiles_per_page),
+                      "+s"(b.part_ml16), "+s"(b.counters16), "+s"(b.v_mark16), "+s"(b.v_tag), "+s"(b.n_tokens), "+s"(b.tiles_per_page),
                       "+s"(b.tpp_magic), "+s"(b.gqa), "+s"(b.n_q_heads), "+s"(b.n_kv_heads), "+s"(b.kv_magic), "+s"(b.n_splits),
                       "+s"(b.merge_groups), "+s"(b.merge_rounds));
     if constexpr (AT_ONCE) asm volatile("" : "+s"(b.gqa_magic), "+s"(b.scale_log2), "+s"(b.flags), "+s"(b.split_at), "+s"(b.app_t_old), "+s"(b.app_page),
@@ -80,7 +80,7 @@ __device__ __forceinline__ KvqAttnHead batch_work(const KvqBatchArgs& args, Batc
     P.part_ml = reinterpret_cast<float*>(base + (uint64_t)b.part_ml16 * 16u);
     P.counters = reinterpret_cast<uint32_t*>(base + (uint64_t)b.counters16 * 16u);
     P.v_mark = reinterpret_cast<const uint32_t*>(base + (uint64_t)b.v_mark16 * 16u);
-    P.v_epoch = b.v_epoch; P.n_tokens = b.n_tokens; P.tiles_per_page = b.tiles_per_page; P.tpp_magic = b.tpp_magic;
+    P.v_tag = b.v_tag; P.n_tokens = b.n_tokens; P.tiles_per_page = b.tiles_per_page; P.tpp_magic = b.tpp_magic;
     P.gqa = b.gqa; P.n_q_heads = b.n_q_heads; P.n_kv_heads = b.n_kv_heads; P.kv_magic = b.kv_magic;
     P.n_splits = b.n_splits; P.merge_groups = b.merge_groups; P.merge_rounds = b.merge_rounds; P.gqa_magic = b.gqa_magic;
     P.out_fp32 = (int)(b.flags & 1u); P.fused_merge = (int)(b.flags >> 1 & 1u); P.deterministic = (int)(b.flags >> 2 & 1u);

@@ -1083,11 +1083,16 @@ __device__ inline void store_new_token(const KvqAttnHead& P, const AttnShared& s
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the elements below go to addresses other lanes have just zeroed
     }
     if constexpr (narrow) {
+        uint32_t mark = 0u;
+        if (which) mark = __hip_atomic_load(P.v_mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // on its way with the older codes
         store_new_codes(sh, code, t, which, bits, lane);
-        if (lane == 0 && which)
+        if (lane == 0 && which) {
+            bool large = false;
 #pragma unroll
-            for (int g = 0; g < KVQ_NGRP; ++g)
-                kvq_q::note_large_v_scale(KvqVMark{const_cast<uint32_t*>(P.v_mark), P.v_epoch}, 1, sh.new_sz[1][g][0]);
+            for (int g = 0; g < KVQ_NGRP; ++g) large = large || kvq_dev::h2f(sh.new_sz[1][g][0]) >= 256.0f;  // as kvq_q::note_large_v_scale has it
+            const uint32_t left = kvq_v_mark_left(mark, P.v_tag, large);
+            if (left != mark) __hip_atomic_store(const_cast<uint32_t*>(P.v_mark), left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     } else if (!which) {  // lane = 4 grp + j: channels 32 grp + 8 j .. + 7 are consecutive slots of one lane's string
         int ln, slot;
         const int ch = 8 * ((lane & 3) + 4 * ((lane >> 2) & 3));
@@ -1387,7 +1392,7 @@ __device__ __forceinline__ void attention_body(const KvqAttnHead& P, const int t
     __syncthreads();
     KVQ_STAMP(1);
     WaveState st;
-    if (__builtin_amdgcn_readfirstlane(mark) == P.v_epoch) stream_range<true, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
+    if (kvq_v_marked(__builtin_amdgcn_readfirstlane(mark), P.v_tag, APPEND == KVQ_APPEND_NARROW)) stream_range<true, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
     else stream_range<false, I16>(P, sh, st, unit, t_begin, t_end, p_first, p_last);
 
     KVQ_STAMP(2);

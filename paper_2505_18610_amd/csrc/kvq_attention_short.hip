@@ -23,7 +23,7 @@ __device__ __forceinline__ KvqAttnHead read_head(const KvqAttnParams& params) {
     const _Float16* q = static_cast<const _Float16*>(h.q);
     float* out = static_cast<float*>(h.out);
     asm volatile("" : "+s"(h.arena), "+s"(h.table), "+s"(q), "+s"(h.lambda), "+s"(out), "+s"(h.part_o), "+s"(h.part_ml),
-                      "+s"(h.counters), "+s"(h.v_mark), "+s"(h.v_epoch), "+s"(h.n_tokens), "+s"(h.tiles_per_page),
+                      "+s"(h.counters), "+s"(h.v_mark), "+s"(h.v_tag), "+s"(h.n_tokens), "+s"(h.tiles_per_page),
                       "+s"(h.tpp_magic), "+s"(h.gqa), "+s"(h.n_q_heads), "+s"(h.n_kv_heads), "+s"(h.kv_magic),
                       "+s"(h.n_splits), "+s"(h.out_fp32), "+s"(h.fused_merge), "+s"(h.scale_log2),
                       "+s"(h.merge_groups), "+s"(h.merge_rounds), "+s"(h.gqa_magic));
@@ -35,7 +35,7 @@ __device__ __forceinline__ KvqAttnHead read_head(const KvqAttnParams& params) {
 }
 
 template <class T>
-__device__ inline T scalar_load(const T* p) {  // through the constant cache; p uniform, not written by this launch
+__device__ inline T scalar_load(const T* p) {  // through the constant cache; p uniform, not written by this launch (but for the mark, see kvq_v_marked)
     return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
 }
 
@@ -227,7 +227,7 @@ __device__ __forceinline__ void short_range(const KvqAttnHead& P, const int t_be
     asm volatile("" : "+v"(st.o[0]), "+v"(st.o[1]), "+v"(st.o[2]), "+v"(st.o[3]), "+v"(st.o[4]), "+v"(st.o[5]), "+v"(st.o[6]),
                       "+v"(st.o[7]), "+v"(st.zl), "+v"(st.m));  // while the page entry is on its way
     asm volatile("" : "+s"(mark), "+s"(pd[0]), "+s"(pd[1]));
-    st.safe_v = mark == P.v_epoch ? 1 : 0;
+    st.safe_v = kvq_v_marked(mark, P.v_tag, APPEND == KVQ_APPEND_NARROW) ? 1 : 0;
     QOps Q;
     KVQ_STAMP(1);
     bool fresh = true;

@@ -165,7 +165,8 @@ struct kvq_cache {
     uint64_t unit_bytes = 0;
     uint64_t table_off = 0, jobs_off = 0, part_o_off = 0, part_ml_off = 0, counters_off = 0, flags_off = 0, pages_off = 0;
     uint64_t reparam_off = 0;  // per block: lambda [n_kv_heads][128] fp32, then 1 / lambda
-    uint32_t v_epoch = 1;      // see KvqVMark; 0 is what a cleared word holds
+    uint32_t v_epoch = 4;      // see KvqVMark; 0 is what a cleared word holds
+    uint32_t v_turn = 1;       // tag of the next launch that appends below 16 bits, above the epoch; see kvq_v_marked
     KvqVMark v_mark() const { return KvqVMark{reinterpret_cast<uint32_t*>(arena + flags_off), v_epoch}; }
     Buddy buddy;
     std::vector<Layer> layers;
@@ -1068,7 +1069,7 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
     p.part_ml = reinterpret_cast<float*>(c->arena + c->part_ml_off);
     p.counters = reinterpret_cast<uint32_t*>(c->arena + c->counters_off);
     p.v_mark = c->v_mark().word;
-    p.v_epoch = c->v_epoch;
+    p.v_tag = c->v_epoch | (app && app->active && app->desc.bits < 16 ? c->v_turn : 0u);
     p.n_tokens = n_tokens;
     p.tiles_per_page = c->tpp;
     p.tpp_magic = c->tpp > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)c->tpp - 1) / (uint64_t)c->tpp) : 0u;
@@ -1113,7 +1114,9 @@ kvq_status_t attention_impl(kvq_cache_t* c, int32_t layer, const void* q_dev, vo
     kvq_status_t st = fill_attn_params(c, layer, q_dev, out_dev, out_is_fp32, softmax_scale, app, k_new, v_new,
                                        cos_sin_dev, 0, p);
     if (st != KVQ_OK) return st;
-    return kvq_launch_attention(p, c->units, as_stream(hip_stream)) == hipSuccess ? KVQ_OK : KVQ_E_HIP;
+    if (kvq_launch_attention(p, c->units, as_stream(hip_stream)) != hipSuccess) return KVQ_E_HIP;
+    if (p.v_tag != c->v_epoch) c->v_turn ^= 3u;
+    return KVQ_OK;
 }
 
 // One cache's part in dealing a batch's workgroups: the tile time of one of its (sequence, KV head) units, how many units it
@@ -1600,7 +1603,7 @@ kvq_status_t kvq_cache_reset(kvq_cache_t* c, int32_t layer) {
     bool all_empty = true;
     for (const Layer& L : c->layers) all_empty = all_empty && L.T == 0;
     if (all_empty) {
-        if (++c->v_epoch == 0) c->v_epoch = 1;
+        if ((c->v_epoch += 4) == 0) c->v_epoch = 4;
         if (c->enqueue_failed) c->device_ready = c->enqueue_failed = false;
     }
     return KVQ_OK;

@@ -7,12 +7,26 @@
 #include "kvq_layout.h"
 
 // Mark of a cache that holds a V scale >= 256 (it selects the attention kernels' overflow-proof V path): the quantizing kernels
-// store the cache's current epoch into the word, the mark is set while the word equals it, and emptying the cache moves the
-// epoch on, so that nothing has to be cleared on the device.
+// store the cache's current epoch into the word, the mark is set while the word holds a value of that epoch, and emptying the cache
+// moves the epoch on, so that nothing has to be cleared on the device.  Epochs are multiples of four.
 struct KvqVMark {
     uint32_t* word;
     uint32_t epoch;
 };
+// An attention launch that appends a token below 16 bits reads the mark and may set it, and which of its workgroups reads behind
+// which other's store is chance.  No decision may hang on that: the V path changes the rounding, also where the caller asked for
+// reproducible results, and the wavefronts of a workgroup have to take the same one.  The launch does not need its own token's mark
+// (it attends to it in fp32).  So its tag is the epoch plus 1 or 2, in turn from one such launch to the next; it sets the mark by
+// storing the tag, which it does not act on itself and every other launch does, and where it found another launch's tag it stores
+// the epoch in its place before the turn comes back to that one.  The tag of every other launch is the epoch.
+__host__ __device__ inline bool kvq_v_marked(uint32_t word, uint32_t tag, bool sets) {
+    const uint32_t of = sets && word == tag ? 0u : word & ~3u;  // (no epoch is 0)
+    return of == (sets ? tag & ~3u : tag);
+}
+// What such a launch leaves in the word.  large: the scale of its token's V is.
+__host__ __device__ inline uint32_t kvq_v_mark_left(uint32_t word, uint32_t tag, bool large) {
+    return kvq_v_marked(word, tag, true) ? tag & ~3u : large ? tag : word;
+}
 
 // The device page tables are written by the kernels that make the pages: an append, a re-quantization or the attention
 // launch that appends a token gets the new entries in its arguments and stores them beside its other output.  (A copy
@@ -50,8 +64,8 @@ struct KvqAttnHead {
     float* part_o;             // [unit][split][16][128] un-normalised partial outputs
     float* part_ml;            // [unit][split][16] pairs (running max in log2 units, sum)
     uint32_t* counters;        // [unit * KVQ_COUNTER_STRIDE] arrival counters of the fused merge (kept at zero between launches)
-    const uint32_t* v_mark;    // equal to v_epoch: some V scale of the cache is >= 256 (set by the quantizing kernels)
-    uint32_t v_epoch;
+    const uint32_t* v_mark;    // the word of KvqVMark: some V scale of the cache is >= 256 (set by the kernels that quantize)
+    uint32_t v_tag;            // see kvq_v_marked
     int32_t n_tokens;          // tokens read from the cache (without the one this launch appends)
     int32_t tiles_per_page;
     uint32_t tpp_magic;        // ceil(2^32 / tiles_per_page) (unused when tiles_per_page == 1)
@@ -147,7 +161,7 @@ struct KvqBatchCache {
     void* out;
     const float* app_rope;
     uint32_t table16, lambda16, part_o16, part_ml16, counters16, v_mark16;
-    uint32_t v_epoch;
+    uint32_t v_tag;
     int32_t n_tokens, tiles_per_page;
     uint32_t tpp_magic;
     int32_t gqa, n_q_heads, n_kv_heads;

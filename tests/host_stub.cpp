@@ -58,6 +58,33 @@ void check_table(const uint8_t* arena, const KvqPageDesc* table, int n_tokens, i
         CHECK((uint64_t)d.code_off256 * 256 < arena_size[arena], "page %d of %d lies at %u", i, pages, d.code_off256);
     }
 }
+// The launch's workgroups, one a unit, start and end in an order of chance; each reads the mark of large V scales at its start and,
+// where the launch quantizes a token, leaves its own at its end.
+std::mt19937 chance(3);
+bool token_is_large = false;  // the V scale of the token that a step appends, in one unit
+int acted = 0;                // how many workgroups of the last launch took the path for large scales
+void mark_of_large_scales(const KvqAttnParams& p, int units) {
+    uint32_t* const word = const_cast<uint32_t*>(p.v_mark);
+    const bool sets = p.app_t_old >= 0 && p.app_desc.bits < 16;
+    const int large_unit = token_is_large ? (int)(chance() % (unsigned)units) : -1;
+    std::vector<int> waiting, running;
+    for (int i = 0; i < units; ++i) waiting.push_back(i);
+    acted = 0;
+    while (!waiting.empty() || !running.empty()) {
+        const bool start = running.empty() || (!waiting.empty() && chance() % 2);
+        std::vector<int>& from = start ? waiting : running;
+        const size_t k = chance() % from.size();
+        const int unit = from[k];
+        from.erase(from.begin() + (long)k);
+        if (start) {
+            acted += kvq_v_marked(*word, p.v_tag, sets) ? 1 : 0;
+            running.push_back(unit);
+        } else if (sets) {
+            *word = kvq_v_mark_left(*word, p.v_tag, unit == large_unit);
+        }
+    }
+    CHECK(acted == 0 || acted == units, "%d of %d workgroups saw the mark", acted, units);
+}
 void attention(const KvqAttnParams& p) {
     last = p;
     check_table(p.arena, p.table, p.n_tokens, p.tiles_per_page);
@@ -117,9 +144,9 @@ hipError_t kvq_launch_fill_u32(uint32_t* dst, uint32_t value, size_t n, hipStrea
     return e;
 }
 hipError_t kvq_static_scratch(unsigned char** ptr) { static unsigned char scratch[KVQ_STATIC_SCRATCH_BYTES]; *ptr = scratch; return hipSuccess; }
-hipError_t kvq_launch_attention(const KvqAttnParams& p, int, hipStream_t) {
+hipError_t kvq_launch_attention(const KvqAttnParams& p, int units, hipStream_t) {
     const hipError_t e = launched();
-    if (e == hipSuccess) attention(p);
+    if (e == hipSuccess) { attention(p); mark_of_large_scales(p, units); }
     return e;
 }
 hipError_t kvq_launch_merge(const KvqAttnParams&, int, hipStream_t) { return launched(); }
@@ -217,6 +244,74 @@ void batch_failing_launch() {
         }
         CHECK(kvq_cache_reset(a.c, -1) == KVQ_OK && a.append(64) == KVQ_OK && a.attend() == KVQ_OK, "reset");
     }
+}
+
+// Steps below 16 bits set the mark of large V scales in the launch that reads it.  A launch's workgroups agree on it whatever their
+// order (checked above), the launch that sets it does not act on it, every later one does, also behind a step whose launch
+// failed, until the cache is emptied.
+void mark_set_by_a_step() {
+    for (int round = 0; round < 300; ++round) {
+        Cache a(32, 40, round % 2, KVQ_POLICY_PAPER, 0, 2, 8, 2);
+        for (int life = 0; life < 3; ++life) {
+            CHECK(a.append(64, 4) == KVQ_OK, "prompt");
+            bool marked = false;
+            for (int step = 0; step < 24; ++step) {
+                switch (chance() % 6) {
+                    case 0: CHECK(a.attend() == KVQ_OK && acted == (marked ? 16 : 0), "attention: %d", acted); break;
+                    case 1: {
+                        std::vector<kvq_cache_t*> one{a.c};
+                        std::vector<const void*> in{input};
+                        std::vector<void*> out{input};
+                        CHECK(kvq_decode_attention_batch(one.data(), 1, 0, in.data(), out.data(), 0, 0.f, nullptr) == KVQ_OK, "batch");
+                        CHECK(kvq_v_marked(*last.v_mark, last.v_tag, false) == marked, "batch");
+                        break;
+                    }
+                    default:
+                        token_is_large = chance() % 8 == 0;
+                        CHECK(a.step() == KVQ_OK && acted == (marked ? 16 : 0), "step %d, large %d: %d", step, token_is_large, acted);
+                        marked = marked || token_is_large;
+                        token_is_large = false;
+                }
+            }
+            if (life == 1) {
+                fail_launch = launches;
+                CHECK(a.step() == KVQ_E_HIP, "a failing step");
+                fail_launch = -1;
+            }
+            CHECK(kvq_cache_reset(a.c, -1) == KVQ_OK, "reset");
+        }
+    }
+}
+
+// A step that fails in one block does not lose the mark that another block's step has set.
+void mark_outlives_a_failing_step() {
+    kvq_config_t cfg{};
+    cfg.n_layers = 2; cfg.batch = 1; cfg.n_kv_heads = 4; cfg.n_q_heads = 4; cfg.head_dim = 128; cfg.group = 32;
+    cfg.max_tokens = 1 << 12; cfg.page_tokens = 32; cfg.policy = KVQ_POLICY_PAPER;
+    const uint64_t budget[2] = {1ull << 50, 1ull << 50};
+    const uint8_t fbit[2] = {2, 2};
+    const uint64_t bytes = kvq_arena_bytes(&cfg, 1 << 22);
+    uint8_t* const arena = static_cast<uint8_t*>(aligned_alloc(256, (bytes + 255) / 256 * 256));
+    arena_size[arena] = bytes;
+    kvq_cache_t* c = nullptr;
+    CHECK(kvq_cache_create(&cfg, budget, fbit, arena, bytes, &c) == KVQ_OK, "create");
+    const auto step = [&](int layer) { return kvq_append_decode_attention(c, layer, input, input, nullptr, input, input, 0, 0.f, nullptr); };
+    for (int l = 0; l < 2; ++l) CHECK(kvq_quantize_append(c, l, input, input, 40, 8, nullptr) == KVQ_OK, "prompt");
+    for (int before = 0; before < 2; ++before) {
+        CHECK(step(0) == KVQ_OK && acted == 0, "step");
+        if (before) CHECK(step(0) == KVQ_OK && acted == 0, "step");
+        token_is_large = true;
+        CHECK(step(0) == KVQ_OK && acted == 0, "the step that sets it");
+        token_is_large = false;
+        fail_launch = launches;
+        CHECK(step(1) == KVQ_E_HIP, "a failing step");
+        fail_launch = -1;
+        for (int k = 0; k < 4; ++k) CHECK(step(0) == KVQ_OK && acted == 4, "step %d behind it: %d", k, acted);
+        CHECK(kvq_cache_reset(c, -1) == KVQ_OK, "reset");
+        for (int l = 0; l < 2; ++l) CHECK(kvq_quantize_append(c, l, input, input, 40, 8, nullptr) == KVQ_OK, "prompt");
+    }
+    kvq_cache_destroy(c);
+    free(arena);
 }
 
 // A block whose launch failed after the bookkeeping is refused by every call that reads it, until it is emptied.
@@ -422,6 +517,8 @@ const std::map<std::string, std::function<void()>> scenarios = {
     {"batch_full_arena", batch_full_arena},
     {"batch_failing_launch", batch_failing_launch},
     {"failed_block_is_refused", failed_block_is_refused},
+    {"mark_set_by_a_step", mark_set_by_a_step},
+    {"mark_outlives_a_failing_step", mark_outlives_a_failing_step},
     {"split_plans", split_plans},
     {"plans_follow_the_pages", plans_follow_the_pages},
     {"tile_costs_are_relative", tile_costs_are_relative},

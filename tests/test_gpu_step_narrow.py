@@ -96,3 +96,46 @@ def test_steps_and_shrinks_take_turns():
                 c.kvq_progressive_requant(0)
             _same_contents(two, one)
     _same_contents(two, one)
+
+
+@pytest.mark.parametrize("units,tokens,page", [
+    (700, 40, 32),     # more workgroups than the device holds at a time: the first end before the last start
+    (700, 700, 64),    # the same, streamed
+    (264, 8300, 32),   # ranges of more pages than the kernel looks up at a time
+])
+def test_step_that_sets_the_mark_of_large_scales(units, tokens, page):
+    """The step whose token brings the first V scale of 256 and more does not act on it: every other unit's output is, bit for bit, that of
+    the same step without that scale, however the workgroups follow one another.  The calls behind it do act on it."""
+    H = 4
+    B = units // H
+    g = torch.Generator("cuda").manual_seed(units)
+    half = tokens // 2
+    kv = [torch.randn((B, H, half, 128), device="cuda", generator=g).half() for _ in range(2)]
+    k, v = (torch.randn(B, H, 1, 128, generator=g, device="cuda").half() for _ in range(2))
+    large = v.clone()
+    large[0, 0, 0, 64:96] *= 5000.0
+    q = torch.randn(B, H, 128, generator=g, device="cuda").half()
+    caches = []
+    for _ in range(2):
+        cfg = kq.KvqConfig(1, B, H, H, tokens + 64, page_tokens=page, policy=kq.KVQ_POLICY_PAPER, group=32)
+        arena = torch.empty(kq.kvq_arena_bytes(cfg, (tokens + 4 * page) * units * 104 + (4 << 20)), dtype=torch.uint8, device="cuda")
+        c = kq.KvqCache(cfg, [1 << 50], [2], arena=arena)
+        c.kvq_cache_set_option(kq.KVQ_OPT_DETERMINISTIC, 1)
+        for _ in range(2):
+            c.kvq_quantize_append(0, *kv, 2)
+        caches.append(c)
+    outs = [torch.empty(B, H, 128, device="cuda") for _ in range(2)]
+    for c, token, o in zip(caches, (large, v), outs):
+        c.kvq_append_decode_attention(0, k, token, q, o)
+    a, b = (o.view(units, 128) for o in outs)
+    assert torch.equal(a[1:], b[1:])
+    assert torch.equal(a[0, :64], b[0, :64]) and torch.equal(a[0, 96:], b[0, 96:]) and not torch.equal(a[0, 64:96], b[0, 64:96])
+    for step in range(3):  # the overflow-proof path is another way to round the same
+        for c, o in zip(caches, outs):
+            if step == 1:
+                c.kvq_append_decode_attention(0, k, v, q, o)
+            else:
+                c.kvq_decode_attention(0, q, o)
+        assert not torch.equal(a[1:], b[1:]), step
+        assert (a[1:] - b[1:]).abs().max() <= MAX_ABS, step
+        assert torch.isfinite(a).all()
