@@ -86,7 +86,8 @@ hipError_t kvq_launch_attention(const KvqAttnParams& p, int units, hipStream_t s
     return e;
 }
 
-// The parameter blocks as kernel arguments.
+// The parameter blocks as kernel arguments.  (Whatever they point to in the arena is aligned to 16 bytes, and the reciprocal factors follow the
+// factors.)
 static bool pack_batch_args(const KvqAttnParams* params, const KvqBatchMap& map, int n, KvqBatchArgs& a) {
     if (!kvq_batch_fits_args(params, n)) return false;
     a.n = n;
@@ -95,20 +96,10 @@ static bool pack_batch_args(const KvqAttnParams* params, const KvqBatchMap& map,
     for (int i = 0; i < n; ++i) {
         const KvqAttnParams& p = params[i];
         KvqBatchCache& c = a.cache[i];
-        bool ok = true;
-        const auto offset = [&](const void* x) {
-            if (!x) return 0u;
-            const uint64_t d = (uint64_t)(static_cast<const uint8_t*>(x) - p.arena);
-            ok = ok && d % 16 == 0 && d / 16 <= 0xffffffffull && d != 0;
-            return (uint32_t)(d / 16);
-        };
-        const uint64_t table = (uint64_t)(reinterpret_cast<const uint8_t*>(p.table) - p.arena);  // (the first block's is the arena's start)
+        const auto offset = [&](const void* x) { return x ? (uint32_t)((uint64_t)(static_cast<const uint8_t*>(x) - p.arena) / 16) : 0u; };
         c.arena = p.arena; c.q = p.q; c.out = p.out; c.app_k = p.app_k; c.app_v = p.app_v; c.app_rope = p.app_rope;
-        c.table16 = (uint32_t)(table / 16);
-        ok = ok && table % 16 == 0 && table / 16 <= 0xffffffffull;
-        c.lambda16 = offset(p.lambda); c.part_o16 = offset(p.part_o); c.part_ml16 = offset(p.part_ml);
+        c.table16 = offset(p.table); c.lambda16 = offset(p.lambda); c.part_o16 = offset(p.part_o); c.part_ml16 = offset(p.part_ml);
         c.counters16 = offset(p.counters); c.v_mark16 = offset(p.v_mark);
-        ok = ok && (!p.app_rinv || (p.lambda && p.app_rinv == p.lambda + (size_t)p.n_kv_heads * KVQ_D));
         c.v_tag = p.v_tag; c.n_tokens = p.n_tokens; c.tiles_per_page = p.tiles_per_page; c.tpp_magic = p.tpp_magic;
         c.gqa = p.gqa; c.n_q_heads = p.n_q_heads; c.n_kv_heads = p.n_kv_heads; c.kv_magic = p.kv_magic;
         c.n_splits = p.n_splits; c.merge_groups = p.merge_groups; c.merge_rounds = p.merge_rounds; c.gqa_magic = p.gqa_magic;
@@ -119,7 +110,6 @@ static bool pack_batch_args(const KvqAttnParams* params, const KvqBatchMap& map,
         c.app_t_old = p.app_t_old; c.app_page = p.app_page;
         c.app_code_off256 = p.app_desc.code_off256; c.app_meta_off256 = p.app_desc.meta_off256;
         for (int k = 0; k <= p.n_splits; ++k) a.split_begin[at++] = p.split_begin[k];
-        if (!ok) return false;
     }
     return true;
 }

@@ -152,7 +152,7 @@ struct KvqBatchMap {
 };
 
 // A batch of few caches has its parameters in the kernel arguments instead: what differs from cache to cache, pointers into the arena as
-// offsets in units of 16 bytes (0: none), and the ranges of all caches one after the other.
+// offsets in units of 16 bytes (0: none; the table alone may lie at the arena's start), and the ranges of all caches one after the other.
 #define KVQ_BATCH_ARG_CACHES 16
 #define KVQ_BATCH_ARG_SPLITS 320
 struct KvqBatchCache {
@@ -181,11 +181,18 @@ struct KvqBatchArgs {
     int32_t split_begin[KVQ_BATCH_ARG_SPLITS];
 };
 static_assert(sizeof(KvqBatchArgs) <= 3840, "kernel arguments end at 4 KiB");
-// Whether the parameters of these caches fit (their parameter blocks need not be in device-visible memory then).
+// Whether the parameters of these caches fit (their parameter blocks need not be in device-visible memory then).  An offset reaches
+// 64 GiB, which an arena's tables exceed where the cache has tens of thousands of units (1 MiB of partials each) or thousands of blocks.
 inline bool kvq_batch_fits_args(const KvqAttnParams* p, int n) {
+    if (n > KVQ_BATCH_ARG_CACHES) return false;
     int ranges = 0;
-    for (int i = 0; i < n; ++i) ranges += p[i].n_splits + 1;
-    return n <= KVQ_BATCH_ARG_CACHES && ranges <= KVQ_BATCH_ARG_SPLITS;
+    for (int i = 0; i < n; ++i) {
+        ranges += p[i].n_splits + 1;
+        for (const void* x : {(const void*)p[i].table, (const void*)p[i].lambda, (const void*)p[i].part_o, (const void*)p[i].part_ml,
+                              (const void*)p[i].counters, (const void*)p[i].v_mark})
+            if (x && (uint64_t)(static_cast<const uint8_t*>(x) - p[i].arena) >> 36) return false;
+    }
+    return ranges <= KVQ_BATCH_ARG_SPLITS;
 }
 
 // Static scratch of kvq_decode_attention_static (kvq_attention.hip): room for the partials of KVQ_STATIC_MAX_WGS

@@ -3,6 +3,7 @@
 // what the kernels would read.  tests/test_host_stub.py builds it with kvq_host.cpp and a HIP runtime that is stubbed below;
 // argument: the scenario.  Exit code 0 = pass.  No GPU and no HIP library is involved.
 #include <hip/hip_runtime.h>
+#include <sys/mman.h>
 
 #include <algorithm>
 #include <chrono>
@@ -150,7 +151,10 @@ hipError_t kvq_launch_attention(const KvqAttnParams& p, int units, hipStream_t) 
     return e;
 }
 hipError_t kvq_launch_merge(const KvqAttnParams&, int, hipStream_t) { return launched(); }
-hipError_t kvq_launch_attention_batch(const KvqAttnParams*, const KvqAttnParams* p, const int*, int n, hipStream_t) {
+bool batch_by_args = false;  // the last batched launch had no parameter blocks in device-visible memory
+hipError_t kvq_launch_attention_batch(const KvqAttnParams* dev, const KvqAttnParams* p, const int*, int n, hipStream_t) {
+    batch_by_args = !dev;
+    CHECK(dev || kvq_batch_fits_args(p, n), "%d caches do not fit the arguments", n);
     const hipError_t e = launched();
     for (int i = 0; i < n && e == hipSuccess; ++i) attention(p[i]);
     last_batch.assign(p, p + n);
@@ -312,6 +316,32 @@ void mark_outlives_a_failing_step() {
     }
     kvq_cache_destroy(c);
     free(arena);
+}
+
+// Arenas whose tables reach beyond what the offsets in the kernel arguments hold (the partials of 65,528 units are 64 GiB) go by the
+// parameter blocks in memory.
+void batch_of_large_arenas() {
+    for (int batch : {1, 8000, 8191}) {
+        kvq_config_t cfg{};
+        cfg.n_layers = 1; cfg.batch = batch; cfg.n_kv_heads = 8; cfg.n_q_heads = 8; cfg.head_dim = 128; cfg.group = 32;
+        cfg.max_tokens = 1 << 10; cfg.page_tokens = 32; cfg.policy = KVQ_POLICY_PAPER;
+        const uint64_t budget = 1ull << 50, bytes = kvq_arena_bytes(&cfg, 1);
+        const uint8_t fbit = 2;
+        void* const mem = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);  // (little of it is touched)
+        if (mem == MAP_FAILED) { printf("no address space for %llu bytes\n", (unsigned long long)bytes); continue; }
+        arena_size[static_cast<uint8_t*>(mem)] = bytes;
+        kvq_cache_t* c = nullptr;
+        CHECK(kvq_cache_create(&cfg, &budget, &fbit, mem, bytes, &c) == KVQ_OK, "create");
+        const void* in = input;
+        void* out = input;
+        CHECK(kvq_quantize_append(c, 0, input, input, 8, 16, nullptr) == KVQ_OK, "prompt");
+        for (int step = 0; step < 2; ++step) {
+            CHECK(kvq_append_decode_attention_batch(&c, 1, 0, &in, &in, nullptr, &in, &out, 0, 0.f, nullptr) == KVQ_OK, "batch %d", batch);
+            CHECK(batch_by_args == (batch < 8191), "batch %d", batch);
+        }
+        kvq_cache_destroy(c);
+        munmap(mem, bytes);
+    }
 }
 
 // A block whose launch failed after the bookkeeping is refused by every call that reads it, until it is emptied.
@@ -517,6 +547,7 @@ const std::map<std::string, std::function<void()>> scenarios = {
     {"batch_full_arena", batch_full_arena},
     {"batch_failing_launch", batch_failing_launch},
     {"failed_block_is_refused", failed_block_is_refused},
+    {"batch_of_large_arenas", batch_of_large_arenas},
     {"mark_set_by_a_step", mark_set_by_a_step},
     {"mark_outlives_a_failing_step", mark_outlives_a_failing_step},
     {"split_plans", split_plans},
