@@ -1040,9 +1040,10 @@ kvq_status_t fill_attn_params(kvq_cache_t* c, int32_t layer, const void* q_dev, 
         // and 23.6, 112 x 64 25.0 and 22.4, 128 x 64 25.9 and 25.3.
         if (4 * t.n2 < t.n_all && t.bytes * (uint64_t)c->units > 320000ull * (uint64_t)wgs && wgs * 3 / 4 / c->units * c->units * 8 >= wgs * 5)
             wgs = wgs * 3 / 4;
-        // (as long as the tiles of each width are as many as last time, so are the splits)
+        // (as long as the tiles of each width are as many as last time, and the tier's the same, so are the splits)
         const bool planes = c->int16() && t.n16 > 0;
-        const uint64_t key[3] = {t.time, (uint64_t)n_tiles << 32 | (uint32_t)t.n16, (uint64_t)t.widest << 32 | (uint32_t)(wgs / c->units)};
+        const uint64_t key[3] = {t.time, (uint64_t)n_tiles << 32 | (uint32_t)t.n16,
+                                 (uint64_t)t.widest << 32 | (uint64_t)planes << 31 | (uint32_t)(wgs / c->units)};
         if (std::memcmp(L.count_key, key, sizeof key) != 0) {
             L.count_splits = (planes ? planned_splits_planes : planned_splits)(c, t, n_tiles, wgs / c->units);
             std::memcpy(L.count_key, key, sizeof key);

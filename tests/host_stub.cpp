@@ -434,6 +434,24 @@ void plans_follow_the_pages() {
     }
 }
 
+// A block that is emptied, changes to the other 16-bit tier and is filled alike is split as a fresh one of that tier: the tiers have
+// different rules, though the tiles are as many and as wide.
+void plans_follow_the_tier() {
+    for (int units : {1, 2, 8, 16})
+        for (int tiles : {12, 24, 40, 64, 120, 250})
+            for (int tier16 : {0, 1}) {
+                Cache a(64, 200, tier16, KVQ_POLICY_PAPER, 0, 1, units, 4), b(64, 200, 1 - tier16, KVQ_POLICY_PAPER, 0, 1, units, 4);
+                CHECK(a.append(32 * tiles, 16) == KVQ_OK && a.attend() == KVQ_OK, "the first tier");
+                CHECK(kvq_cache_reset(a.c, -1) == KVQ_OK && kvq_cache_set_option(a.c, KVQ_OPT_TIER16, 1 - tier16) == KVQ_OK, "the other tier");
+                std::vector<int32_t> plan[2];
+                for (Cache* c : {&a, &b}) {
+                    CHECK(c->append(32 * tiles, 16) == KVQ_OK && c->attend() == KVQ_OK, "attention");
+                    plan[c == &b].assign(last.split_begin, last.split_begin + last.n_splits + 1);
+                }
+                CHECK(plan[0] == plan[1], "%d units x %d tiles: %zu ranges, %zu in a fresh block", units, tiles, plan[0].size() - 1, plan[1].size() - 1);
+            }
+}
+
 // The tile costs are relative: their scale changes neither how many splits a launch takes nor where they lie.
 void tile_costs_are_relative() {
     for (int narrow : {8, 30, 200}) {
@@ -552,6 +570,7 @@ const std::map<std::string, std::function<void()>> scenarios = {
     {"mark_outlives_a_failing_step", mark_outlives_a_failing_step},
     {"split_plans", split_plans},
     {"plans_follow_the_pages", plans_follow_the_pages},
+    {"plans_follow_the_tier", plans_follow_the_tier},
     {"tile_costs_are_relative", tile_costs_are_relative},
     {"batch_shares", batch_shares},
 };

@@ -24,7 +24,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["batch_full_arena", "batch_failing_launch", "failed_block_is_refused", "mark_set_by_a_step",
-                                      "mark_outlives_a_failing_step", "split_plans", "plans_follow_the_pages",
+                                      "mark_outlives_a_failing_step", "split_plans", "plans_follow_the_pages", "plans_follow_the_tier",
                                       "tile_costs_are_relative", "batch_shares", "batch_of_large_arenas"])
 def test_host_code_over_a_fake_device(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=300)
