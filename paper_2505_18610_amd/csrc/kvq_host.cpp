@@ -1483,7 +1483,10 @@ kvq_status_t cache_error(kvq_cache_t* c, int32_t layer, bool l1, const void* k_r
     // waiting longer than a millisecond, work in front of the kernel as a rule, or an error, is left to the stream's synchronization.
     // Whole calls with the synchronization and now: 16 units x 137 tokens 16.9 and 11.5 us, 64 x 2,048 with gradients 50.7 and 42.1.
     const int n = 2 * kvq_error_workgroups(L.T, c->units);
-    if (!c->sums_at_rest) std::fill_n(c->sums, 2 * KVQ_ERR_MAX_WGS, kNoSum);
+    if (!c->sums_at_rest) {  // an earlier call failed: its kernel may still have sums to store
+        if (hipStreamSynchronize(s) != hipSuccess) return KVQ_E_HIP;
+        std::fill_n(c->sums, 2 * KVQ_ERR_MAX_WGS, kNoSum);
+    }
     c->sums_at_rest = false;
     if (kvq_launch_error(l1, c->arena, c->table_dev(layer), k_ref_dev, v_ref_dev, gk_dev, gv_dev, L.T, c->tpp, c->units,
                          reinterpret_cast<double*>(c->ring_dev + c->ring_ctl.total_bytes()), s) != hipSuccess)

@@ -30,7 +30,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; retu
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t);  // (below, with the launches)
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) { memset(p, 0, sizeof *p); p->multiProcessorCount = 256; return hipSuccess; }
@@ -46,6 +46,14 @@ int failures = 0;
 
 int launches = 0, fail_launch = -1;  // the launch with this number fails
 hipError_t launched() { return launches++ == fail_launch ? hipErrorLaunchFailure : hipSuccess; }
+
+std::vector<std::function<void()>> in_flight;  // what the device has still to do, in stream order (sums of the error kernel)
+bool sums_late = false;                        // a kernel's sums arrive when the next kernel starts or the stream is waited for
+bool fail_sync = false;
+void finish_in_flight() {
+    for (const auto& f : in_flight) f();
+    in_flight.clear();
+}
 
 std::map<const uint8_t*, uint64_t> arena_size;  // every arena by its address
 KvqAttnParams last;                             // parameters of the last attention launch
@@ -105,6 +113,11 @@ void attention(const KvqAttnParams& p) {
 
 }  // namespace
 
+extern "C" hipError_t hipStreamSynchronize(hipStream_t) {
+    if (fail_sync) return hipErrorUnknown;
+    finish_in_flight();
+    return hipSuccess;
+}
 hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const void*, const void*, int t_old, int n_new, int tpp,
                              int, const KvqAppendPages& ap, KvqVMark, int, const float*, int, const float*, bool int16, hipStream_t) {
     const hipError_t e = launched();
@@ -135,7 +148,9 @@ hipError_t kvq_launch_error(bool, const uint8_t* arena, const KvqPageDesc* table
     const hipError_t e = launched();
     if (e != hipSuccess) return e;
     check_table(arena, table, n_tokens, tpp);
-    partial[0] = partial[1] = 0.0;
+    finish_in_flight();
+    in_flight.push_back([=] { partial[0] = n_tokens; partial[1] = -n_tokens; });
+    if (!sums_late) finish_in_flight();
     return hipSuccess;
 }
 hipError_t kvq_launch_stream_read(const void*, size_t, int, uint32_t*, hipStream_t) { return launched(); }
@@ -366,6 +381,29 @@ void failed_block_is_refused() {
         }
 }
 
+// The sums of a call that failed while its kernel was on its way are not taken for the next call's.
+void sums_behind_a_failing_call() {
+    Cache a(32, 8, 0);
+    CHECK(a.append(40) == KVQ_OK, "prompt");
+    sums_late = true;
+    for (int round = 0; round < 3; ++round) {
+        fail_sync = true;
+        CHECK(kvq_cache_sq_error(a.c, 0, input, input, sums, nullptr) == KVQ_E_HIP, "a wait that fails");
+        CHECK(kvq_cache_sq_error(a.c, 0, input, input, sums, nullptr) == KVQ_E_HIP, "and fails again");
+        fail_sync = false;
+        CHECK(a.append(1) == KVQ_OK, "a token more");
+        for (int again = 0; again < 2; ++again) {
+            CHECK(kvq_cache_sq_error(a.c, 0, input, input, sums, nullptr) == KVQ_OK, "the next call");
+            CHECK(sums[0] == a.tokens() && sums[1] == -a.tokens(), "%g and %g of %d tokens", sums[0], sums[1], a.tokens());
+        }
+    }
+    fail_launch = launches;
+    CHECK(kvq_cache_sq_error(a.c, 0, input, input, sums, nullptr) == KVQ_E_HIP, "a launch that fails");
+    fail_launch = -1;
+    CHECK(kvq_cache_sensitivity(a.c, 0, input, input, factors, factors, sums, nullptr) == KVQ_OK && sums[0] == a.tokens(), "the next call");
+    sums_late = false;
+}
+
 // The split plan over lengths, widths, page sizes and split counts: what check and attention() above ask of every launch.
 void split_plans() {
     for (int page : {32, 64, 96, 256})
@@ -565,6 +603,7 @@ const std::map<std::string, std::function<void()>> scenarios = {
     {"batch_full_arena", batch_full_arena},
     {"batch_failing_launch", batch_failing_launch},
     {"failed_block_is_refused", failed_block_is_refused},
+    {"sums_behind_a_failing_call", sums_behind_a_failing_call},
     {"batch_of_large_arenas", batch_of_large_arenas},
     {"mark_set_by_a_step", mark_set_by_a_step},
     {"mark_outlives_a_failing_step", mark_outlives_a_failing_step},

@@ -25,7 +25,7 @@ def program(tmp_path_factory):
 
 @pytest.mark.parametrize("scenario", ["batch_full_arena", "batch_failing_launch", "failed_block_is_refused", "mark_set_by_a_step",
                                       "mark_outlives_a_failing_step", "split_plans", "plans_follow_the_pages", "plans_follow_the_tier",
-                                      "tile_costs_are_relative", "batch_shares", "batch_of_large_arenas"])
+                                      "tile_costs_are_relative", "batch_shares", "batch_of_large_arenas", "sums_behind_a_failing_call"])
 def test_host_code_over_a_fake_device(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
