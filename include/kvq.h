@@ -12,8 +12,9 @@
  *   - The caller owns the arena, the q/k/v/out buffers and the stream.  The library owns the kvq_cache_t
  *     (host tables) and sub-allocates inside the arena; it never allocates or frees device memory.
  *   - Every kernel is enqueued on the given HIP stream (hipStream_t passed as void*, NULL = default stream).
- *     No entry point waits for the stream, except the three that copy results to the host
- *     (kvq_cache_export_segment, kvq_cache_sq_error, kvq_cache_sensitivity).  Page table
+ *     No entry point waits for the stream, except the three that give results to the host:
+ *     kvq_cache_export_segment waits for the stream; kvq_cache_sq_error and kvq_cache_sensitivity wait for their own sums,
+ *     which arrive behind all earlier work of the stream but before the stream is known to be idle.  Page table
  *     entries ride in the arguments of the kernels that make the pages.  What is too long for that (appends over more than
  *     128 pages, shrinks of more than 192, the parameter blocks of large ragged batches) travels through a pinned staging ring
  *     of 4 segments of 1 MiB whose reuse is guarded by one HIP event per segment: a call blocks the host only when it has

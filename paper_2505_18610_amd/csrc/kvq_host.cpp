@@ -585,7 +585,9 @@ kvq_status_t kvq_cache_create(const kvq_config_t* cfg, const uint64_t* block_bud
     }
     if (!c->dry) {
         c->ring_ctl.init(kRingSegmentBytes);
-        if (hipHostMalloc(reinterpret_cast<void**>(&c->ring), c->ring_ctl.total_bytes() + 2 * KVQ_ERR_MAX_WGS * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
+        // (coherent: the host reads sums while the kernel that stores them runs)
+        if (hipHostMalloc(reinterpret_cast<void**>(&c->ring), c->ring_ctl.total_bytes() + 2 * KVQ_ERR_MAX_WGS * sizeof(uint64_t),
+                          hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
             delete c;
             return KVQ_E_HIP;
         }

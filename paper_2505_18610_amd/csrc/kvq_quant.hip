@@ -781,7 +781,8 @@ __global__ __launch_bounds__(64 * KVQ_ERR_WAVES) __attribute__((amdgpu_waves_per
     for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
     if (thread_lane == 0) sums[wave] = total;
     __syncthreads();
-    if (threadIdx.x < 2) partial[2 * blockIdx.x + threadIdx.x] = sums[threadIdx.x] + sums[threadIdx.x + 2];
+    if (threadIdx.x < 2)  // (the host is waiting for it)
+        __hip_atomic_store(&partial[2 * blockIdx.x + threadIdx.x], sums[threadIdx.x] + sums[threadIdx.x + 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ------------------------------------------------------------------------ channel-wise reparameterization

@@ -23,7 +23,8 @@
 
 // ---- the HIP runtime, as far as the host code uses it
 extern "C" {
-hipError_t hipHostMalloc(void** p, size_t n, unsigned int) { *p = aligned_alloc(256, n); return hipSuccess; }
+unsigned host_memory_flags = 0;
+hipError_t hipHostMalloc(void** p, size_t n, unsigned int flags) { host_memory_flags = flags; *p = aligned_alloc(256, n); return hipSuccess; }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned int) { *d = h; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
@@ -384,6 +385,7 @@ void failed_block_is_refused() {
 // The sums of a call that failed while its kernel was on its way are not taken for the next call's.
 void sums_behind_a_failing_call() {
     Cache a(32, 8, 0);
+    CHECK(host_memory_flags & hipHostMallocCoherent, "the host reads them while the kernel runs");
     CHECK(a.append(40) == KVQ_OK, "prompt");
     sums_late = true;
     for (int round = 0; round < 3; ++round) {
