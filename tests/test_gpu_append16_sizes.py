@@ -41,3 +41,9 @@ def test_one_append_writes_what_its_pieces_write(units, T, prepared, tier16):
         gc.close()
         arenas.append(arena)
     assert torch.equal(*arenas)
+
+
+@pytest.mark.parametrize("units,T,prepared,tier16", [(256, 3105, False, 1)])
+def test_one_append_of_many_strings_writes_what_its_pieces_write(units, T, prepared, tier16):
+    """More than 32,768 strings of ready keys into the integer tier: a string a wavefront."""
+    test_one_append_writes_what_its_pieces_write(units, T, prepared, tier16)
