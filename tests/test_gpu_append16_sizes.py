@@ -43,7 +43,7 @@ def test_one_append_writes_what_its_pieces_write(units, T, prepared, tier16):
     assert torch.equal(*arenas)
 
 
-@pytest.mark.parametrize("units,T,prepared,tier16", [(256, 3105, False, 1)])
+@pytest.mark.parametrize("units,T,prepared,tier16", [(256, 3105, False, 0), (256, 3105, False, 1), (128, 2081, False, 0)])
 def test_one_append_of_many_strings_writes_what_its_pieces_write(units, T, prepared, tier16):
-    """More than 32,768 strings of ready keys into the integer tier: a string a wavefront."""
+    """More than 49,152 strings of ready keys (a string a workgroup), an odd number of tiles in workgroups of two."""
     test_one_append_writes_what_its_pieces_write(units, T, prepared, tier16)
