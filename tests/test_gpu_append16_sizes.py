@@ -43,7 +43,7 @@ def test_one_append_writes_what_its_pieces_write(units, T, prepared, tier16):
     assert torch.equal(*arenas)
 
 
-@pytest.mark.parametrize("units,T,prepared,tier16", [(256, 3105, False, 0), (256, 3105, False, 1), (128, 2081, False, 0)])
+@pytest.mark.parametrize("units,T,prepared,tier16", [(256, 3105, False, 0), (256, 3105, False, 1), (32, 3177, True, 0), (128, 2081, False, 0)])
 def test_one_append_of_many_strings_writes_what_its_pieces_write(units, T, prepared, tier16):
-    """More than 49,152 strings of ready keys (a string a workgroup), an odd number of tiles in workgroups of two."""
+    """More than 49,152 strings of ready keys (a string a workgroup), 98,304 rows of 32 units, an odd number of tiles in workgroups of two."""
     test_one_append_writes_what_its_pieces_write(units, T, prepared, tier16)
