@@ -288,42 +288,48 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
 // 27.4 and 24.3 / 35.8 and 31.0, 4,096 x 128 116 and 108; rotated and scaled 2,048 x 32 20.2 and 18.0 / 23.0 and 20.0; neither 1,024 x 16
 // 6.6 and 6.2 / 7.0 and 6.7, 2,048 x 32 13.3 and 12.1 / 14.5 and 15.7, 2,048 x 64 23.0 and 22.4 / 29.6 and 28.4.  (A wavefront a string and a
 // tile a workgroup: 3 to 14 % behind that, but for 4,096 strings of scaled keys, 16.5 / 18.3.)
-template <bool PLAIN>
-__global__ __launch_bounds__(256) void kvq_append_i16_kernel(const AppendArgs args) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds_all[2][2][KVQ_LDS_CODES];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
+// SHARE: how many wavefronts share a string.  Ready keys of more than 32,768 strings take one, a workgroup each: with two and one,
+// 8,192 x 64 (32,768) 106.8 and 107.1 / 106 and 107, 6,144 x 96 117.7 and 116.9 / 117.6 and 118.3, 5,120 x 128 (40,960) 139.5 and 132.8 / 136 and 135, 12,288 x
+// 64 160.6 and 157.7 / 166 and 158.5, 16,384 x 64 215.5 and 209.9 / 220 and 209, 4,096 x 256 216 and 200 / 215 and 203.5, 16,384 x 128 451 and 417 / 456 and
+// 421; rotated ones gain by two at every size (16,384 x 64 230 and 219), scaled ones are alike from 65,536 strings on.
+template <bool PLAIN, int SHARE>
+__device__ __forceinline__ void append_i16(const AppendArgs& args, uint8_t (*lds_all)[2][KVQ_LDS_CODES]) {
+    static_assert(SHARE == 2 || PLAIN, "keys to rotate and scale are always shared");
+    const int wave = SHARE == 2 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0, half = wave & 1;
     auto& lds = lds_all[wave >> 1];
     const int lane = threadIdx.x & 63, j = lane >> 4, n = lane & 15;
     AppendArgs A;
     read_append_args<PLAIN>(args, A);
     AppendString t;
-    append_string<PLAIN, 2>(A, wave >> 1, t);  // (the number of strings is even)
-    if (wave == 3) write_fresh_pages(A.table, args.pages, lane);
+    append_string<PLAIN, SHARE>(A, wave >> 1, t);  // (the number of strings is even)
+    if (SHARE == 1 || wave == 3) write_fresh_pages(A.table, args.pages, lane);
     const int which = t.which, t_old = A.t_old, gspan = A.gspan;
     const int tok0 = t.tile * KVQ_TILE_TOKENS;
     const kvq_dev::NewRows rows((which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, t_old, A.n_new);
     const int grp = lane & 3;
-    const int tl = 16 * half + (lane >> 2), tok = tok0 + tl;
-    uint32_t w[1][16];
+    uint32_t w[2 / SHARE][16];
     load_owner_rows(w, rows, tok0 + 16 * half, lane);
     const bool rotates = !PLAIN && !which && A.rope;
     OwnerAngles angles;
-    if (rotates) load_owner_angles(angles, rows, tok, lane, A.rope);
+    if (rotates) load_owner_angles(angles, rows, tok0 + 16 * half + (lane >> 2), lane, A.rope);
     __builtin_amdgcn_sched_barrier(0);  // all of these loads first
     const KvqPageDesc pd = append_desc<PLAIN>(A.table, args.pages, t.page);
     uint8_t* code = A.arena + (uint64_t)pd.code_off256 * 256u + (t.tslot * 2 + which) * (512u * 16);
     uint8_t* meta = A.arena + (uint64_t)pd.meta_off256 * 256u + t.tslot * KVQ_META_TILE_BYTES;
-    if (rotates) rotate_owner_keys(w[0], angles, rows.has(tok), rows.all(tok0), lane);
+    if (rotates) rotate_owner_keys(w[0], angles, rows.has(tok0 + 16 * half + (lane >> 2)), rows.all(tok0), lane);
     if (!PLAIN && !which && t.rinv_head) scale_owner_keys(w[0], lane, t.rinv_head);
-    {
+#pragma unroll
+    for (int pass = 0; pass < 2 / SHARE; ++pass) {
+        const int tl = 16 * (half + pass) + (lane >> 2), tok = tok0 + tl;
         uint32_t codes[32];
         uint16_t S, Z;
-        quantize_owner<16>(w[0], codes, &S, &Z, gspan);
+        quantize_owner<16>(w[pass], codes, &S, &Z, gspan);
         scatter_codes<1>(lds[0], which, tl, grp, codes);
         scatter_codes<0>(lds[1], which, tl, grp, codes);
         if (tok >= t_old) store_meta_owner(meta, which, tl, grp, S, Z);
     }
-    __syncthreads();
+    if (SHARE == 2) __syncthreads();
+    else wave_sync_lds();
     uint32_t keep = 0;  // stored tokens keep their bits
     if (!which) {
 #pragma unroll
@@ -334,24 +340,36 @@ __global__ __launch_bounds__(256) void kvq_append_i16_kernel(const AppendArgs ar
         for (int i = 0; i < 8; ++i)
             if (tok0 + 8 * j + i < t_old) keep |= 1u << i;
     }
-    uint32_t str[16];
-    gather_string<8>(lds[half], which, lane, str);
-    uint8_t* dst = code + half * (512u * 8);
-    if (tok0 < t_old && keep) {
-        uint32_t old[16];
-        load_chunks<8>(dst, lane, old);
 #pragma unroll
-        for (int d = 0; d < 16; ++d) {
-            uint32_t m = which ? v_token_mask<8>(keep, d) : (((keep >> (d / 8)) & 1u) ? 0xffffffffu : 0u);
-            str[d] = (old[d] & m) | (str[d] & ~m);
+    for (int plane = half; plane < half + 2 / SHARE; ++plane) {
+        uint32_t str[16];
+        gather_string<8>(lds[plane], which, lane, str);
+        uint8_t* dst = code + plane * (512u * 8);
+        if (tok0 < t_old && keep) {
+            uint32_t old[16];
+            load_chunks<8>(dst, lane, old);
+#pragma unroll
+            for (int d = 0; d < 16; ++d) {
+                uint32_t m = which ? v_token_mask<8>(keep, d) : (((keep >> (d / 8)) & 1u) ? 0xffffffffu : 0u);
+                str[d] = (old[d] & m) | (str[d] & ~m);
+            }
+        }
+        if (tok0 >= t_old) {
+            store_chunks_stream<8>(dst, lane, str);
+        } else {
+            store_chunks<8>(dst, lane, str);
+            asm volatile("" ::: "memory");  // keeps the two kinds of store apart
         }
     }
-    if (tok0 >= t_old) {
-        store_chunks_stream<8>(dst, lane, str);
-    } else {
-        store_chunks<8>(dst, lane, str);
-        asm volatile("" ::: "memory");  // keeps the two kinds of store apart
-    }
+}
+template <bool PLAIN>
+__global__ __launch_bounds__(256) void kvq_append_i16_kernel(const AppendArgs args) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][2][KVQ_LDS_CODES];
+    append_i16<PLAIN, 2>(args, lds);
+}
+__global__ __launch_bounds__(64) void kvq_append_i16_bulk_kernel(const AppendArgs args) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[1][2][KVQ_LDS_CODES];
+    append_i16<true, 1>(args, lds);
 }
 
 // ------------------------------------------------------------------------------------- fp16 page -> b bits
@@ -936,7 +954,8 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     } while (0)
     switch (bits + (int16 && bits == 16 ? 1 : 0)) {
         case 17:
-            if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 2, 2);
+            if (plain && strings > 32768) KVQ_APPEND_LAUNCH(kvq_append_i16_bulk_kernel, 1, 1);
+            else if (plain) KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<true>, 2, 2);
             else KVQ_APPEND_LAUNCH(kvq_append_i16_kernel<false>, 2, 2);
             break;
         case 16:
