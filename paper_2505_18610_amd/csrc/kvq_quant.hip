@@ -111,18 +111,21 @@ __global__ __launch_bounds__(128) void kvq_append16_kernel(const AppendArgs args
     else kvq_dev::append16_k_tile<FIVE, 2>(code, rows, tok0, lane, PLAIN ? nullptr : A.rope, PLAIN ? nullptr : t.rinv_head, 0);
     if (wave == 1) write_fresh_pages(A.table, args.pages, lane);
 }
-// The same for keys that need no preparation, two tiles a workgroup, half as many workgroups to dispatch.  For more than 16,384
-// strings.  One tile a workgroup and two, over the same input / from memory: 4,096 tokens x 128 units 87 and 80 us / 105 and 101,
-// 8,192 x 64 84 and 80 / 107 and 106, 16,384 x 64 189 and 188 (one string a workgroup 97 / 105, 84 / 105, 187); 4,096 x 64 (16,384 strings)
-// 39.7 and 39.1 / 54 and 55, 2,048 x 64 20.8 and 20.1 / 29.2 and 30.7.
-__global__ __launch_bounds__(256) void kvq_append16_bulk_kernel(const AppendArgs args) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2][32 * 256];
+// The same for keys that need no preparation and more than 16,384 strings.  Two tiles a workgroup, half as many workgroups to
+// dispatch: one tile a workgroup and two, over the same input / from memory, 4,096 tokens x 96 units (24,576 strings) 62.6 and 60.7 us / 76.7
+// and 76.4, 8,192 x 64 88.8 and 81.0 / 104 and 101, 4,096 x 128 92 and 88 / 113 and 107; 4,096 x 64 (16,384) 40.0 and 40.0 / 55.1 and 55.8.  One string a
+// workgroup beyond that: with two tiles and one string, 8,192 x 64 (32,768) 81.2 and 88.4 / 101 and 101, 10,240 x 64 (40,960) 104 and
+// 108 / 126 and 126, 12,288 x 64 (49,152) 129.0 and 127.4 / 149 and 146, 14,336 x 64 151.5 and 147.9 / 173 and 170.6, 8,192 x 128 216 and 205 /
+// 221 and 218, 16,384 x 64 183.6 and 180.6 / 196 and 193, 16,384 x 128 450 and 435 / 433 and 424.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void kvq_append16_bulk_kernel(const AppendArgs args) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[(WAVES + 1) / 2][32 * 256];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     AppendArgs A;
     read_append_args<true>(args, A);
     AppendString t;
-    const bool mine = append_string<true, 4>(A, wave, t);
-    if (wave == 1) write_fresh_pages(A.table, args.pages, lane);
+    const bool mine = append_string<true, WAVES>(A, wave, t);
+    if (wave == (WAVES > 1 ? 1 : 0)) write_fresh_pages(A.table, args.pages, lane);
     if (!mine) return;
     const kvq_dev::NewRows rows((t.which ? A.v : A.k) + (uint64_t)t.unit * A.n_new * KVQ_D, A.t_old, A.n_new);
     const int tok0 = t.tile * KVQ_TILE_TOKENS;
@@ -960,7 +963,8 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
             break;
         case 16:
             if (plain && few) KVQ_APPEND_LAUNCH(kvq_append16_pair_kernel<true>, 2, 2);
-            else if (plain && bulk) KVQ_APPEND_LAUNCH(kvq_append16_bulk_kernel, 4, 1);
+            else if (plain && strings >= 49152) KVQ_APPEND_LAUNCH(kvq_append16_bulk_kernel<1>, 1, 1);
+            else if (plain && bulk) KVQ_APPEND_LAUNCH(kvq_append16_bulk_kernel<4>, 4, 1);
             else if (plain) KVQ_APPEND_LAUNCH((kvq_append16_kernel<true, false>), 2, 1);
             else if (few) KVQ_APPEND_LAUNCH(kvq_append16_pair_kernel<false>, 2, 2);
             else if (five) KVQ_APPEND_LAUNCH((kvq_append16_kernel<false, true>), 2, 1);
