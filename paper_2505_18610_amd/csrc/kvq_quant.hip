@@ -22,11 +22,12 @@ using kvq_dev::as_global;
 // the bulk of the general kernels' registers.
 // by_unit: the units of a string follow one another in the grid instead of the strings of a unit.  The table rows of the
 // string's tokens, 512 bytes a token and as much as its keys and values in one unit, are then read by all units at about
-// the same time and come from the caches.  For the raw 16-bit tier, 64 units and more and at least 98,304 rows of all units together.
+// the same time and come from the caches.  For the raw 16-bit tier, 32 units and more and at least 98,304 rows of all units together.
 // Rotated keys, with and without, over the same input / from memory: 2,048 x 64 25.6 and 27.7 / 27.5 and 30.4 us, 4,096 x 128 84
-// and 90 / 99 and 103; 4,096 x 32 25.5 and 24.5 / 27.2 and 27.0, 2,048 x 48 20.5
-// and 19.2 / 21.8 and 21.4, 1,024 x 64 (65,536 rows) 14.4 and 14.5 / 15.9 and 17.6, 8,192 x 8 17.9 and 14.3 / 17.5 and 18.7.  Into the integer
-// tier it loses: 4,096 x 128 113 and 108 / 112 and 109, 2,048 x 64 25.0 and 24.3 / 32.7 and 31.0, 8,192 x 8 17.9 and 15.1.  Into 8,
+// and 90 / 99 and 103; of 32 units what memory gains outweighs what the caches lose, 4,096 x 32 25.6 and 25.0 / 28.6 and 30.1, scaled too
+// 26.3 and 26.7 / 28.8 and 31.9, 8,192 x 32 46.3 and 44.4 / 51.7 and 54.0, scaled too 46.4 and 45.7 / 53.0 and 55.7; of fewer it loses, 16,384
+// x 16 50.5 and 43.3 / 54.4 and 52.0, x 8 30.8 and 24.2 / 32.0 and 27.8; 1,024 x 64 (65,536 rows) 14.4 and 14.5 / 15.9 and 17.6.  Into the
+// integer tier it loses: 4,096 x 128 113 and 108 / 112 and 109, 2,048 x 64 25.0 and 24.3 / 32.7 and 31.0, 8,192 x 8 17.9 and 15.1.  Into 8,
 // 4 and 2 bits, where the arithmetic weighs more, it loses 3 to 7 % at every size.
 // What a launch's kernels need, read at once at their start: left alone the compiler reads the arguments one by one where they
 // are used first, each a trip to the constant cache or beyond, and three quotients and the lookup of the page entry stood in
@@ -933,7 +934,7 @@ hipError_t kvq_launch_append(int bits, uint8_t* arena, KvqPageDesc* table, const
     const bool bulk = strings > 16384;  // see kvq_append16_bulk_kernel
     const bool few = strings < 1024;  // see kvq_append16_pair_kernel
     const bool five = rinv && strings > 4096 && strings <= 5632 && (strings + 511) / 512 % 2 == 1;  // see kvq_append16_kernel
-    const int by_unit = !plain && bits == 16 && !int16 && units >= 64 && (int64_t)units * n_new >= 98304 ? units : 0;
+    const int by_unit = !plain && bits == 16 && !int16 && units >= 32 && (int64_t)units * n_new >= 98304 ? units : 0;
     AppendArgs A;
     A.arena = arena; A.table = table; A.k = k; A.v = v; A.rinv = rinv; A.rope = rope; A.v_word = mark.word; A.v_epoch = mark.epoch;
     A.t_old = t_old; A.n_new = n_new; A.tpp = tiles_per_page; A.tile0 = tile0; A.n_strings = n_strings; A.by_unit = by_unit;
