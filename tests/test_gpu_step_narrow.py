@@ -6,7 +6,8 @@ import pytest
 import torch
 
 import paper_2505_18610_amd as kq
-from gpu_util import MAX_ABS, REL_L2
+from gpu_util import MAX_ABS, REL_L2, append_both, assert_same_cache, dev, make_pair
+from oracle.attention import decode_attention_fp64
 
 pytestmark = pytest.mark.gpu
 
@@ -70,13 +71,80 @@ def test_step_below_16_bits(bits, group, tier16, page, start, heads, kv, batch, 
         two.kvq_decode_attention(0, q, outs[2])
         one.kvq_decode_attention(0, q, outs[3])
         a, b, c, d = (o.cpu().numpy() for o in outs)
-        # either way rounds p and p * S_v to fp16, 2^-11 each, of sum p |V|, which is the output's size where the large token dominates: 2^-9 of it
-        scale = max(1.0, float(np.abs(a).max()))
         assert np.array_equal(c, d), step                    # the cached block, token included, read alike
-        assert np.abs(a - b).max() <= MAX_ABS * scale, step
-        assert np.linalg.norm(a - b) <= REL_L2 * np.linalg.norm(a), step
+        # either way rounds p and p * S_v to fp16, 2^-11 each, of sum p |V|, which is the output's size where the large token dominates: 2^-9 of
+        # it.  S_v is of one quantization group: the channels of the others are held to their own size.
+        for g0 in range(0, 128, group):
+            x, y = a[..., g0:g0 + group], b[..., g0:g0 + group]
+            assert np.abs(x - y).max() <= MAX_ABS * max(1.0, float(np.abs(x).max())), (step, g0)
+            assert np.linalg.norm(x - y) <= REL_L2 * np.linalg.norm(x), (step, g0)
         if step in (0, 3, 20, 35):
             _same_contents(two, one)
+
+
+@pytest.mark.parametrize("bits", [8, 4, 2])
+@pytest.mark.parametrize("group,tier16,page,start", [
+    (32, 0, 64, 30),      # into a tile, across its end
+    (64, 1, 64, 62),      # across the end of a page
+    (128, 0, 96, 95),
+    (32, 1, 32, 700),
+])
+def test_step_below_16_bits_against_the_oracle(bits, group, tier16, page, start):
+    rng = np.random.default_rng(100 * start + bits)
+    B, H, G = 2, 2, 3
+    oc, gc = make_pair(1, B, H * G, H, start + 64, page, group=group, tier16=tier16)
+    draw = lambda *shape: rng.standard_normal(shape, dtype=np.float32).astype(np.float16)
+    append_both(oc, gc, 0, draw(B, H, start, 128), draw(B, H, start, 128), bits)
+    for step in range(6):
+        k, v, q = draw(B, H, 1, 128), draw(B, H, 1, 128), draw(B, H * G, 128)
+        if step == 3:
+            v[..., 32:64] = (v[..., 32:64].astype(np.float32) * 20000.0).clip(-65504, 65504).astype(np.float16)
+        out = torch.empty(B, H * G, 128, device="cuda")
+        gc.kvq_append_decode_attention(0, dev(k), dev(v), dev(q), out)
+        oc.append(0, k, v)
+        got, want = out.cpu().numpy().astype(np.float64), oc.attention(0, q)
+        size = np.abs(want)
+        if step >= 3:  # (what is rounded: the terms of sum p V, which large ones can make larger than the output.  Their size: all V positive.)
+            K, V = oc.dequantized(0)
+            size = decode_attention_fp64(q, K, np.abs(V))
+        for g0 in range(0, 128, group):
+            at = slice(g0, g0 + group)
+            assert np.abs(got[..., at] - want[..., at]).max() <= MAX_ABS * max(1.0, size[..., at].max()), (step, g0)
+            assert np.linalg.norm(got[..., at] - want[..., at]) <= REL_L2 * np.linalg.norm(size[..., at]), (step, g0)
+        if step in (0, 2, 5):
+            assert_same_cache(oc, gc, 0)
+    gc.close()
+
+
+@pytest.mark.parametrize("group", [32, 128])
+@pytest.mark.parametrize("bits", [8, 4, 2])
+def test_step_of_elements_that_are_no_numbers(bits, group):
+    """NaN beside numbers is code 0 and leaves attention finite; infinities and groups of NaN alone are stored as the append stores them."""
+    (two, one), g = _pair(bits, group, 0, 64, 62, 4, 2, 1, False, 9)
+    for step in range(4):
+        k, v = (torch.randn(1, 2, 1, 128, generator=g, device="cuda").half() for _ in range(2))
+        for x in (k, v):
+            x[..., 5::17] = float("nan")
+            if step == 1:
+                x[..., 7::32] = -x[..., 7::32].abs()
+                x[..., 40] = torch.tensor(-443, dtype=torch.int16).view(torch.float16)  # a NaN of the other sign, with a payload
+            if step == 2:
+                x[:, 0, :, 9], x[:, 1, :, 40] = float("inf"), -float("inf")
+            if step == 3:
+                x[..., 64:96], x[:, 1, :, 70] = float("nan"), float("inf")
+        q = torch.randn(1, 8, 128, generator=g, device="cuda").half()
+        outs = [torch.empty(1, 8, 128, device="cuda") for _ in range(2)]
+        two.kvq_quantize_append(0, k, v)
+        two.kvq_decode_attention(0, q, outs[0])
+        one.kvq_append_decode_attention(0, k, v, q, outs[1])
+        a, b = (o.cpu().numpy() for o in outs)
+        if step < 2:
+            assert np.isfinite(b).all() and np.abs(a - b).max() <= MAX_ABS and np.linalg.norm(a - b) <= REL_L2 * np.linalg.norm(a), step
+        for which in (0, 1):
+            got, want = (c.kvq_cache_export_segment(0, 0, which) for c in (one, two))
+            assert np.array_equal(got[0], want[0]), (step, which)
+            for x, y in zip(got[1:], want[1:]):
+                assert np.array_equal(x.astype(np.float32), y.astype(np.float32), equal_nan=True), (step, which)
 
 
 def test_steps_and_shrinks_take_turns():

@@ -1,6 +1,7 @@
 """Reconstruction error and sensitivity: the host takes the workgroups' sums as they arrive.  Calls of different sizes in turn, behind
-work that keeps the stream busy, and over what is no number give what they give by themselves."""
+work that keeps the stream busy, from several threads and over what is no number give what they give by themselves."""
 import math
+import threading
 
 import pytest
 import torch
@@ -34,6 +35,28 @@ def test_sums_of_calls_in_turn(busy):
                 for _ in range(6):
                     a = torch.tanh(a @ a)  # some milliseconds in front of the kernel
             assert (c.kvq_cache_sensitivity(0, k, v, gk, gv), c.kvq_cache_sq_error(0, k, v)) == want
+
+
+def test_sums_of_threads_with_a_cache_each():
+    blocks = [_block(*x) for x in ((2, 65, 4, 7), (64, 1500, 2, 8), (16, 300, 8, 9), (8, 4000, 4, 10))]
+    want = [(c.kvq_cache_sensitivity(0, k, v, gk, gv), c.kvq_cache_sq_error(0, k, v)) for c, k, v, gk, gv in blocks]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        c, k, v, gk, gv = blocks[i]
+        stream = torch.cuda.Stream()
+        for call in range(60):
+            got = (c.kvq_cache_sensitivity(0, k, v, gk, gv, stream=stream.cuda_stream), c.kvq_cache_sq_error(0, k, v, stream=stream.cuda_stream))
+            if got != want[i]:
+                wrong.append((i, call, got, want[i]))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(blocks))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong[:3]
 
 
 def test_sums_that_are_no_numbers():
