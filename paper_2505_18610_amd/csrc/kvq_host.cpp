@@ -1483,7 +1483,8 @@ kvq_status_t cache_error(kvq_cache_t* c, int32_t layer, bool l1, const void* k_r
     // sum.  A sum that is not there yet reads as a NaN no sum can be (its quiet bit is clear: arithmetic gives quiet ones).  All that a
     // workgroup reads it has read before it stores, so that with the last sum the inputs are the caller's again.  What keeps the host
     // waiting longer than a millisecond, work in front of the kernel as a rule, or an error, is left to the stream's synchronization.
-    // Whole calls with the synchronization and now: 16 units x 137 tokens 16.9 and 11.5 us, 64 x 2,048 with gradients 50.7 and 42.1.
+    // Whole calls with gradients, with the synchronization and now, the first over a cache and repeated ones: 16 units x 137 tokens 24.3 and
+    // 13.1 us, 17.0 and 11.8; 64 x 2,048 56 and 46, 52 and 43; 4 x 4,000 25 and 15, 20.1 and 13.9.
     const int n = 2 * kvq_error_workgroups(L.T, c->units);
     if (!c->sums_at_rest) {  // an earlier call failed: its kernel may still have sums to store
         if (hipStreamSynchronize(s) != hipSuccess) return KVQ_E_HIP;
