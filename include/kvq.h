@@ -201,8 +201,8 @@ kvq_status_t kvq_append_decode_attention(kvq_cache_t* cache, int32_t layer, cons
  *   launch was to write; the others hold their new token or, if their append had not begun, are unchanged.
  * The device's workgroups are shared among the caches in proportion to the time their tiles take.  Results per cache
  * are those of the single-cache calls up to floating-point summation order.  The parameter blocks of the launch travel in
- * the kernel arguments or, of more caches than fit there (16, less where ranges are many), are read from the pinned staging
- * memory of caches[0]: calls that involve that cache must be issued on one stream. */
+ * the kernel arguments or, of more caches than fit there (16, less where ranges are many or a cache's tables lie beyond 64 GiB
+ * of its arena), are read from the pinned staging memory of caches[0]: calls that involve that cache must be issued on one stream. */
 kvq_status_t kvq_decode_attention_batch(kvq_cache_t* const* caches, int32_t n_caches, int32_t layer,
                                         const void* const* q_dev, void* const* out_dev, int32_t out_is_fp32,
                                         float softmax_scale, void* hip_stream);

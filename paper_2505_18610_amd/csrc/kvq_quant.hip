@@ -89,7 +89,8 @@ __device__ __forceinline__ bool append_string(const AppendArgs& A, int wave, App
 // its second the values.  Workgroups go to the eight XCDs in turn: with one string each, keys and values in turn, all keys, which
 // are rotated and scaled, were on every other XCD and the others had little to do.  One wavefront a workgroup and now: 1,024 tokens x
 // 16 units rotated 6.1 and 5.1 us, 2,500 x 8 7.0 and 6.0, 1,024 x 32 9.3 and 7.5, 2,048 x 32 15.4 and 14.3, neither rotated nor scaled
-// 2,500 x 8 4.4 and 4.1, 1,024 x 32 5.5 and 5.0.
+// 2,500 x 8 4.4 and 4.1, 1,024 x 32 5.5 and 5.0; 3,840 to 4,224 strings of such keys take 0.3 us longer over a repeated input, 2,048 x 32 10.0 and
+// 10.3, and the same from memory, 16.1 and 16.2.
 // FIVE: with 92 registers five wavefronts fit on a SIMD, otherwise, with 104, four.  Scaled keys of 4,097 to 4,608 and 5,121 to 5,632
 // strings, the odd steps of half a wavefront a SIMD beyond four, end earlier with five (16 units x 144 tiles 16.4 us and 17.8, from memory
 // 18.1 and 19.4; x 164 19.1 and 19.2, 19.2 and 20.1); 4,992 strings are alike, and keys that are only rotated lose 1 to 4 % of it.
@@ -141,7 +142,8 @@ __global__ __launch_bounds__(64 * WAVES) void kvq_append16_bulk_kernel(const App
 // than 1,024 strings, launches that leave SIMDs without a wavefront otherwise, where the chain of one is what counts.  One wavefront per
 // string and two, over the same input / from memory: rotated and scaled, 64 tokens x 8 units 3.8 and 3.5 us / 3.8 and 3.6, 700 x 8 4.2 and
 // 3.9 / 4.3 and 4.1, 1,500 x 8 5.1 and 4.9 / 5.5 and 5.4, 1,024 x 16 (1,024 strings) 5.6 and 5.4 / 5.6 and 5.9, 1,536 x 16 6.4 and 6.3 / 6.9 and
-// 7.6; neither, 64 x 8 2.9 and 2.7 / 2.9 and 2.8, 1,500 x 8 alike, 1,536 x 16 4.2 and 4.6 / 5.3 and 5.6.
+// 7.6; neither, 64 x 8 2.9 and 2.7 / 2.9 and 2.8, 1,500 x 8 alike, 1,280 x 8 3.6 and 3.6 / 4.5
+// and 4.2, 1,536 x 16 4.2 and 4.6 / 5.3 and 5.6.
 template <bool PLAIN>
 __global__ __launch_bounds__(256) void kvq_append16_pair_kernel(const AppendArgs args) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][32 * 128];
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(64 * KVQ_APPEND_WG_WAVES) void kvq_append_q_kernel(
 // workgroup of one string and one wavefront, and now, over the same input / from memory: rotated 64 tokens x 8 units 5.2 and 4.5 us,
 // 1,024 x 16 7.8 and 7.0 / 8.7 and 7.4, 1,280 x 32 13.2 and 10.7 / 14.5 and 11.4, 2,048 x 32 18.0 and 14.8 / 21.1 and 18.3, 2,048 x 64
 // 27.4 and 24.3 / 35.8 and 31.0, 4,096 x 128 116 and 108; rotated and scaled 2,048 x 32 20.2 and 18.0 / 23.0 and 20.0; neither 1,024 x 16
-// 6.6 and 6.2 / 7.0 and 6.7, 2,048 x 32 13.3 and 12.1 / 14.5 and 15.7, 2,048 x 64 23.0 and 22.4 / 29.6 and 28.4.  (A wavefront a string and a
+// 6.6 and 6.2 / 7.0 and 6.7, 2,048 x 32 14.3 and 13.8 / 17.4 and 17.3, 2,048 x 64 23.0 and 22.4 / 29.6 and 28.4.  (A wavefront a string and a
 // tile a workgroup: 3 to 14 % behind that, but for 4,096 strings of scaled keys, 16.5 / 18.3.)
 // SHARE: how many wavefronts share a string.  Ready keys of more than 32,768 strings take one, a workgroup each: with two and one,
 // 8,192 x 64 (32,768) 106.8 and 107.1 / 106 and 107, 6,144 x 96 117.7 and 116.9 / 117.6 and 118.3, 5,120 x 128 (40,960) 139.5 and 132.8 / 136 and 135, 12,288 x
